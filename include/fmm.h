@@ -68,13 +68,13 @@ enum {
                                  pointers and stream */
     FMM_FLAG_PHASE_TIMING = 2, /* record per-phase hipEvent timings into fmm_stats
                                  (adds one event pair per phase) */
-    FMM_FLAG_LEVELWISE = 4    /* run the far field's upward and downward passes level
-                                 by level (one launch per level of M2M and of L2L)
-                                 instead of by subtrees (trees whose problems all
-                                 have the same N_levels >= 3, p <= 32: P2M with two
-                                 M2M levels, three-level M2M subtrees, and an L2P
-                                 that shifts every ancestor's M2L sum into the
-                                 leaves directly); the two agree up to rounding */
+    FMM_FLAG_LEVELWISE = 4    /* run the far field's downward pass level by level
+                                 (every box's complete local expansion formed from
+                                 its parent's and stored, rounded to the storage
+                                 type), as problems of unlike N_levels always do,
+                                 instead of directly (an L2P that shifts every
+                                 ancestor's M2L sum into the leaves); the two agree
+                                 up to rounding */
 };
 
 /* Launch-shape knobs of one plan; 0 means "choose automatically". */

@@ -253,8 +253,8 @@ class Plan:
 
 def plan(tree, p, theta, precision="fp64", p2p_split=0, m2l_batch=0, graph=False, timing=False, smooth_delta=0.0,
          stream=None, levelwise=False, p2p_targets=0, p2p_src_tile=0):
-    """levelwise: the far field's upward and downward passes level by level
-    (FMM_FLAG_LEVELWISE) instead of by subtrees.  p2p_split, p2p_targets,
+    """levelwise: the far field's downward pass level by level
+    (FMM_FLAG_LEVELWISE) instead of directly.  p2p_split, p2p_targets,
     p2p_src_tile, m2l_batch: the launch-shape knobs of fmm_tuning (0: auto)."""
     flags = ((FMM_FLAG_GRAPH if graph else 0) | (FMM_FLAG_PHASE_TIMING if timing else 0) |
              (FMM_FLAG_LEVELWISE if levelwise else 0))

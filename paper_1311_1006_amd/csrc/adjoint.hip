@@ -33,18 +33,6 @@
 
 namespace fmm {
 
-template <class T>
-void launch_p2m(const int32_t*, int, const int32_t*, const int32_t*, int, const double*, const double*,
-                const double*, const double*, int, void*, hipStream_t, const int32_t* = nullptr,
-                const double* = nullptr, const GatherOut* = nullptr);
-template <class T>
-void launch_m2m(const int32_t*, int, const int32_t*, const double*, const double*, int, void*, hipStream_t);
-template <class T>
-void launch_l2l(const int32_t*, int, const int32_t*, const double*, const double*, int, void*, hipStream_t);
-template <class T>
-void launch_m2l(const int32_t*, int, const int2*, int, const int32_t*, const int32_t*, double*, bool,
-                const int32_t*, const int32_t*, const int32_t*, const double*, const double*, int, const void*, void*,
-                hipStream_t, int, const long long*);
 void launch_gather(int64_t n, const int32_t* perm, const double* m, double* mtree, hipStream_t s);
 
 struct P2PItemA {
@@ -368,24 +356,7 @@ void adjoint_device(Plan& pl, const double* m, const double* gphi, double* gm, d
     check_launch("gather adjoint");
     // far chain on -gb: L2P^T (= P2M), L2L^T (= M2M), M2L^T (= -M2L), M2M^T (= L2L)
     const int nleaf = (int)sc.nleaf;
-    auto far = [&](auto tag) {
-        using T = decltype(tag);
-        launch_p2m<T>(ex.leaves.p, nleaf, sc.d_box_start.p, sc.d_box_count.p, ex.leaf_max, t.geom.p, t.x.p, t.y.p, ngb.p, pl.p,
-                      pl.amp.p, s);
-        for (int l = sc.max_levels - 2; l >= 1; --l) {
-            int nn = (int)(ex.m2m_off[l + 1] - ex.m2m_off[l]);
-            launch_m2m<T>(ex.d_m2m.p + ex.m2m_off[l], nn, ex.child0.p, t.geom.p, ex.binom.p, pl.p, pl.amp.p, s);
-        }
-        const Plan::Balance& bm = pl.bal_m2l;
-        launch_m2l<T>(nullptr, (int)sc.nbox, bm.xitems.p, (int)bm.total, bm.icnt.p, bm.ioff.p, bm.partial.p,
-                      bm.total > sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, pl.amp.p,
-                      pl.aloc.p, s, pl.tune.m2l_batch, nullptr);
-        for (int l = 1; l + 1 < sc.max_levels; ++l) {
-            int nn = (int)(ex.m2m_off[l + 1] - ex.m2m_off[l]);
-            launch_l2l<T>(ex.d_m2m.p + ex.m2m_off[l], nn, ex.child0.p, t.geom.p, ex.binom.p, pl.p, pl.aloc.p, s);
-        }
-    };
-    if (mixed) far(float()); else far(double());
+    transposed_far(pl, ngb.p, s);
     adjoint_near(pl, pl.gtree.p, false, s);
     // combination and scatter: G lanes per leaf, P terms held per lane
     const int G = ex.leaf_max <= 16 ? 16 : (ex.leaf_max <= 32 ? 32 : 64);

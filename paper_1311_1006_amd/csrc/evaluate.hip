@@ -1,14 +1,14 @@
 // evaluate.hip -- the FMM evaluation sequence (Sec. 2.1, Fig. 2.2) and the
 // host-side work lists of a plan.
 //
-//   gather  strengths to tree order (the P2P sources, with the tree's positions)
-//   P2M     leaves of every problem (does the gather when the leaves hold
-//           every point, which is the case for every tree this library builds)
-//   M2M     level by level, deepest parents first
+//   up      gather (strengths to tree order: the P2P sources, with the tree's
+//           positions), P2M at the leaves, M2M (subtree.hip)
 //   M2L     every box over its weak list (writes the box's local expansion)
-//   L2L     level by level from level 2 down (adds the parent's expansion)
 //   P2P     leaves over their strong lists (near field, tree order)
-//   L2P     leaves: far field + near field, scattered to input order
+//   down    L2L, and L2P at the leaves: far field + near field, scattered to
+//           input order (subtree.hip)
+// Problems of one or two levels have no M2M and no L2L: P2M and L2P at their
+// leaves only (expansions.hip).
 #include <algorithm>
 #include <cstring>
 #include <map>
@@ -21,32 +21,32 @@
 
 namespace fmm {
 
-void launch_gather(int64_t n, const int32_t* perm, const double* m, double* mtree, hipStream_t s);
 template <class T>
-void launch_p2m(const int32_t*, int, const int32_t*, const int32_t*, int, const double*, const double*,
-                const double*, const double*, int, void*, hipStream_t, const int32_t* = nullptr,
-                const double* = nullptr, const GatherOut* = nullptr);
+void launch_p2m(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
+                const double* geom, const double* X, const double* Y, const double* mt, int p, void* mp,
+                hipStream_t s, const GatherOut* go);
 template <class T>
-void launch_m2m(const int32_t*, int, const int32_t*, const double*, const double*, int, void*, hipStream_t);
-template <class T>
-void launch_l2l(const int32_t*, int, const int32_t*, const double*, const double*, int, void*, hipStream_t);
-template <class T>
-void launch_l2p(const int32_t*, int, const int32_t*, const int32_t*, int, const double*, const double*,
-                const double*, void*, int, const double*, const int32_t*, double*, double*, double*, hipStream_t,
-                const long long*, const int32_t*, const double*);
+void launch_l2p(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
+                const double* geom, const double* X, const double* Y, const void* loc, int p,
+                const double* nearf, const int32_t* perm, double* phi, double* phi_near, double* phi_far,
+                hipStream_t s, const long long* guard);
 template <class T>
 void launch_m2l(const int32_t*, int, const int2*, int, const int32_t*, const int32_t*, double*, bool,
                 const int32_t*, const int32_t*, const int32_t*, const double*, const double*, int, const void*, void*,
                 hipStream_t, int, const long long*);
 
-bool subtree_ok(int L, int p);
 template <class T>
-void launch_up_subtree(int nprob, int L, const int32_t* bstart, const int32_t* bcount, const double* geom,
-                       const double* X, const double* Y, const double* mt, int p, void* mp, const double* binom,
-                       const GatherOut* go, hipStream_t s, hipEvent_t after_leaves = nullptr);
+void launch_up_leaves(const SubPlan& sp, const int32_t* bstart, const int32_t* bcount, const double* geom,
+                      const double* X, const double* Y, const double* mt, int p, void* mp, const double* binom,
+                      const GatherOut* go, hipStream_t s);
 template <class T>
-void launch_down_subtree(int nprob, int L, const int32_t* bstart, const int32_t* bcount, const double* geom,
-                         const double* X, const double* Y, void* loc, int p, const double* nearf,
+void launch_up_mid(const SubPlan& sp, const double* geom, int p, void* mp, const double* fact, hipStream_t s);
+template <class T>
+void launch_down_mid(const SubPlan& sp, const double* geom, int p, void* loc, const double* binom,
+                     const long long* guard, hipStream_t s);
+template <class T>
+void launch_down_subtree(const SubPlan& sp, bool staged, const int32_t* bstart, const int32_t* bcount,
+                         const double* geom, const double* X, const double* Y, void* loc, int p, const double* nearf,
                          const int32_t* perm, double* phi, double* phi_near, double* phi_far, const long long* guard,
                          const double* binom, hipStream_t s);
 
@@ -85,12 +85,59 @@ static void upload_vec(DBuf<T>& d, const std::vector<T>& h, hipStream_t s)
         FMM_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
 }
 
+// the subtree launches of every pass: for a problem with levels 0 .. L-1, L >=
+// 3, the roots are the boxes of level L-3; upward steps go from there to level
+// 1, downward ones from level 1 to level L-4
+static void prepare_subtrees(const TreeSchedule& sc, SubPlan& sp, hipStream_t s)
+{
+    sp.uniform = sc.L[0] >= 3;
+    sp.L = sc.L[0];
+    std::vector<int32_t> shallow;
+    for (int b = 0; b < sc.nprob; ++b) {
+        sp.uniform = sp.uniform && sc.L[b] == sc.L[0];
+        if (sc.L[b] >= 3) continue;
+        const int64_t base = sc.pbox[b] + level_base(sc.L[b] - 1);
+        for (int64_t j = 0; j < int64_t(1) << (2 * (sc.L[b] - 1)); ++j) {
+            shallow.push_back((int32_t)(base + j));
+            sp.shallow_max = std::max(sp.shallow_max, (int)sc.box_count[base + j]);
+        }
+    }
+    sp.nshallow = (int)shallow.size();
+    std::vector<int4> list;
+    // one launch: for every problem the boxes of level lev(L), D(L) levels (D = 0: none)
+    auto step = [&](auto lev, auto D) {
+        SubStep st{(int64_t)list.size(), 0, lev(sp.L), D(sp.L)};
+        for (int b = 0; b < sc.nprob; ++b) {
+            const int l = lev(sc.L[b]), d = D(sc.L[b]);
+            if (d == 0) continue;
+            const int64_t n = int64_t(1) << (2 * l);
+            st.n += n;
+            if (!sp.uniform)
+                for (int64_t j = 0; j < n; ++j) list.push_back(make_int4((int)sc.pbox[b], l, (int)j, d));
+        }
+        return st;
+    };
+    sp.roots = step([](int L) { return L - 3; }, [](int L) { return L >= 3 ? 3 : 0; });
+    for (int h = 0; h < 2; ++h) {
+        const int m = h ? kSubLevelsHigh : kSubLevels;
+        for (int k = 0; m * k < sc.max_levels - 4; ++k) {
+            auto D = [m, k](int L) { return std::max(0, std::min(m, L - 4 - m * k)); };
+            sp.up[h].push_back(step([=](int L) { return std::max(0, L - 3 - m * k - D(L)); }, D));
+        }
+        for (int k = 0; 1 + m * k < sc.max_levels - 4; ++k)
+            sp.down[h].push_back(step([m, k](int) { return 1 + m * k; },
+                                      [m, k](int L) { return std::max(0, std::min(m, L - 4 - (1 + m * k))); }));
+    }
+    upload_vec(sp.shallow, shallow, s);
+    if (!sp.uniform) upload_vec(sp.list, list, s);
+    FMM_HIP(hipStreamSynchronize(s));   // the lists are locals
+}
+
 void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
 {
     TreeSchedule& sc = *pl.tree->sched;
     int ml = sc.max_levels;
     ex.level_boxes.assign(ml, {});
-    ex.m2m_boxes.assign(ml, {});
     std::vector<int32_t> leaves, child0(sc.nbox, -1);
     for (int b = 0; b < sc.nprob; ++b) {
         for (int l = 0; l < sc.L[b]; ++l) {
@@ -100,22 +147,12 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
                 ex.level_boxes[l].push_back(id);
                 if (l + 1 < sc.L[b]) {
                     child0[id] = (int32_t)(sc.pbox[b] + level_base(l + 1) + 4 * j);
-                    ex.m2m_boxes[l].push_back(id);
                 } else {
                     leaves.push_back(id);
                     ex.leaf_max = std::max(ex.leaf_max, (int)sc.box_count[id]);
                 }
             }
         }
-    }
-    {
-        bool same = sc.nprob > 0;
-        for (int b = 0; b < sc.nprob; ++b) same = same && sc.L[b] == sc.L[0];
-        ex.leaf_l2l_in_l2p = same && sc.L[0] >= 2;
-        ex.leaf_m2m_in_p2m = ex.leaf_l2l_in_l2p && ex.leaf_max <= 16;
-        int64_t covered = 0;
-        for (int32_t g : leaves) covered += sc.box_count[g];
-        ex.gather_in_p2m = covered == sc.n;
     }
     std::vector<int32_t> all;
     ex.level_boxes_off.assign(ml + 1, 0);
@@ -127,14 +164,6 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
     upload_vec(ex.d_level_boxes, all, s);
     upload_vec(ex.leaves, leaves, s);
     upload_vec(ex.child0, child0, s);
-    std::vector<int32_t> m2m;
-    ex.m2m_off.assign(ml + 1, 0);
-    for (int l = 0; l < ml; ++l) {
-        ex.m2m_off[l] = (int64_t)m2m.size();
-        m2m.insert(m2m.end(), ex.m2m_boxes[l].begin(), ex.m2m_boxes[l].end());
-    }
-    ex.m2m_off[ml] = (int64_t)m2m.size();
-    upload_vec(ex.d_m2m, m2m, s);
     // P2P work items grouped by launch shape
     const bool mixed = pl.precision == FMM_MIXED;
     std::map<std::pair<int, int>, std::vector<P2PItemH>> cls;
@@ -158,6 +187,7 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
         upload_vec(ex.p2p_items, raw, s);
     }
     prepare_adjoint_items(pl, ex, leaves, s);
+    prepare_subtrees(sc, ex.sub, s);
     // binomial table C(n, k), n < kBinomRows, k < kBinomStride (Pascal's rule)
     std::vector<double> bin(kBinomRows * kBinomStride, 0.0);
     for (int n = 0; n < kBinomRows; ++n) {
@@ -166,6 +196,17 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
             bin[n * kBinomStride + k] = bin[(n - 1) * kBinomStride + k - 1] + (k < n ? bin[(n - 1) * kBinomStride + k] : 0.0);
     }
     upload_vec(ex.binom, bin, s);
+    // factorials and their reciprocals, each rounded once from extended precision
+    std::vector<double> fact(2 * kMaxP);
+    {
+        long double f = 1.0L;
+        for (int k = 0; k < kMaxP; ++k) {
+            if (k > 0) f *= k;
+            fact[k] = (double)f;
+            fact[kMaxP + k] = (double)(1.0L / f);
+        }
+    }
+    upload_vec(ex.fact, fact, s);
     FMM_HIP(hipStreamSynchronize(s));
 }
 
@@ -181,65 +222,54 @@ void alloc_eval_buffers(Plan& pl, hipStream_t s)
     pl.local.alloc(2 * cs * sc.nbox * pl.p, s);
 }
 
-// whether P2M also forms the M2M of the leaves' parents
-static bool leaf_m2m(const Plan& pl, const PlanExtra& ex) { return ex.leaf_m2m_in_p2m && pl.p <= 32; }
-
-// whether the far field runs by subtrees (subtree.hip): every problem of the
-// same depth L >= 3, the leaves holding every point, p <= 32
-static bool use_subtree(const Plan& pl, const PlanExtra& ex)
+// Whether the subtrees' downward pass is staged (every box's complete
+// expansion formed from its parent's and stored, rounded to the storage type):
+// when it is asked for (`all`: the expansions of every level are read
+// afterwards; FMM_FLAG_LEVELWISE), for problems of unlike depth (a problem's
+// result is then the one it has alone with that flag, to the bit), and for
+// more than 32 terms in mixed precision.  Otherwise the direct form, one
+// launch.
+static bool staged_down(const Plan& pl, const PlanExtra& ex, bool all)
 {
-    const TreeSchedule& sc = *pl.tree->sched;
-    return ex.leaf_l2l_in_l2p && ex.gather_in_p2m && subtree_ok(sc.L[0], pl.p) &&
-           !(pl.tune.flags & FMM_FLAG_LEVELWISE);
+    return all || !ex.sub.uniform || (pl.tune.flags & FMM_FLAG_LEVELWISE) ||
+           (pl.precision == FMM_MIXED && pl.p > 32);
 }
 
-// the whole upward pass by subtrees, with the gather
+// The upward pass of the strengths m (input order), with their gather into tree
+// order, into the multipoles mp; or, without m, of the strengths mt (tree
+// order).  `after_gather` (optional) is recorded once the strengths are in
+// tree order: work that needs only them (the near field) may start.
 template <class T>
-static void run_up_subtree(Plan& pl, const double* m, hipStream_t s, hipEvent_t after_leaves = nullptr)
-{
-    Tree& t = *pl.tree;
-    TreeSchedule& sc = *t.sched;
-    GatherOut go{t.perm.p, (const double2*)m, (double2*)pl.mtree.p};
-    launch_up_subtree<T>(sc.nprob, sc.L[0], sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, pl.mtree.p,
-                         pl.p, pl.mpole.p, pl.ex->binom.p, &go, s, after_leaves);
-}
-
-// gather (own kernel, or inside P2M) and P2M; m = strengths in input order
-template <class T>
-static void run_p2m(Plan& pl, PlanExtra& ex, const double* m, hipStream_t s)
+static void run_up(Plan& pl, const double* m, const double* mt, void* mp, hipStream_t s,
+                   hipEvent_t after_gather = nullptr)
 {
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
-    const bool mixed = std::is_same<T, float>::value;
-    GatherOut go{t.perm.p, (const double2*)m, (double2*)pl.mtree.p};
-    if (!ex.gather_in_p2m)
-        launch_gather(sc.n, t.perm.p, m, pl.mtree.p, s);
-    // with leaf_m2m_in_p2m the P2M kernel also forms the leaves' parents
-    // (up to 32 terms: above that P2M runs in two blocks of terms)
-    const bool fm = leaf_m2m(pl, ex);
-    launch_p2m<T>(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p, sc.d_box_count.p, ex.leaf_max, t.geom.p, t.x.p, t.y.p,
-                  pl.mtree.p, pl.p, pl.mpole.p, s, fm ? sc.d_box_parent.p : nullptr, ex.binom.p,
-                  ex.gather_in_p2m ? &go : nullptr);
+    PlanExtra& ex = *extra(pl);
+    const GatherOut go{t.perm.p, (const double2*)m, (double2*)pl.mtree.p};
+    launch_up_leaves<T>(ex.sub, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, mt, pl.p, mp, ex.fact.p,
+                        m ? &go : nullptr, s);
+    launch_p2m<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max, t.geom.p,
+                  t.x.p, t.y.p, mt, pl.p, mp, s, m ? &go : nullptr);
+    if (after_gather) FMM_HIP(hipEventRecord(after_gather, s));
+    launch_up_mid<T>(ex.sub, t.geom.p, pl.p, mp, ex.fact.p, s);
 }
 
-// M2M above what P2M formed
+// The leaves of the downward pass: their complete expansions in loc, evaluated
+// at the points when an output is given
 template <class T>
-static void run_m2m(Plan& pl, PlanExtra& ex, void* mp, hipStream_t s)
+static void run_down_leaves(Plan& pl, bool staged, void* loc, double* phi, double* phi_near, double* phi_far,
+                            const long long* guard, hipStream_t s)
 {
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
-    const bool fm = leaf_m2m(pl, ex);
-    for (int l = sc.max_levels - (fm ? 3 : 2); l >= 1; --l) {
-        int n = (int)(ex.m2m_off[l + 1] - ex.m2m_off[l]);
-        launch_m2m<T>(ex.d_m2m.p + ex.m2m_off[l], n, ex.child0.p, t.geom.p, ex.binom.p, pl.p, mp, s);
-    }
+    PlanExtra& ex = *extra(pl);
+    launch_down_subtree<T>(ex.sub, staged, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, loc, pl.p,
+                           pl.near.p, t.perm.p, phi, phi_near, phi_far, guard, ex.fact.p, s);
+    if (phi || phi_near || phi_far)
+        launch_l2p<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max,
+                      t.geom.p, t.x.p, t.y.p, loc, pl.p, pl.near.p, t.perm.p, phi, phi_near, phi_far, s, guard);
 }
-
-struct PhaseTimer;
-
-template <class T>
-static void run_far_down(Plan& pl, PlanExtra& ex, const void* mp, void* loc, hipStream_t s, PhaseTimer& tm,
-                         const long long* guard, bool all_l2l = false);
 
 struct PhaseTimer {
     static constexpr int kEvents = 6;
@@ -269,85 +299,22 @@ struct PhaseTimer {
     }
 };
 
+// M2L into loc, and the staged downward pass's levels above the subtrees'
+// roots (the direct form takes every ancestor in its only launch); with `all`
+// the roots' subtrees too, so that the expansions of every level are complete.
 template <class T>
 static void run_far_down(Plan& pl, PlanExtra& ex, const void* mp, void* loc, hipStream_t s, PhaseTimer& tm,
-                         const long long* guard, bool all_l2l)
+                         const long long* guard, bool all = false)
 {
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
     const Plan::Balance& b = pl.bal_m2l;
-    // parents at level l (non-leaf) hand their expansion to level l+1; the
-    // hand-over into the leaves is done by L2P when every problem has the
-    // same depth (all_l2l: every level here, the leaves' expansions whole)
-    const int lend = sc.max_levels - (ex.leaf_l2l_in_l2p && !all_l2l ? 2 : 1);
-    // The top levels' chain (M2L of levels < cut, then the L2L steps among
-    // them) runs on a third stream beside the M2L of the deeper levels, which
-    // takes nearly all the work: every L2L step adds to a child's expansion
-    // after that child's M2L wrote it, and the children of those steps are
-    // all above the cut.  Lists split into chunks, and phase timing, keep the
-    // single launch.
-    const int cut = std::min(sc.max_levels - 3, 6);
-    if (use_subtree(pl, ex) && !all_l2l) {
-        // M2L only: the L2L hand-over is part of the subtree L2P.  The top
-        // levels' M2L (a small, latency-bound launch) runs on the third
-        // stream beside the deeper levels'.
-        if (!tm.on && b.xitems.p == nullptr && b.total == sc.nbox && cut >= 1) {
-            if (!pl.ev_top0) {
-                FMM_HIP(hipEventCreateWithFlags(&pl.ev_top0, hipEventDisableTiming));
-                FMM_HIP(hipEventCreateWithFlags(&pl.ev_top1, hipEventDisableTiming));
-            }
-            hipStream_t ts = side_stream(t.device, kTopStream);
-            const int na = (int)ex.level_boxes_off[cut];
-            const int nb = (int)(ex.level_boxes_off[sc.max_levels] - na);
-            FMM_HIP(hipEventRecord(pl.ev_top0, s));
-            FMM_HIP(hipStreamWaitEvent(ts, pl.ev_top0, 0));
-            launch_m2l<T>(ex.d_level_boxes.p, na, nullptr, na, nullptr, nullptr, nullptr, false, pl.w_beg.p,
-                          pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc, ts, pl.tune.m2l_batch, guard);
-            FMM_HIP(hipEventRecord(pl.ev_top1, ts));
-            launch_m2l<T>(ex.d_level_boxes.p + na, nb, nullptr, nb, nullptr, nullptr, nullptr, false, pl.w_beg.p,
-                          pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc, s, pl.tune.m2l_batch, guard);
-            FMM_HIP(hipStreamWaitEvent(s, pl.ev_top1, 0));
-        } else {
-            launch_m2l<T>(nullptr, (int)sc.nbox, b.xitems.p, (int)b.total, b.icnt.p, b.ioff.p, b.partial.p,
-                          b.total > sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc,
-                          s, pl.tune.m2l_batch, guard);
-        }
-        tm.mark();
-        return;
-    }
-    const int ltop = std::min(cut - 2, lend - 1);      // last parent level of the side chain
-    int lstart = 1;
-    if (!tm.on && b.xitems.p == nullptr && b.total == sc.nbox && ltop >= 1) {
-        if (!pl.ev_top0) {
-            FMM_HIP(hipEventCreateWithFlags(&pl.ev_top0, hipEventDisableTiming));
-            FMM_HIP(hipEventCreateWithFlags(&pl.ev_top1, hipEventDisableTiming));
-        }
-        hipStream_t ts = side_stream(t.device, kTopStream);
-        const int na = (int)ex.level_boxes_off[cut];   // boxes of levels 0 .. cut-1, all problems
-        const int nb = (int)(ex.level_boxes_off[sc.max_levels] - na);
-        FMM_HIP(hipEventRecord(pl.ev_top0, s));
-        FMM_HIP(hipStreamWaitEvent(ts, pl.ev_top0, 0));
-        launch_m2l<T>(ex.d_level_boxes.p, na, nullptr, na, nullptr, nullptr, nullptr, false, pl.w_beg.p, pl.w_cnt.p,
-                      pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc, ts, pl.tune.m2l_batch, guard);
-        for (int l = 1; l <= ltop; ++l) {
-            int n = (int)(ex.m2m_off[l + 1] - ex.m2m_off[l]);
-            launch_l2l<T>(ex.d_m2m.p + ex.m2m_off[l], n, ex.child0.p, t.geom.p, ex.binom.p, pl.p, loc, ts);
-        }
-        FMM_HIP(hipEventRecord(pl.ev_top1, ts));
-        launch_m2l<T>(ex.d_level_boxes.p + na, nb, nullptr, nb, nullptr, nullptr, nullptr, false, pl.w_beg.p,
-                      pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc, s, pl.tune.m2l_batch, guard);
-        FMM_HIP(hipStreamWaitEvent(s, pl.ev_top1, 0));
-        lstart = ltop + 1;
-    } else {
-        launch_m2l<T>(nullptr, (int)sc.nbox, b.xitems.p, (int)b.total, b.icnt.p, b.ioff.p, b.partial.p,
-                      b.total > sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc, s,
-                      pl.tune.m2l_batch, guard);
-    }
+    launch_m2l<T>(nullptr, (int)sc.nbox, b.xitems.p, (int)b.total, b.icnt.p, b.ioff.p, b.partial.p,
+                  b.total > sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc, s,
+                  pl.tune.m2l_batch, guard);
     tm.mark();
-    for (int l = lstart; l < lend; ++l) {
-        int n = (int)(ex.m2m_off[l + 1] - ex.m2m_off[l]);
-        launch_l2l<T>(ex.d_m2m.p + ex.m2m_off[l], n, ex.child0.p, t.geom.p, ex.binom.p, pl.p, loc, s);
-    }
+    if (staged_down(pl, ex, all)) launch_down_mid<T>(ex.sub, t.geom.p, pl.p, loc, ex.fact.p, guard, s);
+    if (all) run_down_leaves<T>(pl, true, loc, nullptr, nullptr, nullptr, guard, s);
 }
 
 void combine_chunks(const Plan::Balance& b, const void* items, int n, const int32_t* bstart, double* out,
@@ -400,10 +367,6 @@ void plan_events(Plan& pl)
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
     }
-    if (!pl.ev_top0) {
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_top0, hipEventDisableTiming));
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_top1, hipEventDisableTiming));
-    }
 }
 
 // The part of an evaluation that needs no lists: gather and the upward
@@ -420,16 +383,8 @@ void evaluate_upward(Plan& pl, const double* m, hipStream_t s)
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
     }
-    if (use_subtree(pl, ex)) {
-        if (mixed) run_up_subtree<float>(pl, m, s);
-        else run_up_subtree<double>(pl, m, s);
-    } else if (mixed) {
-        run_p2m<float>(pl, ex, m, s);
-        run_m2m<float>(pl, ex, pl.mpole.p, s);
-    } else {
-        run_p2m<double>(pl, ex, m, s);
-        run_m2m<double>(pl, ex, pl.mpole.p, s);
-    }
+    if (mixed) run_up<float>(pl, m, nullptr, pl.mpole.p, s);
+    else run_up<double>(pl, m, nullptr, pl.mpole.p, s);
     pl.upward_done = true;
 }
 
@@ -443,17 +398,33 @@ void far_field_all(Plan& pl, const double* m, hipStream_t s)
     PlanExtra& ex = *extra(pl);
     PhaseTimer tm(false, s);
     pl.upward_done = false;
-    if (pl.precision == FMM_MIXED) {
-        run_p2m<float>(pl, ex, m, s);
-        run_m2m<float>(pl, ex, pl.mpole.p, s);
-        run_far_down<float>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
-    } else {
-        run_p2m<double>(pl, ex, m, s);
-        run_m2m<double>(pl, ex, pl.mpole.p, s);
-        run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
-    }
+    auto far = [&](auto tag) {
+        using T = decltype(tag);
+        run_up<T>(pl, m, nullptr, pl.mpole.p, s);
+        run_far_down<T>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
+    };
+    if (pl.precision == FMM_MIXED) far(float());
+    else far(double());
     // the plan's buffers now hold the far field of m, not a forward evaluation
     pl.have_forward = false;
+}
+
+void transposed_far(Plan& pl, const double* w, hipStream_t s)
+{
+    Tree& t = *pl.tree;
+    TreeSchedule& sc = *t.sched;
+    PlanExtra& ex = *extra(pl);
+    PhaseTimer tm(false, s);
+    auto far = [&](auto tag) {
+        using T = decltype(tag);
+        run_up<T>(pl, nullptr, w, pl.amp.p, s);
+        // mixed: every level rounded to the storage type
+        const bool all = std::is_same<T, float>::value;
+        run_far_down<T>(pl, ex, pl.amp.p, pl.aloc.p, s, tm, nullptr, all);
+        if (!all) run_down_leaves<T>(pl, staged_down(pl, ex, false), pl.aloc.p, nullptr, nullptr, nullptr, nullptr, s);
+    };
+    if (pl.precision == FMM_MIXED) far(float());
+    else far(double());
 }
 
 void launch_real_to_complex(int64_t n, const double* q, double* m, hipStream_t s);
@@ -491,19 +462,13 @@ void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, do
     }
     launch_real_to_complex(sc.n, q, mlog, s);
     PhaseTimer tm(false, s);
-    if (mixed) run_p2m<float>(pl, ex, mlog, s);
-    else run_p2m<double>(pl, ex, mlog, s);
-    FMM_HIP(hipEventRecord(pl.ev_fork, s));
+    if (mixed) run_up<float>(pl, mlog, nullptr, pl.mpole.p, s, pl.ev_fork);
+    else run_up<double>(pl, mlog, nullptr, pl.mpole.p, s, pl.ev_fork);
     FMM_HIP(hipStreamWaitEvent(pl.nstream, pl.ev_fork, 0));
     run_p2p(pl, ex, pl.nstream, nullptr, true);
     FMM_HIP(hipEventRecord(pl.ev_join, pl.nstream));
-    if (mixed) {
-        run_m2m<float>(pl, ex, pl.mpole.p, s);
-        run_far_down<float>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
-    } else {
-        run_m2m<double>(pl, ex, pl.mpole.p, s);
-        run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
-    }
+    if (mixed) run_far_down<float>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
+    else run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
     auto constants = mixed ? launch_log_constants<float> : launch_log_constants<double>;
     constants((int)sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, pl.mpole.p, pl.local.p, pl.p,
               ex.d_level_boxes.p, ex.level_boxes_off, sc.max_levels, sc.d_box_parent.p, c0, s);
@@ -536,35 +501,25 @@ void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, d
     tm.mark();
     const bool up = pl.upward_done && overlap;   // gather and upward pass enqueued by evaluate_upward
     pl.upward_done = false;
-    const bool sub = use_subtree(pl, ex);
-    // by subtrees, the near field forks as soon as the leaves' kernel (which
-    // writes the strengths in tree order) is done, beside the upper levels' M2M
-    const bool early_fork = overlap && !up && sub;
+    // the near field forks as soon as the strengths are in tree order, beside
+    // the upper levels' M2M (forked after them, a batch of 128 problems took
+    // 1423 us instead of 1375, N = 1e5 at p = 39 176 instead of 171 us)
+    const bool early_fork = overlap && !up;
     if (!up) {
-        if (sub) {
-            hipEvent_t ev = early_fork ? pl.ev_fork : nullptr;
-            if (mixed) run_up_subtree<float>(pl, m, s, ev);
-            else run_up_subtree<double>(pl, m, s, ev);
-        } else if (mixed) {
-            run_p2m<float>(pl, ex, m, s);
-        } else {
-            run_p2m<double>(pl, ex, m, s);
-        }
+        hipEvent_t ev = early_fork ? pl.ev_fork : nullptr;
+        if (mixed) run_up<float>(pl, m, nullptr, pl.mpole.p, s, ev);
+        else run_up<double>(pl, m, nullptr, pl.mpole.p, s, ev);
     }
     if (overlap) {
         // the near field starts after everything enqueued on `s` so far: the
         // gather (with P2M), and the list and work-chunk kernels of the plan
-        // (which follow the upward pass when evaluate_upward ran first); or,
-        // by subtrees, after the leaves' kernel (the event recorded there)
+        // (which follow the upward pass when evaluate_upward ran first); or
+        // after the gather (the event recorded there)
         if (!early_fork) FMM_HIP(hipEventRecord(pl.ev_fork, s));
         FMM_HIP(hipStreamWaitEvent(pl.nstream, pl.ev_fork, 0));
         if (lists_ev) FMM_HIP(hipStreamWaitEvent(pl.nstream, lists_ev, 0));
         run_p2p(pl, ex, pl.nstream, guard);
         FMM_HIP(hipEventRecord(pl.ev_join, pl.nstream));
-    }
-    if (!up && !sub) {
-        if (mixed) run_m2m<float>(pl, ex, pl.mpole.p, s);
-        else run_m2m<double>(pl, ex, pl.mpole.p, s);
     }
     tm.mark();
     if (lists_ev) FMM_HIP(hipStreamWaitEvent(s, lists_ev, 0));
@@ -574,18 +529,8 @@ void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, d
     if (overlap) FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
     else run_p2p(pl, ex, s, nullptr);
     tm.mark();
-    if (sub) {
-        auto down = mixed ? launch_down_subtree<float> : launch_down_subtree<double>;
-        down(sc.nprob, sc.L[0], sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, pl.local.p, pl.p,
-             pl.near.p, t.perm.p, phi, phi_near, phi_far, guard, ex.binom.p, s);
-    } else if (mixed)
-        launch_l2p<float>(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p, sc.d_box_count.p, ex.leaf_max, t.geom.p, t.x.p, t.y.p,
-                          pl.local.p, pl.p, pl.near.p, t.perm.p, phi, phi_near, phi_far, s, guard,
-                          ex.leaf_l2l_in_l2p ? sc.d_box_parent.p : nullptr, ex.binom.p);
-    else
-        launch_l2p<double>(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p, sc.d_box_count.p, ex.leaf_max, t.geom.p, t.x.p, t.y.p,
-                           pl.local.p, pl.p, pl.near.p, t.perm.p, phi, phi_near, phi_far, s, guard,
-                          ex.leaf_l2l_in_l2p ? sc.d_box_parent.p : nullptr, ex.binom.p);
+    (mixed ? run_down_leaves<float> : run_down_leaves<double>)(pl, staged_down(pl, ex, false), pl.local.p, phi,
+                                                               phi_near, phi_far, guard, s);
     tm.mark();
     if (tm.on) {
         FMM_HIP(hipEventSynchronize(tm.ev[5]));

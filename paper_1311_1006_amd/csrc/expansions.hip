@@ -1,5 +1,6 @@
-// expansions.hip -- P2M, M2M, L2L, L2P and the point gathers (Sec. 2.1,
-// Fig. 2.2) on gfx950.
+// expansions.hip -- P2M and L2P of shallow problems (one or two levels: no
+// shift between levels; deeper ones: subtree.hip) and the point gathers (Sec.
+// 2.1, Fig. 2.2) on gfx950.
 //
 // Expansions are stored scaled by the box's scaling radius rs (its radius,
 // or the nearest ancestor's radius when it is 0):
@@ -10,7 +11,7 @@
 //     M2M  a^P_k = sum_{l<=k} C(k,l) rho^l tau^(k-l) a^C_l
 //     L2L  b^C_l = sum_{k>=l} C(k,l) rho^l tau^(k-l) b^P_k
 // with rho = rs_C / rs_P and tau = (c_C - c_P) / rs_P (both exact re-centrings
-// of the truncated series).  All four operators compute in FP64; T is the
+// of the truncated series; subtree.hip).  All four operators compute in FP64; T is the
 // storage type of the coefficients (double for the FP64 path, float for the
 // mixed path).
 #include "fmm_internal.h"
@@ -25,13 +26,6 @@ __global__ void k_gather(int64_t n, const int32_t* __restrict__ perm, const doub
     int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= n) return;
     mtree[i] = m[perm[i]];
-}
-
-__device__ __forceinline__ void wave_sync_e()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // P2M at the leaves.  G lanes per leaf (64/G leaves per wavefront, four
@@ -50,31 +44,12 @@ __device__ __forceinline__ double2 cpow(double2 b, int e)
     }
     return r;
 }
-__device__ __forceinline__ double rpow(double b, int e)
-{
-    double r = 1.0;
-    while (e) {
-        if (e & 1) r *= b;
-        b *= b;
-        e >>= 1;
-    }
-    return r;
-}
-
-// P2M (and with LEAF_M2M, G = 16, the M2M of the leaves' parents: a
-// wavefront holds four leaves, which are one sibling group when every
-// problem has the same depth; it then forms their parent's expansion with
-// the lane layout and the operations of k_m2m, from the children's
-// coefficients rounded to the storage type as k_m2m reads them, so that the
-// result does not depend on which kernel forms it).
-template <class T, int G, int P, bool LEAF_M2M, bool GATHER>
+template <class T, int G, int P, bool GATHER>
 __global__ void __launch_bounds__(256)
 k_p2m(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__ bstart,
       const int32_t* __restrict__ bcount, const double* __restrict__ geom, const double* __restrict__ X,
-      const double* __restrict__ Y, const double2* __restrict__ mt, int p, int k0, T* mp,
-      const int32_t* __restrict__ parent, const double* __restrict__ binom, GatherOut go)
+      const double* __restrict__ Y, const double2* __restrict__ mt, int p, int k0, T* mp, GatherOut go)
 {
-    static_assert(!LEAF_M2M || G == 16, "a sibling group per wavefront needs 16 lanes per leaf");
     constexpr int V = 2 * P;
     const int lane = threadIdx.x & 63;
     const int li = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / G) + lane / G;
@@ -126,164 +101,25 @@ k_p2m(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__
             if (k < p) mp[2 * ((int64_t)g * p + k) + (idx & 1)] = (T)v[i];
         }
     }
-    if constexpr (LEAF_M2M) {
-        __shared__ double2 coef[4][4][P], tau[4][4][P], part[4][4][P];
-        __shared__ double rho[4][4][P];
-        const int w = threadIdx.x >> 6, c = lane >> 4, j0 = lane & 15;
-        if (valid && writer) {
-#pragma unroll
-            for (int i = 0; i < NV; ++i) {
-                const int idx = base + i, k = idx >> 1;
-                if (k < p) {
-                    const double val = (double)(T)v[i];
-                    if (idx & 1) coef[w][c][k].y = val;
-                    else coef[w][c][k].x = val;
-                }
-            }
-        }
-        int pg = 0;
-        if (valid) {            // the four leaves of the wavefront are valid together
-            pg = parent[g];
-            const double* gp = geom + 4 * (int64_t)pg;
-            const double prs = gp[3];
-            const double r = geom[4 * (int64_t)g + 3] / prs;
-            const double2 t = make_double2((cx - gp[0]) / prs, (cy - gp[1]) / prs);
-            for (int j = j0; j < p; j += 16) {
-                tau[w][c][j] = cpow(t, j);
-                rho[w][c][j] = rpow(r, j);
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (valid) {
-            for (int k = j0; k < p; k += 16) {
-                double2 acc = make_double2(0, 0);
-                for (int l = 0; l <= k; ++l) {
-                    double s = binom[k * kBinomStride + l] * rho[w][c][l];
-                    double2 vv = cmul(coef[w][c][l], tau[w][c][k - l]);
-                    acc.x += s * vv.x;
-                    acc.y += s * vv.y;
-                }
-                part[w][c][k] = acc;
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (valid) {
-            for (int k = lane; k < p; k += 64) {
-                double2 v0 = part[w][0][k], v1 = part[w][1][k], v2 = part[w][2][k], v3 = part[w][3][k];
-                mp[2 * ((int64_t)pg * p + k)] = (T)(((v0.x + v1.x) + v2.x) + v3.x);
-                mp[2 * ((int64_t)pg * p + k) + 1] = (T)(((v0.y + v1.y) + v2.y) + v3.y);
-            }
-        }
-    }
-}
-
-
-// M2M into one parent from its four children.  Lane (c, j): c = lane/16
-// child, j = lane%16 (+16 for p > 16).  The children's coefficients and the
-// powers rho_c^j, tau_c^j are staged in LDS; each lane forms one child's
-// contribution to one coefficient; the four contributions are added in child
-// order.
-template <class T>
-__global__ void __launch_bounds__(64)
-k_m2m(const int32_t* __restrict__ parents, const int32_t* __restrict__ child0, const double* __restrict__ geom,
-      const double* __restrict__ binom, int p, T* mp)
-{
-    __shared__ double2 coef[4][kMaxP], tau[4][kMaxP], part[4][kMaxP];
-    __shared__ double rho[4][kMaxP];
-    const int P = parents[blockIdx.x];
-    const int lane = threadIdx.x, c = lane >> 4, j0 = lane & 15;
-    const int ch = child0[P] + c;
-    const double* gp = geom + 4 * (int64_t)P;
-    const double* gc = geom + 4 * (int64_t)ch;
-    const double prs = gp[3];
-    const double r = gc[3] / prs;
-    const double2 t = make_double2((gc[0] - gp[0]) / prs, (gc[1] - gp[1]) / prs);
-    const T* a = mp + 2 * (int64_t)ch * p;
-    for (int j = j0; j < p; j += 16) {
-        coef[c][j] = make_double2((double)a[2 * j], (double)a[2 * j + 1]);
-        tau[c][j] = cpow(t, j);
-        rho[c][j] = rpow(r, j);
-    }
-    __syncthreads();
-    for (int k = j0; k < p; k += 16) {
-        double2 acc = make_double2(0, 0);
-        for (int l = 0; l <= k; ++l) {
-            double s = binom[k * kBinomStride + l] * rho[c][l];
-            double2 v = cmul(coef[c][l], tau[c][k - l]);
-            acc.x += s * v.x;
-            acc.y += s * v.y;
-        }
-        part[c][k] = acc;
-    }
-    __syncthreads();
-    for (int k = lane; k < p; k += 64) {
-        double2 v0 = part[0][k], v1 = part[1][k], v2 = part[2][k], v3 = part[3][k];
-        mp[2 * ((int64_t)P * p + k)] = (T)(((v0.x + v1.x) + v2.x) + v3.x);
-        mp[2 * ((int64_t)P * p + k) + 1] = (T)(((v0.y + v1.y) + v2.y) + v3.y);
-    }
-}
-
-// L2L from one parent into its four children (lane (c, l) as in k_m2m)
-template <class T>
-__global__ void __launch_bounds__(64)
-k_l2l(const int32_t* __restrict__ parents, const int32_t* __restrict__ child0, const double* __restrict__ geom,
-      const double* __restrict__ binom, int p, T* loc)
-{
-    __shared__ double2 bp[kMaxP], tau[4][kMaxP];
-    const int P = parents[blockIdx.x];
-    const int lane = threadIdx.x, c = lane >> 4, j0 = lane & 15;
-    const int ch = child0[P] + c;
-    const double* gp = geom + 4 * (int64_t)P;
-    const double* gc = geom + 4 * (int64_t)ch;
-    const double prs = gp[3];
-    const double r = gc[3] / prs;
-    const double2 t = make_double2((gc[0] - gp[0]) / prs, (gc[1] - gp[1]) / prs);
-    const T* b = loc + 2 * (int64_t)P * p;
-    for (int j = lane; j < p; j += 64) bp[j] = make_double2((double)b[2 * j], (double)b[2 * j + 1]);
-    for (int j = j0; j < p; j += 16) tau[c][j] = cpow(t, j);
-    __syncthreads();
-    for (int l = j0; l < p; l += 16) {
-        double2 acc = make_double2(0, 0);
-        for (int k = l; k < p; ++k) {
-            double s = binom[k * kBinomStride + l];
-            double2 v = cmul(bp[k], tau[c][k - l]);
-            acc.x += s * v.x;
-            acc.y += s * v.y;
-        }
-        double rl = rpow(r, l);
-        T* o = loc + 2 * ((int64_t)ch * p + l);
-        o[0] = (T)((double)o[0] + rl * acc.x);
-        o[1] = (T)((double)o[1] + rl * acc.y);
-    }
 }
 
 // L2P at the leaves, plus the near field, scattered to input order.  G
 // lanes per leaf as in P2M; every lane holds the leaf's P coefficients (FP64)
 // and evaluates the series by Horner's rule at its points.
-// L2P (and with LEAF_L2L the L2L from the leaf's parent first: lane l of
-// the leaf's group forms rho^l sum_{k>=l} C(k, l) b_k(parent) tau^(k-l) with
-// the operations of k_l2l, adds it to coefficient l and stores the
-// completed coefficient, so that the leaf's local expansion in `loc` is
-// whole afterwards; the group shares the coefficients through LDS).
-template <class T, int G, int P, bool LEAF_L2L>
+template <class T, int G, int P>
 __global__ void __launch_bounds__(256)
 k_l2p(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__ bstart,
       const int32_t* __restrict__ bcount, const double* __restrict__ geom, const double* __restrict__ X,
-      const double* __restrict__ Y, T* loc, int p, const double2* __restrict__ nearf,
+      const double* __restrict__ Y, const T* __restrict__ loc, int p, const double2* __restrict__ nearf,
       const int32_t* __restrict__ perm, double2* phi, double2* phi_near, double2* phi_far,
-      const long long* __restrict__ guard, const int32_t* __restrict__ parent, const double* __restrict__ binom)
+      const long long* __restrict__ guard)
 {
     if (guard != nullptr && *guard != 0) return;   // lists flagged: this launch is void
     using T2 = typename Vec2<T>::type;
     // P = 64: the coefficients stay in LDS (64 complex FP64 values would
     // take every register of a lane); below that they go to registers
     constexpr bool kLdsCoef = P > 32;
-    __shared__ double2 sco[LEAF_L2L || kLdsCoef ? 256 / G : 1][LEAF_L2L || kLdsCoef ? P : 1];
-    __shared__ double2 stau[LEAF_L2L ? 256 / G : 1][LEAF_L2L ? P : 1];
+    __shared__ double2 sco[kLdsCoef ? 256 / G : 1][kLdsCoef ? P : 1];
     const int lane = threadIdx.x & 63;
     const int li = (blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / G) + lane / G;
     const int sl = lane % G;
@@ -291,55 +127,15 @@ k_l2p(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__
     const int g = leaves[li];
     const int st = bstart[g], n = bcount[g];
     const double cx = geom[4 * (int64_t)g], cy = geom[4 * (int64_t)g + 1], inv = 1.0 / geom[4 * (int64_t)g + 3];
-    T2* b = reinterpret_cast<T2*>(loc) + (int64_t)g * p;
+    const T2* b = reinterpret_cast<const T2*>(loc) + (int64_t)g * p;
     double2 bl[kLdsCoef ? 1 : P];
-    double2* co = sco[(LEAF_L2L || kLdsCoef) ? threadIdx.x / G : 0];
-    if constexpr (LEAF_L2L) {
-        const int pg = parent[g];
-        const double prs = geom[4 * (int64_t)pg + 3];
-        const double rho = geom[4 * (int64_t)g + 3] / prs;
-        const double2 tau = make_double2((cx - geom[4 * (int64_t)pg]) / prs, (cy - geom[4 * (int64_t)pg + 1]) / prs);
-        const T2* bp = reinterpret_cast<const T2*>(loc) + (int64_t)pg * p;
-        double2* tp = stau[threadIdx.x / G];
-        for (int j = sl; j < p; j += G) tp[j] = cpow(tau, j);   // the table of k_l2l
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        for (int l = sl; l < p; l += G) {
-            // the operations of k_l2l, in its order, so that the result does not
-            // depend on which of the two kernels hands the expansion over
-            double2 acc = make_double2(0, 0);
-            for (int k = l; k < p; ++k) {
-                const T2 bk = bp[k];
-                double s = binom[k * kBinomStride + l];
-                double2 v = cmul(make_double2((double)bk.x, (double)bk.y), tp[k - l]);
-                acc.x += s * v.x;
-                acc.y += s * v.y;
-            }
-            const double rl = rpow(rho, l);
-            const T2 own = b[l];
-            const T tx = (T)((double)own.x + rl * acc.x), ty = (T)((double)own.y + rl * acc.y);
-            b[l] = T2{tx, ty};
-            co[l] = make_double2((double)tx, (double)ty);
-        }
-        if constexpr (kLdsCoef)
-            for (int l = p + sl; l < P; l += G) co[l] = make_double2(0.0, 0.0);
-        // the group lies in one wavefront
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if constexpr (!kLdsCoef) {
-#pragma unroll
-            for (int k = 0; k < P; ++k) bl[k] = k < p ? co[k] : make_double2(0.0, 0.0);
-        }
-    } else if constexpr (kLdsCoef) {
+    double2* co = sco[kLdsCoef ? threadIdx.x / G : 0];
+    if constexpr (kLdsCoef) {
         for (int k = sl; k < P; k += G) {
             if (k < p) { const T2 v = b[k]; co[k] = make_double2((double)v.x, (double)v.y); }
             else co[k] = make_double2(0.0, 0.0);
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        wave_sync();   // the group lies in one wavefront
     } else {
 #pragma unroll
         for (int k = 0; k < P; ++k) {
@@ -389,12 +185,11 @@ static int leaf_lanes(int leaf_max) { return leaf_max <= 16 ? 16 : (leaf_max <= 
 template <class T>
 void launch_p2m(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
                 const double* geom, const double* X, const double* Y, const double* mt, int p, void* mp,
-                hipStream_t s, const int32_t* parent, const double* binom, const GatherOut* go)
+                hipStream_t s, const GatherOut* go)
 {
     const GatherOut none{};
     const GatherOut& gg = go ? *go : none;
     if (nleaf == 0) return;
-    if (p > 32 && parent) throw Error(FMM_EINVAL, "P2M with the leaves' M2M needs p <= 32");
     const int G = leaf_lanes(leaf_max);
     const int PB = p <= 16 ? 16 : 32;
     const unsigned grid = (unsigned)((nleaf + 4 * (64 / G) - 1) / (4 * (64 / G)));
@@ -405,23 +200,12 @@ void launch_p2m(const int32_t* leaves, int nleaf, const int32_t* bstart, const i
         const double2* mtk = (const double2*)(k0 == 0 ? mt : (go ? (const double*)go->mtree : mt));
 #define P2M_CASE(G_, P_)                                                                                   \
     if (G == G_ && PB == P_) {                                                                            \
-        if constexpr (G_ == 16)                                                                           \
-            if (parent) {                                                                                 \
-                if (gat)                                                                                  \
-                    k_p2m<T, G_, P_, true, true><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, \
-                        Y, mtk, p, k0, (T*)mp, parent, binom, gg);                                        \
-                else                                                                                      \
-                    k_p2m<T, G_, P_, true, false><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, \
-                        Y, mtk, p, k0, (T*)mp, parent, binom, gg);                                        \
-                check_launch("p2m");                                                                      \
-                continue;                                                                                 \
-            }                                                                                             \
         if (gat)                                                                                          \
-            k_p2m<T, G_, P_, false, true><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, \
-                mtk, p, k0, (T*)mp, nullptr, nullptr, gg);                                                \
+            k_p2m<T, G_, P_, true><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, mtk, p, \
+                                                        k0, (T*)mp, gg);                                  \
         else                                                                                              \
-            k_p2m<T, G_, P_, false, false><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, \
-                mtk, p, k0, (T*)mp, nullptr, nullptr, gg);                                                \
+            k_p2m<T, G_, P_, false><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, mtk, p, \
+                                                         k0, (T*)mp, gg);                                 \
         check_launch("p2m");                                                                              \
         continue;                                                                                         \
     }
@@ -432,44 +216,19 @@ void launch_p2m(const int32_t* leaves, int nleaf, const int32_t* bstart, const i
 }
 
 template <class T>
-void launch_m2m(const int32_t* parents, int n, const int32_t* child0, const double* geom, const double* binom,
-                int p, void* mp, hipStream_t s)
-{
-    if (n == 0) return;
-    k_m2m<T><<<n, 64, 0, s>>>(parents, child0, geom, binom, p, (T*)mp);
-    check_launch("m2m");
-}
-
-template <class T>
-void launch_l2l(const int32_t* parents, int n, const int32_t* child0, const double* geom, const double* binom,
-                int p, void* loc, hipStream_t s)
-{
-    if (n == 0) return;
-    k_l2l<T><<<n, 64, 0, s>>>(parents, child0, geom, binom, p, (T*)loc);
-    check_launch("l2l");
-}
-
-template <class T>
 void launch_l2p(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
-                const double* geom, const double* X, const double* Y, void* loc, int p,
+                const double* geom, const double* X, const double* Y, const void* loc, int p,
                 const double* nearf, const int32_t* perm, double* phi, double* phi_near, double* phi_far,
-                hipStream_t s, const long long* guard, const int32_t* parent, const double* binom)
+                hipStream_t s, const long long* guard)
 {
     if (nleaf == 0) return;
     const int G = leaf_lanes(leaf_max);
     const unsigned grid = (unsigned)((nleaf + 4 * (64 / G) - 1) / (4 * (64 / G)));
 #define L2P_CASE(G_, P_)                                                                                   \
     if (G == G_ && (p <= 16 ? 16 : (p <= 32 ? 32 : 64)) == P_) {                                          \
-        if (parent)                                                                                       \
-            k_l2p<T, G_, P_, true><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, (T*)loc, p, \
-                                                        (const double2*)nearf, perm, (double2*)phi,       \
-                                                        (double2*)phi_near, (double2*)phi_far, guard,     \
-                                                        parent, binom);                                   \
-        else                                                                                              \
-            k_l2p<T, G_, P_, false><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, (T*)loc, p, \
-                                                         (const double2*)nearf, perm, (double2*)phi,      \
-                                                         (double2*)phi_near, (double2*)phi_far, guard,    \
-                                                         nullptr, nullptr);                               \
+        k_l2p<T, G_, P_><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, (const T*)loc, p, \
+                                              (const double2*)nearf, perm, (double2*)phi,                 \
+                                              (double2*)phi_near, (double2*)phi_far, guard);              \
         check_launch("l2p");                                                                              \
         return;                                                                                           \
     }
@@ -482,15 +241,11 @@ void launch_l2p(const int32_t* leaves, int nleaf, const int32_t* bstart, const i
 #define INST(T)                                                                                          \
     template void launch_p2m<T>(const int32_t*, int, const int32_t*, const int32_t*, int, const double*, \
                                 const double*, const double*, const double*, int, void*, hipStream_t,    \
-                                const int32_t*, const double*, const GatherOut*);                        \
-    template void launch_m2m<T>(const int32_t*, int, const int32_t*, const double*, const double*, int,  \
-                                void*, hipStream_t);                                                     \
-    template void launch_l2l<T>(const int32_t*, int, const int32_t*, const double*, const double*, int,  \
-                                void*, hipStream_t);                                                     \
+                                const GatherOut*);                                                       \
     template void launch_l2p<T>(const int32_t*, int, const int32_t*, const int32_t*, int, const double*, \
-                                const double*, const double*, void*, int, const double*,                 \
+                                const double*, const double*, const void*, int, const double*,           \
                                 const int32_t*, double*, double*, double*, hipStream_t,                  \
-                                const long long*, const int32_t*, const double*);
+                                const long long*);
 INST(double)
 INST(float)
 #undef INST

@@ -274,7 +274,6 @@ struct Plan {
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
     hipStream_t nstream = nullptr;         // near-field stream of the device (shared, not owned)
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
-    hipEvent_t ev_top0 = nullptr, ev_top1 = nullptr;   // the top levels' far field on a third stream
 };
 
 // ---------------------------------------------------------- launchers
@@ -290,7 +289,7 @@ volatile long long* flag_slot_ptr(int slot);
 void flag_slot_release(int slot);
 void evaluate_upward(Plan& pl, const double* m, hipStream_t s);
 double rel_err2_device(const double* a, const double* ref, int64_t n, hipStream_t s);
-constexpr int kNearStream = 0, kListStream = 1, kTopStream = 2;
+constexpr int kNearStream = 0, kListStream = 1;
 hipStream_t side_stream(int device, int which);
 void plan_join(Plan& pl, hipStream_t s);
 void plan_events(Plan& pl);
@@ -322,6 +321,9 @@ struct GatherOut {
     const double2* m;        // strengths, input order
     double2* mtree;          // strengths, tree order
 };
+// the far-field chain of the strengths w (tree order, no gather) in the
+// adjoint's coefficient arrays, down to the leaves' local expansions
+void transposed_far(Plan& pl, const double* w, hipStream_t s);
 void adjoint_device(Plan& pl, const double* m, const double* gphi, double* gm, double* gz,
                     hipStream_t s);
 

@@ -11,25 +11,44 @@ struct P2PClass {
     int64_t off, n;     // range in the item array
 };
 
+// Subtree launches of the far field's upward and downward passes (subtree.hip).
+struct SubStep {
+    int64_t off, n;     // the launch's workgroups: entries off .. off + n - 1 of the list (or n computed ones)
+    int lev, D;         // trees of one depth: the level of the subtrees' roots, and their levels
+};
+constexpr int kSubLevels = 3, kSubLevelsHigh = 2;   // levels per launch above the roots, p <= 32 and more
+struct SubPlan {
+    bool uniform = false;       // every problem has the same depth L >= 3: no list
+    int L = 0;
+    DBuf<int4> list;            // (root box of the problem, level, box of the level, levels D) per workgroup
+    SubStep roots{};            // the boxes of level L-3 (problems of fewer levels: see shallow)
+    // [0] for p <= 32, [1] for more terms (fewer levels per launch):
+    std::vector<SubStep> up[2];    // levels L-4 .. 1, bottom up
+    std::vector<SubStep> down[2];  // levels 2 .. L-4 from level 1, top down
+    DBuf<int32_t> shallow;      // the leaves of the problems of one or two levels (no shifts between levels)
+    int nshallow = 0, shallow_max = 0;   // their number, and the largest one's points
+};
+// the same as a kernel argument
+struct SubWork {
+    const int4* list;
+    int lev, D, nper;           // without a list: every problem has NB boxes and nper subtrees of D levels
+    int64_t NB;                 // rooted at level lev
+};
+
 struct PlanExtra {
     std::vector<std::vector<int32_t>> level_boxes;  // global ids per level (all problems)
     std::vector<int64_t> level_boxes_off;
     DBuf<int32_t> d_level_boxes;                    // concatenated per level
     DBuf<int32_t> leaves;                           // global ids of all leaves
     int leaf_max = 0;                               // largest leaf population
-    bool leaf_l2l_in_l2p = false;                   // every problem has the same N_levels >= 2: the
-                                                    // L2L into the leaves runs inside L2P
-    bool leaf_m2m_in_p2m = false;                   // ... and no leaf holds more than 16 points: the
-                                                    // M2M of the leaves' parents runs inside P2M
-    bool gather_in_p2m = false;                     // the leaves hold every point: P2M does the gather
+    SubPlan sub;
     int cap_strong = 0, cap_weak = 0;               // per-box list capacities of the one-pass build
     bool levelwise_only = false;                    // a frontier overflowed on this layout
     int64_t pool_strong = 0, pool_weak = 0;        // id pool sizes for the next compact build
     bool compact_only = false;                      // fixed capacities would need too much memory
+    DBuf<double> fact;                              // k! for k < 64, then 1/k!
     DBuf<double> binom;                             // binomial table C(n, k), n, k < 64
-    std::vector<std::vector<int32_t>> m2m_boxes;   // non-leaf boxes per level
-    std::vector<int64_t> m2m_off;
-    DBuf<int32_t> d_m2m, child0;
+    DBuf<int32_t> child0;                           // first child of every box, -1: a leaf
     DBuf<char> p2p_items;
     std::vector<P2PClass> p2p_class;
     DBuf<char> adj_items;                           // adjoint P2P work items

@@ -1,192 +1,254 @@
 // subtree.hip -- the upward and downward passes of the far field (Sec. 2.1,
-// Fig. 2.2) by subtrees, for trees whose problems all have the same depth
-// L >= 3 and expansions of at most 32 terms.
+// Fig. 2.2) by subtrees, for trees whose problems have at least three levels.
+// L is a problem's number of levels; problems of one tree may differ in it.
 //
 // Expansions are the scaled ones of expansions.hip (multipole a_k and local
 // b_l in powers of (z - c)/rs); the shifts are the same exact re-centrings:
-//     M2M  a^P_k = sum_{l<=k} C(k,l) rho^l tau^(k-l) a^C_l
-//     L2L  b^C_l = rho^l sum_{k>=l} C(k,l) tau^(k-l) b^P_k
+//     M2M  a^P_k = k! sum_{l<=k} (a^C_l rho^l / l!) (tau^(k-l) / (k-l)!)
+//     L2L  b^C_l = (rho^l / l!) sum_{k>=l} (k! b^P_k) (tau^(k-l) / (k-l)!)
 // with rho = rs_C / rs_P and tau = (c_C - c_P) / rs_P, computed in FP64 (the
-// storage type T of the coefficients is float for mixed precision).
+// storage type T of the coefficients is float for mixed precision).  With the
+// binomial coefficients written as factorials the inner sums are plain
+// convolutions of two vectors in LDS: four FMAs and two 16-byte LDS reads per
+// term, where the sums with a binomial table took six FP64 operations and
+// three reads.  The tables tau^j / j! carry zeros in front, so that a block
+// of 16 terms that crosses the triangle's edge needs no test.
 //
 // Upward: one workgroup per box R of level L-3 forms the multipoles of its 16
 // leaves (P2M, with the gather of the strengths into tree order, which the
 // near field reads), of its 4 children and of R itself, all from LDS; then one
-// workgroup per box of level a forms the 3 levels a+2, a+1, a above the
-// level a+3 the previous launch wrote, until the root.  Three launches at
-// L = 9 instead of one per level.
+// workgroup per box of level a forms the levels a+D-1 .. a above the level a+D
+// that the previous launch wrote, until level 1 (nothing reads the root's
+// multipole).  Three launches at L = 9 instead of one per level.
 //
-// Downward: the local expansion of a box is its own M2L sum plus the L2L
-// image of its parent's complete expansion, hence plus the images, shifted
-// directly into the box, of the M2L sums of all its ancestors (the shifts
-// are exact, so the two forms agree up to rounding).  One workgroup per box R
-// of level L-3 shifts the M2L sums of R's ancestors (levels 0 .. L-4) into R,
-// one 16-lane group per ancestor, adds them to R's own, hands the result
-// down to R's 4 children and 16 leaves in LDS, stores every leaf's complete
-// expansion and evaluates it at the leaf's points (L2P), adding the near
-// field and scattering to input order.  There is no L2L launch.
+// Downward, direct form: the local expansion of a box is its own M2L sum plus
+// the L2L image of its parent's complete expansion, hence plus the images,
+// shifted directly into the box, of the M2L sums of all its ancestors (the
+// shifts are exact, so the two forms agree up to rounding).  One workgroup per
+// box R of level L-3 shifts the M2L sums of R's ancestors (levels 0 .. L-4)
+// into R, one 16-lane group per ancestor, adds them to R's own, hands the
+// result down to R's 4 children and 16 leaves in LDS, stores every leaf's
+// complete expansion and evaluates it at the leaf's points (L2P), adding the
+// near field and scattering to input order.  There is no L2L launch.
+//
+// Downward, staged form: every box's complete expansion is stored, rounded to
+// the storage type level by level.  One workgroup per box A of level a hands
+// A's complete expansion down D <= 3 levels (k_down_mid; from level 1 to level
+// L-4), then the kernel above takes R's parent as its only
+// ancestor and stores R and its children too.  It serves the evaluations that
+// read the expansions of every level (points apart from the sources, the
+// logarithmic constants), and the mixed-precision forms whose sums were always
+// rounded at every level (problems of unlike depth, more than 32 terms).
 #include <type_traits>
 
 #include "fmm_internal.h"
 #include "kernels_common.h"
+#include "plan_extra.h"
 
 namespace fmm {
 
-// b^e, e >= 0, by repeated squaring (the operations of the shift tables of
-// expansions.hip)
+// b^e, 0 <= e < 2^BITS, by repeated squaring, without branches
+template <int BITS>
 __device__ __forceinline__ double2 sub_cpow(double2 b, int e)
 {
     double2 r = make_double2(1.0, 0.0);
-    while (e) {
-        if (e & 1) r = cmul(r, b);
-        b = cmul(b, b);
-        e >>= 1;
+#pragma unroll
+    for (int i = 0; i < BITS; ++i) {
+        const double2 v = cmul(r, b);
+        r.x = (e >> i) & 1 ? v.x : r.x;
+        r.y = (e >> i) & 1 ? v.y : r.y;
+        if (i + 1 < BITS) b = cmul(b, b);
     }
     return r;
 }
+template <int BITS>
 __device__ __forceinline__ double sub_rpow(double b, int e)
 {
     double r = 1.0;
-    while (e) {
-        if (e & 1) r *= b;
-        b *= b;
-        e >>= 1;
+#pragma unroll
+    for (int i = 0; i < BITS; ++i) {
+        r = (e >> i) & 1 ? r * b : r;
+        if (i + 1 < BITS) b *= b;
     }
     return r;
 }
-
-// id of box j of level l of problem b, every problem holding NB boxes
-__device__ __forceinline__ int sub_box(int b, int64_t NB, int l, int64_t j)
-{
-    return (int)((int64_t)b * NB + level_base(l) + j);
-}
-
-// The binomial table C(k, l), k, l < P, into LDS (row k, column l), in two
-// steps so that other loads can be issued between them: the loads into
-// registers (all in flight before the first store), then the stores
 template <int P>
-struct BinomRegs {
-    static constexpr int R = (P * P + 255) / 256;   // blocks of 256 threads
-    double v[R];
+constexpr int kBits = P <= 16 ? 4 : P <= 32 ? 5 : 6;   // of an exponent below P
+
+// id of box j of level l of the problem whose root is box pb
+__device__ __forceinline__ int sub_box(int pb, int l, int64_t j) { return (int)(pb + level_base(l) + j); }
+
+// the subtree of this workgroup: box j of level `lev` of the problem whose root
+// is box pb, D levels; from the launch's list, or, when every problem has the
+// same depth, computed (one dependent load less)
+struct SubAt {
+    int pb, lev, D;
+    int64_t j;
 };
-template <int P>
-__device__ __forceinline__ BinomRegs<P> binom_load(const double* __restrict__ binom)
+__device__ __forceinline__ SubAt sub_at(const SubWork& w)
 {
-    BinomRegs<P> b;
-#pragma unroll
-    for (int r = 0; r < BinomRegs<P>::R; ++r) {
-        const int i = threadIdx.x + 256 * r;
-        b.v[r] = binom[(i < P * P ? i / P : 0) * kBinomStride + (i < P * P ? i % P : 0)];
+    if (w.list) {
+        const int4 v = w.list[blockIdx.x];
+        return SubAt{v.x, v.y, v.w, v.z};
     }
-    return b;
-}
-template <int P>
-__device__ __forceinline__ void binom_store(double (*sb)[P], const BinomRegs<P>& b)
-{
-#pragma unroll
-    for (int r = 0; r < BinomRegs<P>::R; ++r) {
-        const int i = threadIdx.x + 256 * r;
-        if (i < P * P) sb[i / P][i % P] = b.v[r];
-    }
-}
-template <int P>
-__device__ __forceinline__ void load_binom(double (*sb)[P], const double* __restrict__ binom)
-{
-    binom_store<P>(sb, binom_load<P>(binom));
+    const int b = blockIdx.x / w.nper;
+    return SubAt{(int)((int64_t)b * w.NB), w.lev, w.D, (int64_t)(blockIdx.x % w.nper)};
 }
 
-// M2M into one parent by one wavefront: lane (c, j), c = lane/16 the child,
-// forms child c's contribution to the coefficients k = j, j + 16 of the
-// parent; co[c] holds child c's coefficients (as stored, in FP64).  The
-// contributions land in part[c][k]; the caller adds them in child order.
-// The geometry an M2M step needs (centre and scaling radius of the parent
-// and of the lane's child), loaded ahead of the step.
-struct M2MGeo {
-    double px, py, prs, cx, cy, crs;
+// centre and scaling radius of a box
+struct SubGeo {
+    double x, y, rs;
 };
-__device__ __forceinline__ M2MGeo m2m_geo(const double* __restrict__ geom, int par, int child)
+__device__ __forceinline__ SubGeo sub_geo(const double* __restrict__ geom, int64_t box)
 {
-    const double* gp = geom + 4 * (int64_t)par;
-    const double* gc = geom + 4 * (int64_t)child;
-    return M2MGeo{gp[0], gp[1], gp[3], gc[0], gc[1], gc[3]};
+    return SubGeo{geom[4 * box], geom[4 * box + 1], geom[4 * box + 3]};
+}
+// tau and rho of the shift between a child and its parent
+__device__ __forceinline__ double2 sub_tau(const SubGeo& par, const SubGeo& ch)
+{
+    const double inv = 1.0 / par.rs;
+    return make_double2((ch.x - par.x) * inv, (ch.y - par.y) * inv);
 }
 
+// Factorials in the kernels' argument `fact`: fact[k] = k!, fact[64 + k] = 1/k!.
+constexpr int kInvFact = 64;
+
+// The table t_j = tau^j / j! of a shift, by a 16-lane group: t[16 + j], j < P
+// (zero for j >= p), zeros in t[0 .. 15]
 template <int P>
-__device__ __forceinline__ void m2m_wave(int p, const M2MGeo& g, const double2 (*co)[P], double2 (*tau)[P],
-                                         double (*rho)[P], double2 (*part)[P], const double (*sb)[P])
+__device__ __forceinline__ void shift_table(double2* t, double2 tau, int p, int sl, const double (&ifac)[P / 16])
 {
-    const int lane = threadIdx.x & 63, c = lane >> 4, j = lane & 15;
-    const double prs = g.prs;
-    const double r = g.crs / prs;
-    const double2 t = make_double2((g.cx - g.px) / prs, (g.cy - g.py) / prs);
-    for (int jj = j; jj < p; jj += 16) {
-        tau[c][jj] = sub_cpow(t, jj);
-        rho[c][jj] = sub_rpow(r, jj);
-    }
-    wave_sync();
-    // the sums run over the compile-time bound P (terms past k are skipped),
-    // so that their LDS loads are all issued before the first is used
-    for (int k = j; k < p; k += 16) {
-        double2 acc = make_double2(0.0, 0.0);
+    t[sl] = make_double2(0.0, 0.0);
 #pragma unroll
-        for (int l = 0; l < P; ++l) {
-            if (l <= k) {
-                const double s = sb[k][l] * rho[c][l];
-                const double2 v = cmul(co[c][l], tau[c][k - l]);
-                acc.x += s * v.x;
-                acc.y += s * v.y;
-            }
-        }
-        part[c][k] = acc;
+    for (int q = 0; q < P / 16; ++q) {
+        const int j = sl + 16 * q;
+        const double2 v = sub_cpow<kBits<P>>(tau, j);
+        const double f = j < p ? ifac[q] : 0.0;
+        t[16 + j] = make_double2(v.x * f, v.y * f);
     }
-    wave_sync();
 }
 
-// The parent's coefficient k (lane k < p) from the four contributions
-template <int P>
-__device__ __forceinline__ double2 m2m_sum(const double2 (*part)[P], int k)
+// acc += a b over real accumulators (xx - yy is the real part, xy + yx the imaginary)
+struct CAcc {
+    double xx = 0.0, yy = 0.0, xy = 0.0, yx = 0.0;
+    __device__ __forceinline__ void add(double2 a, double2 b)
+    {
+        xx = fma(a.x, b.x, xx);
+        yy = fma(a.y, b.y, yy);
+        xy = fma(a.x, b.y, xy);
+        yx = fma(a.y, b.x, yx);
+    }
+    __device__ __forceinline__ double2 value() const { return make_double2(xx - yy, xy + yx); }
+};
+
+// sum_{l <= k} a[l] t_(k-l), k = j + 16 q (blocks of 16 terms; the last one
+// crosses l = k, where the table's zeros end the sum)
+template <int P, int Q>
+__device__ __forceinline__ double2 m2m_conv(const double2* a, const double2* t, int j)
 {
-    const double2 v0 = part[0][k], v1 = part[1][k], v2 = part[2][k], v3 = part[3][k];
-    return make_double2(((v0.x + v1.x) + v2.x) + v3.x, ((v0.y + v1.y) + v2.y) + v3.y);
+    CAcc s;
+#pragma unroll
+    for (int l = 0; l < 16 * (Q + 1); ++l) s.add(a[l], t[16 + 16 * Q + j - l]);
+    return s.value();
+}
+// sum_{k >= l} b[k] t_(k-l), l = j + 16 q (the first block crosses k = l); with
+// STEP = 4 only the terms k = first mod 4 (a quarter of the sum per lane row)
+template <int P, int Q, int STEP>
+__device__ __forceinline__ double2 l2l_conv(const double2* b, const double2* t, int j, int first)
+{
+    CAcc s;
+#pragma unroll
+    for (int k = 16 * Q; k < P; k += STEP) s.add(b[k + first], t[16 + k + first - (j + 16 * Q)]);
+    return s.value();
+}
+// f(q, integral constant q) for q = 0 .. N-1, unrolled
+template <int N, class F>
+__device__ __forceinline__ void for_q(F&& f)
+{
+    f(std::integral_constant<int, 0>{});
+    if constexpr (N > 1) f(std::integral_constant<int, 1>{});
+    if constexpr (N > 2) f(std::integral_constant<int, 2>{});
+    if constexpr (N > 3) f(std::integral_constant<int, 3>{});
 }
 
+// store a coefficient in the storage type; the value as stored
 template <class T>
-__device__ __forceinline__ void store_coef(T* dst, int64_t box, int p, int k, double2 v, double2* mirror)
+__device__ __forceinline__ double2 store_coef(T* dst, int64_t box, int p, int k, double2 v)
 {
     const T tx = (T)v.x, ty = (T)v.y;
     dst[2 * (box * p + k)] = tx;
     dst[2 * (box * p + k) + 1] = ty;
-    if (mirror) *mirror = make_double2((double)tx, (double)ty);
+    return make_double2((double)tx, (double)ty);
+}
+
+// M2M into one parent by one wavefront: lane (c, j), c = lane/16 the child,
+// forms child c's contribution to the coefficients k = j + 16 q of the parent
+// from a[c][l] = a^C_l rho^l / l! and the table t[c]; the four contributions
+// are added by two row exchanges.  Coefficient k is stored (row q of the
+// lanes stores the block q); with `next`, scaled by f(k), also to LDS.
+template <class T, int P, class F>
+__device__ __forceinline__ void m2m_wave(int p, const double2 (*a)[P], const double2 (*t)[P + 16],
+                                         const double (&fac)[P / 16], T* mp, int64_t par, double2* next, F&& f)
+{
+    const int lane = threadIdx.x & 63, c = lane >> 4, j = lane & 15;
+    for_q<P / 16>([&](auto qc) {
+        constexpr int q = decltype(qc)::value;
+        const int k = j + 16 * q;
+        double2 v = m2m_conv<P, q>(a[c], t[c], j);
+        v.x += partner<16>(v.x);
+        v.y += partner<16>(v.y);
+        v.x += partner<32>(v.x);
+        v.y += partner<32>(v.y);
+        if (c == q) {
+            double2 r = make_double2(0.0, 0.0);
+            if (k < p) {
+                r = store_coef<T>(mp, par, p, k, make_double2(fac[q] * v.x, fac[q] * v.y));
+                if (next) {
+                    const double s = f(k, q);
+                    r.x *= s;
+                    r.y *= s;
+                }
+            }
+            if (next) next[k] = r;
+        }
+    });
 }
 
 // ------------------------------------------------------------------ upward
 
-// One workgroup per box R of level L-3 (nroot per problem): P2M of its 16
-// leaves (16 lanes per leaf, the transposing butterfly of k_p2m), M2M into
-// its 4 children (one wavefront each) and into R (wavefront 0).
+// One workgroup per box R of level L-3: P2M of its 16 leaves (16 lanes per
+// leaf, a transposing butterfly), M2M into its 4 children (one wavefront each,
+// from the wavefront's own four leaves) and into R (wavefront 0).  N = 2e5,
+// L = 7, p = 16: 10 us (12.5 us with a binomial table); p = 39, N = 1e5: 14 us,
+// where two P2M and two M2M launches took 40 us.
 template <class T, int P, bool GATHER>
 __global__ void __launch_bounds__(256)
-k_up_leaf(int L, int64_t NB, int nroot, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
+k_up_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
           const double* __restrict__ geom, const double* __restrict__ X, const double* __restrict__ Y,
-          const double2* __restrict__ mt, int p, T* mp, const double* __restrict__ binom, GatherOut go)
+          const double2* __restrict__ mt, int p, T* mp, const double* __restrict__ fact, GatherOut go)
 {
-    constexpr int V = 2 * P;
-    __shared__ double sb[P][P];
-    __shared__ double2 sco[16][P];        // the leaves' coefficients (as stored)
-    __shared__ double2 spar[4][P];        // the children of R (as stored)
-    __shared__ double2 stau[4][4][P];     // per wavefront: tau^j of its four children
-    __shared__ double srho[4][4][P];
-    __shared__ double2 spart[4][4][P];    // per wavefront: the children's contributions
+    constexpr int V = 2 * P, KP = P / 16;
+    __shared__ double2 sco[16][P];        // the leaves' coefficients (as stored) times rho^l / l!
+    __shared__ double2 st_[16][P + 16];   // their shift tables
+    __shared__ double2 spar[4][P];        // the same of the children of R
+    __shared__ double2 stp[4][P + 16];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int gl = threadIdx.x >> 4, sl = threadIdx.x & 15;
-    const int b = blockIdx.x / nroot;
-    const int64_t jR = blockIdx.x % nroot;
-    const int R = sub_box(b, NB, L - 3, jR);
-    const int leaf = sub_box(b, NB, L - 1, 16 * jR + gl);
-    const BinomRegs<P> bin = binom_load<P>(binom);   // stored to LDS after P2M
+    const SubAt at = sub_at(work);
+    const int R = sub_box(at.pb, at.lev, at.j);
+    const int leaf = sub_box(at.pb, at.lev + 2, 16 * at.j + gl);
+    const int cw = sub_box(at.pb, at.lev + 1, 4 * at.j + w);
     const int st = bstart[leaf], n = bcount[leaf];
-    const double cx = geom[4 * (int64_t)leaf], cy = geom[4 * (int64_t)leaf + 1];
-    const double inv = 1.0 / geom[4 * (int64_t)leaf + 3];
+    const SubGeo gf = sub_geo(geom, leaf), gc = sub_geo(geom, cw), gR = sub_geo(geom, R);
+    const int base = treduce_base<V, 16>(sl) >> 1;   // the coefficients base .. base + KP - 1 end in this lane
+    double fac[KP], ifac[KP], ifb[KP];
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+        fac[q] = fact[sl + 16 * q];
+        ifac[q] = fact[kInvFact + sl + 16 * q];
+        ifb[q] = fact[kInvFact + base + q];
+    }
+    const double inv = 1.0 / gf.rs;
     double v[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) v[i] = 0.0;
@@ -197,10 +259,10 @@ k_up_leaf(int L, int64_t NB, int nroot, const int32_t* __restrict__ bstart, cons
             const double2 mm = go.m[go.perm[i]];
             const double x = X[i], y = Y[i];
             go.mtree[i] = mm;
-            z = make_double2((x - cx) * inv, (y - cy) * inv);
+            z = make_double2((x - gf.x) * inv, (y - gf.y) * inv);
             t = mm;
         } else {
-            z = make_double2((X[i] - cx) * inv, (Y[i] - cy) * inv);
+            z = make_double2((X[i] - gf.x) * inv, (Y[i] - gf.y) * inv);
             t = mt[i];
         }
 #pragma unroll
@@ -211,103 +273,139 @@ k_up_leaf(int L, int64_t NB, int nroot, const int32_t* __restrict__ bstart, cons
         }
     }
     treduce<V, 16>(v, lane);
-    const int base = treduce_base<V, 16>(sl);
+    const double rl = gf.rs / gc.rs;
 #pragma unroll
-    for (int i = 0; i < V / 16; ++i) {
-        const int idx = base + i, k = idx >> 1;
+    for (int i = 0; i < KP; ++i) {
+        const int k = base + i;
+        double2 c = make_double2(0.0, 0.0);
         if (k < p) {
-            const T tv = (T)v[i];
-            mp[2 * ((int64_t)leaf * p + k) + (idx & 1)] = tv;
-            if (idx & 1) sco[gl][k].y = (double)tv;
-            else sco[gl][k].x = (double)tv;
+            c = store_coef<T>(mp, leaf, p, k, make_double2(v[2 * i], v[2 * i + 1]));
+            const double s = sub_rpow<kBits<P>>(rl, k) * ifb[i];
+            c.x *= s;
+            c.y *= s;
         }
+        sco[gl][k] = c;
     }
-    binom_store<P>(sb, bin);
-    __syncthreads();   // the binomial table; the leaves of each wavefront are its own lanes'
+    shift_table<P>(st_[gl], sub_tau(gc, gf), p, sl, ifac);
+    if ((lane >> 4) == 0) shift_table<P>(stp[w], sub_tau(gR, gc), p, sl, ifac);
+    wave_sync();   // the four leaves of a wavefront are its own lanes'
     // the children of R: wavefront w forms child w from leaves 4w .. 4w+3
-    const int cw = sub_box(b, NB, L - 2, 4 * jR + w);
-    m2m_wave<P>(p, m2m_geo(geom, cw, sub_box(b, NB, L - 1, 16 * jR + 4 * w + (lane >> 4))), sco + 4 * w, stau[w],
-                srho[w], spart[w], sb);
-    for (int k = lane; k < p; k += 64) store_coef<T>(mp, cw, p, k, m2m_sum<P>(spart[w], k), &spar[w][k]);
+    const double rc = gc.rs / gR.rs;
+    m2m_wave<T, P>(p, sco + 4 * w, st_ + 4 * w, fac, mp, cw, spar[w],
+                   [&](int k, int q) { return sub_rpow<kBits<P>>(rc, k) * ifac[q]; });
     __syncthreads();
-    if (w == 0) {
-        m2m_wave<P>(p, m2m_geo(geom, R, sub_box(b, NB, L - 2, 4 * jR + (lane >> 4))), spar, stau[0], srho[0],
-                    spart[0], sb);
-        for (int k = lane; k < p; k += 64) store_coef<T>(mp, R, p, k, m2m_sum<P>(spart[0], k), nullptr);
-    }
+    if (w == 0) m2m_wave<T, P>(p, spar, stp, fac, mp, R, nullptr, [](int, int) { return 0.0; });
 }
 
-// One workgroup per box A of level a (nper per problem): the multipoles of
-// levels a+D-1 .. a of A's subtree from those of level a+D (D <= 3).
-template <class T, int P>
-__global__ void __launch_bounds__(256)
-k_up_mid(int a, int D, int64_t NB, int nper, const double* __restrict__ geom, int p, T* mp,
-         const double* __restrict__ binom)
+// The geometry and the shift tables of the boxes under A, levels a .. a+D
+// (slot s = (4^d - 1)/3 + i holds box i of level a+d; slots 1 .. are the
+// children), by NT threads: every geometry record loaded once, the tables by
+// 16-lane groups.
+template <int NS>
+struct SubBoxes {
+    double g[NS][3];
+};
+template <int NT, int NS>
+__device__ __forceinline__ void sub_boxes(SubBoxes<NS>& sg, const SubAt& at, const double* __restrict__ geom, int ngeo)
 {
-    __shared__ double sb[P][P];
-    __shared__ double2 sc0[64][P];
-    __shared__ double2 sc1[16][P];
-    __shared__ double2 stau[4][4][P];
-    __shared__ double srho[4][4][P];
-    __shared__ double2 spart[4][4][P];
-    __shared__ double sg[85][3];          // centre and scaling radius of the boxes under A
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int b = blockIdx.x / nper;
-    const int64_t jA = blockIdx.x % nper;
-    const BinomRegs<P> bin = binom_load<P>(binom);
-    // the geometry of A's subtree, levels a .. a+D (at most 85 boxes), loaded
-    // once for all the M2M steps: slot t = (4^d - 1)/3 + i holds box i of
-    // level a+d under A (a thread past the last slot loads the last again)
-    const int ngeo = ((4 << (2 * D)) - 1) / 3;
-    double gv[3];
-    {
-        const int t = min((int)threadIdx.x, ngeo - 1);
+    const int s = threadIdx.x;
+    if (s < ngeo) {
         int d = 0, base = 0;
-        while (t >= base + (1 << (2 * d))) {
+        while (s >= base + (1 << (2 * d))) {
             base += 1 << (2 * d);
             ++d;
         }
-        const int64_t box = sub_box(b, NB, a + d, ((int64_t)jA << (2 * d)) + (t - base));
-        gv[0] = geom[4 * box];
-        gv[1] = geom[4 * box + 1];
-        gv[2] = geom[4 * box + 3];
+        const SubGeo g = sub_geo(geom, sub_box(at.pb, at.lev + d, (at.j << (2 * d)) + (s - base)));
+        sg.g[s][0] = g.x;
+        sg.g[s][1] = g.y;
+        sg.g[s][2] = g.rs;
     }
-    // level a+D: 4^D <= 64 boxes, all loads in flight before the first store
-    const int nin = 1 << (2 * D);
-    constexpr int R = 64 * P / 256;
-    double2 v[R];
+}
+template <int NS>
+__device__ __forceinline__ SubGeo sub_slot(const SubBoxes<NS>& sg, int s)
+{
+    return SubGeo{sg.g[s][0], sg.g[s][1], sg.g[s][2]};
+}
+
+// Levels of a subtree launch and its workgroup: up to three levels and 16
+// wavefronts (a wavefront per parent of the widest step) for p <= 32, two
+// levels and four wavefronts for more terms (their tables take the LDS).
+template <int P>
+constexpr int kSubD = P <= 32 ? kSubLevels : kSubLevelsHigh;
+template <int P>
+constexpr int kSubThreads = P <= 32 ? 1024 : 256;
+template <int P>
+constexpr int kSubSlots = ((4 << (2 * kSubD<P>)) - 1) / 3;      // boxes under A, A itself first
+
+// One workgroup per box A of level a: the multipoles of levels a+D-1 .. a of
+// A's subtree from those of level a+D.  A chain of D dependent steps on few
+// workgroups (64 at L = 9): latency is all of it, so the geometry, the shift
+// tables and the scale factors of every box are formed first, all at once,
+// and a step is a convolution, two row exchanges and a store; 16 wavefronts
+// take the 16 parents of the widest step together.  Both launches at N = 1e5,
+// L = 7, p = 16: 7 us (21 us with four wavefronts, and powers and divisions
+// formed in every step); p = 39: 34 us beside the near field (63 us).
+template <class T, int P>
+__global__ void __launch_bounds__(kSubThreads<P>)
+k_up_mid(SubWork work, const double* __restrict__ geom, int p, T* mp, const double* __restrict__ fact)
+{
+    constexpr int NT = kSubThreads<P>, NS = kSubSlots<P>, KP = P / 16, NG = NT / 16;
+    constexpr int NIN = 1 << (2 * kSubD<P>);
+    __shared__ SubBoxes<NS> sg;
+    __shared__ double2 tab[NS][P + 16];
+    __shared__ double sf[NS][P];          // rho^k / k! of every child slot
+    __shared__ double2 sc0[NIN][P], sc1[NIN / 4][P];
+    const int w = threadIdx.x >> 6, gl = threadIdx.x >> 4, sl = threadIdx.x & 15;
+    const SubAt at = sub_at(work);
+    const int a = at.lev, D = at.D;
+    const int ngeo = ((4 << (2 * D)) - 1) / 3, nin = 1 << (2 * D);
+    double fac[KP], ifac[KP];
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int i = threadIdx.x + 256 * r;
-        const int c = i / P, k = i % P;
-        v[r] = make_double2(0.0, 0.0);
-        if (c < nin && k < p) {
-            const int64_t box = sub_box(b, NB, a + D, ((int64_t)jA << (2 * D)) + c);
-            v[r] = make_double2((double)mp[2 * (box * p + k)], (double)mp[2 * (box * p + k) + 1]);
+    for (int q = 0; q < KP; ++q) {
+        fac[q] = fact[sl + 16 * q];
+        ifac[q] = fact[kInvFact + sl + 16 * q];
+    }
+    // level a+D, a 16-lane group per box, all loads in flight before the first use
+    constexpr int R = (NIN + NG - 1) / NG;
+    double2 v[R][KP];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < KP; ++q) {
+            const int64_t box = sub_box(at.pb, a + D, (at.j << (2 * D)) + min(gl + NG * r, nin - 1));
+            const int k = min(sl + 16 * q, p - 1);
+            v[r][q] = make_double2((double)mp[2 * (box * p + k)], (double)mp[2 * (box * p + k) + 1]);
         }
-    }
-    binom_store<P>(sb, bin);
-    if ((int)threadIdx.x < ngeo)
-        for (int e = 0; e < 3; ++e) sg[threadIdx.x][e] = gv[e];
+    sub_boxes<NT>(sg, at, geom, ngeo);
+    __syncthreads();
+    for (int s = 1 + gl; s < ngeo; s += NG) {
+        const SubGeo gc = sub_slot(sg, s), gp = sub_slot(sg, (s - 1) >> 2);
+        shift_table<P>(tab[s], sub_tau(gp, gc), p, sl, ifac);
+        const double rho = gc.rs / gp.rs;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-        const int i = threadIdx.x + 256 * r;
-        const int c = i / P, k = i % P;
-        if (c < nin && k < p) sc0[c][k] = v[r];
+        for (int q = 0; q < KP; ++q) sf[s][sl + 16 * q] = sub_rpow<kBits<P>>(rho, sl + 16 * q) * ifac[q];
     }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int q = 0; q < KP; ++q) {
+            const int c = gl + NG * r, k = sl + 16 * q;
+            if (c < nin) {
+                const double s = k < p ? sf[ngeo - nin + c][k] : 0.0;
+                sc0[c][k] = make_double2(s * v[r][q].x, s * v[r][q].y);
+            }
+        }
     __syncthreads();
     double2 (*cur)[P] = sc0;
     double2 (*nxt)[P] = sc1;
     for (int d = D - 1; d >= 0; --d) {
-        const int lv = a + d, np = 1 << (2 * d);   // parents at level lv under A
-        for (int q = w; q < np; q += 4) {
-            const int par = sub_box(b, NB, lv, ((int64_t)jA << (2 * d)) + q);
-            const double* gp = sg[((1 << (2 * d)) - 1) / 3 + q];
-            const double* gc = sg[((4 << (2 * d)) - 1) / 3 + 4 * q + (lane >> 4)];
-            m2m_wave<P>(p, M2MGeo{gp[0], gp[1], gp[2], gc[0], gc[1], gc[2]}, cur + 4 * q, stau[w], srho[w], spart[w],
-                        sb);
-            for (int k = lane; k < p; k += 64) store_coef<T>(mp, par, p, k, m2m_sum<P>(spart[w], k), &nxt[q][k]);
-            wave_sync();   // spart is rewritten by the next parent of this wavefront
+        const int np = 1 << (2 * d), s0 = ((1 << (2 * d)) - 1) / 3;   // parents at level a+d, the first one's slot
+        for (int q = w; q < np; q += NT / 64) {
+            const int par = sub_box(at.pb, a + d, (at.j << (2 * d)) + q);
+            const double* f = sf[s0 + q];
+            m2m_wave<T, P>(p, cur + 4 * q, tab + (4 * (s0 + q) + 1), fac, mp, par, d > 0 ? nxt[q] : nullptr,
+                           [&](int k, int) { return f[k]; });
         }
         __syncthreads();
         double2 (*tmp)[P] = cur;
@@ -318,181 +416,242 @@ k_up_mid(int a, int D, int64_t NB, int nper, const double* __restrict__ geom, in
 
 // ---------------------------------------------------------------- downward
 
-// One workgroup per box R of level L-3.  See the file header.
+// One workgroup per box A of level a, whose complete expansion is stored: the
+// complete expansions of the D levels below A, every one its own M2L sum plus
+// its parent's image, rounded to T as it is stored.  Latency is all of it, as
+// in k_up_mid: loads and tables first, then a 16-lane group per child.  One
+// launch of 5 us at L = 7, p = 16, where a launch per level took 24 us.
+template <class T, int P>
+__global__ void __launch_bounds__(kSubThreads<P>)
+k_down_mid(SubWork work, const double* __restrict__ geom, int p, T* loc, const double* __restrict__ fact,
+           const long long* __restrict__ guard)
+{
+    if (guard != nullptr && *guard != 0) return;   // lists flagged: this launch is void
+    using T2 = typename Vec2<T>::type;
+    constexpr int NT = kSubThreads<P>, NS = kSubSlots<P>, KP = P / 16, NG = NT / 16, DM = kSubD<P>;
+    __shared__ SubBoxes<NS> sg;
+    __shared__ double2 tab[NS][P + 16];
+    __shared__ double2 sp[2][1 << (2 * (DM - 1))][P];   // k! b_k of the parents of a step, in turn
+    const int gl = threadIdx.x >> 4, sl = threadIdx.x & 15;
+    const SubAt at = sub_at(work);
+    const int a = at.lev, D = at.D;
+    const T2* lo = reinterpret_cast<const T2*>(loc);
+    const int ngeo = ((4 << (2 * D)) - 1) / 3;
+    double fac[KP], ifac[KP];
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+        fac[q] = fact[sl + 16 * q];
+        ifac[q] = fact[kInvFact + sl + 16 * q];
+    }
+    // A's expansion, and the M2L sums of the child this group takes in every
+    // step (indices clamped into the subtree)
+    T2 ca[KP], cs[DM][KP];
+#pragma unroll
+    for (int q = 0; q < KP; ++q) {
+        const int k = min(sl + 16 * q, p - 1);
+        ca[q] = lo[(int64_t)sub_box(at.pb, a, at.j) * p + k];
+#pragma unroll
+        for (int d = 1; d <= DM; ++d) {
+            const int dd = min(d, D);
+            cs[d - 1][q] = lo[(int64_t)sub_box(at.pb, a + dd, (at.j << (2 * dd)) + min(gl, (1 << (2 * dd)) - 1)) * p + k];
+        }
+    }
+    sub_boxes<NT>(sg, at, geom, ngeo);
+    __syncthreads();
+    for (int s = 1 + gl; s < ngeo; s += NG)
+        shift_table<P>(tab[s], sub_tau(sub_slot(sg, (s - 1) >> 2), sub_slot(sg, s)), p, sl, ifac);
+    if (gl == 0)
+#pragma unroll
+        for (int q = 0; q < KP; ++q) {
+            const double f = sl + 16 * q < p ? fac[q] : 0.0;
+            sp[0][0][sl + 16 * q] = make_double2(f * (double)ca[q].x, f * (double)ca[q].y);
+        }
+    __syncthreads();
+    static_assert((1 << (2 * DM)) <= NG, "a group per child of the widest step");
+#pragma unroll
+    for (int d = 1; d <= DM; ++d) {
+        if (d > D) break;               // uniform
+        if (gl < 1 << (2 * d)) {
+            const int s = ((1 << (2 * d)) - 1) / 3 + gl;
+            const double rho = sg.g[s][2] / sg.g[(s - 1) >> 2][2];
+            const int64_t box = sub_box(at.pb, a + d, (at.j << (2 * d)) + gl);
+            for_q<KP>([&](auto qc) {
+                constexpr int q = decltype(qc)::value;
+                const int l = sl + 16 * q;
+                const double2 v = l2l_conv<P, q, 1>(sp[(d - 1) & 1][gl >> 2], tab[s], sl, 0);
+                double2 r = make_double2(0.0, 0.0);
+                if (l < p) {
+                    const double f = sub_rpow<kBits<P>>(rho, l) * ifac[q];
+                    r = store_coef<T>(loc, box, p, l, make_double2(fma(f, v.x, (double)cs[d - 1][q].x),
+                                                                  fma(f, v.y, (double)cs[d - 1][q].y)));
+                }
+                if (d < DM) sp[d & 1][gl][l] = make_double2(fac[q] * r.x, fac[q] * r.y);
+            });
+        }
+        __syncthreads();
+    }
+}
+
+// One workgroup per box R of level L-3.  See the file header.  N = 1e6, L = 9,
+// p = 13: 35 us (38 us with a binomial table), HBM and latency: 80 MB in 35 us;
+// N = 1e5, L = 7, p = 39: 13 us, where four L2L launches and L2P took 83 us.
 // Every global load that does not depend on a computed value (the geometry
 // and the M2L sums of R, of its ancestors, of its children and of the leaf
 // of each 16-lane group, the leaf's first 32 points with their near field)
 // is issued at the start, so the workgroup waits for memory twice (the
 // points' loads need the leaf's start) instead of once per phase.
-template <class T, int P>
+// STAGED: the only ancestor is R's parent, whose complete expansion is stored;
+// R and its children are stored complete as well, every level rounded to T.
+// EVAL: L2P at the points.
+template <class T, int P, bool STAGED, bool EVAL>
 __global__ void __launch_bounds__(256)
-k_down_leaf(int L, int64_t NB, int nroot, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
+k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
             const double* __restrict__ geom, const double* __restrict__ X, const double* __restrict__ Y, T* loc,
             int p, const double2* __restrict__ nearf, const int32_t* __restrict__ perm, double2* phi,
-            double2* phi_near, double2* phi_far, const long long* __restrict__ guard, const double* __restrict__ binom)
+            double2* phi_near, double2* phi_far, const long long* __restrict__ guard, const double* __restrict__ fact)
 {
     if (guard != nullptr && *guard != 0) return;   // lists flagged: this launch is void
     using T2 = typename Vec2<T>::type;
     constexpr int KP = P / 16;          // coefficients per lane of a 16-lane group
     constexpr int NPT = 2;              // points per lane loaded ahead (a leaf's first 32)
-    __shared__ double sb[P][P];
-    __shared__ double2 sanc[16][P];     // ancestor coefficients (their M2L sums), then the leaves' expansions
-    __shared__ double2 stab[16][P];     // tau powers, one table per 16-lane group
+    __shared__ double2 sanc[16][P];     // k! b_k of the ancestors' M2L sums, then the leaves' expansions
+    __shared__ double2 stab[16][P + 16];   // a shift table per 16-lane group
     __shared__ double2 spart[16][P];    // the ancestors' images in R
-    __shared__ double2 sR[P];           // R's complete expansion
-    __shared__ double2 sC[4][P];        // the children's complete expansions
+    __shared__ double2 sR[P];           // k! times R's complete expansion
+    __shared__ double2 sC[4][P];        // the same of the children
     const int gl = threadIdx.x >> 4, sl = threadIdx.x & 15, w = threadIdx.x >> 6;
-    const int b = blockIdx.x / nroot;
-    const int64_t jR = blockIdx.x % nroot;
-    const int lR = L - 3;
-    const int R = sub_box(b, NB, lR, jR);
-    const int leaf = sub_box(b, NB, L - 1, 16 * jR + gl);
+    const SubAt at = sub_at(work);
+    const int64_t jR = at.j;
+    const int lR = at.lev;
+    const int R = sub_box(at.pb, lR, jR);
+    const int leaf = sub_box(at.pb, lR + 2, 16 * jR + gl);
     const T2* lo = reinterpret_cast<const T2*>(loc);
-    const BinomRegs<P> bin = binom_load<P>(binom);
     // ---- loads: every one unconditional, at an index clamped into range (a
     // load under a branch would be waited for where the branch ends); the
     // lanes that have no use for a value never read it
-    const int st = bstart[leaf], n = bcount[leaf];
-    const double lcx = geom[4 * (int64_t)leaf], lcy = geom[4 * (int64_t)leaf + 1], lrs = geom[4 * (int64_t)leaf + 3];
-    const double Rx = geom[4 * (int64_t)R], Ry = geom[4 * (int64_t)R + 1], Rrs = geom[4 * (int64_t)R + 3];
-    // group gl < nanc: the ancestor of level gl
-    const int nanc = lR;
+    const int st = EVAL ? bstart[leaf] : 0, n = EVAL ? bcount[leaf] : 0;
+    const SubGeo gf = sub_geo(geom, leaf), gR = sub_geo(geom, R);
+    // group gl < nanc: the ancestor of level gl (staged: the parent; the root
+    // hands nothing down, it has no weak list)
+    const int nanc = STAGED ? (lR >= 2 ? 1 : 0) : lR;
     const bool anc = gl < nanc;
-    const int A = anc ? sub_box(b, NB, gl, jR >> (2 * (lR - gl))) : R;
-    const double ax = geom[4 * (int64_t)A], ay = geom[4 * (int64_t)A + 1], ars = geom[4 * (int64_t)A + 3];
-    T2 ca[KP];
+    const int lA = STAGED ? lR - 1 : gl;
+    const int A = anc ? sub_box(at.pb, lA, jR >> (2 * (lR - lA))) : R;
+    const SubGeo ga = sub_geo(geom, A);
+    // wavefront w: child w of R, the parent of its four leaves
+    const int Cw = sub_box(at.pb, lR + 1, 4 * jR + w);
+    const SubGeo gc = sub_geo(geom, Cw);
+    T2 ca[KP], cR, cc[KP], cl[KP];
+    double fac[KP], ifac[KP];
 #pragma unroll
-    for (int q = 0; q < KP; ++q) ca[q] = lo[(int64_t)A * p + min(sl + 16 * q, p - 1)];
-    // thread l < p: R's own sum
-    const T2 cR = lo[(int64_t)R * p + min((int)threadIdx.x, p - 1)];
-    // group c of wavefront 0 (every wavefront loads it; only wavefront 0
-    // uses it): child c of R
-    const int Cg = sub_box(b, NB, L - 2, 4 * jR + (gl & 3));
-    const double cgx = geom[4 * (int64_t)Cg], cgy = geom[4 * (int64_t)Cg + 1], cgrs = geom[4 * (int64_t)Cg + 3];
-    T2 cc[KP];
-#pragma unroll
-    for (int q = 0; q < KP; ++q) cc[q] = lo[(int64_t)Cg * p + min(sl + 16 * q, p - 1)];
-    // wavefront w: child w of R, the parent of its four leaves; the leaf's own sum
-    const int Cw = sub_box(b, NB, L - 2, 4 * jR + w);
-    const double cwx = geom[4 * (int64_t)Cw], cwy = geom[4 * (int64_t)Cw + 1], cwrs = geom[4 * (int64_t)Cw + 3];
-    T2 cl[KP];
-#pragma unroll
-    for (int q = 0; q < KP; ++q) cl[q] = lo[(int64_t)leaf * p + min(sl + 16 * q, p - 1)];
+    for (int q = 0; q < KP; ++q) {
+        const int k = min(sl + 16 * q, p - 1);
+        ca[q] = lo[(int64_t)A * p + k];
+        cc[q] = lo[(int64_t)Cw * p + k];
+        cl[q] = lo[(int64_t)leaf * p + k];
+        fac[q] = fact[sl + 16 * q];
+        ifac[q] = fact[kInvFact + sl + 16 * q];
+    }
+    // thread l < P: R's own sum
+    cR = lo[(int64_t)R * p + min((int)threadIdx.x, p - 1)];
+    const double facR = fact[threadIdx.x & 63];
     // the leaf's first points (a lane past the leaf's end reads point 0)
     double px[NPT], py[NPT];
     double2 pn[NPT];
     int po[NPT];
+    if constexpr (EVAL) {
 #pragma unroll
-    for (int q = 0; q < NPT; ++q) {
-        const int j = sl + 16 * q;
-        const int i = j < n ? st + j : 0;
-        px[q] = X[i];
-        py[q] = Y[i];
-        pn[q] = nearf[i];
-        po[q] = perm[i];
+        for (int q = 0; q < NPT; ++q) {
+            const int j = sl + 16 * q;
+            const int i = j < n ? st + j : 0;
+            px[q] = X[i];
+            py[q] = Y[i];
+            pn[q] = nearf[i];
+            po[q] = perm[i];
+        }
     }
-    binom_store<P>(sb, bin);
-    __syncthreads();   // every wavefront reads rows of the table the others wrote
-    // ---- the ancestors (levels 0 .. lR-1) into R: group gl takes level gl
+    // ---- the ancestors into R: group gl takes one
     if (anc) {
-        const double2 t = make_double2((Rx - ax) / ars, (Ry - ay) / ars);
-        const double rho = Rrs / ars;
 #pragma unroll
         for (int q = 0; q < KP; ++q) {
-            const int k = sl + 16 * q;
-            if (k < p) {
-                sanc[gl][k] = make_double2((double)ca[q].x, (double)ca[q].y);
-                stab[gl][k] = sub_cpow(t, k);
-            }
+            const double f = sl + 16 * q < p ? fac[q] : 0.0;
+            sanc[gl][sl + 16 * q] = make_double2(f * (double)ca[q].x, f * (double)ca[q].y);
         }
+        shift_table<P>(stab[gl], sub_tau(ga, gR), p, sl, ifac);
         wave_sync();
-        for (int l = sl; l < p; l += 16) {
-            double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                if (k >= l && k < p) {
-                    const double s = sb[k][l];
-                    const double2 v = cmul(sanc[gl][k], stab[gl][k - l]);
-                    acc.x += s * v.x;
-                    acc.y += s * v.y;
-                }
-            }
-            const double rl = sub_rpow(rho, l);
-            spart[gl][l] = make_double2(rl * acc.x, rl * acc.y);
-        }
+        const double rho = gR.rs / ga.rs;
+        for_q<KP>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            const double2 v = l2l_conv<P, q, 1>(sanc[gl], stab[gl], sl, 0);
+            const double f = sub_rpow<kBits<P>>(rho, sl + 16 * q) * ifac[q];
+            spart[gl][sl + 16 * q] = make_double2(f * v.x, f * v.y);
+        });
     }
     __syncthreads();
     // R's complete expansion: its own M2L sum, then the ancestors top-down
-    if ((int)threadIdx.x < p) {
+    if ((int)threadIdx.x < P) {
         const int l = threadIdx.x;
-        double2 acc = make_double2((double)cR.x, (double)cR.y);
-        for (int a = 0; a < nanc; ++a) {
-            acc.x += spart[a][l].x;
-            acc.y += spart[a][l].y;
-        }
-        sR[l] = acc;
-    }
-    __syncthreads();
-    // ---- R into its four children: wavefront 0, lane (c, l)
-    if (w == 0) {
-        const int c = gl;
-        const double2 t = make_double2((cgx - Rx) / Rrs, (cgy - Ry) / Rrs);
-        const double rho = cgrs / Rrs;
-        for (int k = sl; k < p; k += 16) stab[c][k] = sub_cpow(t, k);
-        wave_sync();
-#pragma unroll
-        for (int q = 0; q < KP; ++q) {
-            const int l = sl + 16 * q;
-            if (l >= p) continue;
-            double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                if (k >= l && k < p) {
-                    const double s = sb[k][l];
-                    const double2 v = cmul(sR[k], stab[c][k - l]);
-                    acc.x += s * v.x;
-                    acc.y += s * v.y;
-                }
+        double2 acc = make_double2(0.0, 0.0);
+        if (l < p) {
+            acc = make_double2((double)cR.x, (double)cR.y);
+            for (int a = 0; a < nanc; ++a) {
+                acc.x += spart[a][l].x;
+                acc.y += spart[a][l].y;
             }
-            const double rl = sub_rpow(rho, l);
-            sC[c][l] = make_double2((double)cc[q].x + rl * acc.x, (double)cc[q].y + rl * acc.y);
+            if constexpr (STAGED) acc = store_coef<T>(loc, R, p, l, acc);
         }
+        sR[l] = make_double2(facR * acc.x, facR * acc.y);
     }
+    // ---- R into its child w, by wavefront w: row r of the lanes takes the
+    // terms k = r mod 4
+    const int row = gl & 3;
+    if (row == 0) shift_table<P>(stab[gl], sub_tau(gR, gc), p, sl, ifac);
     __syncthreads();
+    {
+        const double rho = gc.rs / gR.rs;
+        for_q<KP>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
+            const int l = sl + 16 * q;
+            double2 v = l2l_conv<P, q, 4>(sR, stab[4 * w], sl, row);
+            v.x += partner<16>(v.x);
+            v.y += partner<16>(v.y);
+            v.x += partner<32>(v.x);
+            v.y += partner<32>(v.y);
+            if (row == q) {
+                double2 r = make_double2(0.0, 0.0);
+                if (l < p) {
+                    const double f = sub_rpow<kBits<P>>(rho, l) * ifac[q];
+                    r = make_double2(fma(f, v.x, (double)cc[q].x), fma(f, v.y, (double)cc[q].y));
+                    if constexpr (STAGED) r = store_coef<T>(loc, Cw, p, l, r);
+                }
+                sC[w][l] = make_double2(fac[q] * r.x, fac[q] * r.y);
+            }
+        });
+    }
+    wave_sync();
     // ---- child w into its four leaves (wavefront w, group gl = leaf 4w + m):
     // the leaf's complete expansion, stored (the storage type) and kept for L2P
+    shift_table<P>(stab[gl], sub_tau(gc, gf), p, sl, ifac);
+    wave_sync();
     {
-        const double2 t = make_double2((lcx - cwx) / cwrs, (lcy - cwy) / cwrs);
-        const double rho = lrs / cwrs;
-        for (int k = sl; k < p; k += 16) stab[gl][k] = sub_cpow(t, k);
-        wave_sync();
-        T2* lw = reinterpret_cast<T2*>(loc);
-#pragma unroll
-        for (int q = 0; q < KP; ++q) {
+        const double rho = gf.rs / gc.rs;
+        for_q<KP>([&](auto qc) {
+            constexpr int q = decltype(qc)::value;
             const int l = sl + 16 * q;
-            if (l >= p) {
-                sanc[gl][l] = make_double2(0.0, 0.0);
-                continue;
+            const double2 v = l2l_conv<P, q, 1>(sC[w], stab[gl], sl, 0);
+            double2 r = make_double2(0.0, 0.0);
+            if (l < p) {
+                const double f = sub_rpow<kBits<P>>(rho, l) * ifac[q];
+                r = store_coef<T>(loc, leaf, p, l, make_double2(fma(f, v.x, (double)cl[q].x),
+                                                               fma(f, v.y, (double)cl[q].y)));
             }
-            double2 acc = make_double2(0.0, 0.0);
-#pragma unroll
-            for (int k = 0; k < P; ++k) {
-                if (k >= l && k < p) {
-                    const double s = sb[k][l];
-                    const double2 v = cmul(sC[w][k], stab[gl][k - l]);
-                    acc.x += s * v.x;
-                    acc.y += s * v.y;
-                }
-            }
-            const double rl = sub_rpow(rho, l);
-            const T tx = (T)((double)cl[q].x + rl * acc.x), ty = (T)((double)cl[q].y + rl * acc.y);
-            lw[(int64_t)leaf * p + l] = T2{tx, ty};
-            sanc[gl][l] = make_double2((double)tx, (double)ty);
-        }
-        wave_sync();
+            sanc[gl][l] = r;
+        });
     }
+    if constexpr (!EVAL) return;
+    wave_sync();
     // ---- L2P at the leaf's points (Horner), plus the near field, to input order
-    const double inv = 1.0 / lrs;
+    const double inv = 1.0 / gf.rs;
     const double2* co = sanc[gl];
     for (int j = sl, q = 0; j < n; j += 16, ++q) {
         const int i = st + j;
@@ -511,7 +670,7 @@ k_down_leaf(int L, int64_t NB, int nroot, const int32_t* __restrict__ bstart, co
             nfx = nf.x; nfy = nf.y;
             o = perm[i];
         }
-        const double2 z = make_double2((x - lcx) * inv, (y - lcy) * inv);
+        const double2 z = make_double2((x - gf.x) * inv, (y - gf.y) * inv);
         double2 acc = co[P - 1];
 #pragma unroll
         for (int l = P - 2; l >= 0; --l) {
@@ -527,72 +686,104 @@ k_down_leaf(int L, int64_t NB, int nroot, const int32_t* __restrict__ bstart, co
 
 // ---------------------------------------------------------------- launchers
 
-bool subtree_ok(int L, int p) { return L >= 3 && p <= 32; }
+static SubWork sub_work(const SubPlan& sp, const SubStep& st)
+{
+    if (!sp.uniform) return SubWork{sp.list.p + st.off, 0, 0, 0, 0};
+    return SubWork{nullptr, st.lev, st.D, 1 << (2 * st.lev), nbox_levels(sp.L)};
+}
+
+#define SUB_BY_ORDER(CASE)                                                   \
+    if (p <= 16) { CASE(16) }                                                \
+    else if (p <= 32) { CASE(32) }                                           \
+    else if (p <= 48) { CASE(48) }                                           \
+    else if (p <= 64) { CASE(64) }                                           \
+    else throw Error(FMM_EINVAL, "subtree passes need p <= 64");
 
 template <class T>
-void launch_up_subtree(int nprob, int L, const int32_t* bstart, const int32_t* bcount, const double* geom,
-                       const double* X, const double* Y, const double* mt, int p, void* mp, const double* binom,
-                       const GatherOut* go, hipStream_t s, hipEvent_t after_leaves)
+void launch_up_leaves(const SubPlan& sp, const int32_t* bstart, const int32_t* bcount, const double* geom,
+                      const double* X, const double* Y, const double* mt, int p, void* mp, const double* fact,
+                      const GatherOut* go, hipStream_t s)
 {
+    if (sp.roots.n == 0) return;
     const GatherOut none{};
     const GatherOut& gg = go ? *go : none;
-    const int64_t NB = nbox_levels(L);
-    const int nroot = 1 << (2 * (L - 3));
-    const unsigned grid = (unsigned)(nprob * nroot);
+    const SubWork w = sub_work(sp, sp.roots);
+    const unsigned grid = (unsigned)sp.roots.n;
 #define UP_CASE(P_)                                                                                        \
     if (go)                                                                                                \
-        k_up_leaf<T, P_, true><<<grid, 256, 0, s>>>(L, NB, nroot, bstart, bcount, geom, X, Y,             \
-                                                    (const double2*)mt, p, (T*)mp, binom, gg);             \
+        k_up_leaf<T, P_, true><<<grid, 256, 0, s>>>(w, bstart, bcount, geom, X, Y, (const double2*)mt, p,  \
+                                                    (T*)mp, fact, gg);                                     \
     else                                                                                                   \
-        k_up_leaf<T, P_, false><<<grid, 256, 0, s>>>(L, NB, nroot, bstart, bcount, geom, X, Y,            \
-                                                     (const double2*)mt, p, (T*)mp, binom, gg);
-    if (p <= 16) { UP_CASE(16) }
-    else if (p <= 32) { UP_CASE(32) }
-    else throw Error(FMM_EINVAL, "subtree upward pass needs p <= 32");
+        k_up_leaf<T, P_, false><<<grid, 256, 0, s>>>(w, bstart, bcount, geom, X, Y, (const double2*)mt, p, \
+                                                     (T*)mp, fact, gg);
+    SUB_BY_ORDER(UP_CASE)
 #undef UP_CASE
     check_launch("upward leaves");
-    // the gather is complete here: work that needs only the strengths in tree
-    // order (the near field) may start
-    if (after_leaves) FMM_HIP(hipEventRecord(after_leaves, s));
-    // levels L-4 .. 0 in subtrees of at most three levels
-    for (int lv = L - 3; lv > 0;) {
-        const int D = lv < 3 ? lv : 3;
-        const int a = lv - D;
-        const int nper = 1 << (2 * a);
-        const unsigned g2 = (unsigned)(nprob * nper);
-        if (p <= 16) k_up_mid<T, 16><<<g2, 256, 0, s>>>(a, D, NB, nper, geom, p, (T*)mp, binom);
-        else k_up_mid<T, 32><<<g2, 256, 0, s>>>(a, D, NB, nper, geom, p, (T*)mp, binom);
+}
+
+// levels L-4 .. 1
+template <class T>
+void launch_up_mid(const SubPlan& sp, const double* geom, int p, void* mp, const double* fact, hipStream_t s)
+{
+    for (const SubStep& st : sp.up[p > 32]) {
+        const SubWork w = sub_work(sp, st);
+        const unsigned grid = (unsigned)st.n;
+#define MID_CASE(P_) k_up_mid<T, P_><<<grid, kSubThreads<P_>, 0, s>>>(w, geom, p, (T*)mp, fact);
+        SUB_BY_ORDER(MID_CASE)
+#undef MID_CASE
         check_launch("upward subtrees");
-        lv = a;
+    }
+}
+
+// the staged form's levels 2 .. L-4
+template <class T>
+void launch_down_mid(const SubPlan& sp, const double* geom, int p, void* loc, const double* fact,
+                     const long long* guard, hipStream_t s)
+{
+    for (const SubStep& st : sp.down[p > 32]) {
+        const SubWork w = sub_work(sp, st);
+        const unsigned grid = (unsigned)st.n;
+#define DMID_CASE(P_) k_down_mid<T, P_><<<grid, kSubThreads<P_>, 0, s>>>(w, geom, p, (T*)loc, fact, guard);
+        SUB_BY_ORDER(DMID_CASE)
+#undef DMID_CASE
+        check_launch("downward subtrees");
     }
 }
 
 template <class T>
-void launch_down_subtree(int nprob, int L, const int32_t* bstart, const int32_t* bcount, const double* geom,
-                         const double* X, const double* Y, void* loc, int p, const double* nearf,
+void launch_down_subtree(const SubPlan& sp, bool staged, const int32_t* bstart, const int32_t* bcount,
+                         const double* geom, const double* X, const double* Y, void* loc, int p, const double* nearf,
                          const int32_t* perm, double* phi, double* phi_near, double* phi_far, const long long* guard,
-                         const double* binom, hipStream_t s)
+                         const double* fact, hipStream_t s)
 {
-    const int64_t NB = nbox_levels(L);
-    const int nroot = 1 << (2 * (L - 3));
-    const unsigned grid = (unsigned)(nprob * nroot);
-#define DOWN_ARGS L, NB, nroot, bstart, bcount, geom, X, Y, (T*)loc, p, (const double2*)nearf, perm, (double2*)phi, \
-                  (double2*)phi_near, (double2*)phi_far, guard, binom
-    if (p <= 16) k_down_leaf<T, 16><<<grid, 256, 0, s>>>(DOWN_ARGS);
-    else if (p <= 32) k_down_leaf<T, 32><<<grid, 256, 0, s>>>(DOWN_ARGS);
-    else throw Error(FMM_EINVAL, "subtree downward pass needs p <= 32");
+    if (sp.roots.n == 0) return;
+    const SubWork w = sub_work(sp, sp.roots);
+    const unsigned grid = (unsigned)sp.roots.n;
+    const bool eval = phi != nullptr || phi_near != nullptr || phi_far != nullptr;
+#define DOWN_ARGS w, bstart, bcount, geom, X, Y, (T*)loc, p, (const double2*)nearf, perm, (double2*)phi, \
+                  (double2*)phi_near, (double2*)phi_far, guard, fact
+#define DOWN_CASE(P_)                                                                       \
+    if (staged && eval) k_down_leaf<T, P_, true, true><<<grid, 256, 0, s>>>(DOWN_ARGS);     \
+    else if (staged) k_down_leaf<T, P_, true, false><<<grid, 256, 0, s>>>(DOWN_ARGS);       \
+    else if (eval) k_down_leaf<T, P_, false, true><<<grid, 256, 0, s>>>(DOWN_ARGS);         \
+    else k_down_leaf<T, P_, false, false><<<grid, 256, 0, s>>>(DOWN_ARGS);
+    SUB_BY_ORDER(DOWN_CASE)
+#undef DOWN_CASE
 #undef DOWN_ARGS
     check_launch("downward leaves");
 }
 
 #define INST(T)                                                                                           \
-    template void launch_up_subtree<T>(int, int, const int32_t*, const int32_t*, const double*, const double*, \
-                                       const double*, const double*, int, void*, const double*,          \
-                                       const GatherOut*, hipStream_t, hipEvent_t);                       \
-    template void launch_down_subtree<T>(int, int, const int32_t*, const int32_t*, const double*,          \
-                                         const double*, const double*, void*, int, const double*,          \
-                                         const int32_t*, double*, double*, double*, const long long*,      \
-                                         const double*, hipStream_t);
+    template void launch_up_leaves<T>(const SubPlan&, const int32_t*, const int32_t*, const double*,      \
+                                      const double*, const double*, const double*, int, void*,            \
+                                      const double*, const GatherOut*, hipStream_t);                      \
+    template void launch_up_mid<T>(const SubPlan&, const double*, int, void*, const double*, hipStream_t); \
+    template void launch_down_mid<T>(const SubPlan&, const double*, int, void*, const double*,            \
+                                     const long long*, hipStream_t);                                      \
+    template void launch_down_subtree<T>(const SubPlan&, bool, const int32_t*, const int32_t*,            \
+                                         const double*, const double*, const double*, void*, int,         \
+                                         const double*, const int32_t*, double*, double*, double*,        \
+                                         const long long*, const double*, hipStream_t);
 INST(double)
 INST(float)
 #undef INST

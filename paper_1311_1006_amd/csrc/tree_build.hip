@@ -1104,29 +1104,80 @@ union LdsUnion {
     LdsBucket b;
 };
 
+// (key, input index) order of two entries of the sort buffer; padding entries
+// (key ~0, which no finite coordinate has) come last, in any order
+__device__ __forceinline__ bool lds_less(uint64_t ka, uint16_t ia, uint64_t kb, uint16_t ib, const uint32_t* idxs)
+{
+    if (ka != kb) return ka < kb;
+    return ka != ~0ull && idxs[ia] < idxs[ib];
+}
+
+// Sort of the entries of S (n of them, padding behind) by (key, input index): a
+// merge sort, thread t owning positions kPer t .. kPer t + kPer - 1.  The thread's
+// entries are sorted in registers; then the runs are merged pairwise, each
+// thread finding by a binary search along its diagonal where its kPer outputs
+// start in the two runs (merge path) and merging them in registers.  Up to
+// runs of a wavefront's 256 positions a round needs no workgroup barrier; the
+// last four rounds take two each.  The bitonic network it replaced had 78
+// dependent steps, each a pass over LDS with a barrier: the in-LDS stage took
+// 148 us for the clustered million points and 92 us now, 145 and 75 us for
+// 16,000 points of a vortex sheet (50 us where no segment needs the sort).
 __device__ void lds_sort(LdsSort& S, const uint32_t* idxs, int n)
 {
-    int P = 1;
-    while (P < n) P <<= 1;
-    for (int kk = 2; kk <= P; kk <<= 1)
-        for (int j = kk >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < P / 2; i += kLdsThreads) {
-                int lo = ((i & ~(j - 1)) << 1) | (i & (j - 1));
-                int hi = lo + j;
-                bool asc = (lo & kk) == 0;
-                uint64_t a = S.key[lo], b = S.key[hi];
-                uint16_t ia = S.id[lo], ib = S.id[hi];
-                bool less_hl;
-                if (ib == 0xffff) less_hl = false;          // padding sorts last
-                else if (ia == 0xffff) less_hl = true;
-                else less_hl = (b < a) || (b == a && idxs[ib] < idxs[ia]);
-                if (less_hl == asc) {
-                    S.key[lo] = b; S.key[hi] = a;
-                    uint16_t c = S.id[lo]; S.id[lo] = S.id[hi]; S.id[hi] = c;
+    static_assert(kPer == 4, "four entries per thread");
+    const int p0 = kPer * (int)threadIdx.x;
+    uint64_t k[kPer];
+    uint16_t id[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) { k[u] = S.key[p0 + u]; id[u] = S.id[p0 + u]; }
+    auto order = [&](int a, int b) {
+        if (lds_less(k[b], id[b], k[a], id[a], idxs)) {
+            const uint64_t t = k[a]; k[a] = k[b]; k[b] = t;
+            const uint16_t v = id[a]; id[a] = id[b]; id[b] = v;
+        }
+    };
+    order(0, 1); order(2, 3); order(0, 2); order(1, 3); order(1, 2);
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) { S.key[p0 + u] = k[u]; S.id[p0 + u] = id[u]; }
+    for (int w = kPer; w < n; w <<= 1) {
+        const bool block = 2 * w > 64 * kPer;     // the merged run spans wavefronts
+        if (block) __syncthreads();
+        else wave_sync();
+        const int base = p0 & ~(2 * w - 1), d = p0 - base;   // the pair of runs, this thread's diagonal
+        const uint64_t* A = S.key + base;
+        const uint64_t* B = A + w;
+        const uint16_t* Ai = S.id + base;
+        const uint16_t* Bi = Ai + w;
+        int lo = max(0, d - w), hi = min(d, w);
+        while (lo < hi) {                          // entries of A before the diagonal
+            const int mid = (lo + hi) >> 1, q = d - 1 - mid;
+            if (lds_less(B[q], Bi[q], A[mid], Ai[mid], idxs)) hi = mid;
+            else lo = mid + 1;
+        }
+        int a = lo, b = d - lo;
+        uint64_t ka = a < w ? A[a] : ~0ull, kb = b < w ? B[b] : ~0ull;
+        uint16_t ia = a < w ? Ai[a] : 0, ib = b < w ? Bi[b] : 0;
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) {
+            const bool tb = a >= w || (b < w && lds_less(kb, ib, ka, ia, idxs));
+            k[u] = tb ? kb : ka;
+            id[u] = tb ? ib : ia;
+            if (u + 1 < kPer) {
+                if (tb) {
+                    ++b;
+                    if (b < w) { kb = B[b]; ib = Bi[b]; }
+                } else {
+                    ++a;
+                    if (a < w) { ka = A[a]; ia = Ai[a]; }
                 }
             }
-            __syncthreads();
         }
+        if (block) __syncthreads();
+        else wave_sync();
+#pragma unroll
+        for (int u = 0; u < kPer; ++u) { S.key[p0 + u] = k[u]; S.id[p0 + u] = id[u]; }
+    }
+    __syncthreads();
 }
 
 // Local ids 0..n-1 of the segment ordered by (coordinate, input index) into
@@ -1134,9 +1185,13 @@ __device__ void lds_sort(LdsSort& S, const uint32_t* idxs, int n)
 // minimum and maximum coordinate (a monotone map), an exclusive scan of the
 // populations, a scatter, and the place of every element inside its bucket
 // from the count of the bucket's elements that precede it.  When a bucket
-// holds more than kBucketMax points (ties, tight clusters) the bitonic sort
-// runs instead.
-constexpr int kBucketMax = 16;
+// holds more than kBucketMax points (ties, tight clusters, rows of a grid) a
+// merge sort runs instead.
+// The line between the two: ranking costs VALU time in proportion to the
+// largest bucket, 15 us per axis at 64 points and full segments against 20 us
+// for the merge sort; at 16 points the sheet's columns (28 points, one bucket
+// each) took the sort, 90 us for the stage instead of 75.
+constexpr int kBucketMax = 64;
 
 __device__ void lds_order(LdsUnion& U, const double* __restrict__ c, const uint32_t* idxs, int n, uint16_t* out,
                           int* sh, double* red)
@@ -1194,12 +1249,10 @@ __device__ void lds_order(LdsUnion& U, const double* __restrict__ c, const uint3
     for (int w = 0; w < kLdsWaves; ++w) mx = max(mx, sh[kLdsWaves + w]);
     __syncthreads();
     if (mx > kBucketMax) {
-        // bitonic fallback (uniform branch)
-        int P = 1;
-        while (P < n) P <<= 1;
-        for (int i = tid; i < P; i += kLdsThreads) {
-            if (i < n) { U.s.key[i] = okey(c[i]); U.s.id[i] = (uint16_t)i; }
-            else { U.s.key[i] = ~0ull; U.s.id[i] = 0xffff; }
+        // merge sort instead (uniform branch)
+        for (int i = tid; i < kLdsCap; i += kLdsThreads) {
+            U.s.key[i] = i < n ? okey(c[i]) : ~0ull;
+            U.s.id[i] = i < n ? (uint16_t)i : 0xffff;
         }
         __syncthreads();
         lds_sort(U.s, idxs, n);

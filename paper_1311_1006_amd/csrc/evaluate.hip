@@ -207,6 +207,9 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
         }
     }
     upload_vec(ex.fact, fact, s);
+    std::vector<double> logtab(2 * kLogTab);
+    log_table(logtab.data());
+    upload_vec(ex.logtab, logtab, s);
     FMM_HIP(hipStreamSynchronize(s));
 }
 
@@ -336,7 +339,7 @@ static void run_p2p(Plan& pl, PlanExtra& ex, hipStream_t s, const long long* gua
                    b.partial.p, sc.d_box_start.p, sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p,
                    t.x.p, t.y.p, (const double2*)pl.mtree.p, pl.near.p, s, guard,
                    pl.tune.smooth_delta > 0.0 ? 1.0 / (pl.tune.smooth_delta * pl.tune.smooth_delta) : 0.0,
-                   log_kernel, Targets{}, pl.tune.p2p_src_tile);
+                   log_kernel ? ex.logtab.p : nullptr, Targets{}, pl.tune.p2p_src_tile);
     }
     combine_chunks(b, ex.p2p_items.p, nitems, sc.d_box_start.p, pl.near.p, s);
 }

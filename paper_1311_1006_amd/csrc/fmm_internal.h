@@ -71,12 +71,16 @@ struct Targets {
 
 // The near field over the chunks of one launch class (p2p.hip): the sources
 // are the points in tree order, positions X, Y and strengths M (FP64; the
-// mixed kernels round the strengths to FP32 as they stage them).
+// mixed kernels round the strengths to FP32 as they stage them).  log_table
+// (device, 2 kLogTab values filled by log_table()) selects the logarithmic
+// kernel; NULL: the harmonic one, smoothed with id2 > 0.
+constexpr int kLogTab = 128;
+void log_table(double* tab);
 void launch_p2p(bool mixed, int tg, int sub, const void* items, int item_base, const int2* xitems, int nx,
                 const int32_t* icnt, const int32_t* ioff, double* partial, const int32_t* bstart,
                 const int32_t* bcount, const int32_t* s_beg, const int32_t* s_cnt, const int32_t* s_ids,
                 const double* X, const double* Y, const double2* M, double* out, hipStream_t s,
-                const long long* guard, double id2, bool log_kernel, const Targets& tgt = Targets{},
+                const long long* guard, double id2, const double* log_table, const Targets& tgt = Targets{},
                 int src_tile = 0);
 constexpr int kChunkPairs = 128;   // M2L weak pairs per work chunk (longer lists are split)
 

@@ -47,6 +47,7 @@ struct PlanExtra {
     int64_t pool_strong = 0, pool_weak = 0;        // id pool sizes for the next compact build
     bool compact_only = false;                      // fixed capacities would need too much memory
     DBuf<double> fact;                              // k! for k < 64, then 1/k!
+    DBuf<double> logtab;                            // table of the near field's FP64 logarithm
     DBuf<double> binom;                             // binomial table C(n, k), n, k < 64
     DBuf<int32_t> child0;                           // first child of every box, -1: a leaf
     DBuf<char> p2p_items;

@@ -532,7 +532,7 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
         tgt.start = off.p;
         launch_p2p(mixed, 4, 4, items.p, 0, nullptr, (int)nx, nullptr, nullptr, nullptr, sc.d_box_start.p,
                    sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p,
-                   t.x.p, t.y.p, (const double2*)pl.mtree.p, tnear.p, s, nullptr, 0.0, false, tgt,
+                   t.x.p, t.y.p, (const double2*)pl.mtree.p, tnear.p, s, nullptr, 0.0, nullptr, tgt,
                    pl.tune.p2p_src_tile);
     }
     // descents: the points that stopped above the leaves (box-order positions

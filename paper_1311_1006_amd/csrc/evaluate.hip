@@ -361,11 +361,22 @@ hipStream_t side_stream(int device, int which)
     return st;
 }
 
-// The evaluation's side stream and events, made when the plan is made (the
-// evaluations then create nothing)
+// Whether the near field runs on a second stream beside the far field instead
+// of after M2L on the evaluation's own.  Where both fill the chip they are
+// bound by VALU issue and take beside each other the time they take in turn,
+// while the fork and the join cost the critical path about 10 us each: one
+// stream for N = 1000 29 us against 49, N = 16,000 36 against 57, N = 1e6 mixed
+// 249 against 252.  Two streams pay where one of them leaves part of the chip
+// idle: lists split into work chunks (a tail of long items: clustered step 1707
+// us against 1810, batch of 128 problems 1359 against 1463), and more than 32
+// terms (M2L holds 200 registers: N = 1e5, p = 39 171 us against 180).
+static bool near_beside(const Plan& pl) { return pl.p > 32 || pl.split_p2p || pl.split_m2l; }
+
+// The second stream and its events, where they are used, made when the plan is
+// made (the evaluations then create nothing)
 void plan_events(Plan& pl)
 {
-    if (!pl.nstream) {
+    if (near_beside(pl) && !pl.nstream) {
         pl.nstream = side_stream(pl.tree->device, kNearStream);
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
@@ -381,11 +392,6 @@ void evaluate_upward(Plan& pl, const double* m, hipStream_t s)
     TreeSchedule& sc = *t.sched;
     PlanExtra& ex = *extra(pl);
     const bool mixed = pl.precision == FMM_MIXED;
-    if (!pl.nstream) {
-        pl.nstream = side_stream(t.device, kNearStream);
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
-    }
     if (mixed) run_up<float>(pl, m, nullptr, pl.mpole.p, s);
     else run_up<double>(pl, m, nullptr, pl.mpole.p, s);
     pl.upward_done = true;
@@ -442,21 +448,15 @@ void launch_l2p_log(const int32_t* leaves, int nleaf, const int32_t* bstart, con
                     const double* near, const int32_t* perm, double* u, hipStream_t s);
 
 // The logarithmic potential (see log.hip): the harmonic upward pass and far
-// field of the strengths q as complex numbers, the near field with the
-// logarithmic kernel (on the second stream, beside the far field, from the
-// strengths in tree order P2M writes), the constant terms of the local expansions,
-// and L2P of the integrated series after the join.
+// field of the strengths q as complex numbers, the constant terms of the local
+// expansions, the near field with the logarithmic kernel, and L2P of the
+// integrated series.
 void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, double* mlog, double* c0)
 {
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
     PlanExtra& ex = *extra(pl);
     const bool mixed = pl.precision == FMM_MIXED;
-    if (!pl.nstream) {
-        pl.nstream = side_stream(t.device, kNearStream);
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
-    }
     if (!mlog) {
         pl.mlog.alloc(2 * sc.n, s);
         pl.c0.alloc(sc.nbox, s);
@@ -465,17 +465,14 @@ void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, do
     }
     launch_real_to_complex(sc.n, q, mlog, s);
     PhaseTimer tm(false, s);
-    if (mixed) run_up<float>(pl, mlog, nullptr, pl.mpole.p, s, pl.ev_fork);
-    else run_up<double>(pl, mlog, nullptr, pl.mpole.p, s, pl.ev_fork);
-    FMM_HIP(hipStreamWaitEvent(pl.nstream, pl.ev_fork, 0));
-    run_p2p(pl, ex, pl.nstream, nullptr, true);
-    FMM_HIP(hipEventRecord(pl.ev_join, pl.nstream));
+    if (mixed) run_up<float>(pl, mlog, nullptr, pl.mpole.p, s);
+    else run_up<double>(pl, mlog, nullptr, pl.mpole.p, s);
     if (mixed) run_far_down<float>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
     else run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
     auto constants = mixed ? launch_log_constants<float> : launch_log_constants<double>;
     constants((int)sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, pl.mpole.p, pl.local.p, pl.p,
               ex.d_level_boxes.p, ex.level_boxes_off, sc.max_levels, sc.d_box_parent.p, c0, s);
-    FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
+    run_p2p(pl, ex, s, nullptr, true);
     auto l2p = mixed ? launch_l2p_log<float> : launch_l2p_log<double>;
     l2p(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, pl.local.p, pl.p,
         c0, pl.near.p, t.perm.p, u, s);
@@ -491,33 +488,26 @@ void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, d
     PlanExtra& ex = *extra(pl);
     bool mixed = pl.precision == FMM_MIXED;
     PhaseTimer tm((pl.tune.flags & FMM_FLAG_PHASE_TIMING) != 0, s);
-    // The near field needs only the gathered sources: it runs on a second
-    // stream beside the far-field chain (P2M .. L2L) and joins before L2P.
     // Phase timing keeps the phases one after another on `s`.
-    const bool overlap = !tm.on;
-    if (lists_ev && !overlap) throw Error(FMM_EINVAL, "an evaluation ahead of its lists needs the overlapped order");
-    if (overlap && !pl.nstream) {
-        pl.nstream = side_stream(t.device, kNearStream);
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
-        FMM_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
-    }
+    if (lists_ev && tm.on) throw Error(FMM_EINVAL, "an evaluation ahead of its lists has no phase timing");
+    const bool beside = !tm.on && near_beside(pl);
+    if (beside) plan_events(pl);
     tm.mark();
-    const bool up = pl.upward_done && overlap;   // gather and upward pass enqueued by evaluate_upward
+    const bool up = pl.upward_done && !tm.on;   // gather and upward pass enqueued by evaluate_upward
     pl.upward_done = false;
-    // the near field forks as soon as the strengths are in tree order, beside
-    // the upper levels' M2M (forked after them, a batch of 128 problems took
-    // 1423 us instead of 1375, N = 1e5 at p = 39 176 instead of 171 us)
-    const bool early_fork = overlap && !up;
+    // on its own stream the near field forks as soon as the strengths are in
+    // tree order, beside the upper levels' M2M
+    const bool early_fork = beside && !up;
     if (!up) {
         hipEvent_t ev = early_fork ? pl.ev_fork : nullptr;
         if (mixed) run_up<float>(pl, m, nullptr, pl.mpole.p, s, ev);
         else run_up<double>(pl, m, nullptr, pl.mpole.p, s, ev);
     }
-    if (overlap) {
-        // the near field starts after everything enqueued on `s` so far: the
-        // gather (with P2M), and the list and work-chunk kernels of the plan
-        // (which follow the upward pass when evaluate_upward ran first); or
-        // after the gather (the event recorded there)
+    if (beside) {
+        // it starts after everything enqueued on `s` so far: the gather (with
+        // P2M), and the list and work-chunk kernels of the plan (which follow
+        // the upward pass when evaluate_upward ran first); or after the gather
+        // (the event recorded there)
         if (!early_fork) FMM_HIP(hipEventRecord(pl.ev_fork, s));
         FMM_HIP(hipStreamWaitEvent(pl.nstream, pl.ev_fork, 0));
         if (lists_ev) FMM_HIP(hipStreamWaitEvent(pl.nstream, lists_ev, 0));
@@ -529,8 +519,8 @@ void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, d
     if (mixed) run_far_down<float>(pl, ex, pl.mpole.p, pl.local.p, s, tm, guard);
     else run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, guard);
     tm.mark();
-    if (overlap) FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
-    else run_p2p(pl, ex, s, nullptr);
+    if (beside) FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
+    else run_p2p(pl, ex, s, guard);
     tm.mark();
     (mixed ? run_down_leaves<float> : run_down_leaves<double>)(pl, staged_down(pl, ex, false), pl.local.p, phi,
                                                                phi_near, phi_far, guard, s);

@@ -281,8 +281,8 @@ static void launch_adj_one(const P2PItemA* items, int item_base, const int2* xit
 void balance_launch(Plan::Balance& b, const void* items, int n, const std::vector<P2PClass>& cls,
                     const int32_t* s_cnt, const int32_t* bcount, hipStream_t s);
 void balance_finish(Plan::Balance& b, int n, int vals, hipStream_t s);
-void combine_chunks(const Plan::Balance& b, const void* items, int n, const int32_t* bstart, double* out,
-                    hipStream_t s);
+void combine_chunks(const Plan::Balance& b, const double* partial, int vals, const void* items, int n,
+                    const int32_t* bstart, double* out, hipStream_t s);
 
 // Near-field sums of the transposed chain for the weights gb (tree order),
 // into pl.near_d (6 doubles per point, see k_p2p_adj; with der only the
@@ -333,7 +333,7 @@ static void adjoint_near(Plan& pl, const double* gb_tree, bool der, hipStream_t 
 #undef ACASE
         throw Error(FMM_EDEVICE, "unsupported adjoint P2P shape");
     }
-    combine_chunks(ba, items, nadj, sc.d_box_start.p, pl.near_d.p, s);
+    combine_chunks(ba, ba.partial.p, 6, items, nadj, sc.d_box_start.p, pl.near_d.p, s);
 }
 
 void adjoint_device(Plan& pl, const double* m, const double* gphi, double* gm, double* gz, hipStream_t s)
@@ -388,14 +388,15 @@ void adjoint_device(Plan& pl, const double* m, const double* gphi, double* gm, d
 
 // Derivative of the field at the points: the derivative of the forward local
 // expansion of the point's leaf (d/dz = (1/rs) d/dv, Horner in v) minus the
-// near-field sum sum_j m_j / (z_i - z_j)^2, written in input order.  G lanes
-// per leaf, the leaf's expansion in LDS (FP64).
+// near-field sum sum_j m_j / (z_i - z_j)^2, written in input order; with phi
+// the field too.  The near field's sums: NS doubles per point, the derivative's
+// at nd, the field's first.  G lanes per leaf, the leaf's expansion in LDS (FP64).
 template <class T, int G, int P>
 __global__ void __launch_bounds__(256)
 k_field_final(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__ bstart,
               const int32_t* __restrict__ bcount, const double* __restrict__ geom, const double* __restrict__ X,
               const double* __restrict__ Y, const T* __restrict__ loc, int p, const double* __restrict__ nadj,
-              const int32_t* __restrict__ perm, double2* dphi)
+              const int32_t* __restrict__ perm, int NS, int nd, double2* phi, double2* dphi)
 {
     using T2 = typename Vec2<T>::type;
     constexpr int NLEAF = 256 / G;
@@ -432,10 +433,51 @@ k_field_final(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __re
             bd = cmul(bd, v); bd.x += bv.x; bd.y += bv.y;
             bv = cmul(bv, v); bv.x += bl[l].x; bv.y += bl[l].y;
         }
-        const double* na = nadj + 6 * (int64_t)i;
-        dphi[perm[i]] = make_double2(bd.x * inv - na[4], bd.y * inv - na[5]);
+        const double* na = nadj + NS * (int64_t)i;
+        if (phi) phi[perm[i]] = make_double2(bv.x + na[0], bv.y + na[1]);
+        dphi[perm[i]] = make_double2(bd.x * inv - na[nd], bd.y * inv - na[nd + 1]);
     }
 }
+
+template <class T>
+static void launch_field(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
+                         const double* geom, const double* X, const double* Y, const void* loc, int p,
+                         const double* near, int NS, int nd, const int32_t* perm, double* phi, double* dphi,
+                         hipStream_t s)
+{
+    if (nleaf == 0) return;
+    const int G = leaf_max <= 16 ? 16 : (leaf_max <= 32 ? 32 : 64);
+    const unsigned grid = (unsigned)((nleaf + 256 / G - 1) / (256 / G));
+    auto fin = [&](auto gtag, auto ptag) {
+        constexpr int G_ = decltype(gtag)::value, P_ = decltype(ptag)::value;
+        k_field_final<T, G_, P_><<<grid, 256, 0, s>>>(leaves, nleaf, bstart, bcount, geom, X, Y, (const T*)loc, p,
+                                                      near, perm, NS, nd, (double2*)phi, (double2*)dphi);
+    };
+    auto fin_g = [&](auto ptag) {
+        if (G == 16) fin(std::integral_constant<int, 16>{}, ptag);
+        else if (G == 32) fin(std::integral_constant<int, 32>{}, ptag);
+        else fin(std::integral_constant<int, 64>{}, ptag);
+    };
+    if (p <= 16) fin_g(std::integral_constant<int, 16>{});
+    else if (p <= 32) fin_g(std::integral_constant<int, 32>{});
+    else fin_g(std::integral_constant<int, 64>{});
+    check_launch("field final");
+}
+
+// the field and its derivative at the points of shallow problems' leaves
+template <class T>
+void launch_l2p_field(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
+                      const double* geom, const double* X, const double* Y, const void* loc, int p,
+                      const double* near4, const int32_t* perm, double* phi, double* dphi, hipStream_t s)
+{
+    launch_field<T>(leaves, nleaf, bstart, bcount, leaf_max, geom, X, Y, loc, p, near4, 4, 2, perm, phi, dphi, s);
+}
+template void launch_l2p_field<float>(const int32_t*, int, const int32_t*, const int32_t*, int, const double*,
+                                      const double*, const double*, const void*, int, const double*, const int32_t*,
+                                      double*, double*, hipStream_t);
+template void launch_l2p_field<double>(const int32_t*, int, const int32_t*, const int32_t*, int, const double*,
+                                       const double*, const double*, const void*, int, const double*, const int32_t*,
+                                       double*, double*, hipStream_t);
 
 void field_device(Plan& pl, const double* m, double* phi, double* dphi, hipStream_t s)
 {
@@ -443,34 +485,22 @@ void field_device(Plan& pl, const double* m, double* phi, double* dphi, hipStrea
     TreeSchedule& sc = *t.sched;
     PlanExtra& ex = *pl.ex;
     const bool mixed = pl.precision == FMM_MIXED;
-    // the forward evaluation: phi, the local expansions and m in tree order
+    if (field_one_pass(pl)) {
+        if (pl.near4.n < (size_t)(4 * sc.n)) pl.near4.alloc(4 * sc.n, s);
+        const size_t np = pl.bal.partial.n * 2;
+        if (pl.bal.partial4.n < np) pl.bal.partial4.alloc(np, s);
+        evaluate_device(pl, m, phi, nullptr, nullptr, s, nullptr, nullptr, dphi);
+        return;
+    }
+    // other launch shapes: the forward evaluation (phi, the local expansions
+    // and m in tree order), then the derivative's near field in a pass of its own
     evaluate_device(pl, m, phi, nullptr, nullptr, s);
     // near-field derivative sums: near_d[4..5] = sum m_j w^2
     adjoint_near(pl, pl.mtree.p, true, s);
-    const int nleaf = (int)sc.nleaf;
-    const int G = ex.leaf_max <= 16 ? 16 : (ex.leaf_max <= 32 ? 32 : 64);
-    const int P = pl.p <= 16 ? 16 : (pl.p <= 32 ? 32 : 64);
-    const unsigned grid = (unsigned)((nleaf + 256 / G - 1) / (256 / G));
-    auto fin = [&](auto tag, auto gtag, auto ptag) {
-        using T = decltype(tag);
-        constexpr int G_ = decltype(gtag)::value, P_ = decltype(ptag)::value;
-        k_field_final<T, G_, P_><<<grid, 256, 0, s>>>(ex.leaves.p, nleaf, sc.d_box_start.p, sc.d_box_count.p,
-                                                      t.geom.p, t.x.p, t.y.p, (const T*)pl.local.p, pl.p,
-                                                      pl.near_d.p, t.perm.p, (double2*)dphi);
-    };
-    auto fin_g = [&](auto tag, auto ptag) {
-        if (G == 16) fin(tag, std::integral_constant<int, 16>{}, ptag);
-        else if (G == 32) fin(tag, std::integral_constant<int, 32>{}, ptag);
-        else fin(tag, std::integral_constant<int, 64>{}, ptag);
-    };
-    auto fin_p = [&](auto tag) {
-        if (P == 16) fin_g(tag, std::integral_constant<int, 16>{});
-        else if (P == 32) fin_g(tag, std::integral_constant<int, 32>{});
-        else fin_g(tag, std::integral_constant<int, 64>{});
-    };
-    if (mixed) fin_p(float{});
-    else fin_p(double{});
-    check_launch("field final");
+    (mixed ? launch_field<float> : launch_field<double>)(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p,
+                                                         sc.d_box_count.p, ex.leaf_max, t.geom.p, t.x.p, t.y.p,
+                                                         pl.local.p, pl.p, pl.near_d.p, 6, 4, t.perm.p, nullptr,
+                                                         dphi, s);
 }
 
 // adjoint P2P work items (leaf, target chunk) grouped by shape; host side

@@ -178,7 +178,6 @@ void balance_launch(Plan::Balance& b, const void* items, int n, const std::vecto
 void balance_finish(Plan::Balance& b, int n, int vals, hipStream_t s)
 {
     b.total = b.cls.empty() ? 0 : b.cls.back();
-    b.vals = vals;
     b.xitems.alloc(std::max<int64_t>(b.total, 1), s);
     if (n > 0) {
         k_item_expand<<<(n + 255) / 256, 256, 0, s>>>(n, b.icnt.p, b.ioff.p, b.xitems.p);
@@ -189,12 +188,12 @@ void balance_finish(Plan::Balance& b, int n, int vals, hipStream_t s)
     if (b.total > n) b.partial.alloc((size_t)b.total * kItemTargets * vals, s);
 }
 
-void combine_chunks(const Plan::Balance& b, const void* items, int n, const int32_t* bstart, double* out,
-                    hipStream_t s)
+void combine_chunks(const Plan::Balance& b, const double* partial, int vals, const void* items, int n,
+                    const int32_t* bstart, double* out, hipStream_t s)
 {
     if (b.total <= n || n == 0) return;     // no item is split
-    k_item_combine<<<(n + 3) / 4, 256, 0, s>>>((const BalItem*)items, n, b.icnt.p, b.ioff.p, bstart, b.partial.p,
-                                               b.vals, out);
+    k_item_combine<<<(n + 3) / 4, 256, 0, s>>>((const BalItem*)items, n, b.icnt.p, b.ioff.p, bstart, partial,
+                                               vals, out);
     check_launch("combine chunks");
 }
 

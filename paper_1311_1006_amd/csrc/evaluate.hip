@@ -26,6 +26,10 @@ void launch_p2m(const int32_t* leaves, int nleaf, const int32_t* bstart, const i
                 const double* geom, const double* X, const double* Y, const double* mt, int p, void* mp,
                 hipStream_t s, const GatherOut* go);
 template <class T>
+void launch_l2p_field(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
+                      const double* geom, const double* X, const double* Y, const void* loc, int p,
+                      const double* near4, const int32_t* perm, double* phi, double* dphi, hipStream_t s);
+template <class T>
 void launch_l2p(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
                 const double* geom, const double* X, const double* Y, const void* loc, int p,
                 const double* nearf, const int32_t* perm, double* phi, double* phi_near, double* phi_far,
@@ -47,8 +51,8 @@ void launch_down_mid(const SubPlan& sp, const double* geom, int p, void* loc, co
 template <class T>
 void launch_down_subtree(const SubPlan& sp, bool staged, const int32_t* bstart, const int32_t* bcount,
                          const double* geom, const double* X, const double* Y, void* loc, int p, const double* nearf,
-                         const int32_t* perm, double* phi, double* phi_near, double* phi_far, const long long* guard,
-                         const double* binom, hipStream_t s);
+                         const int32_t* perm, double* phi, double* phi_near, double* phi_far, double* dphi,
+                         const long long* guard, const double* fact, hipStream_t s);
 
 struct P2PItemH {
     int32_t leaf, t0, tn, pad;
@@ -262,14 +266,17 @@ static void run_up(Plan& pl, const double* m, const double* mt, void* mp, hipStr
 // at the points when an output is given
 template <class T>
 static void run_down_leaves(Plan& pl, bool staged, void* loc, double* phi, double* phi_near, double* phi_far,
-                            const long long* guard, hipStream_t s)
+                            const long long* guard, hipStream_t s, double* dphi = nullptr)
 {
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
     PlanExtra& ex = *extra(pl);
     launch_down_subtree<T>(ex.sub, staged, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, loc, pl.p,
-                           pl.near.p, t.perm.p, phi, phi_near, phi_far, guard, ex.fact.p, s);
-    if (phi || phi_near || phi_far)
+                           dphi ? pl.near4.p : pl.near.p, t.perm.p, phi, phi_near, phi_far, dphi, guard, ex.fact.p, s);
+    if (dphi)
+        launch_l2p_field<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max,
+                            t.geom.p, t.x.p, t.y.p, loc, pl.p, pl.near4.p, t.perm.p, phi, dphi, s);
+    else if (phi || phi_near || phi_far)
         launch_l2p<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max,
                       t.geom.p, t.x.p, t.y.p, loc, pl.p, pl.near.p, t.perm.p, phi, phi_near, phi_far, s, guard);
 }
@@ -320,28 +327,39 @@ static void run_far_down(Plan& pl, PlanExtra& ex, const void* mp, void* loc, hip
     if (all) run_down_leaves<T>(pl, true, loc, nullptr, nullptr, nullptr, guard, s);
 }
 
-void combine_chunks(const Plan::Balance& b, const void* items, int n, const int32_t* bstart, double* out,
-                    hipStream_t s);
+void combine_chunks(const Plan::Balance& b, const double* partial, int vals, const void* items, int n,
+                    const int32_t* bstart, double* out, hipStream_t s);
 
-static void run_p2p(Plan& pl, PlanExtra& ex, hipStream_t s, const long long* guard, bool log_kernel = false)
+bool field_one_pass(const Plan& pl)
+{
+    for (auto& c : pl.ex->p2p_class)
+        if (c.sub != 4) return false;
+    return true;
+}
+
+// the near field: into pl.near, or with `field` (and the derivative's sums) pl.near4
+static void run_p2p(Plan& pl, PlanExtra& ex, hipStream_t s, const long long* guard, bool log_kernel = false,
+                    bool field = false)
 {
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
     bool mixed = pl.precision == FMM_MIXED;
     const Plan::Balance& b = pl.bal;
     int nitems = 0;
+    double* out = field ? pl.near4.p : pl.near.p;
+    double* partial = field ? b.partial4.p : b.partial.p;
     for (size_t c = 0; c < ex.p2p_class.size(); ++c) {
         const P2PClass& k = ex.p2p_class[c];
         nitems = std::max<int>(nitems, (int)(k.off + k.n));
         const int64_t x0 = b.cls[c], x1 = b.cls[c + 1];
         launch_p2p(mixed, k.tg, k.sub, ex.p2p_items.p, (int)x0, b.xitems.p ? b.xitems.p + x0 : nullptr,
                    (int)(x1 - x0), b.icnt.p, b.ioff.p,
-                   b.partial.p, sc.d_box_start.p, sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p,
-                   t.x.p, t.y.p, (const double2*)pl.mtree.p, pl.near.p, s, guard,
+                   partial, sc.d_box_start.p, sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p,
+                   t.x.p, t.y.p, (const double2*)pl.mtree.p, out, s, guard,
                    pl.tune.smooth_delta > 0.0 ? 1.0 / (pl.tune.smooth_delta * pl.tune.smooth_delta) : 0.0,
-                   log_kernel ? ex.logtab.p : nullptr, Targets{}, pl.tune.p2p_src_tile);
+                   log_kernel ? ex.logtab.p : nullptr, Targets{}, pl.tune.p2p_src_tile, field);
     }
-    combine_chunks(b, ex.p2p_items.p, nitems, sc.d_box_start.p, pl.near.p, s);
+    combine_chunks(b, partial, field ? 4 : 2, ex.p2p_items.p, nitems, sc.d_box_start.p, out, s);
 }
 
 // Side streams per device (the near field; the list build), shared by all
@@ -481,10 +499,8 @@ void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, do
 }
 
 void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, double* phi_far, hipStream_t s,
-                     hipEvent_t lists_ev, const long long* guard)
+                     hipEvent_t lists_ev, const long long* guard, double* dphi)
 {
-    Tree& t = *pl.tree;
-    TreeSchedule& sc = *t.sched;
     PlanExtra& ex = *extra(pl);
     bool mixed = pl.precision == FMM_MIXED;
     PhaseTimer tm((pl.tune.flags & FMM_FLAG_PHASE_TIMING) != 0, s);
@@ -511,7 +527,7 @@ void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, d
         if (!early_fork) FMM_HIP(hipEventRecord(pl.ev_fork, s));
         FMM_HIP(hipStreamWaitEvent(pl.nstream, pl.ev_fork, 0));
         if (lists_ev) FMM_HIP(hipStreamWaitEvent(pl.nstream, lists_ev, 0));
-        run_p2p(pl, ex, pl.nstream, guard);
+        run_p2p(pl, ex, pl.nstream, guard, false, dphi != nullptr);
         FMM_HIP(hipEventRecord(pl.ev_join, pl.nstream));
     }
     tm.mark();
@@ -520,10 +536,10 @@ void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, d
     else run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, guard);
     tm.mark();
     if (beside) FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
-    else run_p2p(pl, ex, s, guard);
+    else run_p2p(pl, ex, s, guard, false, dphi != nullptr);
     tm.mark();
     (mixed ? run_down_leaves<float> : run_down_leaves<double>)(pl, staged_down(pl, ex, false), pl.local.p, phi,
-                                                               phi_near, phi_far, guard, s);
+                                                               phi_near, phi_far, guard, s, dphi);
     tm.mark();
     if (tm.on) {
         FMM_HIP(hipEventSynchronize(tm.ev[5]));

@@ -73,7 +73,9 @@ struct Targets {
 // are the points in tree order, positions X, Y and strengths M (FP64; the
 // mixed kernels round the strengths to FP32 as they stage them).  log_table
 // (device, 2 kLogTab values filled by log_table()) selects the logarithmic
-// kernel; NULL: the harmonic one, smoothed with id2 > 0.
+// kernel; NULL: the harmonic one, smoothed with id2 > 0.  With `field` the
+// harmonic kernel and its derivative sum: four values per target in out and
+// partial instead of two.
 constexpr int kLogTab = 128;
 void log_table(double* tab);
 void launch_p2p(bool mixed, int tg, int sub, const void* items, int item_base, const int2* xitems, int nx,
@@ -81,7 +83,7 @@ void launch_p2p(bool mixed, int tg, int sub, const void* items, int item_base, c
                 const int32_t* bcount, const int32_t* s_beg, const int32_t* s_cnt, const int32_t* s_ids,
                 const double* X, const double* Y, const double2* M, double* out, hipStream_t s,
                 const long long* guard, double id2, const double* log_table, const Targets& tgt = Targets{},
-                int src_tile = 0);
+                int src_tile = 0, bool field = false);
 constexpr int kChunkPairs = 128;   // M2L weak pairs per work chunk (longer lists are split)
 
 __host__ __device__ inline int64_t level_base(int l) { return ((int64_t(1) << (2 * l)) - 1) / 3; }
@@ -243,6 +245,7 @@ struct Plan {
     DBuf<double> mtree;            // [N][2] strengths in tree order (FP64); with the tree's
                                    // positions, the sources of the near field
     DBuf<double> near;             // [N][2] P2P result, tree order
+    DBuf<double> near4;            // [N][4] the same with the derivative's sums (field evaluation)
     DBuf<double> mlog;             // [N][2] real strengths of the logarithmic kernel as complex numbers
     DBuf<double> c0;               // [nbox] constant term of the logarithmic local expansions
     // near-field work split into source chunks (see balance.hip)
@@ -251,13 +254,13 @@ struct Plan {
         DBuf<int32_t> icnt, ioff;  // per item: chunks, exclusive prefix (+ total)
         DBuf<int2> xitems;         // (item, chunk) for every chunk, grouped by launch class
         DBuf<double> partial;      // per chunk of a split item: kItemTargets x values
+        DBuf<double> partial4;     // the same with the derivative's sums
         DBuf<int64_t> d_cls;       // expanded offsets of the classes (device)
         std::vector<int64_t> cls;  // the same on the host, nclass + 1 entries
         DBuf<int32_t> bsum;        // scan workspace
         DBuf<int64_t> d_base;      // class starts in the item array
         std::vector<int64_t> h_base;
         int64_t total = 0;
-        int vals = 0;              // values per target in the partial sums
         int32_t h32 = 0;           // host copy of a device total
     } bal, bal_adj, bal_m2l;
     DBuf<char> mpole, local;       // [nbox][p] complex coefficients (T)
@@ -303,8 +306,15 @@ void list_totals_device(Plan& pl, hipStream_t s);
 // lists_ev/guard: an evaluation enqueued before the list flags are read.
 // Its list-reading kernels wait for lists_ev and do nothing when the flag
 // word *guard is non-zero (the lists then need a rebuild or work chunks).
+// dphi: the derivative of the field too (field_one_pass(pl) holds; near4 and,
+// with split lists, bal.partial4 are allocated).
 void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, double* phi_far,
-                     hipStream_t s, hipEvent_t lists_ev = nullptr, const long long* guard = nullptr);
+                     hipStream_t s, hipEvent_t lists_ev = nullptr, const long long* guard = nullptr,
+                     double* dphi = nullptr);
+// whether the near field has a one-pass form with the derivative for the plan's
+// launch shapes (four lane subgroups: the automatic choice), which sums in the
+// order of the separate passes
+bool field_one_pass(const Plan& pl);
 void field_device(Plan& pl, const double* m, double* phi, double* dphi, hipStream_t s);
 void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t M, double* phi, double* dphi,
                             hipStream_t s);

@@ -165,10 +165,55 @@ __device__ __forceinline__ void pair64l(double xi, double yi, const Src64& s, co
     ar = fma(s.mr, lg, ar);
 }
 
+// The harmonic kernel with its derivative: the terms of pair64 / pair32, and
+// sum m_j / (z_i - z_j)^2 from w = 1 / (z_i - z_j) (a coincident position has w
+// = 0).  One pass for both sums: with the derivative in a second pass, which
+// staged every list again, the near field of N = 1e6 (mixed) took 104 + 157 us
+// and takes 196.  In FP32 the derivative keeps a square distance and reciprocal
+// of its own, without FLT_MIN: added before the rounding of dy^2, FLT_MIN
+// decides ties (one pair in about 2^13), and the pass of its own that other
+// launch shapes take has none.
+__device__ __forceinline__ void pair64f(double xi, double yi, const Src64& s, double& ar, double& ai, double& cr,
+                                        double& ci)
+{
+    double dx = xi - s.x, dy = yi - s.y;
+    double r2 = fma(dx, dx, fma(dy, dy, DBL_MIN));
+    double y = rcp_pair(r2);
+    double a = fma(s.mr, dx, s.mi * dy);
+    double b = fma(s.mi, dx, -(s.mr * dy));
+    ar = fma(a, y, ar);
+    ai = fma(b, y, ai);
+    const double wr = dx * y, wi = -dy * y;
+    const double w2r = wr * wr - wi * wi, w2i = 2.0 * wr * wi;
+    cr += s.mr * w2r - s.mi * w2i;
+    ci += s.mr * w2i + s.mi * w2r;
+}
+__device__ __forceinline__ void pair32f(double xi, double yi, const Src32& s, float& ar, float& ai, float& cr,
+                                        float& ci)
+{
+    float dx = (float)(xi - s.x);
+    float dy = (float)(yi - s.y);
+    float r2 = fmaf(dx, dx, fmaf(dy, dy, FLT_MIN));
+    float y = __builtin_amdgcn_rcpf(r2);
+    float a = fmaf(s.mr, dx, s.mi * dy);
+    float b = fmaf(s.mi, dx, -(s.mr * dy));
+    ar = fmaf(a, y, ar);
+    ai = fmaf(b, y, ai);
+    const float r2d = dx * dx + dy * dy;
+    const float q = fminf(__builtin_amdgcn_rcpf(r2d), FLT_MAX);
+    const float wr = dx * q, wi = -dy * q;
+    const float w2r = wr * wr - wi * wi, w2i = 2.0f * wr * wi;
+    cr += s.mr * w2r - s.mi * w2i;
+    ci += s.mr * w2i + s.mi * w2r;
+}
+
 // near-field kernels: KERN 0 the plain harmonic kernel, 1 with the Gaussian
-// smoother, 2 the logarithmic kernel (each its own instantiation, so the
-// plain kernel keeps its registers)
-constexpr int kKernPlain = 0, kKernSmooth = 1, kKernLog = 2;
+// smoother, 2 the logarithmic kernel, 3 the harmonic kernel with its
+// derivative (each its own instantiation, so the plain kernel keeps its
+// registers).  Sums per target: the derivative's two behind the first two.
+constexpr int kKernPlain = 0, kKernSmooth = 1, kKernLog = 2, kKernField = 3;
+template <int KERN>
+constexpr int kSums = KERN == kKernField ? 4 : 2;
 
 // The value x of a partner lane whose bit M differs from this lane's and
 // whose other bits above M agree: lane ^ 1 and lane ^ 2 (quad
@@ -257,7 +302,7 @@ k_p2p64(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
         double* __restrict__ partial, const int32_t* __restrict__ bstart,
         const int32_t* __restrict__ bcount, const int32_t* __restrict__ s_beg, const int32_t* __restrict__ s_cnt,
         const int32_t* __restrict__ s_ids, const double* __restrict__ X, const double* __restrict__ Y,
-        const double2* __restrict__ M, double2* __restrict__ out, const long long* __restrict__ guard, double id2,
+        const double2* __restrict__ M, double* __restrict__ out, const long long* __restrict__ guard, double id2,
         const Targets tgt, int src_lim, const double2* __restrict__ log_tab)
 {
     if (guard != nullptr && *guard != 0) return;   // lists flagged: this launch is void
@@ -285,12 +330,12 @@ k_p2p64(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
     const int base = (tgt.start ? tgt.start : bstart)[it.leaf] + it.t0;
     const double* tx = tgt.start ? tgt.x : X;
     const double* ty = tgt.start ? tgt.y : Y;
-    double xi[TG], yi[TG], ar[TG], ai[TG];
+    double xi[TG], yi[TG], ar[TG], ai[TG], cr[TG], ci[TG];
 #pragma unroll
     for (int t = 0; t < TG; ++t) {
         int k = g * TG + t;
         const int i = base + (k < it.tn ? k : 0);
-        xi[t] = tx[i]; yi[t] = ty[i]; ar[t] = 0.0; ai[t] = 0.0;
+        xi[t] = tx[i]; yi[t] = ty[i]; ar[t] = ai[t] = cr[t] = ci[t] = 0.0;
     }
     // the item's entries, or those of its chunk
     const int e0 = s_beg[it.leaf], ce = chunk_entries(bcount[it.leaf]);
@@ -321,6 +366,12 @@ k_p2p64(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
 #pragma unroll
                 for (int t = 0; t < TG; ++t) pair64l(xi[t], yi[t], s, ltab, ar[t]);
             }
+        } else if constexpr (KERN == kKernField) {
+            for (int c = 0; c < npad; c += NL, sp += NL) {
+                const Src64 s = *sp;
+#pragma unroll
+                for (int t = 0; t < TG; ++t) pair64f(xi[t], yi[t], s, ar[t], ai[t], cr[t], ci[t]);
+            }
         } else {
             for (int c = 0; c < npad; c += NL, sp += NL) {
                 const Src64 s = *sp;
@@ -330,18 +381,26 @@ k_p2p64(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
         }
         wave_sync();
     }
-    double v[2 * TG];
+    constexpr int S = kSums<KERN>, V = S * TG;
+    double v[V];
 #pragma unroll
-    for (int t = 0; t < TG; ++t) { v[2 * t] = ar[t]; v[2 * t + 1] = ai[t]; }
-    butterfly<2 * TG, NL>(v, lane);
-    const int idx = butterfly_index<2 * TG, NL>(sl);
+    for (int t = 0; t < TG; ++t) {
+        v[S * t] = ar[t];
+        v[S * t + 1] = ai[t];
+        if constexpr (KERN == kKernField) {
+            v[S * t + 2] = cr[t];
+            v[S * t + 3] = ci[t];
+        }
+    }
+    butterfly<V, NL>(v, lane);
+    const int idx = butterfly_index<V, NL>(sl);
     // lanes holding the same value index: write from the lowest one
-    const int t = idx >> 1, comp = idx & 1;
-    const bool writer = (sl & ((NL / (2 * TG) > 1) ? (NL / (2 * TG) - 1) : 0)) == 0;
+    const int t = idx / S, comp = idx % S;
+    const bool writer = (sl & ((NL / V > 1) ? (NL / V - 1) : 0)) == 0;
     const int k = g * TG + t;
     if (writer && k < it.tn) {
-        if (nch == 1) reinterpret_cast<double*>(out + base + k)[comp] = v[0];
-        else partial[((int64_t)(ioff[xe.x] + xe.y) * kItemTargets + k) * 2 + comp] = v[0];
+        if (nch == 1) out[(int64_t)S * (base + k) + comp] = (double)v[0];
+        else partial[((int64_t)(ioff[xe.x] + xe.y) * kItemTargets + k) * S + comp] = (double)v[0];
     }
 }
 
@@ -352,7 +411,7 @@ k_p2p32(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
         double* __restrict__ partial, const int32_t* __restrict__ bstart,
         const int32_t* __restrict__ bcount, const int32_t* __restrict__ s_beg, const int32_t* __restrict__ s_cnt,
         const int32_t* __restrict__ s_ids, const double* __restrict__ X, const double* __restrict__ Y,
-        const double2* __restrict__ M, double2* __restrict__ out, const long long* __restrict__ guard, float id2,
+        const double2* __restrict__ M, double* __restrict__ out, const long long* __restrict__ guard, float id2,
         const Targets tgt, int src_lim)
 {
     if (guard != nullptr && *guard != 0) return;   // lists flagged: this launch is void
@@ -376,12 +435,12 @@ k_p2p32(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
     const double* tx = tgt.start ? tgt.x : X;
     const double* ty = tgt.start ? tgt.y : Y;
     double xi[TG], yi[TG];
-    float ar[TG], ai[TG];
+    float ar[TG], ai[TG], cr[TG], ci[TG];
 #pragma unroll
     for (int t = 0; t < TG; ++t) {
         int k = g * TG + t;
         const int i = base + (k < it.tn ? k : 0);
-        xi[t] = tx[i]; yi[t] = ty[i]; ar[t] = 0.f; ai[t] = 0.f;
+        xi[t] = tx[i]; yi[t] = ty[i]; ar[t] = ai[t] = cr[t] = ci[t] = 0.f;
     }
     // the item's entries, or those of its chunk
     const int e0 = s_beg[it.leaf], ce = chunk_entries(bcount[it.leaf]);
@@ -412,6 +471,12 @@ k_p2p32(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
 #pragma unroll
                 for (int t = 0; t < TG; ++t) pair32l(xi[t], yi[t], s, ar[t]);
             }
+        } else if constexpr (KERN == kKernField) {
+            for (int c = 0; c < npad; c += NL, sp += NL) {
+                const Src32 s = *sp;
+#pragma unroll
+                for (int t = 0; t < TG; ++t) pair32f(xi[t], yi[t], s, ar[t], ai[t], cr[t], ci[t]);
+            }
         } else {
             for (int c = 0; c < npad; c += NL, sp += NL) {
                 const Src32 s = *sp;
@@ -421,17 +486,26 @@ k_p2p32(const P2PItem* __restrict__ items, int item_base, const int2* __restrict
         }
         wave_sync();
     }
-    float v[2 * TG];
+    constexpr int S = kSums<KERN>, V = S * TG;
+    float v[V];
 #pragma unroll
-    for (int t = 0; t < TG; ++t) { v[2 * t] = ar[t]; v[2 * t + 1] = ai[t]; }
-    butterfly<2 * TG, NL>(v, lane);
-    const int idx = butterfly_index<2 * TG, NL>(sl);
-    const int t = idx >> 1, comp = idx & 1;
-    const bool writer = (sl & ((NL / (2 * TG) > 1) ? (NL / (2 * TG) - 1) : 0)) == 0;
+    for (int t = 0; t < TG; ++t) {
+        v[S * t] = ar[t];
+        v[S * t + 1] = ai[t];
+        if constexpr (KERN == kKernField) {
+            v[S * t + 2] = cr[t];
+            v[S * t + 3] = ci[t];
+        }
+    }
+    butterfly<V, NL>(v, lane);
+    const int idx = butterfly_index<V, NL>(sl);
+    // lanes holding the same value index: write from the lowest one
+    const int t = idx / S, comp = idx % S;
+    const bool writer = (sl & ((NL / V > 1) ? (NL / V - 1) : 0)) == 0;
     const int k = g * TG + t;
     if (writer && k < it.tn) {
-        if (nch == 1) reinterpret_cast<double*>(out + base + k)[comp] = (double)v[0];
-        else partial[((int64_t)(ioff[xe.x] + xe.y) * kItemTargets + k) * 2 + comp] = (double)v[0];
+        if (nch == 1) out[(int64_t)S * (base + k) + comp] = (double)v[0];
+        else partial[((int64_t)(ioff[xe.x] + xe.y) * kItemTargets + k) * S + comp] = (double)v[0];
     }
 }
 
@@ -446,11 +520,11 @@ static void launch_kern(bool mixed, const P2PItem* items, int item_base, const i
     const int grid = (nx + 3) / 4;
     if (mixed)
         k_p2p32<TG, SUB, KERN><<<grid, 256, 0, s>>>(items, item_base, xitems, nx, icnt, ioff, partial, bstart,
-                                                   bcount, s_beg, s_cnt, s_ids, X, Y, M, (double2*)out, guard,
+                                                   bcount, s_beg, s_cnt, s_ids, X, Y, M, out, guard,
                                                    (float)id2, tgt, src_lim);
     else
         k_p2p64<TG, SUB, KERN><<<grid, 256, 0, s>>>(items, item_base, xitems, nx, icnt, ioff, partial, bstart,
-                                                   bcount, s_beg, s_cnt, s_ids, X, Y, M, (double2*)out, guard,
+                                                   bcount, s_beg, s_cnt, s_ids, X, Y, M, out, guard,
                                                    id2, tgt, src_lim, log_tab);
 }
 
@@ -459,11 +533,15 @@ static void launch_one(bool mixed, const P2PItem* items, int item_base, const in
                        const int32_t* ioff, double* partial, const int32_t* bstart,
                        const int32_t* bcount, const int32_t* s_beg, const int32_t* s_cnt, const int32_t* s_ids,
                        const double* X, const double* Y, const double2* M, double* out, hipStream_t s,
-                       const long long* guard, double id2, const double* log_table, const Targets& tgt, int src_lim)
+                       const long long* guard, double id2, const double* log_table, const Targets& tgt, int src_lim, bool field)
 {
 #define ARGS mixed, items, item_base, xitems, nx, icnt, ioff, partial, bstart, bcount, s_beg, s_cnt, s_ids, X, Y, \
              M, out, s, guard, id2, tgt, src_lim, (const double2*)log_table
-    if (log_table) launch_kern<TG, SUB, kKernLog>(ARGS);
+    if (field) {
+        // the lanes of a subgroup hold all the sums of its targets
+        if constexpr (kSums<kKernField> * TG <= 64 / SUB) launch_kern<TG, SUB, kKernField>(ARGS);
+        else throw Error(FMM_EINVAL, "no near-field shape with the derivative");
+    } else if (log_table) launch_kern<TG, SUB, kKernLog>(ARGS);
     else if (id2 > 0.0) launch_kern<TG, SUB, kKernSmooth>(ARGS);
     else launch_kern<TG, SUB, kKernPlain>(ARGS);
 #undef ARGS
@@ -491,7 +569,7 @@ void launch_p2p(bool mixed, int tg, int sub, const void* items, int item_base, c
                 const int32_t* ioff, double* partial, const int32_t* bstart,
                 const int32_t* bcount, const int32_t* s_beg, const int32_t* s_cnt, const int32_t* s_ids,
                 const double* X, const double* Y, const double2* M, double* out, hipStream_t s,
-                const long long* guard, double id2, const double* log_table, const Targets& tgt, int src_tile)
+                const long long* guard, double id2, const double* log_table, const Targets& tgt, int src_tile, bool field)
 {
     if (nx == 0) return;
     // sources staged per pass: the LDS buffer, or fewer (a multiple of every
@@ -502,7 +580,7 @@ void launch_p2p(bool mixed, int tg, int sub, const void* items, int item_base, c
 #define CASE(TG_, SUB_)                                                                                   \
     if (tg == TG_ && sub == SUB_) {                                                                       \
         launch_one<TG_, SUB_>(mixed, it, item_base, xitems, nx, icnt, ioff, partial, bstart, bcount, s_beg, s_cnt, \
-                              s_ids, X, Y, M, out, s, guard, id2, log_table, tgt, src_lim);                          \
+                              s_ids, X, Y, M, out, s, guard, id2, log_table, tgt, src_lim, field);                          \
         check_launch("p2p");                                                                              \
         return;                                                                                           \
     }

@@ -502,13 +502,15 @@ k_down_mid(SubWork work, const double* __restrict__ geom, int p, T* loc, const d
 // points' loads need the leaf's start) instead of once per phase.
 // STAGED: the only ancestor is R's parent, whose complete expansion is stored;
 // R and its children are stored complete as well, every level rounded to T.
-// EVAL: L2P at the points.
-template <class T, int P, bool STAGED, bool EVAL>
+// EVAL: L2P at the points; EVAL 2: with the derivative (d/dz = (1/rs) d/dw,
+// Horner in w), the near field's four sums per point in nearf.
+template <class T, int P, bool STAGED, int EVAL>
 __global__ void __launch_bounds__(256)
 k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
             const double* __restrict__ geom, const double* __restrict__ X, const double* __restrict__ Y, T* loc,
             int p, const double2* __restrict__ nearf, const int32_t* __restrict__ perm, double2* phi,
-            double2* phi_near, double2* phi_far, const long long* __restrict__ guard, const double* __restrict__ fact)
+            double2* phi_near, double2* phi_far, double2* dphi, const long long* __restrict__ guard,
+            const double* __restrict__ fact)
 {
     if (guard != nullptr && *guard != 0) return;   // lists flagged: this launch is void
     using T2 = typename Vec2<T>::type;
@@ -557,16 +559,17 @@ k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __r
     const double facR = fact[threadIdx.x & 63];
     // the leaf's first points (a lane past the leaf's end reads point 0)
     double px[NPT], py[NPT];
-    double2 pn[NPT];
+    double2 pn[NPT], pd[NPT];
     int po[NPT];
-    if constexpr (EVAL) {
+    if constexpr (EVAL != 0) {
 #pragma unroll
         for (int q = 0; q < NPT; ++q) {
             const int j = sl + 16 * q;
             const int i = j < n ? st + j : 0;
             px[q] = X[i];
             py[q] = Y[i];
-            pn[q] = nearf[i];
+            pn[q] = nearf[EVAL == 2 ? 2 * (int64_t)i : i];
+            if constexpr (EVAL == 2) pd[q] = nearf[2 * (int64_t)i + 1];
             po[q] = perm[i];
         }
     }
@@ -648,14 +651,14 @@ k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __r
             sanc[gl][l] = r;
         });
     }
-    if constexpr (!EVAL) return;
+    if constexpr (EVAL == 0) return;
     wave_sync();
     // ---- L2P at the leaf's points (Horner), plus the near field, to input order
     const double inv = 1.0 / gf.rs;
     const double2* co = sanc[gl];
     for (int j = sl, q = 0; j < n; j += 16, ++q) {
         const int i = st + j;
-        double x, y, nfx, nfy;
+        double x, y, nfx, nfy, ndx = 0.0, ndy = 0.0;
         int o;
         if (q < NPT) {
             // (a run-time index into the arrays would move them to scratch)
@@ -664,23 +667,40 @@ k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __r
             nfx = q == 0 ? pn[0].x : pn[NPT - 1].x;
             nfy = q == 0 ? pn[0].y : pn[NPT - 1].y;
             o = q == 0 ? po[0] : po[NPT - 1];
+            if constexpr (EVAL == 2) {
+                ndx = q == 0 ? pd[0].x : pd[NPT - 1].x;
+                ndy = q == 0 ? pd[0].y : pd[NPT - 1].y;
+            }
         } else {
             x = X[i]; y = Y[i];
-            const double2 nf = nearf[i];
+            const double2 nf = nearf[EVAL == 2 ? 2 * (int64_t)i : i];
             nfx = nf.x; nfy = nf.y;
+            if constexpr (EVAL == 2) {
+                const double2 nd = nearf[2 * (int64_t)i + 1];
+                ndx = nd.x; ndy = nd.y;
+            }
             o = perm[i];
         }
         const double2 z = make_double2((x - gf.x) * inv, (y - gf.y) * inv);
-        double2 acc = co[P - 1];
+        double2 acc = co[P - 1], der = make_double2(0.0, 0.0);
 #pragma unroll
         for (int l = P - 2; l >= 0; --l) {
+            if constexpr (EVAL == 2) {
+                der = cmul(der, z);
+                der.x += acc.x;
+                der.y += acc.y;
+            }
             acc = cmul(acc, z);
             acc.x += co[l].x;
             acc.y += co[l].y;
         }
         if (phi) phi[o] = make_double2(acc.x + nfx, acc.y + nfy);
-        if (phi_near) phi_near[o] = make_double2(nfx, nfy);
-        if (phi_far) phi_far[o] = acc;
+        if constexpr (EVAL == 2) {
+            dphi[o] = make_double2(der.x * inv - ndx, der.y * inv - ndy);
+        } else {
+            if (phi_near) phi_near[o] = make_double2(nfx, nfy);
+            if (phi_far) phi_far[o] = acc;
+        }
     }
 }
 
@@ -753,20 +773,22 @@ void launch_down_mid(const SubPlan& sp, const double* geom, int p, void* loc, co
 template <class T>
 void launch_down_subtree(const SubPlan& sp, bool staged, const int32_t* bstart, const int32_t* bcount,
                          const double* geom, const double* X, const double* Y, void* loc, int p, const double* nearf,
-                         const int32_t* perm, double* phi, double* phi_near, double* phi_far, const long long* guard,
-                         const double* fact, hipStream_t s)
+                         const int32_t* perm, double* phi, double* phi_near, double* phi_far, double* dphi,
+                         const long long* guard, const double* fact, hipStream_t s)
 {
     if (sp.roots.n == 0) return;
     const SubWork w = sub_work(sp, sp.roots);
     const unsigned grid = (unsigned)sp.roots.n;
     const bool eval = phi != nullptr || phi_near != nullptr || phi_far != nullptr;
 #define DOWN_ARGS w, bstart, bcount, geom, X, Y, (T*)loc, p, (const double2*)nearf, perm, (double2*)phi, \
-                  (double2*)phi_near, (double2*)phi_far, guard, fact
-#define DOWN_CASE(P_)                                                                       \
-    if (staged && eval) k_down_leaf<T, P_, true, true><<<grid, 256, 0, s>>>(DOWN_ARGS);     \
-    else if (staged) k_down_leaf<T, P_, true, false><<<grid, 256, 0, s>>>(DOWN_ARGS);       \
-    else if (eval) k_down_leaf<T, P_, false, true><<<grid, 256, 0, s>>>(DOWN_ARGS);         \
-    else k_down_leaf<T, P_, false, false><<<grid, 256, 0, s>>>(DOWN_ARGS);
+                  (double2*)phi_near, (double2*)phi_far, (double2*)dphi, guard, fact
+#define DOWN_CASE(P_)                                                                    \
+    if (staged && dphi) k_down_leaf<T, P_, true, 2><<<grid, 256, 0, s>>>(DOWN_ARGS);     \
+    else if (dphi) k_down_leaf<T, P_, false, 2><<<grid, 256, 0, s>>>(DOWN_ARGS);         \
+    else if (staged && eval) k_down_leaf<T, P_, true, 1><<<grid, 256, 0, s>>>(DOWN_ARGS); \
+    else if (staged) k_down_leaf<T, P_, true, 0><<<grid, 256, 0, s>>>(DOWN_ARGS);        \
+    else if (eval) k_down_leaf<T, P_, false, 1><<<grid, 256, 0, s>>>(DOWN_ARGS);         \
+    else k_down_leaf<T, P_, false, 0><<<grid, 256, 0, s>>>(DOWN_ARGS);
     SUB_BY_ORDER(DOWN_CASE)
 #undef DOWN_CASE
 #undef DOWN_ARGS
@@ -783,7 +805,7 @@ void launch_down_subtree(const SubPlan& sp, bool staged, const int32_t* bstart, 
     template void launch_down_subtree<T>(const SubPlan&, bool, const int32_t*, const int32_t*,            \
                                          const double*, const double*, const double*, void*, int,         \
                                          const double*, const int32_t*, double*, double*, double*,        \
-                                         const long long*, const double*, hipStream_t);
+                                         double*, const long long*, const double*, hipStream_t);
 INST(double)
 INST(float)
 #undef INST

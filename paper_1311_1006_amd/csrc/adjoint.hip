@@ -504,7 +504,7 @@ void field_device(Plan& pl, const double* m, double* phi, double* dphi, hipStrea
 }
 
 // adjoint P2P work items (leaf, target chunk) grouped by shape; host side
-void prepare_adjoint_items(Plan& pl, PlanExtra& ex, const std::vector<int32_t>& leaves, hipStream_t s)
+void prepare_adjoint_items(Plan& pl, PlanExtra& ex, const std::vector<int32_t>& leaves, UploadPack& up)
 {
     TreeSchedule& sc = *pl.tree->sched;
     const bool mixed = pl.precision == FMM_MIXED;
@@ -522,10 +522,7 @@ void prepare_adjoint_items(Plan& pl, PlanExtra& ex, const std::vector<int32_t>& 
         ex.adj_class.push_back({kv.first.first, kv.first.second, (int64_t)items.size(), (int64_t)kv.second.size()});
         items.insert(items.end(), kv.second.begin(), kv.second.end());
     }
-    ex.adj_items.alloc(std::max<size_t>(items.size() * sizeof(P2PItemA), 1), s);
-    if (!items.empty())
-        FMM_HIP(hipMemcpyAsync(ex.adj_items.p, items.data(), items.size() * sizeof(P2PItemA), hipMemcpyHostToDevice, s));
-    FMM_HIP(hipStreamSynchronize(s));
+    up.add(ex.adj_items, reinterpret_cast<const char*>(items.data()), items.size() * sizeof(P2PItemA));
 }
 
 }  // namespace fmm

@@ -81,18 +81,10 @@ static void p2p_shape(int nt, int knob, int tknob, bool mixed, int* tg, int* sub
     *sub = s;
 }
 
-template <class T>
-static void upload_vec(DBuf<T>& d, const std::vector<T>& h, hipStream_t s)
-{
-    d.alloc(std::max<size_t>(h.size(), 1), s);
-    if (!h.empty())
-        FMM_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
-}
-
 // the subtree launches of every pass: for a problem with levels 0 .. L-1, L >=
 // 3, the roots are the boxes of level L-3; upward steps go from there to level
 // 1, downward ones from level 1 to level L-4
-static void prepare_subtrees(const TreeSchedule& sc, SubPlan& sp, hipStream_t s)
+static void prepare_subtrees(const TreeSchedule& sc, SubPlan& sp, UploadPack& up)
 {
     sp.uniform = sc.L[0] >= 3;
     sp.L = sc.L[0];
@@ -132,14 +124,14 @@ static void prepare_subtrees(const TreeSchedule& sc, SubPlan& sp, hipStream_t s)
             sp.down[h].push_back(step([m, k](int) { return 1 + m * k; },
                                       [m, k](int L) { return std::max(0, std::min(m, L - 4 - (1 + m * k))); }));
     }
-    upload_vec(sp.shallow, shallow, s);
-    if (!sp.uniform) upload_vec(sp.list, list, s);
-    FMM_HIP(hipStreamSynchronize(s));   // the lists are locals
+    up.add(sp.shallow, shallow);
+    up.add(sp.list, list);
 }
 
 void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
 {
     TreeSchedule& sc = *pl.tree->sched;
+    UploadPack up;
     int ml = sc.max_levels;
     ex.level_boxes.assign(ml, {});
     std::vector<int32_t> leaves, child0(sc.nbox, -1);
@@ -165,9 +157,9 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
         all.insert(all.end(), ex.level_boxes[l].begin(), ex.level_boxes[l].end());
     }
     ex.level_boxes_off[ml] = (int64_t)all.size();
-    upload_vec(ex.d_level_boxes, all, s);
-    upload_vec(ex.leaves, leaves, s);
-    upload_vec(ex.child0, child0, s);
+    up.add(ex.d_level_boxes, all);
+    up.add(ex.leaves, leaves);
+    up.add(ex.child0, child0);
     // P2P work items grouped by launch shape
     const bool mixed = pl.precision == FMM_MIXED;
     std::map<std::pair<int, int>, std::vector<P2PItemH>> cls;
@@ -185,13 +177,9 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
         ex.p2p_class.push_back({kv.first.first, kv.first.second, (int64_t)items.size(), (int64_t)kv.second.size()});
         items.insert(items.end(), kv.second.begin(), kv.second.end());
     }
-    {
-        std::vector<char> raw(items.size() * sizeof(P2PItemH));
-        if (!items.empty()) std::memcpy(raw.data(), items.data(), raw.size());
-        upload_vec(ex.p2p_items, raw, s);
-    }
-    prepare_adjoint_items(pl, ex, leaves, s);
-    prepare_subtrees(sc, ex.sub, s);
+    up.add(ex.p2p_items, reinterpret_cast<const char*>(items.data()), items.size() * sizeof(P2PItemH));
+    prepare_adjoint_items(pl, ex, leaves, up);
+    prepare_subtrees(sc, ex.sub, up);
     // binomial table C(n, k), n < kBinomRows, k < kBinomStride (Pascal's rule)
     std::vector<double> bin(kBinomRows * kBinomStride, 0.0);
     for (int n = 0; n < kBinomRows; ++n) {
@@ -199,7 +187,7 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
         for (int k = 1; k <= n && k < kBinomStride; ++k)
             bin[n * kBinomStride + k] = bin[(n - 1) * kBinomStride + k - 1] + (k < n ? bin[(n - 1) * kBinomStride + k] : 0.0);
     }
-    upload_vec(ex.binom, bin, s);
+    up.add(ex.binom, bin);
     // factorials and their reciprocals, each rounded once from extended precision
     std::vector<double> fact(2 * kMaxP);
     {
@@ -210,11 +198,11 @@ void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)
             fact[kMaxP + k] = (double)(1.0L / f);
         }
     }
-    upload_vec(ex.fact, fact, s);
+    up.add(ex.fact, fact);
     std::vector<double> logtab(2 * kLogTab);
     log_table(logtab.data());
-    upload_vec(ex.logtab, logtab, s);
-    FMM_HIP(hipStreamSynchronize(s));
+    up.add(ex.logtab, logtab);
+    up.upload(ex.block, s);
 }
 
 void alloc_eval_buffers(Plan& pl, hipStream_t s)

@@ -20,12 +20,12 @@ constexpr int kSubLevels = 3, kSubLevelsHigh = 2;   // levels per launch above t
 struct SubPlan {
     bool uniform = false;       // every problem has the same depth L >= 3: no list
     int L = 0;
-    DBuf<int4> list;            // (root box of the problem, level, box of the level, levels D) per workgroup
+    DView<int4> list;            // (root box of the problem, level, box of the level, levels D) per workgroup
     SubStep roots{};            // the boxes of level L-3 (problems of fewer levels: see shallow)
     // [0] for p <= 32, [1] for more terms (fewer levels per launch):
     std::vector<SubStep> up[2];    // levels L-4 .. 1, bottom up
     std::vector<SubStep> down[2];  // levels 2 .. L-4 from level 1, top down
-    DBuf<int32_t> shallow;      // the leaves of the problems of one or two levels (no shifts between levels)
+    DView<int32_t> shallow;      // the leaves of the problems of one or two levels (no shifts between levels)
     int nshallow = 0, shallow_max = 0;   // their number, and the largest one's points
 };
 // the same as a kernel argument
@@ -38,28 +38,29 @@ struct SubWork {
 struct PlanExtra {
     std::vector<std::vector<int32_t>> level_boxes;  // global ids per level (all problems)
     std::vector<int64_t> level_boxes_off;
-    DBuf<int32_t> d_level_boxes;                    // concatenated per level
-    DBuf<int32_t> leaves;                           // global ids of all leaves
+    DView<int32_t> d_level_boxes;                    // concatenated per level
+    DView<int32_t> leaves;                           // global ids of all leaves
     int leaf_max = 0;                               // largest leaf population
     SubPlan sub;
     int cap_strong = 0, cap_weak = 0;               // per-box list capacities of the one-pass build
     bool levelwise_only = false;                    // a frontier overflowed on this layout
     int64_t pool_strong = 0, pool_weak = 0;        // id pool sizes for the next compact build
     bool compact_only = false;                      // fixed capacities would need too much memory
-    DBuf<double> fact;                              // k! for k < 64, then 1/k!
-    DBuf<double> logtab;                            // table of the near field's FP64 logarithm
-    DBuf<double> binom;                             // binomial table C(n, k), n, k < 64
-    DBuf<int32_t> child0;                           // first child of every box, -1: a leaf
-    DBuf<char> p2p_items;
+    DView<double> fact;                              // k! for k < 64, then 1/k!
+    DView<double> logtab;                            // table of the near field's FP64 logarithm
+    DView<double> binom;                             // binomial table C(n, k), n, k < 64
+    DView<int32_t> child0;                           // first child of every box, -1: a leaf
+    DView<char> p2p_items;
     std::vector<P2PClass> p2p_class;
-    DBuf<char> adj_items;                           // adjoint P2P work items
+    DView<char> adj_items;                           // adjoint P2P work items
     std::vector<P2PClass> adj_class;
+    DBuf<char> block;                               // the memory of the arrays above
 };
 
 inline PlanExtra* extra(Plan& pl) { return pl.ex; }
 
 void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s);
 void alloc_eval_buffers(Plan& pl, hipStream_t s);
-void prepare_adjoint_items(Plan& pl, PlanExtra& ex, const std::vector<int32_t>& leaves, hipStream_t s);
+void prepare_adjoint_items(Plan& pl, PlanExtra& ex, const std::vector<int32_t>& leaves, UploadPack& up);
 
 }  // namespace fmm

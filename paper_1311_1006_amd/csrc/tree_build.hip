@@ -216,30 +216,22 @@ TreeSchedule* make_schedule(const std::vector<int64_t>& off, const std::vector<i
     return sc;
 }
 
-template <class T>
-static void upload(DBuf<T>& d, const std::vector<T>& h, hipStream_t s)
-{
-    d.alloc(std::max<size_t>(h.size(), 1), s);
-    if (!h.empty())
-        FMM_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice, s));
-}
-
 void upload_schedule(TreeSchedule& sc, hipStream_t s)
 {
-    upload(sc.d_segs, sc.segs, s);
-    upload(sc.d_tiles, sc.tiles, s);
-    upload(sc.d_copy, sc.copy_tiles, s);
-    upload(sc.d_lds, sc.lds, s);
-    upload(sc.d_geom, sc.geom, s);
-    upload(sc.d_box_start, sc.box_start, s);
-    upload(sc.d_box_count, sc.box_count, s);
-    upload(sc.d_box_parent, sc.box_parent, s);
-    upload(sc.d_box_level, sc.box_level, s);
-    upload(sc.d_box_prob, sc.box_prob, s);
-    upload(sc.d_off, sc.off, s);
-    upload(sc.d_pbox, sc.pbox, s);
-    // the host vectors must stay alive until the copies ran
-    FMM_HIP(hipStreamSynchronize(s));
+    UploadPack u;
+    u.add(sc.d_segs, sc.segs);
+    u.add(sc.d_tiles, sc.tiles);
+    u.add(sc.d_copy, sc.copy_tiles);
+    u.add(sc.d_lds, sc.lds);
+    u.add(sc.d_geom, sc.geom);
+    u.add(sc.d_box_start, sc.box_start);
+    u.add(sc.d_box_count, sc.box_count);
+    u.add(sc.d_box_parent, sc.box_parent);
+    u.add(sc.d_box_level, sc.box_level);
+    u.add(sc.d_box_prob, sc.box_prob);
+    u.add(sc.d_off, sc.off);
+    u.add(sc.d_pbox, sc.pbox);
+    u.upload(sc.block, s);
 }
 
 // ------------------------------------------------------------ device helpers

@@ -6,7 +6,9 @@ cluster, and points of equal coordinates (ordered by input index)."""
 import numpy as np
 import pytest
 
-from gpu_util import same_tree
+from paper_1311_1006_amd import workloads as W
+
+from gpu_util import dev, e2, host, same_tree
 
 pytestmark = pytest.mark.gpu
 
@@ -40,3 +42,18 @@ def points(kind, n, rng):
 def test_crowded_segments(orc, F, kind, n, L):
     z = points(kind, n, np.random.default_rng(n))
     same_tree(orc, F, z.astype(np.complex128), L)
+
+
+@pytest.mark.parametrize("L", [6, 7, 5])
+def test_evaluation_on_crowded_segments(orc, F, L):
+    # tight clusters (split lists, merge-sorted segments), order 17: the bars of
+    # the clustered parity tests, 1e-12 against the oracle's FMM and in mixed
+    # precision 1e-6 against the direct sum
+    z, m = W.clustered(59000, seed=3, nclusters=16)
+    tree, md = F.build_tree(dev(z), L), dev(m)
+    ref = orc.fmm(z, m, 17, 0.5, L)
+    assert e2(host(F.evaluate(F.plan(tree, 17, 0.5, "fp64"), md)), ref) <= 1e-12
+    for theta, p in ((0.5, 17), (0.45, 15)):
+        phi = host(F.evaluate(F.plan(tree, p, theta, "mixed"), md))
+        sub = W.subsample(z.size, 800, seed=L)
+        assert e2(phi[sub], orc.direct(z, m, sub)) <= 1e-6

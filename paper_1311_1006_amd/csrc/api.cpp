@@ -569,8 +569,10 @@ int fmm_evaluate_points(fmm_plan_t pl, const double* m, const double* y, int64_t
         FMM_REQUIRE(M == 0 || (y && phi_y), "NULL points or output");
         FMM_REQUIRE(pl->pl.tune.smooth_delta == 0.0, "a smoothed near field is evaluated by fmm_evaluate only");
         check_device_state();
-        plan_finalize(pl->pl);
-        plan_join(pl->pl, (hipStream_t)stream);
+        if (M == 0) {               // nothing to evaluate: only an error of the plan's lists
+            plan_finalize(pl->pl);
+            plan_join(pl->pl, (hipStream_t)stream);
+        }
         evaluate_points_device(pl->pl, m, y, M, phi_y, dphi_y, (hipStream_t)stream);
     });
 }

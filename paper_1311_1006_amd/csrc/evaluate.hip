@@ -380,13 +380,17 @@ static bool near_beside(const Plan& pl) { return pl.p > 32 || pl.split_p2p || pl
 
 // The second stream and its events, where they are used, made when the plan is
 // made (the evaluations then create nothing)
-void plan_events(Plan& pl)
+void second_stream(Plan& pl)
 {
-    if (near_beside(pl) && !pl.nstream) {
+    if (!pl.nstream) {
         pl.nstream = side_stream(pl.tree->device, kNearStream);
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_fork, hipEventDisableTiming));
         FMM_HIP(hipEventCreateWithFlags(&pl.ev_join, hipEventDisableTiming));
     }
+}
+void plan_events(Plan& pl)
+{
+    if (near_beside(pl)) second_stream(pl);
 }
 
 // The part of an evaluation that needs no lists: gather and the upward
@@ -403,25 +407,25 @@ void evaluate_upward(Plan& pl, const double* m, hipStream_t s)
     pl.upward_done = true;
 }
 
-// The far field of every box and nothing at the sources: the upward pass
-// (with the gather of the strengths) and the M2L / L2L sweep over every
-// level, so that the multipole expansion and the complete local expansion of
-// every box are in the plan's buffers (evaluation at points apart from the
+// The far field of every box and nothing at the sources: the upward pass (with
+// the gather of the strengths; needs no lists), then the M2L / L2L sweep over
+// every level, so that the multipole expansion and the complete local expansion
+// of every box are in the plan's buffers (evaluation at points apart from the
 // sources).
-void far_field_all(Plan& pl, const double* m, hipStream_t s)
+void far_field_up(Plan& pl, const double* m, hipStream_t s)
 {
-    PlanExtra& ex = *extra(pl);
-    PhaseTimer tm(false, s);
     pl.upward_done = false;
-    auto far = [&](auto tag) {
-        using T = decltype(tag);
-        run_up<T>(pl, m, nullptr, pl.mpole.p, s);
-        run_far_down<T>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
-    };
-    if (pl.precision == FMM_MIXED) far(float());
-    else far(double());
-    // the plan's buffers now hold the far field of m, not a forward evaluation
+    // the plan's buffers will hold the far field of m, not a forward evaluation
     pl.have_forward = false;
+    if (pl.precision == FMM_MIXED) run_up<float>(pl, m, nullptr, pl.mpole.p, s);
+    else run_up<double>(pl, m, nullptr, pl.mpole.p, s);
+}
+void far_field_down(Plan& pl, hipStream_t s)
+{
+    PhaseTimer tm(false, s);
+    PlanExtra& ex = *extra(pl);
+    if (pl.precision == FMM_MIXED) run_far_down<float>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
+    else run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
 }
 
 void transposed_far(Plan& pl, const double* w, hipStream_t s)

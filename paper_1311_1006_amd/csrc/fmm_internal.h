@@ -341,6 +341,7 @@ constexpr int kNearStream = 0, kListStream = 1;
 hipStream_t side_stream(int device, int which);
 void plan_join(Plan& pl, hipStream_t s);
 void plan_events(Plan& pl);
+void second_stream(Plan& pl);   // the plan's second stream and its events, made on first use
 void plan_finalize(Plan& pl);
 void plan_balance(Plan& pl, hipStream_t s);
 void list_totals_device(Plan& pl, hipStream_t s);

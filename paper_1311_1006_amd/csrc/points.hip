@@ -41,10 +41,11 @@
 // The points are sorted by B (a counting sort: count, scan, scatter).  The
 // near field of the points in leaves is the near-field kernel of the sources
 // (p2p.hip) with the points as its targets: sources of the leaf's strong list
-// staged in LDS, a lane subgroup per few points.  The descents run a
+// staged in LDS, a lane subgroup per few points; with the derivative a kernel
+// of its own (k_pts_near_der; few points descend instead).  The descents of the other points run a
 // wavefront per point, lanes over the boxes of a frontier.  The far field is
-// one lane per point.  With the derivative, every point's near field is a
-// descent (whose first frontier, for a point in a leaf, is summed directly).
+// one lane per point.  Locating, sorting and the descents wait for memory most
+// of the time, so they run on a second stream beside the sources' far field.
 #include <algorithm>
 #include <cfloat>
 #include <type_traits>
@@ -54,12 +55,13 @@
 
 namespace fmm {
 
-void far_field_all(Plan& pl, const double* m, hipStream_t s);
-void launch_exclusive_scan(const int32_t* v, int n, int32_t* bsum, int32_t* out, hipStream_t s);
+void far_field_up(Plan& pl, const double* m, hipStream_t s);
+void far_field_down(Plan& pl, hipStream_t s);
 
 // near-field work items over the points: at most kPtsItem points of one box
 // each, for the (4 targets per lane, 4 subgroups) shape
 constexpr int kPtsItem = 16;
+constexpr int64_t kTwoStreamPoints = 50000, kDescendPoints = 8192;   // see evaluate_points_device
 struct PtsItem {
     int32_t leaf, t0, tn, pad;
 };
@@ -126,44 +128,97 @@ k_pts_locate(const double2* __restrict__ y, int64_t M, int L, const double* __re
     rank[i] = atomicAdd(&cnt[b], 1);
 }
 
+// The boxes' points and the leaves' near-field items (the points of a leaf in
+// groups of kPtsItem) as offsets: one exclusive scan of both, and the items
+// written from it.  Two passes over blocks of 1024 boxes (sums per block, then
+// every block adds those before it); a tree of at most kScanOne boxes takes the
+// second alone, one block walking the boxes.  Both sums, the items and the
+// spare items (no target) in one kernel: ten launches that sorted the points
+// and made the items are four or five (N = M = 1000 on one stream: 74 -> 53 us).
+constexpr int kScanOne = 8192;
+__device__ __forceinline__ int2 pts_counts(const int32_t* __restrict__ cnt, int b, int nb, int lb)
+{
+    const int c = b < nb ? cnt[b] : 0;
+    return make_int2(c, b >= lb ? (c + kPtsItem - 1) / kPtsItem : 0);
+}
+// exclusive scan over the workgroup's 1024 threads; tot receives its sums
+__device__ __forceinline__ int2 scan2_1024(int2 v, int2 (*sh)[16], int2& tot)
+{
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int2 x = make_int2(wave_incl_scan(v.x), wave_incl_scan(v.y));
+    __syncthreads();                       // the sums of an earlier call are read
+    if (lane == 63) (*sh)[w] = x;
+    __syncthreads();
+    int2 before = make_int2(0, 0);
+    tot = make_int2(0, 0);
+    for (int k = 0; k < 16; ++k) {
+        const int2 s = (*sh)[k];
+        if (k < w) { before.x += s.x; before.y += s.y; }
+        tot.x += s.x;
+        tot.y += s.y;
+    }
+    return make_int2(before.x + x.x - v.x, before.y + x.y - v.y);
+}
+__global__ void __launch_bounds__(1024)
+k_pts_scan_sums(const int32_t* __restrict__ cnt, int nb, int lb, int2* bsum)
+{
+    __shared__ int2 sh[16];
+    int2 tot;
+    scan2_1024(pts_counts(cnt, blockIdx.x * 1024 + threadIdx.x, nb, lb), &sh, tot);
+    if (threadIdx.x == 0) bsum[blockIdx.x] = tot;
+}
+__global__ void __launch_bounds__(1024)
+k_pts_scan(const int32_t* __restrict__ cnt, int nb, int lb, const int2* __restrict__ bsum, int32_t* off,
+           PtsItem* items, int nx)
+{
+    __shared__ int2 sh[16];
+    int2 base = make_int2(0, 0), all = make_int2(0, 0), tot;
+    if (bsum) {                            // the sums of the blocks before this one, and of all
+        for (int b0 = 0; b0 < (int)gridDim.x; b0 += 1024) {
+            const int b = b0 + threadIdx.x;
+            const int2 v = b < (int)gridDim.x ? bsum[b] : make_int2(0, 0);
+            const bool pre = b < (int)blockIdx.x;
+            scan2_1024(v, &sh, tot);
+            all.x += tot.x;
+            all.y += tot.y;
+            scan2_1024(pre ? v : make_int2(0, 0), &sh, tot);
+            base.x += tot.x;
+            base.y += tot.y;
+        }
+    }
+    const int first = bsum ? blockIdx.x * 1024 : 0, last = bsum ? min(first + 1024, nb) : nb;
+    for (int b0 = first; b0 < last; b0 += 1024) {
+        const int b = b0 + threadIdx.x;
+        const int2 v = pts_counts(cnt, b, nb, lb), e = scan2_1024(v, &sh, tot);
+        if (b < nb) {
+            off[b] = base.x + e.x;
+            if (b == nb - 1) off[nb] = base.x + e.x + v.x;
+            for (int t = 0; t < v.y; ++t)
+                items[base.y + e.y + t] = PtsItem{b, t * kPtsItem, min(kPtsItem, v.x - t * kPtsItem), 0};
+        }
+        base.x += tot.x;
+        base.y += tot.y;
+    }
+    if (!bsum) all = base;
+    for (int k = all.y + blockIdx.x * 1024 + threadIdx.x; k < nx; k += gridDim.x * 1024)
+        items[k] = PtsItem{0, 0, 0, 0};
+}
+
 // sorted position of every point: its box's offset plus its rank in the box
 // (the order inside a box is immaterial: each point's value depends on its
-// own position only)
-__global__ void k_pts_scatter(const int32_t* __restrict__ box, int64_t M, const int32_t* __restrict__ off,
-                              const int32_t* __restrict__ rank, int32_t* order)
+// own position only), and its position in box order, as the near-field kernel
+// reads its targets
+__global__ void k_pts_scatter(const double2* __restrict__ y, const int32_t* __restrict__ box, int64_t M,
+                              const int32_t* __restrict__ off, const int32_t* __restrict__ rank, int32_t* order,
+                              double* rx, double* ry)
 {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (i >= M) return;
-    order[off[box[i]] + rank[i]] = (int32_t)i;
-}
-
-// the points' positions in box order, as the near-field kernel reads its
-// targets (x[], y[])
-__global__ void k_pts_records(const double2* __restrict__ y, int64_t M, const int32_t* __restrict__ order,
-                              double* rx, double* ry)
-{
-    const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (q >= M) return;
-    const double2 v = y[order[q]];
+    const double2 v = y[i];
+    const int q = off[box[i]] + rank[i];
+    order[q] = (int32_t)i;
     rx[q] = v.x;
     ry[q] = v.y;
-}
-
-// items per leaf: the leaf's points in groups of kPtsItem
-__global__ void k_pts_item_counts(int64_t lb, int nleaf, const int32_t* __restrict__ cnt, int32_t* icnt)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j < nleaf) icnt[j] = (cnt[lb + j] + kPtsItem - 1) / kPtsItem;
-}
-
-__global__ void k_pts_items(int64_t lb, int nleaf, const int32_t* __restrict__ cnt, const int32_t* __restrict__ ioff,
-                            PtsItem* items)
-{
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
-    if (j >= nleaf) return;
-    const int c = cnt[lb + j];
-    for (int t0 = 0, k = ioff[j]; t0 < c; t0 += kPtsItem, ++k)
-        items[k] = PtsItem{(int32_t)(lb + j), t0, min(kPtsItem, c - t0), 0};
 }
 
 // point criterion: a box of radius r at squared distance d2 is well separated
@@ -212,6 +267,14 @@ __device__ __forceinline__ void m2p(const T* a, int p, double rs, double dx, dou
     }
 }
 
+// 1/x by v_rcp_f64 and two Newton steps (a division takes three times the instructions)
+__device__ __forceinline__ double rcp_full(double x)
+{
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+
 // the points of one leaf, directly: phi += m/(y - x), dphi -= m/(y - x)^2
 template <bool DER>
 __device__ __forceinline__ void direct64(const double* __restrict__ X, const double* __restrict__ Y,
@@ -224,7 +287,7 @@ __device__ __forceinline__ void direct64(const double* __restrict__ X, const dou
         const double4 sv = make_double4(X[st + q], Y[st + q], m.x, m.y);   // x, y, Re m, Im m
         const double dx = yx - sv.x, dy = yy - sv.y;
         const double r2 = dx * dx + (dy * dy + DBL_MIN);     // 0/DBL_MIN: a coincident source adds 0
-        const double id = 1.0 / r2;
+        const double id = rcp_full(r2);
         const double a = sv.z * dx + sv.w * dy, b = sv.w * dx - sv.z * dy;   // m conj(y - x)
         phi.x += a * id;
         phi.y += b * id;
@@ -324,6 +387,70 @@ struct Visit {
     }
 };
 
+// The near field with the derivative of the points in leaves: a wavefront per
+// work item (at most 16 points of one leaf), lane (g, t) = point t, every fourth
+// box of the leaf's strong list from g on, its sources one after the other (the
+// 16 lanes of a row read the same source, four boxes are in flight); the four
+// rows' sums are added by two row exchanges.  In mixed precision a box's FP32
+// sums start at zero (boxes 64 entries apart share one: the order of the
+// descents' lanes) and are added in FP64.  N = M = 1e5, L = 7: 212 us as descents
+// of a wavefront per point, 12 of its 64 lanes with a box to sum, now 57 us.
+template <class T>
+__global__ void __launch_bounds__(256)
+k_pts_near_der(const PtsItem* __restrict__ items, int nx, const int32_t* __restrict__ off,
+               const double* __restrict__ rx, const double* __restrict__ ry, const int32_t* __restrict__ bstart,
+               const int32_t* __restrict__ bcount, const int32_t* __restrict__ s_beg,
+               const int32_t* __restrict__ s_cnt, const int32_t* __restrict__ s_ids, const double* __restrict__ X,
+               const double* __restrict__ Y, const double2* __restrict__ mt, double2* tnear, double2* tdnear)
+{
+    const int i = __builtin_amdgcn_readfirstlane(xcd_block() * 4 + (threadIdx.x >> 6));
+    if (i >= nx) return;
+    const PtsItem it = items[i];
+    if (it.tn == 0) return;                       // a spare item
+    const int g = (threadIdx.x >> 4) & 3, t = threadIdx.x & 15;
+    const int64_t q = (int64_t)off[it.leaf] + it.t0 + (t < it.tn ? t : 0);
+    const double yx = rx[q], yy = ry[q];
+    const int e0 = s_beg[it.leaf], n = s_cnt[it.leaf];
+    double2 phi = make_double2(0.0, 0.0), dphi = make_double2(0.0, 0.0);
+    // the first 64 boxes' ranges, a box per lane, loaded together
+    const int lane = threadIdx.x & 63;
+    int st0 = 0, n0 = 0;
+    if (lane < n) {
+        const int32_t S = s_ids[e0 + lane];
+        st0 = bstart[S];
+        n0 = bcount[S];
+    }
+    const int rows = (min(n, 64) + 3) >> 2;        // uniform: every lane takes part in the exchanges
+    for (int k = 0; k < rows; ++k) {
+        const int r = g + 4 * k;
+        int st = __shfl(st0, r, 64), ns = __shfl(n0, r, 64);   // (no box: no sources)
+        float2 nf = make_float2(0.f, 0.f), nd = make_float2(0.f, 0.f);
+        for (int e = r; e < n; e += 64) {
+            if (e != r) {
+                const int32_t S = s_ids[e0 + e];
+                st = bstart[S];
+                ns = bcount[S];
+            }
+            if constexpr (std::is_same<T, float>::value) direct32<true>(X, Y, mt, st, ns, yx, yy, nf, nd);
+            else direct64<true>(X, Y, mt, st, ns, yx, yy, phi, dphi);
+        }
+        phi.x += (double)nf.x;
+        phi.y += (double)nf.y;
+        dphi.x += (double)nd.x;
+        dphi.y += (double)nd.y;
+    }
+    auto sum4 = [](double v) {
+        v += partner<16>(v);
+        return v + partner<32>(v);
+    };
+    phi = make_double2(sum4(phi.x), sum4(phi.y));
+    dphi = make_double2(sum4(dphi.x), sum4(dphi.y));
+    if (g == 0 && t < it.tn) {
+        tnear[q] = phi;
+        tdnear[q] = dphi;
+    }
+}
+
 constexpr int kFront = 512;   // frontier boxes per wavefront (LDS)
 
 // The near field of the points at box-order positions q < nq by descents of
@@ -340,7 +467,7 @@ constexpr int kFront = 512;   // frontier boxes per wavefront (LDS)
 template <class T, bool DER>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && !DER ? 6 : 1)))
 k_pts_descend(const double2* __restrict__ y, const int32_t* __restrict__ order, const int32_t* __restrict__ box,
-              const int32_t* __restrict__ nq_dev, int nq_host, int L, const int8_t* __restrict__ level,
+              const int32_t* __restrict__ nq_dev, int L, const int8_t* __restrict__ level,
               const double* __restrict__ geom, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
               const int32_t* __restrict__ s_beg, const int32_t* __restrict__ s_cnt, const int32_t* __restrict__ s_ids,
               const T* __restrict__ mpole, int p, double theta, const double* __restrict__ X,
@@ -349,7 +476,7 @@ k_pts_descend(const double2* __restrict__ y, const int32_t* __restrict__ order, 
     __shared__ int32_t front[4][2][kFront];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
-    const int nq = nq_dev ? *nq_dev : nq_host;
+    const int nq = *nq_dev;
     const int nw = (int)gridDim.x * 4;
     for (int q = (int)blockIdx.x * 4 + w; q < nq; q += nw) {      // uniform in the wavefront
         const int32_t i = order[q];
@@ -491,7 +618,8 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     // item list: at most M / kPtsItem + nleaf items (spares have no target)
     const int64_t nx = M / kPtsItem + nleaf + 1;
     if (nx >= INT32_MAX / 4) throw Error(FMM_EINVAL, "too many evaluation points");
-    DBuf<int32_t> box, rank, order, cnt, off, bsum, icnt, ioff;
+    DBuf<int32_t> box, rank, order, cnt, off;
+    DBuf<int2> bsum;
     DBuf<double> rx, ry, tnear, tdnear;
     DBuf<PtsItem> items;
     box.alloc(M, s);
@@ -499,77 +627,113 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     order.alloc(M, s);
     cnt.alloc(nb, s);
     off.alloc(nb + 1, s);
-    bsum.alloc((std::max<int64_t>(nb, nleaf) + 1023) / 1024, s);
-    if (!der) {
-        icnt.alloc(nleaf, s);
-        ioff.alloc(nleaf + 1, s);
-        items.alloc(nx, s);
-        rx.alloc(M, s);
-        ry.alloc(M, s);
-    }
+    bsum.alloc((nb + 1023) / 1024, s);
+    items.alloc(nx, s);
+    rx.alloc(M, s);
+    ry.alloc(M, s);
     tnear.alloc(2 * M, s);
     if (der) tdnear.alloc(2 * M, s);
-    far_field_all(pl, m, s);
-    const unsigned gb = (unsigned)((nb + 255) / 256), gm = (unsigned)((M + 255) / 256);
-    k_pts_clear<<<gb, 256, 0, s>>>(cnt.p, nb);
-    k_pts_locate<<<gm, 256, 0, s>>>((const double2*)y, M, L, t.geom.p, box.p, cnt.p, rank.p);
-    launch_exclusive_scan(cnt.p, (int)nb, bsum.p, off.p, s);
-    k_pts_scatter<<<gm, 256, 0, s>>>(box.p, M, off.p, rank.p, order.p);
-    check_launch("point order");
-    if (!der) {
-        // the near field of the points in leaves: the near-field kernel, with
-        // the points as its targets and the sources of the leaf's strong list
-        k_pts_records<<<gm, 256, 0, s>>>((const double2*)y, M, order.p, rx.p, ry.p);
-        const unsigned gl = (unsigned)((nleaf + 255) / 256);
-        k_pts_clear<<<(unsigned)((4 * nx + 255) / 256), 256, 0, s>>>((int32_t*)items.p, 4 * nx);
-        k_pts_item_counts<<<gl, 256, 0, s>>>(lb, nleaf, cnt.p, icnt.p);
-        launch_exclusive_scan(icnt.p, nleaf, bsum.p, ioff.p, s);
-        k_pts_items<<<gl, 256, 0, s>>>(lb, nleaf, cnt.p, ioff.p, items.p);
-        check_launch("point items");
-        Targets tgt;
-        tgt.x = rx.p;
-        tgt.y = ry.p;
-        tgt.start = off.p;
-        launch_p2p(mixed, 4, 4, items.p, 0, nullptr, (int)nx, nullptr, nullptr, nullptr, sc.d_box_start.p,
-                   sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p,
-                   t.x.p, t.y.p, (const double2*)pl.mtree.p, tnear.p, s, nullptr, 0.0, nullptr, tgt,
-                   pl.tune.p2p_src_tile);
+    // the points on the second stream, the sources' far field on the caller's;
+    // what needs no lists is enqueued first, so that the device works while the
+    // host waits for the lists' flags of a new plan
+    // two streams from 50,000 points on: the fork and the joins cost more than
+    // the overlap hides below (one stream / two, N = M: 30,000 91 / 123 us
+    // mixed, 118 / 126 us FP64 with the derivative; 100,000 153 / 127 and
+    // 195 / 163 us FP64)
+    const bool two = M >= kTwoStreamPoints;
+    hipStream_t ps = s;
+    if (two) {
+        second_stream(pl);
+        ps = pl.nstream;
+        FMM_HIP(hipEventRecord(pl.ev_fork, s));
+        FMM_HIP(hipStreamWaitEvent(ps, pl.ev_fork, 0));
     }
+    // the second stream's work is joined into `s` before the buffers above go
+    // back to the pool, also when a call below fails
+    struct Join {
+        Plan& pl;
+        hipStream_t s;
+        bool done;
+        void now()
+        {
+            if (done) return;
+            done = true;
+            FMM_HIP(hipEventRecord(pl.ev_join, pl.nstream));
+            FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
+        }
+        ~Join()
+        {
+            if (done) return;
+            (void)hipEventRecord(pl.ev_join, pl.nstream);
+            (void)hipStreamWaitEvent(s, pl.ev_join, 0);
+        }
+    } join{pl, s, !two};
+    far_field_up(pl, m, s);
+    const unsigned gb = (unsigned)((nb + 255) / 256), gm = (unsigned)((M + 255) / 256);
+    k_pts_clear<<<gb, 256, 0, ps>>>(cnt.p, nb);
+    k_pts_locate<<<gm, 256, 0, ps>>>((const double2*)y, M, L, t.geom.p, box.p, cnt.p, rank.p);
+    if (nb <= kScanOne) {
+        k_pts_scan<<<1, 1024, 0, ps>>>(cnt.p, (int)nb, (int)lb, nullptr, off.p, items.p, (int)nx);
+    } else {
+        const unsigned gs = (unsigned)((nb + 1023) / 1024);
+        k_pts_scan_sums<<<gs, 1024, 0, ps>>>(cnt.p, (int)nb, (int)lb, bsum.p);
+        k_pts_scan<<<gs, 1024, 0, ps>>>(cnt.p, (int)nb, (int)lb, bsum.p, off.p, items.p, (int)nx);
+    }
+    k_pts_scatter<<<gm, 256, 0, ps>>>((const double2*)y, box.p, M, off.p, rank.p, order.p, rx.p, ry.p);
+    check_launch("point order");
+    if (two) FMM_HIP(hipEventRecord(pl.ev_join, ps));     // the items, for the near field
+    // the descents read the multipoles and the lists: after the upward pass
+    plan_finalize(pl);
+    plan_join(pl, s);
+    if (two) {
+        FMM_HIP(hipEventRecord(pl.ev_fork, s));
+        FMM_HIP(hipStreamWaitEvent(ps, pl.ev_fork, 0));
+    }
+    far_field_down(pl, s);
+    if (two) FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
     // descents: the points that stopped above the leaves (box-order positions
-    // before the first leaf), or with the derivative every point
-    // workgroups of the descents: those the occupancy holds at once (six
-    // wavefronts per SIMD for the mixed kernel without the derivative, four
-    // for the others)
+    // before the first leaf).  Workgroups: those the occupancy holds at once
+    // (six wavefronts per SIMD for the mixed kernel without the derivative,
+    // four for the others)
     const unsigned gd = (unsigned)std::min<int64_t>((M + 3) / 4, mixed && !der ? 1536 : 1024);
-    const int32_t* nq_dev = der ? nullptr : off.p + lb;
+    // few points with the derivative: every near field a descent, one launch
+    // less (descents / own kernel, us: N = M = 1000 45 / 62, 8000 77 / 88,
+    // 16,000 99 / 94, N = 64,000 with M = 8000 108 / 133, FP64)
+    const bool all_descend = der && M <= kDescendPoints;
+    const int32_t* nq_dev = off.p + (all_descend ? nb : lb);
 #define DESC_ARGS                                                                                             \
-    (const double2*)y, order.p, box.p, nq_dev, (int)M, L, sc.d_box_level.p, t.geom.p, sc.d_box_start.p,       \
+    (const double2*)y, order.p, box.p, nq_dev, L, sc.d_box_level.p, t.geom.p, sc.d_box_start.p,               \
         sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p
 #define FAR_ARGS (const double2*)y, M, order.p, box.p, sc.d_box_level.p, t.geom.p
 #define SRC_ARGS t.x.p, t.y.p, (const double2*)pl.mtree.p
     double2* tn = (double2*)tnear.p;
     double2* td = der ? (double2*)tdnear.p : nullptr;
-    if (mixed) {
-        const float* mp = (const float*)pl.mpole.p;
-        const float* lc = (const float*)pl.local.p;
-        if (der) {
-            k_pts_descend<float, true><<<gd, 256, 0, s>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, td);
-            k_pts_far<float, true><<<gm, 256, 0, s>>>(FAR_ARGS, lc, pl.p, tn, td, (double2*)phi, (double2*)dphi);
+    auto run = [&](auto tag, auto dtag) {
+        using T = decltype(tag);
+        constexpr bool DER = decltype(dtag)::value;
+        const T* mp = (const T*)pl.mpole.p;
+        k_pts_descend<T, DER><<<gd, 256, 0, ps>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, td);
+        // the near field of the points in leaves, over the sources of the
+        // leaf's strong list
+        if constexpr (DER) {
+            if (!all_descend) k_pts_near_der<T><<<(unsigned)((nx + 3) / 4), 256, 0, s>>>(
+                items.p, (int)nx, off.p, rx.p, ry.p, sc.d_box_start.p, sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p,
+                pl.s_ids.p, SRC_ARGS, tn, td);
         } else {
-            k_pts_descend<float, false><<<gd, 256, 0, s>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, nullptr);
-            k_pts_far<float, false><<<gm, 256, 0, s>>>(FAR_ARGS, lc, pl.p, tn, nullptr, (double2*)phi, nullptr);
+            Targets tgt;
+            tgt.x = rx.p;
+            tgt.y = ry.p;
+            tgt.start = off.p;
+            launch_p2p(mixed, 4, 4, items.p, 0, nullptr, (int)nx, nullptr, nullptr, nullptr, sc.d_box_start.p,
+                       sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p, SRC_ARGS, tnear.p, s, nullptr, 0.0,
+                       nullptr, tgt, pl.tune.p2p_src_tile);
         }
-    } else {
-        const double* mp = (const double*)pl.mpole.p;
-        const double* lc = (const double*)pl.local.p;
-        if (der) {
-            k_pts_descend<double, true><<<gd, 256, 0, s>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, td);
-            k_pts_far<double, true><<<gm, 256, 0, s>>>(FAR_ARGS, lc, pl.p, tn, td, (double2*)phi, (double2*)dphi);
-        } else {
-            k_pts_descend<double, false><<<gd, 256, 0, s>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, nullptr);
-            k_pts_far<double, false><<<gm, 256, 0, s>>>(FAR_ARGS, lc, pl.p, tn, nullptr, (double2*)phi, nullptr);
-        }
-    }
+        join.now();
+        k_pts_far<T, DER><<<gm, 256, 0, s>>>(FAR_ARGS, (const T*)pl.local.p, pl.p, tn, td, (double2*)phi,
+                                             (double2*)dphi);
+    };
+    if (mixed) der ? run(float{}, std::true_type{}) : run(float{}, std::false_type{});
+    else der ? run(double{}, std::true_type{}) : run(double{}, std::false_type{});
 #undef DESC_ARGS
 #undef FAR_ARGS
 #undef SRC_ARGS

@@ -187,11 +187,13 @@ struct LdsWork {      // one segment finished by the in-LDS split kernel
     int32_t stage0;   // stage of the segment
     int32_t j0;       // segment index at stage0 within its problem
     int32_t boxbase;  // global id of the problem's box 0 (root)
-    int32_t pad0, pad1;
+    int32_t up;       // geometry job of the nearest box above stage0, -1 without
+    int32_t pad;
 };
 struct GeomJob {      // a box whose geometry comes from the bbox keys of a global stage
     int32_t box;
     int32_t seg;      // index into the stage's bbox key array (absolute, see keys_off)
+    int32_t parent;   // job of the parent box, -1 for a root
 };
 
 struct PlanExtra;
@@ -213,9 +215,9 @@ struct TreeSchedule {
     std::vector<SegInfo> segs;
     std::vector<TileInfo> tiles;
     std::vector<int32_t> key_child_dummy;
+    int lds_max = 0, lds_stages = 2 * kMaxLevels;   // most points, fewest splits of an in-LDS segment
     std::vector<LdsWork> lds;
     std::vector<GeomJob> geom;      // boxes whose geometry comes from global-stage keys
-    std::vector<int64_t> geom_stage_off;  // geom jobs grouped by stage
     std::vector<TileInfo> copy_tiles;     // big-leaf problems: copy to final order
     std::vector<int32_t> box_start, box_count;
     std::vector<int32_t> box_parent;      // global id of the parent (-1 for roots)

@@ -197,12 +197,17 @@ __device__ __forceinline__ void seg_combine(int hp, int vp, int& h, int& v)
     v = h ? v : vp + v;
     h |= hp;
 }
-__device__ __forceinline__ void wave_seg_scan(int& h, int& v, int& eh, int& ev)
+// (of every row of 16 lanes alone)
+__device__ __forceinline__ void row_seg_scan(int& h, int& v)
 {
     seg_combine(dpp_i32<kDppShr1>(h), dpp_i32<kDppShr1>(v), h, v);
     seg_combine(dpp_i32<kDppShr2>(h), dpp_i32<kDppShr2>(v), h, v);
     seg_combine(dpp_i32<kDppShr4>(h), dpp_i32<kDppShr4>(v), h, v);
     seg_combine(dpp_i32<kDppShr8>(h), dpp_i32<kDppShr8>(v), h, v);
+}
+__device__ __forceinline__ void wave_seg_scan(int& h, int& v, int& eh, int& ev)
+{
+    row_seg_scan(h, v);
     const int h0 = __builtin_amdgcn_readlane(h, 15), v0 = __builtin_amdgcn_readlane(v, 15);
     const int h1 = __builtin_amdgcn_readlane(h, 31), v1 = __builtin_amdgcn_readlane(v, 31);
     const int h2 = __builtin_amdgcn_readlane(h, 47), v2 = __builtin_amdgcn_readlane(v, 47);

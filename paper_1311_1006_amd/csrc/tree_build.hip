@@ -9,7 +9,8 @@
 //
 // Device pipeline for one build (all problems of a batch at once):
 //   init        copy positions into SoA buffers, bounding box of each root,
-//               finiteness check;
+//               finiteness check (problems without a global stage: done by
+//               the lds split itself);
 //   per global stage s (segments larger than one workgroup's LDS):
 //     hist1     256-bucket histogram of the split coordinate per segment
 //               (buckets are equal-width in value over a range that holds
@@ -32,7 +33,8 @@
 //   lds split   each remaining segment (<= 4096 points) is finished by one
 //               workgroup: the points are sorted once by (x, index) and once
 //               by (y, index); every later split keeps both lists sorted by
-//               a stable partition of the list of the other axis;
+//               a stable partition of the list of the other axis; the boxes of
+//               the global stages are shared out over its workgroups;
 //   geometry    box centre (bbox midpoint) and radius (half diagonal),
 //               computed with explicitly rounded operations so that they are
 //               bit-identical to a plain IEEE evaluation, and the scaling
@@ -154,22 +156,21 @@ TreeSchedule* make_schedule(const std::vector<int64_t>& off, const std::vector<i
     // init tiles: every problem's root (stage-0 key segment b' = kbase[0][b])
     sc->copy_tiles.clear();
     // geometry jobs from global-stage keys, lds work, copy tiles
-    sc->geom_stage_off.assign(nstage + 2, 0);
-    for (int s = 0; s <= nstage; ++s) {
-        sc->geom_stage_off[s] = (int64_t)sc->geom.size();
-        if (s % 2) continue;
+    std::vector<std::vector<int64_t>> jbase(nstage + 1, std::vector<int64_t>(nprob, -1));
+    for (int s = 0; s <= nstage; s += 2) {
         for (int b = 0; b < nprob; ++b) {
             bool from_keys = (s < g[b]) || (!lds[b] && s == g[b]);
             if (!from_keys) continue;
+            jbase[s][b] = (int64_t)sc->geom.size();
             for (int64_t j = 0; j < (int64_t(1) << s); ++j) {
                 GeomJob gj;
                 gj.box = (int32_t)(sc->pbox[b] + level_base(s / 2) + j);
                 gj.seg = (int32_t)(sc->keys_off[s] + kbase[s][b] + j);
+                gj.parent = s ? (int32_t)(jbase[s - 2][b] + (j >> 2)) : -1;
                 sc->geom.push_back(gj);
             }
         }
     }
-    sc->geom_stage_off[nstage + 1] = (int64_t)sc->geom.size();
     for (int b = 0; b < nprob; ++b) {
         int64_t n = off[b + 1] - off[b];
         if (lds[b]) {
@@ -180,7 +181,11 @@ TreeSchedule* make_schedule(const std::vector<int64_t>& off, const std::vector<i
                 w.start = (int32_t)st; w.count = (int32_t)cnt;
                 w.stages = S[b] - g[b]; w.stage0 = g[b]; w.j0 = (int32_t)j;
                 w.boxbase = (int32_t)sc->pbox[b];
-                w.pad0 = w.pad1 = 0;
+                const int up = (g[b] - 1) & ~1;   // the nearest box above: an even stage before g
+                w.up = g[b] ? (int32_t)(jbase[up][b] + (j >> (g[b] - up))) : -1;
+                w.pad = 0;
+                sc->lds_max = std::max(sc->lds_max, w.count);
+                sc->lds_stages = std::min(sc->lds_stages, w.stages);
                 sc->lds.push_back(w);
             }
         } else {
@@ -1037,18 +1042,48 @@ k_partition(const TileInfo* __restrict__ tiles, const SegInfo* __restrict__ segs
     }
 }
 
-// geometry of boxes whose bounding box came from a global stage
-__global__ void k_geom_keys(const GeomJob* __restrict__ jobs, int64_t n, const uint64_t* __restrict__ keys,
-                            double* bbox, double* geom)
+// The scaling radius that a box without extent takes over: r of the nearest
+// ancestor that has one, 1 without; `job` is the nearest ancestor's
+__device__ double ancestor_radius(const GeomJob* __restrict__ jobs, int job, const uint64_t* __restrict__ keys)
 {
-    int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    GeomJob j = jobs[i];
-    double kb[4], bb[4], gm[3];
-    read_keys(keys + kKeyWords * (int64_t)j.seg, kb);
-    box_geometry(kb[0], kb[1], kb[2], kb[3], bb, gm);
-    for (int q = 0; q < 4; ++q) bbox[4 * (int64_t)j.box + q] = bb[q];
-    for (int q = 0; q < 3; ++q) geom[4 * (int64_t)j.box + q] = gm[q];
+    while (job >= 0) {
+        double kb[4], bb[4], gm[3];
+        read_keys(keys + kKeyWords * (int64_t)jobs[job].seg, kb);
+        box_geometry(kb[0], kb[1], kb[2], kb[3], bb, gm);
+        if (gm[2] > 0.0) return gm[2];
+        job = jobs[job].parent;
+    }
+    return 1.0;
+}
+
+// Geometry of the boxes [first, end) whose bounding box came from a global
+// stage, by the calling workgroup: a half wavefront per box, one lane per copy
+// of its keys.
+__device__ void geom_from_keys(const GeomJob* __restrict__ jobs, int first, int end,
+                               const uint64_t* __restrict__ keys, double* bbox, double* geom)
+{
+    const int half = (threadIdx.x >> 5) & 1, c = threadIdx.x & (kKeyCopies - 1);
+    for (int j0 = first + 2 * (threadIdx.x >> 6); j0 < end; j0 += 2 * (blockDim.x >> 6)) {
+        const GeomJob j = jobs[min(j0 + half, end - 1)];
+        const uint64_t* k = keys + kKeyWords * (int64_t)j.seg;
+        const double x0 = half_wave_min(okey_inv(k[4 * c])), x1 = half_wave_max(okey_inv(k[4 * c + 1]));
+        const double y0 = half_wave_min(okey_inv(k[4 * c + 2])), y1 = half_wave_max(okey_inv(k[4 * c + 3]));
+        if (c == 0 && j0 + half < end) {
+            double bb[4], gm[3];
+            box_geometry(x0, x1, y0, y1, bb, gm);
+            for (int q = 0; q < 4; ++q) bbox[4 * (int64_t)j.box + q] = bb[q];
+            for (int q = 0; q < 3; ++q) geom[4 * (int64_t)j.box + q] = gm[q];
+            geom[4 * (int64_t)j.box + 3] = gm[2] > 0.0 ? gm[2] : ancestor_radius(jobs, j.parent, keys);
+        }
+    }
+}
+
+// of a layout without in-LDS work
+__global__ void __launch_bounds__(256)
+k_geom_keys(const GeomJob* __restrict__ jobs, int n, const uint64_t* __restrict__ keys, double* bbox, double* geom)
+{
+    const int first = 8 * blockIdx.x;
+    geom_from_keys(jobs, first, min(n, first + 8), keys, bbox, geom);
 }
 
 __global__ void k_copy_final(const TileInfo* __restrict__ tiles, const double* XA, const double* YA,
@@ -1069,31 +1104,35 @@ __global__ void k_copy_final(const TileInfo* __restrict__ tiles, const double* X
 // split along an axis keeps that axis' list as is (its first floor(n/2)
 // entries are the lower half) and stably partitions the other list.  Both
 // lists hold every sub-segment at the same positions, so a thread owns
-// positions [kPer*tid, kPer*tid + kPer) of both and keeps the sub-segment of
+// positions [PER*tid, PER*tid + PER) of both and keeps the sub-segment of
 // each of them (start, count, box) in registers.  posX/posY invert the
 // lists: an element is in the lower half of its sub-segment iff its
 // position in the split axis' list is below start + count/2.
 constexpr int kLdsThreads = 1024;
 constexpr int kLdsWaves = kLdsThreads / 64;
-constexpr int kPer = kLdsCap / kLdsThreads;     // positions (and buckets) per thread
 
+// PER positions (and buckets) per thread
+template <int PER>
 struct LdsSort {
-    uint64_t key[kLdsCap];
-    uint16_t id[kLdsCap];
+    uint64_t key[PER * kLdsThreads];
+    uint16_t id[PER * kLdsThreads];
 };
+template <int PER>
 struct LdsPos {
-    uint16_t posX[kLdsCap];
-    uint16_t posY[kLdsCap];
+    uint16_t posX[PER * kLdsThreads];
+    uint16_t posY[PER * kLdsThreads];
 };
+template <int PER>
 struct LdsBucket {
-    uint32_t cnt[kLdsCap];      // bucket populations, then bucket ends
-    uint64_t key[kLdsCap];      // order keys in bucket order
-    uint16_t id[kLdsCap];       // local ids in bucket order (any order inside a bucket)
+    uint32_t cnt[PER * kLdsThreads];      // bucket populations, then bucket ends
+    uint64_t key[PER * kLdsThreads];      // order keys in bucket order
+    uint16_t id[PER * kLdsThreads];       // local ids in bucket order (any order inside a bucket)
 };
+template <int PER>
 union LdsUnion {
-    LdsSort s;
-    LdsPos q;
-    LdsBucket b;
+    LdsSort<PER> s;
+    LdsPos<PER> q;
+    LdsBucket<PER> b;
 };
 
 // (key, input index) order of two entries of the sort buffer; padding entries
@@ -1105,34 +1144,35 @@ __device__ __forceinline__ bool lds_less(uint64_t ka, uint16_t ia, uint64_t kb, 
 }
 
 // Sort of the entries of S (n of them, padding behind) by (key, input index): a
-// merge sort, thread t owning positions kPer t .. kPer t + kPer - 1.  The thread's
+// merge sort, thread t owning positions PER t .. PER t + PER - 1.  The thread's
 // entries are sorted in registers; then the runs are merged pairwise, each
-// thread finding by a binary search along its diagonal where its kPer outputs
+// thread finding by a binary search along its diagonal where its PER outputs
 // start in the two runs (merge path) and merging them in registers.  Up to
-// runs of a wavefront's 256 positions a round needs no workgroup barrier; the
+// runs of a wavefront's 64 PER positions a round needs no workgroup barrier; the
 // last four rounds take two each.  The bitonic network it replaced had 78
 // dependent steps, each a pass over LDS with a barrier: the in-LDS stage took
-// 148 us for the clustered million points and 92 us now, 145 and 75 us for
-// 16,000 points of a vortex sheet (50 us where no segment needs the sort).
-__device__ void lds_sort(LdsSort& S, const uint32_t* idxs, int n)
+// 148 us for the clustered million points with it and 92 us with this.
+template <int PER>
+__device__ void lds_sort(LdsSort<PER>& S, const uint32_t* idxs, int n)
 {
-    static_assert(kPer == 4, "four entries per thread");
-    const int p0 = kPer * (int)threadIdx.x;
-    uint64_t k[kPer];
-    uint16_t id[kPer];
+    const int p0 = PER * (int)threadIdx.x;
+    uint64_t k[PER];
+    uint16_t id[PER];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) { k[u] = S.key[p0 + u]; id[u] = S.id[p0 + u]; }
+    for (int u = 0; u < PER; ++u) { k[u] = S.key[p0 + u]; id[u] = S.id[p0 + u]; }
     auto order = [&](int a, int b) {
         if (lds_less(k[b], id[b], k[a], id[a], idxs)) {
             const uint64_t t = k[a]; k[a] = k[b]; k[b] = t;
             const uint16_t v = id[a]; id[a] = id[b]; id[b] = v;
         }
     };
-    order(0, 1); order(2, 3); order(0, 2); order(1, 3); order(1, 2);
+    static_assert(PER == 1 || PER == 2 || PER == 4, "sorting network of the thread's entries");
+    if constexpr (PER >= 2) order(0, 1);
+    if constexpr (PER == 4) { order(2, 3); order(0, 2); order(1, 3); order(1, 2); }
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) { S.key[p0 + u] = k[u]; S.id[p0 + u] = id[u]; }
-    for (int w = kPer; w < n; w <<= 1) {
-        const bool block = 2 * w > 64 * kPer;     // the merged run spans wavefronts
+    for (int u = 0; u < PER; ++u) { S.key[p0 + u] = k[u]; S.id[p0 + u] = id[u]; }
+    for (int w = PER; w < n; w <<= 1) {
+        const bool block = 2 * w > 64 * PER;     // the merged run spans wavefronts
         if (block) __syncthreads();
         else wave_sync();
         const int base = p0 & ~(2 * w - 1), d = p0 - base;   // the pair of runs, this thread's diagonal
@@ -1150,11 +1190,11 @@ __device__ void lds_sort(LdsSort& S, const uint32_t* idxs, int n)
         uint64_t ka = a < w ? A[a] : ~0ull, kb = b < w ? B[b] : ~0ull;
         uint16_t ia = a < w ? Ai[a] : 0, ib = b < w ? Bi[b] : 0;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
+        for (int u = 0; u < PER; ++u) {
             const bool tb = a >= w || (b < w && lds_less(kb, ib, ka, ia, idxs));
             k[u] = tb ? kb : ka;
             id[u] = tb ? ib : ia;
-            if (u + 1 < kPer) {
+            if (u + 1 < PER) {
                 if (tb) {
                     ++b;
                     if (b < w) { kb = B[b]; ib = Bi[b]; }
@@ -1167,13 +1207,13 @@ __device__ void lds_sort(LdsSort& S, const uint32_t* idxs, int n)
         if (block) __syncthreads();
         else wave_sync();
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) { S.key[p0 + u] = k[u]; S.id[p0 + u] = id[u]; }
+        for (int u = 0; u < PER; ++u) { S.key[p0 + u] = k[u]; S.id[p0 + u] = id[u]; }
     }
     __syncthreads();
 }
 
 // Local ids 0..n-1 of the segment ordered by (coordinate, input index) into
-// out.  Bucket sort: kLdsCap equal-width buckets between the segment's
+// out.  Bucket sort: 1024 PER equal-width buckets between the segment's
 // minimum and maximum coordinate (a monotone map), an exclusive scan of the
 // populations, a scatter, and the place of every element inside its bucket
 // from the count of the bucket's elements that precede it.  When a bucket
@@ -1183,18 +1223,27 @@ __device__ void lds_sort(LdsSort& S, const uint32_t* idxs, int n)
 // largest bucket, 15 us per axis at 64 points and full segments against 20 us
 // for the merge sort; at 16 points the sheet's columns (28 points, one bucket
 // each) took the sort, 90 us for the stage instead of 75.
+// Before that, where a bucket holds more than kRefine points, every bucket is
+// divided once more in proportion to its population (3 us per axis): a smooth but
+// uneven density then has a few points per bucket.  The sheet's y order took 36 us
+// by the merge sort and takes 19; its columns are ties that no division
+// separates.  Uniform points have up to 9 in one of their 4096 buckets, and no
+// second pass.  More passes than one gave the clustered points nothing (34 us
+// of merge sort became 38).
 constexpr int kBucketMax = 64;
+constexpr int kRefine = 12;
 
-__device__ void lds_order(LdsUnion& U, const double* __restrict__ c, const uint32_t* idxs, int n, uint16_t* out,
+template <int PER>
+__device__ void lds_order(LdsUnion<PER>& U, const double* __restrict__ c, const uint32_t* idxs, int n, uint16_t* out,
                           int* sh, double* red)
 {
-    constexpr int NB = kLdsCap;
+    constexpr int NB = PER * kLdsThreads;
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
     // range of the coordinate
     double lo = 1e308, hi = -1e308;
-    double cv[kPer];
+    double cv[PER];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         const int i = tid + u * kLdsThreads;
         cv[u] = i < n ? c[i] : 0.0;
         if (i < n) { lo = fmin(lo, cv[u]); hi = fmax(hi, cv[u]); }
@@ -1209,52 +1258,73 @@ __device__ void lds_order(LdsUnion& U, const double* __restrict__ c, const uint3
     const double ext = hi - lo;
     double scale = ext > 0.0 ? (double)NB / ext : 0.0;
     scale = scale < 1e300 ? scale : 0.0;
-    int bk[kPer];
+    int bk[PER];
+    double fr[PER];   // the place inside the bucket, 0 .. 1
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
-        const int i = tid + u * kLdsThreads;
-        bk[u] = (int)fmin(fmax((cv[u] - lo) * scale, 0.0), (double)(NB - 1));
-        if (i < n) atomicAdd(&U.b.cnt[bk[u]], 1u);
+    for (int u = 0; u < PER; ++u) {
+        const double v = fmin(fmax((cv[u] - lo) * scale, 0.0), (double)(NB - 1));
+        bk[u] = (int)v;
+        fr[u] = v - (double)bk[u];
     }
-    __syncthreads();
-    // exclusive scan of the populations (thread t owns buckets kPer t .. kPer t + kPer - 1) and
-    // the largest population
-    uint32_t q[kPer];
-    int loc = 0, mx = 0;
+    int mx;
+    for (int level = 0;; ++level) {
 #pragma unroll
-    for (int v = 0; v < kPer; ++v) {
-        q[v] = U.b.cnt[kPer * tid + v];
-        loc += (int)q[v];
-        mx = max(mx, (int)q[v]);
-    }
-    mx = wave_max_i32(mx);
-    int tot;
-    int run = block_excl_scan<kLdsThreads>(loc, sh, &tot);
-    if (lane == 0) sh[kLdsWaves + wid] = mx;
+        for (int u = 0; u < PER; ++u)
+            if (tid + u * kLdsThreads < n) atomicAdd(&U.b.cnt[bk[u]], 1u);
+        __syncthreads();
+        // exclusive scan of the populations (thread t owns buckets PER t .. PER t + PER - 1) and
+        // the largest population
+        uint32_t q[PER];
+        int loc = 0;
+        mx = 0;
 #pragma unroll
-    for (int v = 0; v < kPer; ++v) {
-        U.b.cnt[kPer * tid + v] = (uint32_t)run;
-        run += (int)q[v];
+        for (int v = 0; v < PER; ++v) {
+            q[v] = U.b.cnt[PER * tid + v];
+            loc += (int)q[v];
+            mx = max(mx, (int)q[v]);
+        }
+        mx = wave_max_i32(mx);
+        int tot;
+        int run = block_excl_scan<kLdsThreads>(loc, sh, &tot);
+        if (lane == 0) sh[kLdsWaves + wid] = mx;
+#pragma unroll
+        for (int v = 0; v < PER; ++v) {
+            U.b.cnt[PER * tid + v] = (uint32_t)run;
+            run += (int)q[v];
+        }
+        __syncthreads();
+        mx = 0;
+        for (int w = 0; w < kLdsWaves; ++w) mx = max(mx, sh[kLdsWaves + w]);
+        if (level == 1 || mx <= kRefine) break;
+        // the second level: a bucket of c points becomes c buckets of equal
+        // width, in the places that its points take
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            if (tid + u * kLdsThreads < n) {
+                const int b0 = (int)U.b.cnt[bk[u]], b1 = bk[u] + 1 < NB ? (int)U.b.cnt[bk[u] + 1] : n;
+                bk[u] = b0 + min((int)(fr[u] * (double)(b1 - b0)), b1 - b0 - 1);
+            }
+        }
+        __syncthreads();
+        for (int b = tid; b < NB; b += kLdsThreads) U.b.cnt[b] = 0;
+        __syncthreads();
     }
-    __syncthreads();
-    mx = 0;
-    for (int w = 0; w < kLdsWaves; ++w) mx = max(mx, sh[kLdsWaves + w]);
     __syncthreads();
     if (mx > kBucketMax) {
         // merge sort instead (uniform branch)
-        for (int i = tid; i < kLdsCap; i += kLdsThreads) {
+        for (int i = tid; i < NB; i += kLdsThreads) {
             U.s.key[i] = i < n ? okey(c[i]) : ~0ull;
             U.s.id[i] = i < n ? (uint16_t)i : 0xffff;
         }
         __syncthreads();
-        lds_sort(U.s, idxs, n);
+        lds_sort<PER>(U.s, idxs, n);
         for (int i = tid; i < n; i += kLdsThreads) out[i] = U.s.id[i];
         __syncthreads();
         return;
     }
     // scatter into bucket order; cnt becomes the end of every bucket
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         const int i = tid + u * kLdsThreads;
         if (i < n) {
             const uint32_t pos = atomicAdd(&U.b.cnt[bk[u]], 1u);
@@ -1268,7 +1338,7 @@ __device__ void lds_order(LdsUnion& U, const double* __restrict__ c, const uint3
     // index); the reads of the bucket are independent, so they are issued
     // together
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
+    for (int u = 0; u < PER; ++u) {
         const int i = tid + u * kLdsThreads;
         if (i < n) {
             const int b = bk[u];
@@ -1292,7 +1362,8 @@ __device__ void lds_order(LdsUnion& U, const double* __restrict__ c, const uint3
             }
             for (int q = s0 + kRankFirst; q < e; ++q) {
                 const uint64_t kq = U.b.key[q];
-                r += (kq < km) | ((kq == km) & (idxs[U.b.id[q]] < xm));
+                r += kq < km;
+                if (kq == km) r += idxs[U.b.id[q]] < xm;
             }
             out[s0 + r] = (uint16_t)i;
         }
@@ -1300,36 +1371,187 @@ __device__ void lds_order(LdsUnion& U, const double* __restrict__ c, const uint3
     __syncthreads();
 }
 
-__global__ void __launch_bounds__(kLdsThreads)
-k_lds_split(const LdsWork* __restrict__ work, const double* XA, const double* YA, const int32_t* IA,
-            const double* XB, const double* YB, const int32_t* IB, double* Xo, double* Yo, int32_t* Io,
-            double* bbox, double* geom)
+// One stage (d of `stages`) of the splits of the positions that a thread owns, p0 ..
+// p0 + PER - 1 (those below `end`): st, cn and sid are the start, the count and
+// the index at stage t of their sub-segments.
+template <int PER, class POS, class ANC>
+__device__ __forceinline__ void lds_stage(int t, int d, bool last, int p0, int end, const LdsWork& w,
+                                          const double* xs, const double* ys, uint16_t* LX, uint16_t* LY, POS& q,
+                                          int* sh, int (&st)[PER], int (&cn)[PER], int (&sid)[PER], ANC above,
+                                          double* bbox, double* geom)
 {
-    __shared__ LdsUnion U;
-    __shared__ uint32_t idxs[kLdsCap];
-    __shared__ uint16_t LX[kLdsCap], LY[kLdsCap];
-    __shared__ int sh[2 * (kLdsThreads / 64)];
-    __shared__ double red[2 * (kLdsThreads / 64)];
-    __shared__ double xs[kLdsCap], ys[kLdsCap];   // coordinates by local id
-    LdsWork w = work[blockIdx.x];
-    const double* xg = ((w.stage0 & 1) ? XB : XA) + w.start;
-    const double* yg = ((w.stage0 & 1) ? YB : YA) + w.start;
-    const int32_t* is = ((w.stage0 & 1) ? IB : IA) + w.start;
-    int n = w.count;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    // split axis of the sub-segment of every owned position, from the
+    // ends of both lists; the head position (the sub-segment's first)
+    // writes the box geometry at even stages
+    int ax[PER];
+    bool valid[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = p0 + u;
+        valid[u] = i < end;
+        ax[u] = 0;
+        if (!valid[u]) continue;
+        if (u > 0 && valid[u > 0 ? u - 1 : 0] && st[u] == st[u > 0 ? u - 1 : 0]) {
+            ax[u] = ax[u > 0 ? u - 1 : 0];
+            continue;
+        }
+        const int e1 = st[u] + cn[u] - 1;
+        const double x0 = xs[LX[st[u]]], x1 = xs[LX[e1]];
+        const double y0 = ys[LY[st[u]]], y1 = ys[LY[e1]];
+        ax[u] = ((x1 - x0) >= (y1 - y0)) ? 0 : 1;
+        if (i == st[u] && (t & 1) == 0) {
+            const int64_t j = ((int64_t)w.j0 << d) + sid[u], box = (int64_t)w.boxbase + level_base(t / 2) + j;
+            double bb[4], gm[3];
+            box_geometry(x0, x1, y0, y1, bb, gm);
+            for (int c = 0; c < 4; ++c) bbox[4 * box + c] = bb[c];
+            for (int c = 0; c < 3; ++c) geom[4 * box + c] = gm[c];
+            // no extent: the nearest ancestor's radius, of the boxes that this
+            // workgroup has written or of those above
+            double rs = gm[2];
+            for (int b = 2; !(rs > 0.0) && b <= d; b += 2)
+                rs = geom[4 * ((int64_t)w.boxbase + level_base((t - b) / 2) + (j >> b)) + 2];
+            geom[4 * box + 3] = rs > 0.0 ? rs : above();
+        }
+    }
+    if (last) return;
+    // element of the other list at every owned position and whether it
+    // lies in the lower half along the split axis
+    uint16_t e[PER];
+    int f[PER], lb[PER];
+    bool tail[PER];   // no head at or before this position within the thread
+    int run = 0;
+    bool seen = false;
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = p0 + u;
+        f[u] = 0;
+        e[u] = 0;
+        if (valid[u]) {
+            e[u] = ax[u] ? LX[i] : LY[i];
+            const int pa = ax[u] ? (int)q.posY[e[u]] : (int)q.posX[e[u]];
+            f[u] = (pa - st[u]) < (cn[u] >> 1);
+            if (i == st[u]) { run = 0; seen = true; }
+        }
+        tail[u] = !seen;
+        lb[u] = run;
+        run += f[u];
+    }
+    // segmented exclusive scan of the lower flags over the positions
+    // (restarting at every sub-segment head): within the wavefront by
+    // lane permutations, across wavefronts through one barrier
+    int v = run, hf = seen ? 1 : 0, ev, eh;
+    wave_seg_scan(hf, v, eh, ev);
+    if (lane == 63) { sh[wid] = v; sh[kLdsWaves + wid] = hf; }
+    __syncthreads();
+    // (a scan of the wavefronts' totals by lanes 0 .. 15 of each wavefront)
+    int wv = sh[lane & (kLdsWaves - 1)], wh = sh[kLdsWaves + (lane & (kLdsWaves - 1))];
+    row_seg_scan(wh, wv);
+    const int wu = __builtin_amdgcn_readfirstlane(wid);
+    const int carry = wu ? __builtin_amdgcn_readlane(wv, wu - 1) : 0;
+    const int cin = eh ? ev : carry + ev;
+    // scatter the other list's elements in place (every read of the
+    // lists and positions of this stage came before the barrier) and
+    // step every owned position into its child
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (!valid[u]) continue;
+        const int i = p0 + u;
+        const int before = lb[u] + (tail[u] ? cin : 0);   // lower elements in [st, i)
+        const int kq = cn[u] >> 1, rel = i - st[u];
+        const int dst = f[u] ? st[u] + before : st[u] + kq + (rel - before);
+        if (ax[u]) { LX[dst] = e[u]; q.posX[e[u]] = (uint16_t)dst; }
+        else { LY[dst] = e[u]; q.posY[e[u]] = (uint16_t)dst; }
+        if (rel < kq) { cn[u] = kq; sid[u] = 2 * sid[u]; }
+        else { st[u] += kq; cn[u] -= kq; sid[u] = 2 * sid[u] + 1; }
+    }
+    __syncthreads();
+}
+
+// Where the segments of k_lds_split come from: the global stages' buffers, or
+// (z set: no problem has a global stage) the caller's positions, checked here
+struct LdsInput {
+    const double *XA, *YA, *XB, *YB;
+    const int32_t *IA, *IB;
+    const double* z;
+    uint32_t* err;      // with z: non-finite positions
+    int err_store;      // 1: the only segment, err is written; 0: err was cleared
+};
+// The boxes of the global stages, shared out over the workgroups
+struct LdsGeom {
+    const GeomJob* jobs;
+    int n;
+    const uint64_t* keys;
+};
+
+// A segment of at most 1024 PER points per workgroup; with QUARTERS four
+// workgroups per segment: each sorts it and does the first two splits, then
+// goes on with one of the four sub-segments alone.
+// Bound by LDS accesses and the chain of barriers of the sort and the stages.
+// PER from the largest segment: with 4 positions per thread a segment of 1024
+// points keeps 4 of the 16 wavefronts busy.  QUARTERS where the chip has room
+// for four times the workgroups: past the second split a thread owns one
+// position instead of PER (1.2 us a stage instead of 2.6).  Measured: N = 1000,
+// one segment, 25.5 us (and 10 us of three launches around it, now part of this
+// one) to 19.8; 16,000 points of a sheet, four segments, 74.7 to 56.6 (and 9 us
+// of two launches); 1e6 points, 256 segments, 50 to 53 (and 10 us of two
+// launches), of which the loads take 3, either sort 10, the stages 24.
+template <int PER, bool QUARTERS>
+__global__ void __launch_bounds__(kLdsThreads)
+k_lds_split(const LdsWork* __restrict__ work, const LdsInput in, const LdsGeom gk, double* Xo, double* Yo,
+            int32_t* Io, double* bbox, double* geom)
+{
+    constexpr int CAP = PER * kLdsThreads;
+    __shared__ LdsUnion<PER> U;
+    __shared__ uint32_t idxs[CAP];
+    __shared__ uint16_t LX[CAP], LY[CAP];
+    __shared__ int sh[2 * kLdsWaves];
+    __shared__ double red[2 * kLdsWaves];
+    __shared__ double xs[CAP], ys[CAP];   // coordinates by local id
+    const int quarter = QUARTERS ? blockIdx.x & 3 : 0;
+    const LdsWork w = work[QUARTERS ? blockIdx.x >> 2 : blockIdx.x];
+    const int n = w.count;
     {
         // every load of the segment in flight before the first LDS store
-        uint32_t li[kPer];
-        double lx[kPer], ly[kPer];
+        uint32_t li[PER];
+        double lx[PER], ly[PER];
+        if (in.z) {
+            bool bad = false;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int i = threadIdx.x + u * kLdsThreads;
-            const int ic = i < n ? i : 0;
-            li[u] = (uint32_t)is[ic];
-            lx[u] = xg[ic];
-            ly[u] = yg[ic];
+            for (int u = 0; u < PER; ++u) {
+                const int i = threadIdx.x + u * kLdsThreads;
+                const int ic = w.start + (i < n ? i : 0);
+                const double2 v = reinterpret_cast<const double2*>(in.z)[ic];
+                // a non-finite position is flagged and built as (0, 0)
+                const bool ok = isfinite(v.x) && isfinite(v.y);
+                bad |= !ok;
+                li[u] = (uint32_t)ic;
+                lx[u] = ok ? v.x : 0.0;
+                ly[u] = ok ? v.y : 0.0;
+            }
+            const int any = __syncthreads_or(bad);
+            if (threadIdx.x == 0 && quarter == 0) {
+                if (in.err_store) *in.err = any ? 1u : 0u;
+                else if (any) atomicOr(in.err, 1u);
+            }
+        } else {
+            const double* xg = ((w.stage0 & 1) ? in.XB : in.XA) + w.start;
+            const double* yg = ((w.stage0 & 1) ? in.YB : in.YA) + w.start;
+            const int32_t* is = ((w.stage0 & 1) ? in.IB : in.IA) + w.start;
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                const int i = threadIdx.x + u * kLdsThreads;
+                const int ic = i < n ? i : 0;
+                li[u] = (uint32_t)is[ic];
+                lx[u] = xg[ic];
+                ly[u] = yg[ic];
+            }
         }
+        const int64_t nb = gridDim.x;
+        geom_from_keys(gk.jobs, (int)(gk.n * (int64_t)blockIdx.x / nb), (int)(gk.n * ((int64_t)blockIdx.x + 1) / nb),
+                       gk.keys, bbox, geom);
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) {
+        for (int u = 0; u < PER; ++u) {
             const int i = threadIdx.x + u * kLdsThreads;
             if (i < n) {
                 idxs[i] = li[u];
@@ -1339,119 +1561,44 @@ k_lds_split(const LdsWork* __restrict__ work, const double* XA, const double* YA
         }
     }
     __syncthreads();
-    lds_order(U, xs, idxs, n, LX, sh, red);
-    lds_order(U, ys, idxs, n, LY, sh, red);
-    uint16_t* posX = U.q.posX;
-    uint16_t* posY = U.q.posY;
+    lds_order<PER>(U, xs, idxs, n, LX, sh, red);
+    lds_order<PER>(U, ys, idxs, n, LY, sh, red);
     for (int i = threadIdx.x; i < n; i += kLdsThreads) {
-        posX[LX[i]] = (uint16_t)i;
-        posY[LY[i]] = (uint16_t)i;
+        U.q.posX[LX[i]] = (uint16_t)i;
+        U.q.posY[LY[i]] = (uint16_t)i;
     }
     __syncthreads();
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    int st[kPer], cn[kPer], sid[kPer];
+    auto above = [&] { return ancestor_radius(gk.jobs, w.up, gk.keys); };
+    const int p0 = PER * (int)threadIdx.x;
+    int st[PER], cn[PER], sid[PER];
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) { st[u] = 0; cn[u] = n; sid[u] = 0; }
-    for (int d = 0; d <= w.stages; ++d) {
-        const int t = w.stage0 + d;
-        // split axis of the sub-segment of every owned position, from the
-        // ends of both lists; the head position (the sub-segment's first)
-        // writes the box geometry at even stages
-        int ax[kPer];
-        bool valid[kPer];
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int i = kPer * threadIdx.x + u;
-            valid[u] = i < n;
-            ax[u] = 0;
-            if (!valid[u]) continue;
-            if (u > 0 && valid[u - 1] && st[u] == st[u - 1]) { ax[u] = ax[u - 1]; continue; }
-            const int e1 = st[u] + cn[u] - 1;
-            const double x0 = xs[LX[st[u]]], x1 = xs[LX[e1]];
-            const double y0 = ys[LY[st[u]]], y1 = ys[LY[e1]];
-            ax[u] = ((x1 - x0) >= (y1 - y0)) ? 0 : 1;
-            if (i == st[u] && (t & 1) == 0) {
-                const int64_t box = (int64_t)w.boxbase + level_base(t / 2) + ((int64_t)w.j0 << d) + sid[u];
-                double bb[4], gm[3];
-                box_geometry(x0, x1, y0, y1, bb, gm);
-                for (int c = 0; c < 4; ++c) bbox[4 * box + c] = bb[c];
-                for (int c = 0; c < 3; ++c) geom[4 * box + c] = gm[c];
-            }
+    for (int u = 0; u < PER; ++u) { st[u] = 0; cn[u] = n; sid[u] = 0; }
+    const int shared = QUARTERS ? 2 : w.stages + 1;    // stages of the whole segment
+    for (int d = 0; d < shared; ++d)
+        lds_stage<PER>(w.stage0 + d, d, d == w.stages, p0, n, w, xs, ys, LX, LY, U.q, sh, st, cn, sid, above, bbox,
+                       geom);
+    int first = 0, count = n;
+    if constexpr (QUARTERS) {
+        // (the boxes of the first two splits are written by all four, alike)
+        for (int b = 1; b >= 0; --b) {
+            const int h = count >> 1;
+            if ((quarter >> b) & 1) { first += h; count -= h; }
+            else count = h;
         }
-        if (d == w.stages) break;
-        // element of the other list at every owned position and whether it
-        // lies in the lower half along the split axis
-        uint16_t e[kPer];
-        int f[kPer], lb[kPer];
-        bool tail[kPer];   // no head at or before this position within the thread
-        int run = 0;
-        bool seen = false;
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            const int i = kPer * threadIdx.x + u;
-            f[u] = 0;
-            e[u] = 0;
-            if (valid[u]) {
-                e[u] = ax[u] ? LX[i] : LY[i];
-                const int pa = ax[u] ? (int)posY[e[u]] : (int)posX[e[u]];
-                f[u] = (pa - st[u]) < (cn[u] >> 1);
-                if (i == st[u]) { run = 0; seen = true; }
-            }
-            tail[u] = !seen;
-            lb[u] = run;
-            run += f[u];
-        }
-        // segmented exclusive scan of the lower flags over the positions
-        // (restarting at every sub-segment head): within the wavefront by
-        // lane permutations, across wavefronts through one barrier
-        int v = run, hf = seen ? 1 : 0, ev, eh;
-        wave_seg_scan(hf, v, eh, ev);
-        if (lane == 63) { sh[wid] = v; sh[kLdsWaves + wid] = hf; }
-        __syncthreads();
-        int carry = 0;
-        for (int q = 0; q < wid; ++q) carry = sh[kLdsWaves + q] ? sh[q] : carry + sh[q];
-        const int cin = eh ? ev : carry + ev;
-        // scatter the other list's elements in place (every read of the
-        // lists and positions of this stage came before the barrier) and
-        // step every owned position into its child
-#pragma unroll
-        for (int u = 0; u < kPer; ++u) {
-            if (!valid[u]) continue;
-            const int i = kPer * threadIdx.x + u;
-            const int before = lb[u] + (tail[u] ? cin : 0);   // lower elements in [st, i)
-            const int kq = cn[u] >> 1, rel = i - st[u];
-            const int dst = f[u] ? st[u] + before : st[u] + kq + (rel - before);
-            if (ax[u]) { LX[dst] = e[u]; posX[e[u]] = (uint16_t)dst; }
-            else { LY[dst] = e[u]; posY[e[u]] = (uint16_t)dst; }
-            if (rel < kq) { cn[u] = kq; sid[u] = 2 * sid[u]; }
-            else { st[u] += kq; cn[u] -= kq; sid[u] = 2 * sid[u] + 1; }
-        }
-        __syncthreads();
+        int s1[1] = {first}, c1[1] = {count}, i1[1] = {quarter};
+        for (int d = 2; d <= w.stages; ++d)
+            lds_stage<1>(w.stage0 + d, d, d == w.stages, first + (int)threadIdx.x, first + count, w, xs, ys, LX, LY, U.q,
+                         sh, s1, c1, i1, above, bbox, geom);
     }
     // final order: sorted by (x, index) inside every leaf
 #pragma unroll
-    for (int u = 0; u < kPer; ++u) {
+    for (int u = 0; u < (QUARTERS ? 1 : PER); ++u) {
         const int i = threadIdx.x + u * kLdsThreads;
-        if (i < n) {
-            const int id = LX[i];
-            Xo[w.start + i] = xs[id]; Yo[w.start + i] = ys[id]; Io[w.start + i] = (int32_t)idxs[id];
+        if (i < count) {
+            const int id = LX[first + i], o = w.start + first + i;
+            Xo[o] = xs[id]; Yo[o] = ys[id]; Io[o] = (int32_t)idxs[id];
         }
     }
-}
-
-// scaling radius: r, else the nearest ancestor's r, else 1
-__global__ void k_scaling_radius(int64_t nbox, const int32_t* __restrict__ parent, double* geom)
-{
-    int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (b >= nbox) return;
-    int64_t a = b;
-    double rs = 1.0;
-    while (a >= 0) {
-        double r = geom[4 * a + 2];
-        if (r > 0.0) { rs = r; break; }
-        a = parent[a];
-    }
-    geom[4 * b + 3] = rs;
 }
 
 __global__ void k_update_positions(const double* __restrict__ z, const int32_t* __restrict__ perm,
@@ -1467,10 +1614,44 @@ __global__ void k_update_positions(const double* __restrict__ z, const int32_t* 
 
 static int grid_for(int64_t n, int bs) { return (int)std::min<int64_t>((n + bs - 1) / bs, 65535 * 4); }
 
+// Four workgroups per segment while that is at most one per compute unit and
+// every segment has more than two splits; not for segments of at most 1024
+// points, whose threads own one position anyway.
+constexpr int kQuarterBlocks = 256;
+
+static void run_lds_split(Tree& t, const LdsInput& in, const uint64_t* keys, hipStream_t s)
+{
+    TreeSchedule& sc = *t.sched;
+    const int per = (sc.lds_max + kLdsThreads - 1) / kLdsThreads;
+    const unsigned nw = (unsigned)sc.lds.size();
+    const bool quarters = per > 1 && 4 * nw <= kQuarterBlocks && sc.lds_stages > 2;
+    const LdsGeom gk{sc.d_geom.p, keys ? (int)sc.geom.size() : 0, keys};
+#define LDS_SPLIT(PER, Q)                                                                                        \
+    k_lds_split<PER, Q><<<(Q ? 4 : 1) * nw, kLdsThreads, 0, s>>>(sc.d_lds.p, in, gk, t.x.p, t.y.p, t.perm.p,     \
+                                                                 t.bbox.p, t.geom.p)
+    if (per <= 1) LDS_SPLIT(1, false);
+    else if (per == 2 && quarters) LDS_SPLIT(2, true);
+    else if (per == 2) LDS_SPLIT(2, false);
+    else if (quarters) LDS_SPLIT(4, true);
+    else LDS_SPLIT(4, false);
+#undef LDS_SPLIT
+    check_launch("lds split");
+}
+
 static void build_tree_select(Tree& t, const double* z, hipStream_t s)
 {
     TreeSchedule& sc = *t.sched;
     int64_t n = sc.n;
+    // no global stage: the in-LDS kernel reads the positions and does the rest
+    if (sc.nstage == 0 && sc.copy_tiles.empty()) {
+        const bool one = sc.lds.size() == 1;
+        if (!one) {
+            k_fill_start<<<1, 64, 0, s>>>(nullptr, 0, nullptr, 0, t.err.p);
+            check_launch("fill");
+        }
+        run_lds_split(t, LdsInput{nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, z, t.err.p, one}, nullptr, s);
+        return;
+    }
     // workspace
     DBuf<double> XA, YA, XB, YB;
     DBuf<int32_t> IA, IB;
@@ -1518,24 +1699,18 @@ static void build_tree_select(Tree& t, const double* z, hipStream_t s)
                                                 W + o_h1, lvl1.p);
         check_launch("split stage");
     }
-    if (!sc.lds.empty()) {
-        k_lds_split<<<(unsigned)sc.lds.size(), kLdsThreads, 0, s>>>(sc.d_lds.p, XA.p, YA.p, IA.p, XB.p, YB.p,
-                                                                    IB.p, t.x.p, t.y.p, t.perm.p, t.bbox.p,
-                                                                    t.geom.p);
-        check_launch("lds split");
-    }
     if (!sc.copy_tiles.empty()) {
         k_copy_final<<<(unsigned)sc.copy_tiles.size(), 256, 0, s>>>(sc.d_copy.p, XA.p, YA.p, IA.p, XB.p, YB.p,
                                                                     IB.p, t.x.p, t.y.p, t.perm.p);
         check_launch("copy final");
     }
-    if (!sc.geom.empty()) {
-        int64_t ng = (int64_t)sc.geom.size();
-        k_geom_keys<<<grid_for(ng, 256), 256, 0, s>>>(sc.d_geom.p, ng, keys.p, t.bbox.p, t.geom.p);
+    if (!sc.lds.empty()) {
+        run_lds_split(t, LdsInput{XA.p, YA.p, XB.p, YB.p, IA.p, IB.p, nullptr, nullptr, 0}, keys.p, s);
+    } else if (!sc.geom.empty()) {
+        const int ng = (int)sc.geom.size();
+        k_geom_keys<<<(unsigned)((ng + 7) / 8), 256, 0, s>>>(sc.d_geom.p, ng, keys.p, t.bbox.p, t.geom.p);
         check_launch("geom");
     }
-    k_scaling_radius<<<grid_for(sc.nbox, 256), 256, 0, s>>>(sc.nbox, sc.d_box_parent.p, t.geom.p);
-    check_launch("scaling radius");
     // non-finite positions: t.err, read at the next synchronising call on the tree
 }
 

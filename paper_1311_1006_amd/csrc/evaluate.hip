@@ -449,13 +449,12 @@ void transposed_far(Plan& pl, const double* w, hipStream_t s)
 void launch_real_to_complex(int64_t n, const double* q, double* m, hipStream_t s);
 template <class T>
 void launch_log_constants(int nbox, const int32_t* w_beg, const int32_t* w_cnt, const int32_t* w_ids,
-                          const double* geom, const void* mp, const void* loc, int p, const int32_t* level_boxes,
-                          const std::vector<int64_t>& level_off, int nlevels, const int32_t* parent, double* c0,
-                          hipStream_t s);
+                          const int32_t* parent, const double* geom, const void* mp, const void* loc, int p,
+                          double* c0, hipStream_t s);
 template <class T>
 void launch_l2p_log(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount,
-                    const double* geom, const double* X, const double* Y, const void* loc, int p, const double* c0,
-                    const double* near, const int32_t* perm, double* u, hipStream_t s);
+                    const int32_t* parent, const double* geom, const double* X, const double* Y, const void* loc,
+                    int p, const double* c0, const double* near, const int32_t* perm, double* u, hipStream_t s);
 
 // The logarithmic potential (see log.hip): the harmonic upward pass and far
 // field of the strengths q as complex numbers, the constant terms of the local
@@ -480,12 +479,12 @@ void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, do
     if (mixed) run_far_down<float>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
     else run_far_down<double>(pl, ex, pl.mpole.p, pl.local.p, s, tm, nullptr, true);
     auto constants = mixed ? launch_log_constants<float> : launch_log_constants<double>;
-    constants((int)sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, pl.mpole.p, pl.local.p, pl.p,
-              ex.d_level_boxes.p, ex.level_boxes_off, sc.max_levels, sc.d_box_parent.p, c0, s);
+    constants((int)sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, sc.d_box_parent.p, t.geom.p, pl.mpole.p, pl.local.p,
+              pl.p, c0, s);
     run_p2p(pl, ex, s, nullptr, true);
     auto l2p = mixed ? launch_l2p_log<float> : launch_l2p_log<double>;
-    l2p(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, pl.local.p, pl.p,
-        c0, pl.near.p, t.perm.p, u, s);
+    l2p(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p, sc.d_box_count.p, sc.d_box_parent.p, t.geom.p, t.x.p, t.y.p,
+        pl.local.p, pl.p, c0, pl.near.p, t.perm.p, u, s);
     // the harmonic state of the plan now holds these strengths: no adjoint of it
     pl.have_forward = false;
 }

@@ -42,18 +42,30 @@ constexpr InvK make_inv_k()
 }
 __constant__ InvK kInvK = make_inv_k();
 
-// c0 of every box from its weak list (zero without one): 32 lanes per box,
-// lane e takes pairs e, e + 32, ... (on uniform inputs at theta = 0.5 most
-// lists are shorter than 64, so one or two passes; clustered inputs reach
-// lists of a few hundred entries, which take more passes of the same lanes);
-// the lanes' sums are added by a butterfly (a fixed order, so the result is
-// reproducible)
+// The constant term of every box without its ancestors' part: M2L over its weak
+// list, plus the parent's local series (complete: M2L and L2L done) at the box's
+// centre.  The whole constant of a leaf is the sum over it and its ancestors
+// (k_l2p_log).
+//
+// 32 lanes per box, lane e takes pairs e, e + 32, ... (on uniform inputs at
+// theta = 0.5 most lists are shorter than 64, so one or two passes; clustered
+// inputs reach lists of a few hundred entries, which take more passes of the
+// same lanes); then lane l takes term l of the parent's series; the lanes' sums
+// are added by a butterfly (a fixed order, so the result is reproducible).
+// Bound by the gathers of the sources' coefficients: kLogRun of them are in
+// flight per lane, so that a line is used while it is in the cache (one at a
+// time: 45.6 us for 500,000 points on 8 levels, and 35.8 us of one launch per
+// level for the parents' part; now 40.5 us for both).
+constexpr int kLogRun = 8;
+
 template <class T>
 __global__ void __launch_bounds__(256)
-k_m2l_log0(int nbox, const int32_t* __restrict__ w_beg, const int32_t* __restrict__ w_cnt,
-           const int32_t* __restrict__ w_ids, const double* __restrict__ geom, const T* __restrict__ mp, int p,
-           double* __restrict__ c0)
+k_log_constants(int nbox, const int32_t* __restrict__ w_beg, const int32_t* __restrict__ w_cnt,
+                const int32_t* __restrict__ w_ids, const int32_t* __restrict__ parent,
+                const double* __restrict__ geom, const T* __restrict__ mp, const T* __restrict__ loc, int p,
+                double* __restrict__ c0)
 {
+    struct alignas(2 * sizeof(T)) C { T x, y; };
     const int g = blockIdx.x * 8 + (threadIdx.x >> 5), lane = threadIdx.x & 31;
     const bool live = g < nbox;   // every lane stays for the butterfly
     const int b = live ? w_beg[g] : 0, n = live ? w_cnt[g] : 0;
@@ -64,14 +76,41 @@ k_m2l_log0(int nbox, const int32_t* __restrict__ w_beg, const int32_t* __restric
         const double dx = cx - geom[4 * (int64_t)S], dy = cy - geom[4 * (int64_t)S + 1];
         const double rs = geom[4 * (int64_t)S + 3];
         const double r2 = dx * dx + dy * dy;   // > 0: weak pairs are well separated
-        const T* a = mp + 2 * (int64_t)S * p;
-        acc += (double)a[0] * 0.5 * log(r2);
+        const C* a = (const C*)(mp + 2 * (int64_t)S * p);
+        const double a0 = (double)a[0].x;
         const double2 u = make_double2(rs * dx / r2, -rs * dy / r2);   // rs_S / d
         double2 pw = u;
-        for (int k = 1; k < p; ++k) {
-            const double2 x = cmul(pw, make_double2((double)a[2 * k], (double)a[2 * k + 1]));
-            acc -= x.x * kInvK.v[k];
-            pw = cmul(pw, u);
+        for (int k0 = 1; k0 < p; k0 += kLogRun) {
+            C c[kLogRun];
+#pragma unroll
+            for (int q = 0; q < kLogRun; ++q) c[q] = a[min(k0 + q, p - 1)];
+#pragma unroll
+            for (int q = 0; q < kLogRun; ++q) {
+                if (k0 + q < p) {
+                    const double2 x = cmul(pw, make_double2((double)c[q].x, (double)c[q].y));
+                    acc -= x.x * kInvK.v[k0 + q];
+                    pw = cmul(pw, u);
+                }
+            }
+        }
+        acc += a0 * 0.5 * log(r2);
+    }
+    const int P = live ? parent[g] : -1;
+    if (P >= 0) {
+        const double rs = geom[4 * (int64_t)P + 3];
+        if (rs > 0.0) {
+            const double2 tau = make_double2((cx - geom[4 * (int64_t)P]) / rs, (cy - geom[4 * (int64_t)P + 1]) / rs);
+            const C* bl = (const C*)(loc + 2 * (int64_t)P * p);
+            for (int l = lane; l < p; l += 32) {
+                const C c = bl[l];
+                // tau^(l+1) by squaring
+                double2 pw = make_double2(1.0, 0.0), t = tau;
+                for (int e = l + 1; e; e >>= 1) {
+                    if (e & 1) pw = cmul(pw, t);
+                    t = cmul(t, t);
+                }
+                acc += rs * cmul(make_double2((double)c.x, (double)c.y), pw).x / (double)(l + 1);
+            }
         }
     }
 #pragma unroll
@@ -79,52 +118,33 @@ k_m2l_log0(int nbox, const int32_t* __restrict__ w_beg, const int32_t* __restric
     if (live && lane == 0) c0[g] = acc;
 }
 
-// c0 of the boxes of one level += Re F_parent(centre): the parent's constant
-// plus its local series (complete: M2L and L2L done) at the child's centre
+// L2P of the logarithmic series at the points of every leaf (32 lanes per leaf,
+// eight leaves per workgroup: leaves hold about 30 points), plus the near field,
+// scattered to input order.  The constant term is summed over the leaf and its
+// ancestors, root last.
 template <class T>
-__global__ void k_c0_shift(const int32_t* __restrict__ boxes, int n, const int32_t* __restrict__ parent,
-                           const double* __restrict__ geom, const T* __restrict__ loc, int p, double* c0)
+__global__ void __launch_bounds__(256)
+k_l2p_log(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__ bstart,
+          const int32_t* __restrict__ bcount, const int32_t* __restrict__ parent, const double* __restrict__ geom,
+          const double* __restrict__ X, const double* __restrict__ Y, const T* __restrict__ loc, int p,
+          const double* __restrict__ c0, const double* __restrict__ near, const int32_t* __restrict__ perm,
+          double* __restrict__ u)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const int g = boxes[i], P = parent[g];
-    if (P < 0) return;
-    const double rs = geom[4 * (int64_t)P + 3];
-    double v = c0[P];
-    if (rs > 0.0) {
-        const double2 tau = make_double2((geom[4 * (int64_t)g] - geom[4 * (int64_t)P]) / rs,
-                                         (geom[4 * (int64_t)g + 1] - geom[4 * (int64_t)P + 1]) / rs);
-        const T* b = loc + 2 * (int64_t)P * p;
-        double2 acc = make_double2(0.0, 0.0);
-        for (int l = p - 1; l >= 0; --l) {
-            acc = cmul(acc, tau);
-            acc.x += (double)b[2 * l] / (l + 1);
-            acc.y += (double)b[2 * l + 1] / (l + 1);
-        }
-        v += rs * cmul(acc, tau).x;
-    }
-    c0[g] += v;
-}
-
-// L2P of the logarithmic series at the points of every leaf (a workgroup of
-// 64 per leaf), plus the near field, scattered to input order
-template <class T>
-__global__ void __launch_bounds__(64)
-k_l2p_log(const int32_t* __restrict__ leaves, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
-          const double* __restrict__ geom, const double* __restrict__ X, const double* __restrict__ Y,
-          const T* __restrict__ loc, int p, const double* __restrict__ c0, const double* __restrict__ near,
-          const int32_t* __restrict__ perm, double* __restrict__ u)
-{
-    __shared__ double2 cf[kMaxP];
-    const int g = leaves[blockIdx.x];
+    __shared__ double2 scf[8][kMaxP];
+    const int lane = threadIdx.x & 31;
+    const int li = blockIdx.x * 8 + (threadIdx.x >> 5);
+    if (li >= nleaf) return;   // (no workgroup barrier below)
+    double2* cf = scf[threadIdx.x >> 5];
+    const int g = leaves[li];
     const int st = bstart[g], n = bcount[g];
     const double cx = geom[4 * (int64_t)g], cy = geom[4 * (int64_t)g + 1], rs = geom[4 * (int64_t)g + 3];
     const T* b = loc + 2 * (int64_t)g * p;
-    for (int l = threadIdx.x; l < p; l += 64)
+    for (int l = lane; l < p; l += 32)
         cf[l] = make_double2((double)b[2 * l] / (l + 1), (double)b[2 * l + 1] / (l + 1));
-    __syncthreads();
-    const double base = c0[g];
-    for (int i = threadIdx.x; i < n; i += 64) {
+    double base = 0.0;
+    for (int a = g; a >= 0; a = parent[a]) base += c0[a];
+    wave_sync();
+    for (int i = lane; i < n; i += 32) {
         const int pos = st + i;
         double v = base;
         if (rs > 0.0) {
@@ -148,47 +168,36 @@ void launch_real_to_complex(int64_t n, const double* q, double* m, hipStream_t s
     check_launch("log strengths");
 }
 
-// the constant terms of every box: M2L part, then top-down shifts
 template <class T>
 void launch_log_constants(int nbox, const int32_t* w_beg, const int32_t* w_cnt, const int32_t* w_ids,
-                          const double* geom, const void* mp, const void* loc, int p,
-                          const int32_t* level_boxes, const std::vector<int64_t>& level_off, int nlevels,
-                          const int32_t* parent, double* c0, hipStream_t s)
+                          const int32_t* parent, const double* geom, const void* mp, const void* loc, int p,
+                          double* c0, hipStream_t s)
 {
     if (nbox == 0) return;
-    k_m2l_log0<T><<<(unsigned)((nbox + 7) / 8), 256, 0, s>>>(nbox, w_beg, w_cnt, w_ids, geom, (const T*)mp, p, c0);
-    check_launch("log m2l constants");
-    for (int l = 1; l < nlevels; ++l) {
-        const int n = (int)(level_off[l + 1] - level_off[l]);
-        if (n == 0) continue;
-        k_c0_shift<T><<<(unsigned)((n + 255) / 256), 256, 0, s>>>(level_boxes + level_off[l], n, parent, geom,
-                                                                  (const T*)loc, p, c0);
-        check_launch("log constant shift");
-    }
+    k_log_constants<T><<<(unsigned)((nbox + 7) / 8), 256, 0, s>>>(nbox, w_beg, w_cnt, w_ids, parent, geom,
+                                                                  (const T*)mp, (const T*)loc, p, c0);
+    check_launch("log constants");
 }
 
 template <class T>
 void launch_l2p_log(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount,
-                    const double* geom, const double* X, const double* Y, const void* loc, int p, const double* c0,
-                    const double* near, const int32_t* perm, double* u, hipStream_t s)
+                    const int32_t* parent, const double* geom, const double* X, const double* Y, const void* loc,
+                    int p, const double* c0, const double* near, const int32_t* perm, double* u, hipStream_t s)
 {
     if (nleaf == 0) return;
-    k_l2p_log<T><<<(unsigned)nleaf, 64, 0, s>>>(leaves, bstart, bcount, geom, X, Y, (const T*)loc, p, c0, near, perm,
-                                                u);
+    k_l2p_log<T><<<(unsigned)((nleaf + 7) / 8), 256, 0, s>>>(leaves, nleaf, bstart, bcount, parent, geom, X, Y,
+                                                             (const T*)loc, p, c0, near, perm, u);
     check_launch("log l2p");
 }
 
-template void launch_log_constants<float>(int, const int32_t*, const int32_t*, const int32_t*, const double*,
-                                          const void*, const void*, int, const int32_t*, const std::vector<int64_t>&,
-                                          int, const int32_t*, double*, hipStream_t);
-template void launch_log_constants<double>(int, const int32_t*, const int32_t*, const int32_t*, const double*,
-                                           const void*, const void*, int, const int32_t*,
-                                           const std::vector<int64_t>&, int, const int32_t*, double*, hipStream_t);
-template void launch_l2p_log<float>(const int32_t*, int, const int32_t*, const int32_t*, const double*, const double*,
-                                    const double*, const void*, int, const double*, const double*, const int32_t*,
-                                    double*, hipStream_t);
-template void launch_l2p_log<double>(const int32_t*, int, const int32_t*, const int32_t*, const double*,
-                                     const double*, const double*, const void*, int, const double*, const double*,
-                                     const int32_t*, double*, hipStream_t);
+#define LOG_INSTANCE(T)                                                                                            \
+    template void launch_log_constants<T>(int, const int32_t*, const int32_t*, const int32_t*, const int32_t*,     \
+                                          const double*, const void*, const void*, int, double*, hipStream_t);     \
+    template void launch_l2p_log<T>(const int32_t*, int, const int32_t*, const int32_t*, const int32_t*,           \
+                                    const double*, const double*, const double*, const void*, int, const double*,  \
+                                    const double*, const int32_t*, double*, hipStream_t);
+LOG_INSTANCE(float)
+LOG_INSTANCE(double)
+#undef LOG_INSTANCE
 
 }  // namespace fmm

@@ -210,8 +210,8 @@ k_adj_final(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __rest
         cx = geom[4 * (int64_t)g];
         cy = geom[4 * (int64_t)g + 1];
         inv = 1.0 / geom[4 * (int64_t)g + 3];
-        const T2* bsrc = reinterpret_cast<const T2*>(loc) + (int64_t)g * p;
-        const T2* lsrc = reinterpret_cast<const T2*>(lam) + (int64_t)g * p;
+        const T2* bsrc = reinterpret_cast<const T2*>(loc) + (int64_t)g * coef_ld<T>(p);
+        const T2* lsrc = reinterpret_cast<const T2*>(lam) + (int64_t)g * coef_ld<T>(p);
         for (int k = sl; k < P; k += G) {
             const T2 zero = {(T)0, (T)0};
             const T2 b = k < p ? bsrc[k] : zero, a = k < p ? lsrc[k] : zero;
@@ -347,8 +347,9 @@ void adjoint_device(Plan& pl, const double* m, const double* gphi, double* gm, d
     if (pl.gtree.n < (size_t)(2 * n)) pl.gtree.alloc(2 * n, s);
     DBuf<double> ngb;
     ngb.alloc(2 * n, s);
-    if (pl.amp.n < 2 * cs * sc.nbox * pl.p) pl.amp.alloc(2 * cs * sc.nbox * pl.p, s);
-    if (pl.aloc.n < 2 * cs * sc.nbox * pl.p) pl.aloc.alloc(2 * cs * sc.nbox * pl.p, s);
+    const size_t nc = 2 * cs * sc.nbox * coef_ld(pl.p, 2 * cs);
+    if (pl.amp.n < nc) pl.amp.alloc(nc, s);
+    if (pl.aloc.n < nc) pl.aloc.alloc(nc, s);
     // strengths m in tree order (the forward's gather, repeated for safety)
     launch_gather(n, t.perm.p, m, pl.mtree.p, s);
     k_gather_adj<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, t.perm.p, (const double2*)gphi,
@@ -415,7 +416,7 @@ k_field_final(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __re
         cx = geom[4 * (int64_t)g];
         cy = geom[4 * (int64_t)g + 1];
         inv = 1.0 / geom[4 * (int64_t)g + 3];
-        const T2* bsrc = reinterpret_cast<const T2*>(loc) + (int64_t)g * p;
+        const T2* bsrc = reinterpret_cast<const T2*>(loc) + (int64_t)g * coef_ld<T>(p);
         for (int k = sl; k < P; k += G) {
             const T2 zero = {(T)0, (T)0};
             const T2 b = k < p ? bsrc[k] : zero;

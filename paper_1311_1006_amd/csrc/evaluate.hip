@@ -213,8 +213,8 @@ void alloc_eval_buffers(Plan& pl, hipStream_t s)
     size_t cs = mixed ? sizeof(float) : sizeof(double);
     pl.mtree.alloc(2 * n, s);
     pl.near.alloc(2 * n, s);
-    pl.mpole.alloc(2 * cs * sc.nbox * pl.p, s);
-    pl.local.alloc(2 * cs * sc.nbox * pl.p, s);
+    pl.mpole.alloc(2 * cs * sc.nbox * coef_ld(pl.p, 2 * cs), s);
+    pl.local.alloc(2 * cs * sc.nbox * coef_ld(pl.p, 2 * cs), s);
 }
 
 // Whether the subtrees' downward pass is staged (every box's complete

@@ -98,7 +98,7 @@ k_p2m(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int idx = base + i, k = k0 + (idx >> 1);
-            if (k < p) mp[2 * ((int64_t)g * p + k) + (idx & 1)] = (T)v[i];
+            if (k < p) mp[2 * ((int64_t)g * coef_ld<T>(p) + k) + (idx & 1)] = (T)v[i];
         }
     }
 }
@@ -127,7 +127,7 @@ k_l2p(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__
     const int g = leaves[li];
     const int st = bstart[g], n = bcount[g];
     const double cx = geom[4 * (int64_t)g], cy = geom[4 * (int64_t)g + 1], inv = 1.0 / geom[4 * (int64_t)g + 3];
-    const T2* b = reinterpret_cast<const T2*>(loc) + (int64_t)g * p;
+    const T2* b = reinterpret_cast<const T2*>(loc) + (int64_t)g * coef_ld<T>(p);
     double2 bl[kLdsCoef ? 1 : P];
     double2* co = sco[kLdsCoef ? threadIdx.x / G : 0];
     if constexpr (kLdsCoef) {

@@ -76,7 +76,7 @@ k_log_constants(int nbox, const int32_t* __restrict__ w_beg, const int32_t* __re
         const double dx = cx - geom[4 * (int64_t)S], dy = cy - geom[4 * (int64_t)S + 1];
         const double rs = geom[4 * (int64_t)S + 3];
         const double r2 = dx * dx + dy * dy;   // > 0: weak pairs are well separated
-        const C* a = (const C*)(mp + 2 * (int64_t)S * p);
+        const C* a = (const C*)(mp + 2 * (int64_t)S * coef_ld<T>(p));
         const double a0 = (double)a[0].x;
         const double2 u = make_double2(rs * dx / r2, -rs * dy / r2);   // rs_S / d
         double2 pw = u;
@@ -100,7 +100,7 @@ k_log_constants(int nbox, const int32_t* __restrict__ w_beg, const int32_t* __re
         const double rs = geom[4 * (int64_t)P + 3];
         if (rs > 0.0) {
             const double2 tau = make_double2((cx - geom[4 * (int64_t)P]) / rs, (cy - geom[4 * (int64_t)P + 1]) / rs);
-            const C* bl = (const C*)(loc + 2 * (int64_t)P * p);
+            const C* bl = (const C*)(loc + 2 * (int64_t)P * coef_ld<T>(p));
             for (int l = lane; l < p; l += 32) {
                 const C c = bl[l];
                 // tau^(l+1) by squaring
@@ -138,7 +138,7 @@ k_l2p_log(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restri
     const int g = leaves[li];
     const int st = bstart[g], n = bcount[g];
     const double cx = geom[4 * (int64_t)g], cy = geom[4 * (int64_t)g + 1], rs = geom[4 * (int64_t)g + 3];
-    const T* b = loc + 2 * (int64_t)g * p;
+    const T* b = loc + 2 * (int64_t)g * coef_ld<T>(p);
     for (int l = lane; l < p; l += 32)
         cf[l] = make_double2((double)b[2 * l] / (l + 1), (double)b[2 * l + 1] / (l + 1));
     double base = 0.0;

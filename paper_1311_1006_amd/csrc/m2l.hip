@@ -105,7 +105,7 @@ template <class T, int KS>
 __device__ __forceinline__ void load_coef(typename Vec2<T>::type (&a)[KS], int S, int kq, int p,
                                           const T* __restrict__ mp)
 {
-    const typename Vec2<T>::type* src = reinterpret_cast<const typename Vec2<T>::type*>(mp) + (int64_t)S * p;
+    const typename Vec2<T>::type* src = reinterpret_cast<const typename Vec2<T>::type*>(mp) + (int64_t)S * coef_ld<T>(p);
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
         const int k = kq + 4 * i;
@@ -392,7 +392,7 @@ k_m2l(const int32_t* __restrict__ boxes, const int2* __restrict__ xitems, int nx
                 const int row = 16 * rb + r0 + (M::kRowsConsecutive ? j : 4 * j);
                 if (row >= p) continue;
                 if (nch == 1) {
-                    T* dst = loc + 2 * ((int64_t)g * p + row);
+                    T* dst = loc + 2 * ((int64_t)g * coef_ld<T>(p) + row);
                     dst[0] = ore[rb][j];
                     dst[1] = oim[rb][j];
                 } else {                          // partial sum of a split list
@@ -450,7 +450,7 @@ __global__ void k_m2l_combine(const int32_t* __restrict__ boxes, int n, const in
         re += pr[k * step];
         im += pr[k * step + 1];
     }
-    T* dst = loc + 2 * ((int64_t)(boxes ? boxes[i] : i) * p + row);
+    T* dst = loc + 2 * ((int64_t)(boxes ? boxes[i] : i) * coef_ld<T>(p) + row);
     dst[0] = (T)re;
     dst[1] = (T)im;
 }

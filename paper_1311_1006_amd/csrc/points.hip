@@ -352,7 +352,7 @@ struct Visit {
         const double* g = geom + 4 * (int64_t)bx;
         const double dx = y.x - g[0], dy = y.y - g[1];
         if (!direct && lv > 0 && point_separated(g[2], dx, dy, theta)) {
-            m2p<T, DER>(mpole + 2 * (int64_t)bx * p, p, g[3], dx, dy, phi, dphi);
+            m2p<T, DER>(mpole + 2 * (int64_t)bx * coef_ld<T>(p), p, g[3], dx, dy, phi, dphi);
             return true;
         }
         if (lv != L - 1) return false;
@@ -567,7 +567,7 @@ k_pts_far(const double2* __restrict__ y, int64_t M, const int32_t* __restrict__ 
         const double* g = geom + 4 * (int64_t)B;
         const double irs = 1.0 / g[3];
         const double2 w = make_double2((yv.x - g[0]) * irs, (yv.y - g[1]) * irs);
-        const T* b = local + 2 * (int64_t)B * p;
+        const T* b = local + 2 * (int64_t)B * coef_ld<T>(p);
         double2 s = coef(b, p - 1), t = make_double2((double)(p - 1) * s.x, (double)(p - 1) * s.y);
         for (int l = p - 2; l >= 0; --l) {
             const double2 bl = coef(b, l);

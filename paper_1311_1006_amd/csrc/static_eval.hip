@@ -23,7 +23,9 @@ constexpr size_t kStaticBytes = size_t(64) << 20;
 constexpr size_t kStaticAlign = 256;
 constexpr int kStaticMaxDevices = 64;
 
-static __device__ __align__(256) unsigned char scratch[kStaticBytes];
+// with room for the padding of the coefficient rows (at most one in eight
+// coefficients), which is not counted against the limit
+static __device__ __align__(256) unsigned char scratch[kStaticBytes + kStaticBytes / 8 + 2 * kStaticAlign];
 
 // the device address of `scratch` on `device` (the current device), taken
 // on the first call there
@@ -65,6 +67,12 @@ void add(std::vector<Slot>& v, DBuf<T>& b)
     if (b.p) v.push_back(Slot{&b, &set_ptr<T>, b.p, b.bytes()});
 }
 
+// bytes of a coefficient array without the padding of its rows
+size_t coef_bytes(const Plan& pl)
+{
+    return 2 * (pl.precision == FMM_MIXED ? sizeof(float) : sizeof(double)) * pl.tree->sched->nbox * pl.p;
+}
+
 struct Swap {
     std::vector<Slot> slots;
     ~Swap()
@@ -76,7 +84,7 @@ struct Swap {
 }  // namespace
 
 // Bytes of the array the evaluation of `pl` needs (each buffer rounded up
-// to kStaticAlign).
+// to kStaticAlign), the padding of the coefficient rows aside.
 size_t static_eval_bytes(Plan& pl)
 {
     std::vector<Slot> v;
@@ -86,6 +94,8 @@ size_t static_eval_bytes(Plan& pl)
     add(v, pl.local);
     add(v, pl.bal.partial);
     add(v, pl.bal_m2l.partial);
+    for (auto& s : v)
+        if (s.buf == &pl.mpole || s.buf == &pl.local) s.bytes = coef_bytes(pl);
     size_t need = 0;
     for (auto& s : v) need += (s.bytes + kStaticAlign - 1) / kStaticAlign * kStaticAlign;
     return need;

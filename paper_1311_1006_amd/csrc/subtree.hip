@@ -176,8 +176,8 @@ template <class T>
 __device__ __forceinline__ double2 store_coef(T* dst, int64_t box, int p, int k, double2 v)
 {
     const T tx = (T)v.x, ty = (T)v.y;
-    dst[2 * (box * p + k)] = tx;
-    dst[2 * (box * p + k) + 1] = ty;
+    dst[2 * (box * coef_ld<T>(p) + k)] = tx;
+    dst[2 * (box * coef_ld<T>(p) + k) + 1] = ty;
     return make_double2((double)tx, (double)ty);
 }
 
@@ -374,7 +374,7 @@ k_up_mid(SubWork work, const double* __restrict__ geom, int p, T* mp, const doub
         for (int q = 0; q < KP; ++q) {
             const int64_t box = sub_box(at.pb, a + D, (at.j << (2 * D)) + min(gl + NG * r, nin - 1));
             const int k = min(sl + 16 * q, p - 1);
-            v[r][q] = make_double2((double)mp[2 * (box * p + k)], (double)mp[2 * (box * p + k) + 1]);
+            v[r][q] = make_double2((double)mp[2 * (box * coef_ld<T>(p) + k)], (double)mp[2 * (box * coef_ld<T>(p) + k) + 1]);
         }
     sub_boxes<NT>(sg, at, geom, ngeo);
     __syncthreads();
@@ -449,11 +449,11 @@ k_down_mid(SubWork work, const double* __restrict__ geom, int p, T* loc, const d
 #pragma unroll
     for (int q = 0; q < KP; ++q) {
         const int k = min(sl + 16 * q, p - 1);
-        ca[q] = lo[(int64_t)sub_box(at.pb, a, at.j) * p + k];
+        ca[q] = lo[(int64_t)sub_box(at.pb, a, at.j) * coef_ld<T>(p) + k];
 #pragma unroll
         for (int d = 1; d <= DM; ++d) {
             const int dd = min(d, D);
-            cs[d - 1][q] = lo[(int64_t)sub_box(at.pb, a + dd, (at.j << (2 * dd)) + min(gl, (1 << (2 * dd)) - 1)) * p + k];
+            cs[d - 1][q] = lo[(int64_t)sub_box(at.pb, a + dd, (at.j << (2 * dd)) + min(gl, (1 << (2 * dd)) - 1)) * coef_ld<T>(p) + k];
         }
     }
     sub_boxes<NT>(sg, at, geom, ngeo);
@@ -548,14 +548,14 @@ k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __r
 #pragma unroll
     for (int q = 0; q < KP; ++q) {
         const int k = min(sl + 16 * q, p - 1);
-        ca[q] = lo[(int64_t)A * p + k];
-        cc[q] = lo[(int64_t)Cw * p + k];
-        cl[q] = lo[(int64_t)leaf * p + k];
+        ca[q] = lo[(int64_t)A * coef_ld<T>(p) + k];
+        cc[q] = lo[(int64_t)Cw * coef_ld<T>(p) + k];
+        cl[q] = lo[(int64_t)leaf * coef_ld<T>(p) + k];
         fac[q] = fact[sl + 16 * q];
         ifac[q] = fact[kInvFact + sl + 16 * q];
     }
     // thread l < P: R's own sum
-    cR = lo[(int64_t)R * p + min((int)threadIdx.x, p - 1)];
+    cR = lo[(int64_t)R * coef_ld<T>(p) + min((int)threadIdx.x, p - 1)];
     const double facR = fact[threadIdx.x & 63];
     // the leaf's first points (a lane past the leaf's end reads point 0)
     double px[NPT], py[NPT];

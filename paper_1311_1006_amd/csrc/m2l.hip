@@ -30,8 +30,14 @@
 // FP32 path: v_mfma_f32_16x16x4f32 (output rows 4 kq + j), FP32 accumulation.
 // FP64 path: v_mfma_f64_16x16x4f64 (output rows kq + 4 j).
 // p <= 16 uses one 16-row block (PB = 1), p <= 32 two, p <= 48 three and
-// p <= 64 four (those with one box per wavefront: the expansion orders of the
-// strictest tolerances, where a wavefront's 16 pair slots stay full anyway).
+// p <= 64 four; the k-steps are as many as the order needs (KS = ceil(p / 4) in
+// the automatic shapes; the columns beyond it would be zero).  1e6 points, FP64 /
+// mixed, with KS = 4 PB before and as needed now: p = 8 143 / 84 to 102 / 57 us,
+// p = 12 143 / 84 to 128 / 70, p = 17 497 / 218 to 278 / 155, p = 24 517 / 221 to
+// 315 / 181.
+// Bound by issue: at p = 16 in FP64 the matrix instructions take 64 cycles each
+// (52 us of 155 for 1e6 points) and the vector ones 44 us, on units that they
+// share in part.
 #include "fmm_internal.h"
 #include "kernels_common.h"
 
@@ -185,7 +191,7 @@ __device__ __forceinline__ PairGeo<double> make_geo(double, double ctx, double c
     return g;
 }
 
-template <class T, int PB, int G>
+template <class T, int PB, int KS, int G>
 __global__ void __launch_bounds__(256)
 k_m2l(const int32_t* __restrict__ boxes, const int2* __restrict__ xitems, int nx, const int32_t* __restrict__ icnt,
       const int32_t* __restrict__ ioff, double* __restrict__ partial, const int32_t* __restrict__ w_beg,
@@ -195,7 +201,7 @@ k_m2l(const int32_t* __restrict__ boxes, const int2* __restrict__ xitems, int nx
 {
     using M = Mfma<T>;
     using T2 = typename Vec2<T>::type;
-    constexpr int KS = 4 * PB;       // k-steps of 4 (K = 16 PB)
+    static_assert(KS <= 4 * PB, "k-steps of 4: terms k >= 4 KS do not exist");
     constexpr int S = 16 / G;        // pair slots of one item in a block of 16
     const int w = threadIdx.x >> 6;
     const int lane = threadIdx.x & 63;
@@ -404,16 +410,16 @@ k_m2l(const int32_t* __restrict__ boxes, const int2* __restrict__ xitems, int nx
     }
 }
 
-template <class T, int PB, int G>
+template <class T, int PB, int KS, int G>
 static void m2l_one(const int32_t* boxes, const int2* xitems, int nx, const int32_t* icnt, const int32_t* ioff,
                     double* partial, const int32_t* w_beg, const int32_t* w_cnt, const int32_t* w_ids,
                     const double* geom, const double* binom, int p, const void* mp, void* loc, hipStream_t s,
                     const long long* guard)
 {
     const int per_block = 4 * G;   // items per workgroup (4 wavefronts)
-    k_m2l<T, PB, G><<<(nx + per_block - 1) / per_block, 256, 0, s>>>(boxes, xitems, nx, icnt, ioff, partial, w_beg,
-                                                                     w_cnt, w_ids, geom, binom, p, (const T*)mp,
-                                                                     (T*)loc, guard);
+    k_m2l<T, PB, KS, G><<<(nx + per_block - 1) / per_block, 256, 0, s>>>(boxes, xitems, nx, icnt, ioff, partial,
+                                                                         w_beg, w_cnt, w_ids, geom, binom, p,
+                                                                         (const T*)mp, (T*)loc, guard);
 }
 
 // the partial local expansions of split lists, added in chunk order
@@ -461,7 +467,13 @@ __global__ void k_m2l_combine(const int32_t* __restrict__ boxes, int n, const in
 // one item in each 16-pair MFMA block: 16 (one item per wavefront), 8 (two)
 // or 4 (four items share a wavefront); 0 = automatic (4, the fastest in both
 // precisions on the uniform million-point case: mixed 81 us against 93 us
-// with 8 slots, FP64 146 us against 161 us).
+// with 8 slots, FP64 146 us against 161 us).  Above 32 terms the slots are fixed: 8
+// in FP64 up to 48 terms (p = 39, before with 16: 1e6 points 1324 to 990 us, 1e5 96
+// to 74, 30,000 35 to 30, 4000 18 to 23), where wavefronts of more boxes leave
+// small problems idle (4 slots: 838, 79, 45 and 33 us), and 16 in mixed
+// precision and above 48 terms (64 terms, 4000 points: 32 us against 41).  The
+// choice depends on the order and the precision alone, so that a problem's
+// sums are the same in a batch as alone.
 template <class T>
 void launch_m2l(const int32_t* boxes, int n, const int2* xitems, int nx, const int32_t* icnt, const int32_t* ioff,
                 double* partial, bool split, const int32_t* w_beg, const int32_t* w_cnt, const int32_t* w_ids,
@@ -469,29 +481,37 @@ void launch_m2l(const int32_t* boxes, int n, const int2* xitems, int nx, const i
                 const long long* guard)
 {
     if (nx == 0) return;
-    const int slots = batch != 0 ? batch : 4;
+    const int slots = batch != 0 ? batch : 4, ks = (p + 3) / 4;
 #define ARGS boxes, xitems, nx, icnt, ioff, partial, w_beg, w_cnt, w_ids, geom, binom, p, mp, loc, s, guard
+#define FOUR(PB, K0, G)                                       \
+    {                                                         \
+        if (ks <= K0) m2l_one<T, PB, K0, G>(ARGS);            \
+        else if (ks == K0 + 1) m2l_one<T, PB, K0 + 1, G>(ARGS); \
+        else if (ks == K0 + 2) m2l_one<T, PB, K0 + 2, G>(ARGS); \
+        else m2l_one<T, PB, 4 * PB, G>(ARGS);                 \
+    }
     if (p <= 16) {
-        if (slots == 16) m2l_one<T, 1, 1>(ARGS);
-        else if (slots == 8) m2l_one<T, 1, 2>(ARGS);
-        else if (slots == 4) m2l_one<T, 1, 4>(ARGS);
-        else if (slots == 2) m2l_one<T, 1, 8>(ARGS);
-        else if (slots == 1) m2l_one<T, 1, 16>(ARGS);
+        if (slots == 16) m2l_one<T, 1, 4, 1>(ARGS);
+        else if (slots == 8) m2l_one<T, 1, 4, 2>(ARGS);
+        else if (slots == 4) FOUR(1, 2, 4)
+        else if (slots == 2) m2l_one<T, 1, 4, 8>(ARGS);
+        else if (slots == 1) m2l_one<T, 1, 4, 16>(ARGS);
         else throw Error(FMM_EINVAL, "unsupported M2L batch");
     } else if (p <= 32) {
-        if (slots == 16) m2l_one<T, 2, 1>(ARGS);
-        else if (slots == 8) m2l_one<T, 2, 2>(ARGS);
-        else if (slots == 4) m2l_one<T, 2, 4>(ARGS);
-        else if (slots == 2) m2l_one<T, 2, 8>(ARGS);
-        else if (slots == 1) m2l_one<T, 2, 16>(ARGS);
+        if (slots == 16) m2l_one<T, 2, 8, 1>(ARGS);
+        else if (slots == 8) m2l_one<T, 2, 8, 2>(ARGS);
+        else if (slots == 4) FOUR(2, 5, 4)
+        else if (slots == 2) m2l_one<T, 2, 8, 8>(ARGS);
+        else if (slots == 1) m2l_one<T, 2, 8, 16>(ARGS);
         else throw Error(FMM_EINVAL, "unsupported M2L batch");
-    } else if (p <= 48) {          // three and four row blocks: one box per wavefront
-        m2l_one<T, 3, 1>(ARGS);
+    } else if (p <= 48) {
+        FOUR(3, 9, (sizeof(T) == 8 ? 2 : 1))
     } else if (p <= 64) {
-        m2l_one<T, 4, 1>(ARGS);
+        FOUR(4, 13, 1)
     } else {
         throw Error(FMM_EINVAL, "unsupported M2L configuration");
     }
+#undef FOUR
 #undef ARGS
     check_launch("m2l");
     if (split) {

@@ -62,3 +62,22 @@ def test_fixed_memory_limit_leaves_out_the_padding(F):
     out = dev(np.zeros(n, np.complex128))
     F.evaluate_static(pl, md, out)
     assert np.array_equal(host(out), phi)
+
+
+@pytest.mark.parametrize("p", [1, 3, 4, 5, 8, 9, 12, 13, 17, 20, 21, 24, 25, 28, 29, 32])
+def test_m2l_steps_by_order(orc, F, p):
+    # every count of matrix steps of the automatic shape, around its edges: the
+    # oracle's FMM of the same order
+    z, m, _ = W.uniform(9000, seed=p)
+    pl = F.plan(F.build_tree(dev(z), 5), p, 0.5, "fp64")
+    assert e2(host(F.evaluate(pl, dev(m))), orc.fmm(z, m, p, 0.5, 5)) <= 1e-12
+
+
+@pytest.mark.parametrize("p", [33, 36, 37, 40, 41, 44, 45, 48, 49, 52, 53, 56, 57, 60, 61, 64])
+@pytest.mark.parametrize("n,L", [(3000, 3), (9000, 5)])
+def test_m2l_steps_of_high_orders(orc, F, p, n, L):
+    # converged: the direct sum, to the parity bar
+    z, m, _ = W.uniform(n, seed=p)
+    ref, md, tree = orc.direct(z, m), dev(m), F.build_tree(dev(z), L)
+    assert e2(host(F.evaluate(F.plan(tree, p, 0.5, "fp64"), md)), ref) <= 1e-12
+    assert e2(host(F.evaluate(F.plan(tree, p, 0.5, "mixed"), md)), ref) <= 1e-6

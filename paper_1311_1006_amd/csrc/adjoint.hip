@@ -490,7 +490,7 @@ void field_device(Plan& pl, const double* m, double* phi, double* dphi, hipStrea
         if (pl.near4.n < (size_t)(4 * sc.n)) pl.near4.alloc(4 * sc.n, s);
         const size_t np = pl.bal.partial.n * 2;
         if (pl.bal.partial4.n < np) pl.bal.partial4.alloc(np, s);
-        evaluate_device(pl, m, phi, nullptr, nullptr, s, nullptr, nullptr, dphi);
+        evaluate_derivative_device(pl, m, phi, dphi, s);
         return;
     }
     // other launch shapes: the forward evaluation (phi, the local expansions

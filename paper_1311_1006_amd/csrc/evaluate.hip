@@ -489,8 +489,8 @@ void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, do
     pl.have_forward = false;
 }
 
-void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, double* phi_far, hipStream_t s,
-                     hipEvent_t lists_ev, const long long* guard, double* dphi)
+static void evaluate_any(Plan& pl, const double* m, double* phi, double* phi_near, double* phi_far, hipStream_t s,
+                         hipEvent_t lists_ev, const long long* guard, double* dphi)
 {
     PlanExtra& ex = *extra(pl);
     bool mixed = pl.precision == FMM_MIXED;
@@ -542,6 +542,16 @@ void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, d
         pl.t_total = tm.between(0, 5);
     }
     pl.have_forward = true;
+}
+
+void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, double* phi_far, hipStream_t s,
+                     hipEvent_t lists_ev, const long long* guard)
+{
+    evaluate_any(pl, m, phi, phi_near, phi_far, s, lists_ev, guard, nullptr);
+}
+void evaluate_derivative_device(Plan& pl, const double* m, double* phi, double* dphi, hipStream_t s)
+{
+    evaluate_any(pl, m, phi, nullptr, nullptr, s, nullptr, nullptr, dphi);
 }
 
 }  // namespace fmm

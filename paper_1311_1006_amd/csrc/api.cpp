@@ -428,6 +428,13 @@ void plan_join(Plan& P, hipStream_t s)
 {
     if (P.ev_plan_done) FMM_HIP(hipStreamWaitEvent(s, P.ev_plan_done, 0));
 }
+
+// order `s` after the tree's build and the plan's buffers, for work that needs
+// no lists: of a plan whose lists are still in flight, without waiting for them
+void plan_start(Plan& P, hipStream_t s)
+{
+    FMM_HIP(hipStreamWaitEvent(s, P.ev_plan_done ? P.ev_plan_done : P.ev_tree, 0));
+}
 }  // namespace fmm
 
 extern "C" {
@@ -467,6 +474,7 @@ int fmm_evaluate(fmm_plan_t pl, const double* m, double* phi, void* stream)
         hipStream_t s = (hipStream_t)stream;
         Plan& P = pl->pl;
         const bool pending = !P.finalized && !P.final_code && !(P.tune.flags & (FMM_FLAG_GRAPH | FMM_FLAG_PHASE_TIMING));
+        if (pending) plan_start(P, s);
         if (pending && P.lists_pending && P.lists_direct && P.flag_slot >= 0) {
             // The one-pass lists are still in flight.  The whole evaluation
             // is enqueued now for the usual outcome (no flag: every list fit

@@ -296,7 +296,7 @@ struct Plan {
     hipEvent_t ev_lists_k = nullptr;     // recorded after the list kernels (before the copy)
     hipEvent_t ev_spec = nullptr;  // after an evaluation enqueued ahead of the flags
     long long list_flag = -1;      // the flags read by build_lists_finish (-1: not read)
-    hipEvent_t ev_tree = nullptr;  // the tree's work on the caller's stream, before the lists
+    hipEvent_t ev_tree = nullptr;  // the tree's work and the plan's buffers on the caller's stream, before the lists
     hipEvent_t ev_plan_done = nullptr;   // the plan's last device work (list stream)
     bool upward_done = false;      // the evaluation's upward pass is already enqueued
     bool split_p2p = false, split_m2l = false;   // some list may need work chunks
@@ -358,6 +358,7 @@ double rel_err2_device(const double* a, const double* ref, int64_t n, hipStream_
 constexpr int kNearStream = 0, kListStream = 1;
 hipStream_t side_stream(int device, int which);
 void plan_join(Plan& pl, hipStream_t s);
+void plan_start(Plan& pl, hipStream_t s);
 void plan_events(Plan& pl);
 void second_stream(Plan& pl);   // the plan's second stream and its events, made on first use
 void plan_finalize(Plan& pl);

@@ -1,0 +1,123 @@
+"""The library's host code on a model of the HIP runtime (tests/hostmodel): device
+memory is host memory, kernels do nothing, streams and events keep vector
+clocks.  A launch that runs before what it needs shows here for certain, where
+a GPU would show it now and then, and failures of the runtime can be asked for."""
+import concurrent.futures as cf
+import ctypes as C
+import glob
+import os
+import shutil
+import subprocess
+
+import pytest
+
+import paper_1311_1006_amd as F
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1311_1006_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def library(tmp_path_factory):
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    if shutil.which("hipcc") is None or shutil.which("g++") is None:
+        pytest.skip("hipcc / g++ not available")
+    tmp = str(tmp_path_factory.mktemp("hostmodel"))
+    gxx = ["g++", "-D__HIP_PLATFORM_AMD__", "-I" + os.path.join(rocm, "include")]
+
+    def compile_(src):
+        obj = os.path.join(tmp, os.path.basename(src) + ".o")
+        cc = ["hipcc", "--offload-host-only"] if src.endswith(".hip") else gxx
+        subprocess.run(cc + ["-O1", "-std=c++17", "-fPIC", "-c", src, "-o", obj], check=True, capture_output=True)
+        return obj
+
+    srcs = glob.glob(os.path.join(CSRC, "*.hip")) + glob.glob(os.path.join(CSRC, "*.cpp"))
+    srcs.append(os.path.join(ROOT, "tests", "hostmodel", "runtime.cpp"))
+    with cf.ThreadPoolExecutor(max_workers=4) as ex:
+        objs = list(ex.map(compile_, srcs))
+    syms = subprocess.run(["nm", "-u"] + objs, check=True, capture_output=True, text=True).stdout.split()
+    code = ["-Wl,--defsym=%s=0" % s for s in sorted(set(syms)) if s.startswith("__hip_fatbin_")]
+    so = os.path.join(tmp, "model.so")
+    subprocess.run(["g++", "-shared", "-Wl,-z,defs", "-Wl,-Bsymbolic", "-o", so] + objs + code, check=True)
+    return so
+
+
+class Model:
+    """A fresh copy of the library with a runtime of its own."""
+
+    def __init__(self, so):
+        self.lib = C.CDLL(so)
+        for f in ("fmm_last_error",):
+            getattr(self.lib, f).restype = C.c_char_p
+        self.lib.model_stream.restype = C.c_void_p
+        self.lib.model_now.restype = C.c_long
+        self.buf = (C.c_double * 4096)()      # no kernel reads or writes it
+
+    def stream(self):
+        return C.c_void_p(self.lib.model_stream())
+
+    def ok(self, rc):
+        assert rc == 0, self.lib.fmm_last_error().decode()
+
+    def tree(self, n, L, s, nprob=1):
+        off = (C.c_int64 * (nprob + 1))(*[n * b for b in range(nprob + 1)])
+        h = C.c_void_p()
+        self.ok(self.lib.fmm_build_tree(self.buf, off, nprob, (C.c_int * nprob)(*[L] * nprob), s, C.byref(h)))
+        return h
+
+    def plan(self, tree, s, p=12, prec=0, flags=0):
+        t = F._Tuning()
+        t.flags = flags
+        h = C.c_void_p()
+        self.ok(self.lib.fmm_plan(tree, p, C.c_double(0.5), prec, C.byref(t), s, C.byref(h)))
+        return h
+
+    def call(self, op, pl, s):
+        L, b = self.lib, self.buf
+        if op == "evaluate":
+            return L.fmm_evaluate(pl, b, b, s)
+        if op == "parts":
+            return L.fmm_evaluate_parts(pl, b, b, b, s)
+        if op == "field":
+            return L.fmm_evaluate_field(pl, b, b, b, s)
+        if op == "log":
+            return L.fmm_evaluate_log(pl, b, b, s)
+        if op == "adjoint":
+            return L.fmm_evaluate_adjoint(pl, b, b, b, b, s)
+        if op == "static":
+            return L.fmm_evaluate_static(pl, b, b, s)
+        points, field = op.split(":")
+        return L.fmm_evaluate_points(pl, b, b, C.c_int64(int(points)), b, b if field == "field" else None, s)
+
+    def before(self, s, at):
+        name = C.create_string_buffer(256)
+        return self.lib.model_before(s, C.c_long(at), name, 256), name.value.decode()
+
+
+@pytest.fixture
+def model(library, tmp_path):
+    # a copy of its own: the library's statics are fresh
+    so = str(tmp_path / "model.so")
+    shutil.copy(library, so)
+    return Model(so)
+
+
+OPS = ["evaluate", "parts", "field", "log", "100:phi", "100:field", "60000:phi", "60000:field"]
+
+
+@pytest.mark.parametrize("flag", [0, 4, 12])      # no long lists; long strong lists; long weak ones too
+@pytest.mark.parametrize("op", OPS)
+def test_first_call_on_another_stream_follows_the_plan(model, op, flag):
+    # tree and plan on one stream, the first call on another: no kernel of the
+    # call may run before the tree is built (they gather through its permutation)
+    a, b = model.stream(), model.stream()
+    model.lib.model_list_flag(C.c_longlong(flag))
+    model.plan(model.tree(5000, 5, a), a)      # the first of a layout waits on the host
+    pl = model.plan(model.tree(5000, 5, a), a)
+    at = model.lib.model_now(a)
+    model.lib.model_clear()
+    model.ok(model.call(op, pl, b))
+    assert model.lib.model_launches() > 0
+    assert model.before(a, at) == (0, "")
+    # and the caller's stream comes after everything that the call launched
+    assert model.lib.model_not_joined(b) == 0

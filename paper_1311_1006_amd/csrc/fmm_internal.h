@@ -122,8 +122,8 @@ struct DBuf {
     void alloc(size_t count, hipStream_t st) {
         release();
         s = st;
-        n = count;
         if (count) p = static_cast<T*>(dev_alloc(count * sizeof(T), st));
+        n = count;      // not before: a failed allocation leaves an empty buffer
     }
     void release() {
         if (p) dev_free(p, s);

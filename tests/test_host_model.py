@@ -121,3 +121,43 @@ def test_first_call_on_another_stream_follows_the_plan(model, op, flag):
     assert model.before(a, at) == (0, "")
     # and the caller's stream comes after everything that the call launched
     assert model.lib.model_not_joined(b) == 0
+
+
+def live(model):
+    n = C.c_int64()
+    model.ok(model.lib.fmm_debug_live_blocks(C.byref(n)))
+    return n.value
+
+
+@pytest.mark.parametrize("flag", [0, 12])
+@pytest.mark.parametrize("op", OPS + ["adjoint"])
+def test_call_after_a_failed_allocation_has_its_buffers(model, op, flag):
+    # a buffer whose allocation failed is allocated by the next call: it must not
+    # count as there (its kernels would get a null pointer)
+    s = model.stream()
+    model.lib.model_list_flag(C.c_longlong(flag))
+
+    def plan():
+        pl = model.plan(model.tree(5000, 5, s), s)
+        model.ok(model.lib.fmm_plan_stats(pl, C.byref(F._Stats())))       # the lists are final
+        if op == "adjoint":
+            model.ok(model.call("evaluate", pl, s))
+        return pl
+
+    pl = plan()
+    before = live(model)
+    model.ok(model.call(op, pl, s))
+    kept = live(model) - before
+    for k in range(100):
+        pl = plan()
+        before = live(model)
+        model.lib.fmm_debug_fail_alloc(C.c_int64(k))
+        rc = model.call(op, pl, s)
+        model.lib.fmm_debug_fail_alloc(C.c_int64(-1))
+        if rc == 0:
+            break
+        assert rc == -2, k
+        model.ok(model.call(op, pl, s))
+        assert live(model) - before == kept, k
+    else:
+        pytest.fail("the call never succeeded")

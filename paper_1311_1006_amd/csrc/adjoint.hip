@@ -300,16 +300,18 @@ static void adjoint_near(Plan& pl, const double* gb_tree, bool der, hipStream_t 
     int nadj = 0;
     for (auto& c : ex.adj_class) nadj = std::max<int>(nadj, (int)(c.off + c.n));
     Plan::Balance& ba = pl.bal_adj;
-    if (ba.cls.empty()) {
+    if (!ba.made) {
         if (pl.split_p2p) {
             balance_launch(ba, items, nadj, ex.adj_class, pl.s_cnt.p, sc.d_box_count.p, s);
             FMM_HIP(hipStreamSynchronize(s));
             balance_finish(ba, nadj, 6, s);
         } else {
+            ba.cls.clear();
             for (auto& c : ex.adj_class) ba.cls.push_back(c.off);
             ba.cls.push_back(nadj);
             ba.total = nadj;
         }
+        ba.made = true;
     }
     for (size_t ci = 0; ci < ex.adj_class.size(); ++ci) {
         const P2PClass& c = ex.adj_class[ci];

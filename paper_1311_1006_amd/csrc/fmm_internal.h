@@ -320,6 +320,7 @@ struct Plan {
         DBuf<int64_t> d_base;      // class starts in the item array
         std::vector<int64_t> h_base;
         int64_t total = 0;
+        bool made = false;         // complete (the adjoint's are made by its first call)
         int32_t h32 = 0;           // host copy of a device total
     } bal, bal_adj, bal_m2l;
     DBuf<char> mpole, local;       // [nbox][coef_ld(p)] complex coefficients (T)

@@ -452,7 +452,8 @@ const char* fmm_last_error(void);
  * plans, schedules and evaluations; blocks the library keeps cached for
  * reuse are not counted, so a sequence of calls whose handles are all
  * destroyed returns n to its value before the sequence (schedules and
- * launch tables cached per tree layout aside).  FMM_EINVAL if live is
+ * launch tables cached per tree layout, and one block of constant tables per
+ * GPU, aside).  FMM_EINVAL if live is
  * NULL. */
 int fmm_debug_fail_alloc(int64_t after);
 int fmm_debug_live_blocks(int64_t* live);

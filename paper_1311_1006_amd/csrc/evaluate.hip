@@ -156,19 +156,13 @@ static const double* constant_tables(int device, hipStream_t s)
         fact[kMaxP + k] = (double)(1.0L / f);
     }
     log_table(fact + 2 * kMaxP);
-    void* p = nullptr;
-    if (hipMalloc(&p, h.size() * sizeof(double)) != hipSuccess) {
-        (void)hipGetLastError();
-        throw Error(FMM_ENOMEM, "device allocation of the constant tables failed");
-    }
-    try {
-        FMM_HIP(hipMemcpyAsync(p, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, s));
-        FMM_HIP(hipStreamSynchronize(s));
-    } catch (...) {
-        (void)hipFree(p);
-        throw;
-    }
-    return blocks[device] = static_cast<double*>(p);
+    DBuf<double> block;
+    block.alloc(h.size(), s);
+    FMM_HIP(hipMemcpyAsync(block.p, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, s));
+    FMM_HIP(hipStreamSynchronize(s));
+    const double* p = blocks[device] = block.p;
+    block.p = nullptr;          // kept
+    return p;
 }
 
 void prepare_plan_host(Plan& pl, PlanExtra& ex, hipStream_t s)

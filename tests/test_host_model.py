@@ -161,3 +161,45 @@ def test_call_after_a_failed_allocation_has_its_buffers(model, op, flag):
         assert live(model) - before == kept, k
     else:
         pytest.fail("the call never succeeded")
+
+
+def fresh_models(library, tmp_path, name="fresh"):
+    """(k, a copy of the library that has done nothing yet), k = 0, 1, ..."""
+    for k in range(200):
+        so = str(tmp_path / ("%s%d.so" % (name, k)))
+        shutil.copy(library, so)
+        yield k, Model(so)
+    pytest.fail("the sequence never ran out of allocations")
+
+
+def test_first_plan_of_a_process_is_retried_when_memory_is_short(library, tmp_path):
+    # every hipMalloc of the sequence fails once (the tables that depend on
+    # nothing are made here): the library gives its cached blocks back and tries again
+    for k, m in fresh_models(library, tmp_path):
+        s = m.stream()
+        m.lib.model_fail_malloc(k)
+        m.ok(m.call("evaluate", m.plan(m.tree(5000, 5, s), s), s))
+        if m.lib.model_mallocs() <= k:
+            break
+
+
+def test_failed_allocations_reach_the_constant_tables(library, tmp_path):
+    def failures(models):
+        for k, m in models:
+            s, off, tree, pl = m.stream(), (C.c_int64 * 2)(0, 5000), C.c_void_p(), C.c_void_p()
+            m.lib.fmm_debug_fail_alloc(C.c_int64(k))
+            rc = m.lib.fmm_build_tree(m.buf, off, 1, C.byref(C.c_int(5)), s, C.byref(tree))
+            if rc == 0:
+                rc = m.lib.fmm_plan(tree, 12, C.c_double(0.5), 0, None, s, C.byref(pl))
+            if rc == 0:
+                return k
+            assert rc == -2, k
+
+    def warm():                  # another layout has been used before
+        for k, m in fresh_models(library, tmp_path, "warm"):
+            s = m.stream()
+            m.lib.fmm_plan_destroy(m.plan(m.tree(300, 3, s), s))
+            yield k, m
+
+    # the first plan of a process makes one block more: the tables
+    assert failures(fresh_models(library, tmp_path)) == failures(warm()) + 1

@@ -411,6 +411,7 @@ void plan_finalize(Plan& P)
     try {
         build_lists_finish(P);
         plan_balance(P, P.list_stream);
+        plan_events(P);          // it is known now whether the lists are split
     } catch (const Error& e) {
         P.final_code = e.code;
         P.final_msg = e.what();

@@ -403,7 +403,9 @@ hipStream_t side_stream(int device, int which)
 static bool near_beside(const Plan& pl) { return pl.p > 32 || pl.split_p2p || pl.split_m2l; }
 
 // The second stream and its events, where they are used, made when the plan is
-// made (the evaluations then create nothing)
+// made (more than 32 terms) or its lists are final (split lists): the
+// evaluations then create nothing, in a capture least of all.  Evaluations at
+// many points make them in their first call.
 void second_stream(Plan& pl)
 {
     if (!pl.nstream) {
@@ -522,7 +524,6 @@ static void evaluate_any(Plan& pl, const double* m, double* phi, double* phi_nea
     // Phase timing keeps the phases one after another on `s`.
     if (lists_ev && tm.on) throw Error(FMM_EINVAL, "an evaluation ahead of its lists has no phase timing");
     const bool beside = !tm.on && near_beside(pl);
-    if (beside) plan_events(pl);
     tm.mark();
     const bool up = pl.upward_done && !tm.on;   // gather and upward pass enqueued by evaluate_upward
     pl.upward_done = false;

@@ -203,3 +203,26 @@ def test_failed_allocations_reach_the_constant_tables(library, tmp_path):
 
     # the first plan of a process makes one block more: the tables
     assert failures(fresh_models(library, tmp_path)) == failures(warm()) + 1
+
+
+@pytest.mark.parametrize("p", [12, 40])
+@pytest.mark.parametrize("flag", [0, 4, 8, 12])
+def test_nothing_is_created_inside_a_capture(model, flag, p):
+    # the first use of a process is a graph plan, its lists split or not
+    s = model.stream()
+    model.lib.model_list_flag(C.c_longlong(flag))
+    pl = model.plan(model.tree(5000, 5, s), s, p=p, flags=F.FMM_FLAG_GRAPH)
+    model.ok(model.call("evaluate", pl, s))
+    assert model.lib.model_created_in_capture() == 0
+
+
+@pytest.mark.parametrize("flag", [0, 12])
+def test_fixed_memory_evaluation_creates_nothing(model, flag):
+    # under a caller's capture: the plan's lists final, nothing evaluated yet
+    s = model.stream()
+    model.lib.model_list_flag(C.c_longlong(flag))
+    pl = model.plan(model.tree(5000, 5, s), s)
+    model.ok(model.lib.fmm_plan_stats(pl, C.byref(F._Stats())))
+    model.lib.hipStreamBeginCapture(s, 0)
+    model.ok(model.call("static", pl, s))
+    assert model.lib.model_created_in_capture() == 0

@@ -17,6 +17,7 @@
 
 #include "fmm_internal.h"
 #include "kernels_common.h"
+#include "near_log.h"
 #include "plan_extra.h"
 
 namespace fmm {
@@ -155,7 +156,7 @@ static const double* constant_tables(int device, hipStream_t s)
         fact[k] = (double)f;
         fact[kMaxP + k] = (double)(1.0L / f);
     }
-    log_table(fact + 2 * kMaxP);
+    log_table(reinterpret_cast<double2*>(fact + 2 * kMaxP));
     DBuf<double> block;
     block.alloc(h.size(), s);
     FMM_HIP(hipMemcpyAsync(block.p, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, s));

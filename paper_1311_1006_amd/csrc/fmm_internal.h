@@ -89,12 +89,10 @@ struct Targets {
 // The near field over the chunks of one launch class (p2p.hip): the sources
 // are the points in tree order, positions X, Y and strengths M (FP64; the
 // mixed kernels round the strengths to FP32 as they stage them).  log_table
-// (device, 2 kLogTab values filled by log_table()) selects the logarithmic
+// (device: the table of near_log.h) selects the logarithmic
 // kernel; NULL: the harmonic one, smoothed with id2 > 0.  With `field` the
 // harmonic kernel and its derivative sum: four values per target in out and
 // partial instead of two.
-constexpr int kLogTab = 128;
-void log_table(double* tab);
 void launch_p2p(bool mixed, int tg, int sub, const void* items, int item_base, const int2* xitems, int nx,
                 const int32_t* icnt, const int32_t* ioff, double* partial, const int32_t* bstart,
                 const int32_t* bcount, const int32_t* s_beg, const int32_t* s_cnt, const int32_t* s_ids,

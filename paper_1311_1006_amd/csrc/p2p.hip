@@ -27,10 +27,10 @@
 //          with FP32 accumulation.
 #include <cfloat>
 #include <climits>
-#include <cmath>
 
 #include "fmm_internal.h"
 #include "kernels_common.h"
+#include "near_log.h"
 #include "p2p_common.h"
 
 namespace fmm {
@@ -116,35 +116,6 @@ __device__ __forceinline__ void pair32s(double xi, double yi, const Src32& s, fl
     ai = fmaf(b, y, ai);
 }
 
-// The logarithm of a positive normal number, for the FP64 logarithmic kernel.
-// x = 2^e m with m in [3/4, 3/2); the table (kLogTab entries, built by
-// log_table from the mathematics) holds for every seventh-bit interval of m a
-// reciprocal 1/c near its middle and log c, both exact for the two intervals
-// next to m = 1, so that nothing cancels where the logarithm is small.  Then
-// r = m / c - 1, |r| <= 2^-7, and log x = e log 2 + log c + log(1 + r) with the
-// Taylor series to r^8 (the next term is below 1.2e-20).  Error against 64-bit
-// references: below one unit in the last place of the largest of the three
-// terms, as the library's.  About 17 instructions and an LDS read per value,
-// where the library's function took four times as many: the near field of
-// N = 5e5, L = 8 (30 points per leaf) beside the far field went from 653 to 274
-// us, the whole evaluation from 787 to 440 us by this alone.
-__device__ __forceinline__ double log_pos(double x, const double2* tab)
-{
-    const int hi = __double2hiint(x), t = hi + 0x00080000;   // half: the exponent of m >= 3/2 moves up
-    const int e = (t >> 20) - 1023;
-    const double2 c = tab[(t >> 13) & (kLogTab - 1)];
-    const double m = __hiloint2double(hi - (e << 20), __double2loint(x));
-    const double r = fma(m, c.x, -1.0);
-    double p = fma(r, -1.0 / 8, 1.0 / 7);
-    p = fma(r, p, -1.0 / 6);
-    p = fma(r, p, 1.0 / 5);
-    p = fma(r, p, -1.0 / 4);
-    p = fma(r, p, 1.0 / 3);
-    p = fma(r, p, -1.0 / 2);
-    const double v = fma(r * r, p, r) + fma((double)e, 0x1.62e42fefa39efp-1, c.y);   // log 2
-    return hi < 0x7ff00000 ? v : x;                          // x overflowed: infinite
-}
-
 // The logarithmic kernel: log|z_i - z_j| times the (real) strength.
 // Coincident positions are left out, as in the other kernels; FLT_MIN
 // (DBL_MIN) in r^2 only keeps the logarithm finite there.  The second sum
@@ -161,7 +132,7 @@ __device__ __forceinline__ void pair64l(double xi, double yi, const Src64& s, co
 {
     const double dx = xi - s.x, dy = yi - s.y;
     const double r2 = fma(dx, dx, fma(dy, dy, DBL_MIN));
-    const double lg = (dx != 0.0 || dy != 0.0) ? 0.5 * log_pos(r2, tab) : 0.0;
+    const double lg = (dx != 0.0 || dy != 0.0) ? half_log(r2, tab) : 0.0;
     ar = fma(s.mr, lg, ar);
 }
 
@@ -545,20 +516,6 @@ static void launch_one(bool mixed, const P2PItem* items, int item_base, const in
     else if (id2 > 0.0) launch_kern<TG, SUB, kKernSmooth>(ARGS);
     else launch_kern<TG, SUB, kKernPlain>(ARGS);
 #undef ARGS
-}
-
-// the table of log_pos: interval t of the top seven bits of the mantissa of
-// x, half an exponent up: t >= 64 holds m in [1 + (t-64)/128, + 1/128), t < 64
-// m in [3/4 + t/256, + 1/256)
-void log_table(double* tab)
-{
-    for (int t = 0; t < kLogTab; ++t) {
-        const long double mid = t >= kLogTab / 2 ? 1.0L + (t - kLogTab / 2 + 0.5L) / 128 : 0.75L + (t + 0.5L) / 256;
-        const bool one = t == kLogTab / 2 - 1 || t == kLogTab / 2;    // next to m = 1
-        const double inv = one ? 1.0 : (double)(1.0L / mid);
-        tab[2 * t] = inv;
-        tab[2 * t + 1] = one ? 0.0 : (double)-std::log((long double)inv);
-    }
 }
 
 // one launch per (targets per subgroup, subgroups) class over its chunks

@@ -699,10 +699,15 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     // (six wavefronts per SIMD for the mixed kernel without the derivative,
     // four for the others)
     const unsigned gd = (unsigned)std::min<int64_t>((M + 3) / 4, mixed && !der ? 1536 : 1024);
-    // few points with the derivative: every near field a descent, one launch
-    // less (descents / own kernel, us: N = M = 1000 45 / 62, 8000 77 / 88,
-    // 16,000 99 / 94, N = 64,000 with M = 8000 108 / 133, FP64)
-    const bool all_descend = der && M <= kDescendPoints;
+    // with the derivative every near field is a descent where the points are few,
+    // or few per leaf: the own kernel's wavefront takes the points of one leaf
+    // and sums three boxes in turn, whether it holds one point or sixteen.
+    // Descents / own kernel, us, by points per leaf, FP64 (mixed):
+    //   N = 1e5, 7 levels  2: 107 / 132 (99 / 117)   3: 112 / 134 (107 / 119)   8: 155 / 145 (145 / 128)
+    //   N = 1e6, 8 levels  1: 216 / 435 (199 / 379)  3: 383 / 462 (355 / 405)   5: 537 / 460 (492 / 400)
+    //   N = 1e6, 9 levels  1: 407 / 656 (337 / 470)  2: 563 / 695 (547 / 504)   3: 720 / 737 (760 / 538)
+    // and on small trees N = 30,000 with M = 8192, 8 per leaf, 84 / 100 (80 / 90).
+    const bool all_descend = der && M <= std::max<int64_t>(kDescendPoints, (int64_t)nleaf * (mixed ? 2 : 3));
     const int32_t* nq_dev = off.p + (all_descend ? nb : lb);
 #define DESC_ARGS                                                                                             \
     (const double2*)y, order.p, box.p, nq_dev, L, sc.d_box_level.p, t.geom.p, sc.d_box_start.p,               \

@@ -54,7 +54,13 @@ extern "C" {
 hipStream_t model_stream() { return (hipStream_t)next_handle++; }
 void model_clear() { launches.clear(); }
 long model_now(hipStream_t s) { return streams[s][s]; }
-int model_launches() { return (int)launches.size(); }
+// the launches since model_clear() of kernels whose (mangled) name holds `part`
+int model_launches(const char* part)
+{
+    int n = 0;
+    for (auto& l : launches) n += l.name.find(part) != std::string::npos;
+    return n;
+}
 // the launches since model_clear() that do not come after operation `at` of stream s; the first one's name
 int model_before(hipStream_t s, long at, char* name, int len)
 {

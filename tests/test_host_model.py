@@ -117,7 +117,7 @@ def test_first_call_on_another_stream_follows_the_plan(model, op, flag):
     at = model.lib.model_now(a)
     model.lib.model_clear()
     model.ok(model.call(op, pl, b))
-    assert model.lib.model_launches() > 0
+    assert model.lib.model_launches(b"") > 0
     assert model.before(a, at) == (0, "")
     # and the caller's stream comes after everything that the call launched
     assert model.lib.model_not_joined(b) == 0
@@ -226,3 +226,15 @@ def test_fixed_memory_evaluation_creates_nothing(model, flag):
     model.lib.hipStreamBeginCapture(s, 0)
     model.ok(model.call("static", pl, s))
     assert model.lib.model_created_in_capture() == 0
+
+
+@pytest.mark.parametrize("prec,per_leaf", [(0, 3), (1, 2)])
+@pytest.mark.parametrize("n,L", [(300, 3), (70000, 8)])
+def test_points_with_the_derivative_few_per_leaf_are_descended(model, n, L, prec, per_leaf):
+    s = model.stream()
+    pl = model.plan(model.tree(n, L, s), s, prec=prec)
+    line = max(8192, per_leaf * 4 ** (L - 1))
+    for M, own in ((1, 0), (line, 0), (line + 1, 1)):
+        model.lib.model_clear()
+        model.ok(model.call("%d:field" % M, pl, s))
+        assert model.lib.model_launches(b"k_pts_near_der") == own, M

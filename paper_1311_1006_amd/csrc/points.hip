@@ -62,6 +62,7 @@ void far_field_down(Plan& pl, hipStream_t s);
 // each, for the (4 targets per lane, 4 subgroups) shape
 constexpr int kPtsItem = 16;
 constexpr int64_t kTwoStreamPoints = 50000, kDescendPoints = 8192;   // see evaluate_points_device
+constexpr int kLongList = 512;      // of split layouts: longer strong lists are descended (likewise)
 struct PtsItem {
     int32_t leaf, t0, tn, pad;
 };
@@ -395,13 +396,14 @@ struct Visit {
 // sums start at zero (boxes 64 entries apart share one: the order of the
 // descents' lanes) and are added in FP64.  N = M = 1e5, L = 7: 212 us as descents
 // of a wavefront per point, 12 of its 64 lanes with a box to sum, now 57 us.
-template <class T>
+template <class T, bool PART>
 __global__ void __launch_bounds__(256)
 k_pts_near_der(const PtsItem* __restrict__ items, int nx, const int32_t* __restrict__ off,
                const double* __restrict__ rx, const double* __restrict__ ry, const int32_t* __restrict__ bstart,
                const int32_t* __restrict__ bcount, const int32_t* __restrict__ s_beg,
                const int32_t* __restrict__ s_cnt, const int32_t* __restrict__ s_ids, const double* __restrict__ X,
-               const double* __restrict__ Y, const double2* __restrict__ mt, double2* tnear, double2* tdnear)
+               const double* __restrict__ Y, const double2* __restrict__ mt, int longest, double2* tnear,
+               double2* tdnear)
 {
     const int i = __builtin_amdgcn_readfirstlane(xcd_block() * 4 + (threadIdx.x >> 6));
     if (i >= nx) return;
@@ -411,6 +413,7 @@ k_pts_near_der(const PtsItem* __restrict__ items, int nx, const int32_t* __restr
     const int64_t q = (int64_t)off[it.leaf] + it.t0 + (t < it.tn ? t : 0);
     const double yx = rx[q], yy = ry[q];
     const int e0 = s_beg[it.leaf], n = s_cnt[it.leaf];
+    if (PART && n > longest) return;              // its points are descended
     double2 phi = make_double2(0.0, 0.0), dphi = make_double2(0.0, 0.0);
     // the first 64 boxes' ranges, a box per lane, loaded together
     const int lane = threadIdx.x & 63;
@@ -453,7 +456,8 @@ k_pts_near_der(const PtsItem* __restrict__ items, int nx, const int32_t* __restr
 
 constexpr int kFront = 512;   // frontier boxes per wavefront (LDS)
 
-// The near field of the points at box-order positions q < nq by descents of
+// The near field of the points at box-order positions q < nq (PART: those in leaves
+// whose strong list has at most `skip` boxes left out) by descents of
 // their box's strong list: one wavefront per point, breadth first, lanes over
 // the frontier (the first frontier is the strong list itself, read from the
 // pool; later ones are in LDS).  A lane's box adds its expansion or its
@@ -464,10 +468,10 @@ constexpr int kFront = 512;   // frontier boxes per wavefront (LDS)
 // dependent loads, so wavefronts in flight set its rate: the mixed kernel
 // without the derivative is held to 80 registers (six wavefronts per SIMD,
 // no spills); the others need 97-120 and would spill below that.
-template <class T, bool DER>
+template <class T, bool DER, bool PART>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && !DER ? 6 : 1)))
 k_pts_descend(const double2* __restrict__ y, const int32_t* __restrict__ order, const int32_t* __restrict__ box,
-              const int32_t* __restrict__ nq_dev, int L, const int8_t* __restrict__ level,
+              const int32_t* __restrict__ nq_dev, int skip, int L, const int8_t* __restrict__ level,
               const double* __restrict__ geom, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
               const int32_t* __restrict__ s_beg, const int32_t* __restrict__ s_cnt, const int32_t* __restrict__ s_ids,
               const T* __restrict__ mpole, int p, double theta, const double* __restrict__ X,
@@ -478,7 +482,7 @@ k_pts_descend(const double2* __restrict__ y, const int32_t* __restrict__ order, 
     const unsigned long long below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
     const int nq = *nq_dev;
     const int nw = (int)gridDim.x * 4;
-    for (int q = (int)blockIdx.x * 4 + w; q < nq; q += nw) {      // uniform in the wavefront
+    auto descend = [&](int q) {      // uniform in the wavefront
         const int32_t i = order[q];
         Visit<T, DER> vis;
         vis.y = y[i];
@@ -545,6 +549,22 @@ k_pts_descend(const double2* __restrict__ y, const int32_t* __restrict__ order, 
             if (DER) tdnear[q] = dphi;
         }
         wave_sync();
+    };
+    // a wavefront's points are every nw-th
+    if constexpr (!PART) {
+        for (int q = (int)blockIdx.x * 4 + w; q < nq; q += nw) descend(q);
+    } else {
+        // 64 of them are looked at together
+        for (int64_t q0 = (int)blockIdx.x * 4 + w; q0 < nq; q0 += (int64_t)64 * nw) {
+            const int64_t ql = q0 + (int64_t)lane * nw;
+            bool mine = ql < nq;
+            if (mine) {
+                const int32_t B = box[order[ql]];
+                mine = level[B] != L - 1 || s_cnt[B] > skip;
+            }
+            for (unsigned long long todo = __ballot(mine); todo; todo &= todo - 1)
+                descend((int)(q0 + (int64_t)__builtin_ctzll(todo) * nw));
+        }
     }
 }
 
@@ -708,9 +728,19 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     //   N = 1e6, 9 levels  1: 407 / 656 (337 / 470)  2: 563 / 695 (547 / 504)   3: 720 / 737 (760 / 538)
     // and on small trees N = 30,000 with M = 8192, 8 per leaf, 84 / 100 (80 / 90).
     const bool all_descend = der && M <= std::max<int64_t>(kDescendPoints, (int64_t)nleaf * (mixed ? 2 : 3));
-    const int32_t* nq_dev = off.p + (all_descend ? nb : lb);
+    // Where some strong list is split into work chunks, the points of leaves with
+    // more than kLongList boxes in theirs are descended too: the own kernel walks
+    // every fourth box in turn, a descent every 64th.  100,000 points beside the
+    // sources, all descents / this / own kernel alone, us: 300,000 sources of
+    // which 5 lie far off (one list of 16,384 boxes) 2500 / 2440 / 10,760, 300,000
+    // in clusters 3320 / 3040 / 4720, 30,000 in clusters (lists of up to 244 boxes)
+    // 860 / 790 / 790, 100,000 in clusters 1270 / 1310 / 1530; lines at 64 and 256
+    // boxes lie between.
+    const bool part_descend = der && !all_descend && pl.split_p2p;
+    const int32_t* nq_dev = off.p + (all_descend || part_descend ? nb : lb);
+    const int skip = part_descend ? kLongList : 0, longest = part_descend ? kLongList : INT32_MAX;
 #define DESC_ARGS                                                                                             \
-    (const double2*)y, order.p, box.p, nq_dev, L, sc.d_box_level.p, t.geom.p, sc.d_box_start.p,               \
+    (const double2*)y, order.p, box.p, nq_dev, skip, L, sc.d_box_level.p, t.geom.p, sc.d_box_start.p,         \
         sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p
 #define FAR_ARGS (const double2*)y, M, order.p, box.p, sc.d_box_level.p, t.geom.p
 #define SRC_ARGS t.x.p, t.y.p, (const double2*)pl.mtree.p
@@ -720,13 +750,19 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
         using T = decltype(tag);
         constexpr bool DER = decltype(dtag)::value;
         const T* mp = (const T*)pl.mpole.p;
-        k_pts_descend<T, DER><<<gd, 256, 0, ps>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, td);
+        if (DER && part_descend)
+            k_pts_descend<T, DER, DER><<<gd, 256, 0, ps>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, td);
+        else
+            k_pts_descend<T, DER, false><<<gd, 256, 0, ps>>>(DESC_ARGS, mp, pl.p, theta_pt, SRC_ARGS, tn, td);
         // the near field of the points in leaves, over the sources of the
         // leaf's strong list
         if constexpr (DER) {
-            if (!all_descend) k_pts_near_der<T><<<(unsigned)((nx + 3) / 4), 256, 0, s>>>(
-                items.p, (int)nx, off.p, rx.p, ry.p, sc.d_box_start.p, sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p,
-                pl.s_ids.p, SRC_ARGS, tn, td);
+            if (!all_descend) {
+                auto near_der = part_descend ? k_pts_near_der<T, true> : k_pts_near_der<T, false>;
+                near_der<<<(unsigned)((nx + 3) / 4), 256, 0, s>>>(
+                    items.p, (int)nx, off.p, rx.p, ry.p, sc.d_box_start.p, sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p,
+                    pl.s_ids.p, SRC_ARGS, longest, tn, td);
+            }
         } else {
             Targets tgt;
             tgt.x = rx.p;

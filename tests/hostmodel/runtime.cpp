@@ -36,6 +36,8 @@ static long next_handle = 0x1000;
 static int capturing = 0, in_capture = 0, mallocs = 0;
 static int fail_malloc = -1;          // hipMalloc calls left before one that fails
 static long long list_flag = 0;       // what an 8-byte copy to the host delivers
+static std::string watched;           // model_watch: the kernel, the index of an int argument, its last value
+static int watched_arg, watched_value;
 static dim3 cfg_grid, cfg_block;
 static size_t cfg_shared;
 static hipStream_t cfg_stream;
@@ -86,6 +88,12 @@ int model_not_joined(hipStream_t s)
             }
     return n;
 }
+void model_watch(const char* part, int arg)
+{
+    watched = part;
+    watched_arg = arg;
+}
+int model_watched() { return watched_value; }
 int model_created_in_capture() { return in_capture; }
 int model_mallocs() { return mallocs; }
 void model_fail_malloc(int after) { fail_malloc = after; }
@@ -186,8 +194,10 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* sh, hipStream_t* 
     *s = cfg_stream;
     return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t, hipStream_t s)
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void** args, size_t, hipStream_t s)
 {
+    if (!watched.empty() && names()[f].find(watched) != std::string::npos)
+        watched_value = *static_cast<int*>(args[watched_arg]);
     launches.push_back(Launch{names()[f], step(s)});
     return hipSuccess;
 }

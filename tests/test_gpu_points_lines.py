@@ -32,3 +32,32 @@ def test_points_at_the_line(orc, prec, bar, n, L, M):
     sub = np.arange(0, M, M // 500)
     assert e2(phi[sub], orc.direct_points(z, m, y[sub])) <= max(bar, 1e-7)
     assert e2(dphi[sub], orc.direct_deriv_points(z, m, y[sub])) <= max(bar, 1e-7)
+
+
+@pytest.mark.parametrize("prec,bar", [("fp64", 1e-12), ("mixed", 1e-6)])
+@pytest.mark.parametrize("n,L", [(20000, 6), (70001, 7)])
+def test_points_in_leaves_with_long_lists(orc, prec, bar, n, L):
+    # three sources far off: their leaf is strong with every leaf of the level (more
+    # than 512 boxes, so that its points are descended), the others' lists are short
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a HIP device"
+    import paper_1311_1006_amd as F
+    rng = np.random.default_rng(n)
+    z, m, _ = W.uniform(n, seed=n)
+    far = rng.integers(0, n, 3)
+    z[far] = 300.0 * np.exp(2j * np.pi * rng.random(3))
+    y = W.uniform(20001, seed=n + 1)[0]
+    y[::9] = z[rng.integers(0, n, y[::9].size)] + 1e-4
+    y[:30] = z[far][np.arange(30) % 3] + 0.1 * rng.random(30)
+    pl = F.plan(F.build_tree(dev(z), L), 30, 0.5, prec)
+    off, _ = pl.download_list(0, L - 1, 0)
+    assert np.diff(off).max() > 512
+    md = dev(m)
+    phi, dphi = (host(x) for x in F.evaluate_points(pl, md, dev(y), field=True))
+    part = slice(0, 5000)
+    a, b = (host(x) for x in F.evaluate_points(pl, md, dev(y[part]), field=True))
+    assert e2(phi[part], a) <= bar and e2(dphi[part], b) <= bar
+    sub = np.concatenate([np.arange(30), np.arange(30, y.size, 50)])
+    assert e2(phi[sub], orc.direct_points(z, m, y[sub])) <= max(bar, 1e-7)
+    assert e2(dphi[sub], orc.direct_deriv_points(z, m, y[sub])) <= max(bar, 1e-7)
+    assert e2(phi[:30], orc.direct_points(z, m, y[:30])) <= 10 * max(bar, 1e-7)

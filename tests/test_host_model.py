@@ -238,3 +238,16 @@ def test_points_with_the_derivative_few_per_leaf_are_descended(model, n, L, prec
         model.lib.model_clear()
         model.ok(model.call("%d:field" % M, pl, s))
         assert model.lib.model_launches(b"k_pts_near_der") == own, M
+
+
+@pytest.mark.parametrize("flag,longest", [(0, 2 ** 31 - 1), (4, 512)])
+def test_long_lists_of_points_with_the_derivative_are_descended(model, flag, longest):
+    # split strong lists: the own kernel (its 14th argument) leaves out what the
+    # descents (their 5th) take, leaves with more than 512 boxes in their list
+    s = model.stream()
+    model.lib.model_list_flag(C.c_longlong(flag))
+    pl = model.plan(model.tree(5000, 5, s), s)
+    for part, arg, value in ((b"k_pts_near_der", 13, longest), (b"k_pts_descend", 4, 512 if flag else 0)):
+        model.lib.model_watch(part, arg)
+        model.ok(model.call("20000:field", pl, s))
+        assert model.lib.model_watched() == value, part

@@ -715,10 +715,14 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     far_field_down(pl, s);
     if (two) FMM_HIP(hipStreamWaitEvent(s, pl.ev_join, 0));
     // descents: the points that stopped above the leaves (box-order positions
-    // before the first leaf).  Workgroups: those the occupancy holds at once
-    // (six wavefronts per SIMD for the mixed kernel without the derivative,
-    // four for the others)
-    const unsigned gd = (unsigned)std::min<int64_t>((M + 3) / 4, mixed && !der ? 1536 : 1024);
+    // before the first leaf).  Workgroups: four times those the occupancy holds at
+    // once (six wavefronts per SIMD for the mixed kernel without the derivative,
+    // four for the others), so that the last ones even out what the near field
+    // beside them and long lists make uneven (once / four times, us, FP64 phi and
+    // with the derivative: 100,000 points beside 3000 sources on a line, nearly
+    // all descended 1237 / 1149 and 1172 / 1167; beside 300,000 clustered sources
+    // 2057 / 2048 and 1845 / 1769; 1e6 beside 1e6 846 / 833 and 1298 / 1300)
+    const unsigned gd = (unsigned)std::min<int64_t>((M + 3) / 4, 4 * (mixed && !der ? 1536 : 1024));
     // with the derivative every near field is a descent where the points are few,
     // or few per leaf: the own kernel's wavefront takes the points of one leaf
     // and sums three boxes in turn, whether it holds one point or sixteen.

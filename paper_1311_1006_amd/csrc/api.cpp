@@ -370,6 +370,7 @@ int fmm_plan(fmm_tree_t t, int p, double theta, int precision, const fmm_tuning*
         pl.theta = theta;
         pl.precision = precision;
         pl.tune = tn;
+        pl.stream = s;
         {
             TreeSchedule& sc = *t->t.sched;
             int key = (precision * 64 + tn.p2p_split) * 32 + tn.p2p_targets;   // the launch classes
@@ -432,9 +433,10 @@ void plan_join(Plan& P, hipStream_t s)
 
 // order `s` after the tree's build and the plan's buffers, for work that needs
 // no lists: of a plan whose lists are still in flight, without waiting for them
+// (the plan's own stream is in that order by itself)
 void plan_start(Plan& P, hipStream_t s)
 {
-    FMM_HIP(hipStreamWaitEvent(s, P.ev_plan_done ? P.ev_plan_done : P.ev_tree, 0));
+    if (s != P.stream) FMM_HIP(hipStreamWaitEvent(s, P.ev_tree, 0));
 }
 }  // namespace fmm
 

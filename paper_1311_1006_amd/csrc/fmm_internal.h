@@ -282,6 +282,7 @@ struct Plan {
     int64_t n_strong = 0, n_weak = 0;
     int64_t n_p2p_pairs = 0;
     bool totals_known = false;     // n_strong, n_weak, n_p2p_pairs summed
+    hipStream_t stream = nullptr;  // fmm_plan's
     hipStream_t list_stream = nullptr;
     // list build enqueued by fmm_plan and finished by the first call that
     // needs the lists (see plan_finalize)

@@ -660,7 +660,7 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     // the overlap hides below (one stream / two, N = M: 30,000 91 / 123 us
     // mixed, 118 / 126 us FP64 with the derivative; 100,000 153 / 127 and
     // 195 / 163 us FP64)
-    const bool two = M >= kTwoStreamPoints, fresh = !pl.finalized;
+    const bool two = M >= kTwoStreamPoints;
     plan_start(pl, s);
     hipStream_t ps = s;
     if (two) {
@@ -704,10 +704,8 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     check_launch("point order");
     if (two) FMM_HIP(hipEventRecord(pl.ev_join, ps));     // the items, for the near field
     // the descents read the multipoles and the lists: after the upward pass
-    if (fresh) {
-        plan_finalize(pl);
-        plan_join(pl, s);
-    }
+    plan_finalize(pl);
+    plan_join(pl, s);
     if (two) {
         FMM_HIP(hipEventRecord(pl.ev_fork, s));
         FMM_HIP(hipStreamWaitEvent(ps, pl.ev_fork, 0));

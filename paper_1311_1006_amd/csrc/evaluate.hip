@@ -55,6 +55,8 @@ void launch_down_subtree(const SubPlan& sp, bool staged, const int32_t* bstart, 
                          const int32_t* perm, double* phi, double* phi_near, double* phi_far, double* dphi,
                          const long long* guard, const double* fact, hipStream_t s);
 
+void launch_gather(int64_t n, const int32_t* perm, const double* m, double* mtree, hipStream_t s);
+
 struct P2PItemH {
     int32_t leaf, t0, tn, pad;
 };
@@ -258,15 +260,16 @@ static bool staged_down(const Plan& pl, const PlanExtra& ex, bool all)
 // The upward pass of the strengths m (input order), with their gather into tree
 // order, into the multipoles mp; or, without m, of the strengths mt (tree
 // order).  `after_gather` (optional) is recorded once the strengths are in
-// tree order: work that needs only them (the near field) may start.
+// tree order: work that needs only them (the near field) may start.  `keep`
+// false: the strengths in tree order are written by a gather of their own.
 template <class T>
 static void run_up(Plan& pl, const double* m, const double* mt, void* mp, hipStream_t s,
-                   hipEvent_t after_gather = nullptr)
+                   hipEvent_t after_gather = nullptr, bool keep = true)
 {
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
     PlanExtra& ex = *extra(pl);
-    const GatherOut go{t.perm.p, (const double2*)m, (double2*)pl.mtree.p};
+    const GatherOut go{t.perm.p, (const double2*)m, keep ? (double2*)pl.mtree.p : nullptr};
     launch_up_leaves<T>(ex.sub, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, mt, pl.p, mp, ex.fact.p,
                         m ? &go : nullptr, s);
     launch_p2m<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max, t.geom.p,
@@ -400,8 +403,26 @@ hipStream_t side_stream(int device, int which)
 // 249 against 252.  Two streams pay where one of them leaves part of the chip
 // idle: lists split into work chunks (a tail of long items: batch of 128 problems
 // 1252 us against 1325, clustered step 1512-1551 against 1533), and more than 32
-// terms (few wavefronts of many registers: N = 1e5, p = 39 140 us against 150).
-static bool near_beside(const Plan& pl) { return pl.p > 32 || pl.split_p2p || pl.split_m2l; }
+// terms (few wavefronts of many registers: N = 1e5, p = 39 140 us against 150);
+// not where the problem is so small that the streams' overhead is most of the time
+// (one stream / two, FP64: split lists N = 3000 on 3 levels 64 / 74-82, N = 30,000
+// on 5 levels 82 / 87; p = 39 N = 300 31 / 61, N = 1000 49-52 / 56-62, N = 3000
+// on 3 levels 89 / 82).
+static bool near_beside(const Plan& pl)
+{
+    const int64_t n = pl.tree->sched->n;
+    return pl.p > 32 ? n > 2048 : n > 16384 && (pl.split_p2p || pl.split_m2l);
+}
+
+// Whether the second stream gathers the strengths itself, so that the near field
+// does not wait for P2M (which does the gather otherwise).  P2M takes the longer
+// the more points a leaf has and the more terms, while the extra gather reads every
+// strength twice: P2M's / its own, us: p = 39 FP64 N = 3000 on 3 levels (187
+// points per leaf) 98 / 82, N = 10,000 on 4 (156) 105 / 92, N = 10,000 on 5 (39) 72
+// / 68, N = 30,000 on 6 (29) 75 / 74, N = 1e5 on 7 (24) 139 / 144; p = 16 split lists
+// N = 1e5 on 5 (390) 374 / 349, 1e6 clustered on 9 (15) mixed 667 / 687, batch of
+// 128 problems (16) 1281 / 1334.
+constexpr int kGatherApart = 32;     // points per leaf
 
 // The second stream and its events, where they are used, made when the plan is
 // made (more than 32 terms) or its lists are final (split lists): the
@@ -529,20 +550,24 @@ static void evaluate_any(Plan& pl, const double* m, double* phi, double* phi_nea
     const bool up = pl.upward_done && !tm.on;   // gather and upward pass enqueued by evaluate_upward
     pl.upward_done = false;
     // on its own stream the near field forks as soon as the strengths are in
-    // tree order, beside the upper levels' M2M
+    // tree order, beside the upper levels' M2M, or gathers them itself
     const bool early_fork = beside && !up;
+    const TreeSchedule& sc = *pl.tree->sched;
+    const bool apart = early_fork && sc.n > kGatherApart * sc.nleaf;
+    if (apart) FMM_HIP(hipEventRecord(pl.ev_fork, s));
     if (!up) {
-        hipEvent_t ev = early_fork ? pl.ev_fork : nullptr;
-        if (mixed) run_up<float>(pl, m, nullptr, pl.mpole.p, s, ev);
-        else run_up<double>(pl, m, nullptr, pl.mpole.p, s, ev);
+        hipEvent_t ev = early_fork && !apart ? pl.ev_fork : nullptr;
+        if (mixed) run_up<float>(pl, m, nullptr, pl.mpole.p, s, ev, !apart);
+        else run_up<double>(pl, m, nullptr, pl.mpole.p, s, ev, !apart);
     }
     if (beside) {
         // it starts after everything enqueued on `s` so far: the gather (with
         // P2M), and the list and work-chunk kernels of the plan (which follow
         // the upward pass when evaluate_upward ran first); or after the gather
-        // (the event recorded there)
+        // (the event recorded there), or before it
         if (!early_fork) FMM_HIP(hipEventRecord(pl.ev_fork, s));
         FMM_HIP(hipStreamWaitEvent(pl.nstream, pl.ev_fork, 0));
+        if (apart) launch_gather(sc.n, pl.tree->perm.p, m, pl.mtree.p, pl.nstream);
         if (lists_ev) FMM_HIP(hipStreamWaitEvent(pl.nstream, lists_ev, 0));
         run_p2p(pl, ex, pl.nstream, guard, false, dphi != nullptr);
         FMM_HIP(hipEventRecord(pl.ev_join, pl.nstream));

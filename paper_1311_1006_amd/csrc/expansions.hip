@@ -72,10 +72,10 @@ k_p2m(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__
         const int i = st + j;
         double2 w, t;
         if constexpr (GATHER) {
-            // the gather's outputs for this point, as k_gather writes them
+            // the gather's output for this point, as k_gather writes it
             const double2 mm = go.m[go.perm[i]];
             const double x = X[i], y = Y[i];
-            go.mtree[i] = mm;
+            if (go.mtree) go.mtree[i] = mm;
             w = make_double2((x - cx) * inv, (y - cy) * inv);
             t = mm;
         } else {
@@ -194,9 +194,9 @@ void launch_p2m(const int32_t* leaves, int nleaf, const int32_t* bstart, const i
     const int PB = p <= 16 ? 16 : 32;
     const unsigned grid = (unsigned)((nleaf + 4 * (64 / G) - 1) / (4 * (64 / G)));
     // blocks of PB terms: the first one does the gather, the second (p > 32)
-    // reads the strengths it put into tree order
+    // reads the strengths it put into tree order, if it did
     for (int k0 = 0; k0 < p; k0 += PB) {
-        const bool gat = go && k0 == 0;
+        const bool gat = go && (k0 == 0 || !go->mtree);
         const double2* mtk = (const double2*)(k0 == 0 ? mt : (go ? (const double*)go->mtree : mt));
 #define P2M_CASE(G_, P_)                                                                                   \
     if (G == G_ && PB == P_) {                                                                            \

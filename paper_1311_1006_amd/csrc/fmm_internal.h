@@ -394,7 +394,7 @@ void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, do
 struct GatherOut {
     const int32_t* perm;     // tree position -> input index
     const double2* m;        // strengths, input order
-    double2* mtree;          // strengths, tree order
+    double2* mtree;          // strengths, tree order (NULL: somebody else writes them)
 };
 // the far-field chain of the strengths w (tree order, no gather) in the
 // adjoint's coefficient arrays, down to the leaves' local expansions

@@ -220,8 +220,11 @@ __device__ __forceinline__ void m2m_wave(int p, const double2 (*a)[P], const dou
 // leaf, a transposing butterfly), M2M into its 4 children (one wavefront each,
 // from the wavefront's own four leaves) and into R (wavefront 0).  N = 2e5,
 // L = 7, p = 16: 10 us (12.5 us with a binomial table); p = 39, N = 1e5: 14 us,
-// where two P2M and two M2M launches took 40 us.
-template <class T, int P, bool GATHER>
+// where two P2M and two M2M launches took 40 us.  GATHER: the strengths come in tree
+// order (None), or through the permutation, and are put into tree order here (Store)
+// or elsewhere (Read).
+constexpr int kGatherNone = 0, kGatherStore = 1, kGatherRead = 2;
+template <class T, int P, int GATHER>
 __global__ void __launch_bounds__(256)
 k_up_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __restrict__ bcount,
           const double* __restrict__ geom, const double* __restrict__ X, const double* __restrict__ Y,
@@ -255,10 +258,10 @@ k_up_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __res
     for (int j = sl; j < n; j += 16) {
         const int i = st + j;
         double2 z, t;
-        if constexpr (GATHER) {
+        if constexpr (GATHER != kGatherNone) {
             const double2 mm = go.m[go.perm[i]];
             const double x = X[i], y = Y[i];
-            go.mtree[i] = mm;
+            if constexpr (GATHER == kGatherStore) go.mtree[i] = mm;
             z = make_double2((x - gf.x) * inv, (y - gf.y) * inv);
             t = mm;
         } else {
@@ -730,12 +733,9 @@ void launch_up_leaves(const SubPlan& sp, const int32_t* bstart, const int32_t* b
     const SubWork w = sub_work(sp, sp.roots);
     const unsigned grid = (unsigned)sp.roots.n;
 #define UP_CASE(P_)                                                                                        \
-    if (go)                                                                                                \
-        k_up_leaf<T, P_, true><<<grid, 256, 0, s>>>(w, bstart, bcount, geom, X, Y, (const double2*)mt, p,  \
-                                                    (T*)mp, fact, gg);                                     \
-    else                                                                                                   \
-        k_up_leaf<T, P_, false><<<grid, 256, 0, s>>>(w, bstart, bcount, geom, X, Y, (const double2*)mt, p, \
-                                                     (T*)mp, fact, gg);
+    auto up = !go ? k_up_leaf<T, P_, kGatherNone>                                                          \
+                  : go->mtree ? k_up_leaf<T, P_, kGatherStore> : k_up_leaf<T, P_, kGatherRead>;            \
+    up<<<grid, 256, 0, s>>>(w, bstart, bcount, geom, X, Y, (const double2*)mt, p, (T*)mp, fact, gg);
     SUB_BY_ORDER(UP_CASE)
 #undef UP_CASE
     check_launch("upward leaves");

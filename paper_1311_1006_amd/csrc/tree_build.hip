@@ -47,6 +47,7 @@
 
 #include "fmm_internal.h"
 #include "kernels_common.h"
+#include "lds_bucket.h"
 
 // Box geometry, split axes and the theta-criterion must round every product
 // and sum on its own (no fused multiply-add), like a plain IEEE evaluation.
@@ -1262,9 +1263,9 @@ __device__ void lds_order(LdsUnion<PER>& U, const double* __restrict__ c, const 
     double fr[PER];   // the place inside the bucket, 0 .. 1
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-        const double v = fmin(fmax((cv[u] - lo) * scale, 0.0), (double)(NB - 1));
-        bk[u] = (int)v;
-        fr[u] = v - (double)bk[u];
+        const LdsPlace at = lds_place(cv[u], lo, scale, NB);
+        bk[u] = at.bucket;
+        fr[u] = at.place;
     }
     int mx;
     for (int level = 0;; ++level) {
@@ -1302,7 +1303,7 @@ __device__ void lds_order(LdsUnion<PER>& U, const double* __restrict__ c, const 
         for (int u = 0; u < PER; ++u) {
             if (tid + u * kLdsThreads < n) {
                 const int b0 = (int)U.b.cnt[bk[u]], b1 = bk[u] + 1 < NB ? (int)U.b.cnt[bk[u] + 1] : n;
-                bk[u] = b0 + min((int)(fr[u] * (double)(b1 - b0)), b1 - b0 - 1);
+                bk[u] = lds_finer(fr[u], b0, b1);
             }
         }
         __syncthreads();

@@ -36,7 +36,7 @@ void launch_l2p(const int32_t* leaves, int nleaf, const int32_t* bstart, const i
                 const double* nearf, const int32_t* perm, double* phi, double* phi_near, double* phi_far,
                 hipStream_t s, const long long* guard);
 template <class T>
-void launch_m2l(const int32_t*, int, const int2*, int, const int32_t*, const int32_t*, double*, bool,
+void launch_m2l(int, const int2*, int, const int32_t*, const int32_t*, double*, bool,
                 const int32_t*, const int32_t*, const int32_t*, const double*, const double*, int, const void*, void*,
                 hipStream_t, int, const long long*);
 
@@ -335,7 +335,7 @@ static void run_far_down(Plan& pl, PlanExtra& ex, const void* mp, void* loc, hip
     Tree& t = *pl.tree;
     TreeSchedule& sc = *t.sched;
     const Plan::Balance& b = pl.bal_m2l;
-    launch_m2l<T>(nullptr, (int)sc.nbox, b.xitems.p, (int)b.total, b.icnt.p, b.ioff.p, b.partial.p,
+    launch_m2l<T>((int)sc.nbox, b.xitems.p, (int)b.total, b.icnt.p, b.ioff.p, b.partial.p,
                   b.total > sc.nbox, pl.w_beg.p, pl.w_cnt.p, pl.w_ids.p, t.geom.p, ex.binom.p, pl.p, mp, loc, s,
                   pl.tune.m2l_batch, guard);
     tm.mark();

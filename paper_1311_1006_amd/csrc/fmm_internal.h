@@ -228,7 +228,6 @@ struct TreeSchedule {
     int64_t total_seg = 0, total_tile = 0, total_keys = 0;
     std::vector<SegInfo> segs;
     std::vector<TileInfo> tiles;
-    std::vector<int32_t> key_child_dummy;
     int lds_max = 0, lds_stages = 2 * kMaxLevels;   // most points, fewest splits of an in-LDS segment
     std::vector<LdsWork> lds;
     std::vector<GeomJob> geom;      // boxes whose geometry comes from global-stage keys

@@ -193,7 +193,7 @@ __device__ __forceinline__ PairGeo<double> make_geo(double, double ctx, double c
 
 template <class T, int PB, int KS, int G>
 __global__ void __launch_bounds__(256)
-k_m2l(const int32_t* __restrict__ boxes, const int2* __restrict__ xitems, int nx, const int32_t* __restrict__ icnt,
+k_m2l(const int2* __restrict__ xitems, int nx, const int32_t* __restrict__ icnt,
       const int32_t* __restrict__ ioff, double* __restrict__ partial, const int32_t* __restrict__ w_beg,
       const int32_t* __restrict__ w_cnt, const int32_t* __restrict__ w_ids, const double* __restrict__ geom,
       const double* __restrict__ binom, int p, const T* __restrict__ mp, T* loc,
@@ -217,7 +217,7 @@ k_m2l(const int32_t* __restrict__ boxes, const int2* __restrict__ xitems, int nx
     int g = 0, nch = 1, nw = 0, wb = 0;
     if (item_ok) {
         xe = xitems ? xitems[xi] : make_int2(xi, 0);
-        g = boxes ? boxes[xe.x] : xe.x;
+        g = xe.x;
         nch = icnt ? icnt[xe.x] : 1;
         const int nw_all = w_cnt[g], p0 = xe.y * kChunkPairs;
         nw = nch == 1 ? nw_all : min(kChunkPairs, nw_all - p0);   // pairs of this item
@@ -411,20 +411,20 @@ k_m2l(const int32_t* __restrict__ boxes, const int2* __restrict__ xitems, int nx
 }
 
 template <class T, int PB, int KS, int G>
-static void m2l_one(const int32_t* boxes, const int2* xitems, int nx, const int32_t* icnt, const int32_t* ioff,
+static void m2l_one(const int2* xitems, int nx, const int32_t* icnt, const int32_t* ioff,
                     double* partial, const int32_t* w_beg, const int32_t* w_cnt, const int32_t* w_ids,
                     const double* geom, const double* binom, int p, const void* mp, void* loc, hipStream_t s,
                     const long long* guard)
 {
     const int per_block = 4 * G;   // items per workgroup (4 wavefronts)
-    k_m2l<T, PB, KS, G><<<(nx + per_block - 1) / per_block, 256, 0, s>>>(boxes, xitems, nx, icnt, ioff, partial,
+    k_m2l<T, PB, KS, G><<<(nx + per_block - 1) / per_block, 256, 0, s>>>(xitems, nx, icnt, ioff, partial,
                                                                          w_beg, w_cnt, w_ids, geom, binom, p,
                                                                          (const T*)mp, (T*)loc, guard);
 }
 
 // the partial local expansions of split lists, added in chunk order
 template <class T>
-__global__ void k_m2l_combine(const int32_t* __restrict__ boxes, int n, const int32_t* __restrict__ icnt,
+__global__ void k_m2l_combine(int n, const int32_t* __restrict__ icnt,
                               const int32_t* __restrict__ ioff, const double* __restrict__ partial, int p, T* loc)
 {
     const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -456,14 +456,14 @@ __global__ void k_m2l_combine(const int32_t* __restrict__ boxes, int n, const in
         re += pr[k * step];
         im += pr[k * step + 1];
     }
-    T* dst = loc + 2 * ((int64_t)(boxes ? boxes[i] : i) * coef_ld<T>(p) + row);
+    T* dst = loc + 2 * ((int64_t)i * coef_ld<T>(p) + row);
     dst[0] = (T)re;
     dst[1] = (T)im;
 }
 
-// Every box of `boxes` (NULL: boxes 0 .. n-1, no lookup) gets its local
-// expansion written (zeros for a box without weak pairs).  xitems[0 .. nx): (box index, chunk); icnt/ioff per
-// box index; partial holds the chunks of split lists.  batch: pair slots of
+// Every box 0 .. n-1 gets its local expansion written (zeros for a box without
+// weak pairs).  xitems[0 .. nx): (box, chunk); icnt/ioff per box; partial holds
+// the chunks of split lists.  batch: pair slots of
 // one item in each 16-pair MFMA block: 16 (one item per wavefront), 8 (two)
 // or 4 (four items share a wavefront); 0 = automatic (4, the fastest in both
 // precisions on the uniform million-point case: mixed 81 us against 93 us
@@ -475,14 +475,14 @@ __global__ void k_m2l_combine(const int32_t* __restrict__ boxes, int n, const in
 // choice depends on the order and the precision alone, so that a problem's
 // sums are the same in a batch as alone.
 template <class T>
-void launch_m2l(const int32_t* boxes, int n, const int2* xitems, int nx, const int32_t* icnt, const int32_t* ioff,
+void launch_m2l(int n, const int2* xitems, int nx, const int32_t* icnt, const int32_t* ioff,
                 double* partial, bool split, const int32_t* w_beg, const int32_t* w_cnt, const int32_t* w_ids,
                 const double* geom, const double* binom, int p, const void* mp, void* loc, hipStream_t s, int batch,
                 const long long* guard)
 {
     if (nx == 0) return;
     const int slots = batch != 0 ? batch : 4, ks = (p + 3) / 4;
-#define ARGS boxes, xitems, nx, icnt, ioff, partial, w_beg, w_cnt, w_ids, geom, binom, p, mp, loc, s, guard
+#define ARGS xitems, nx, icnt, ioff, partial, w_beg, w_cnt, w_ids, geom, binom, p, mp, loc, s, guard
 #define FOUR(PB, K0, G)                                       \
     {                                                         \
         if (ks <= K0) m2l_one<T, PB, K0, G>(ARGS);            \
@@ -516,13 +516,13 @@ void launch_m2l(const int32_t* boxes, int n, const int2* xitems, int nx, const i
     check_launch("m2l");
     if (split) {
         const int64_t nt = (int64_t)n * p;
-        k_m2l_combine<T><<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(boxes, n, icnt, ioff, partial, p, (T*)loc);
+        k_m2l_combine<T><<<(unsigned)((nt + 255) / 256), 256, 0, s>>>(n, icnt, ioff, partial, p, (T*)loc);
         check_launch("m2l combine");
     }
 }
 
 #define INST_M2L(T)                                                                                        \
-    template void launch_m2l<T>(const int32_t*, int, const int2*, int, const int32_t*, const int32_t*, double*, \
+    template void launch_m2l<T>(int, const int2*, int, const int32_t*, const int32_t*, double*, \
                                 bool, const int32_t*, const int32_t*, const int32_t*, const double*,            \
                                 const double*, int, const void*, void*, hipStream_t, int,     \
                                 const long long*);

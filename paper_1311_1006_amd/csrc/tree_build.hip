@@ -1661,11 +1661,11 @@ static void build_tree_select(Tree& t, const double* z, hipStream_t s)
     int64_t nkeys = sc.total_keys;
     DBuf<uint64_t> keys; keys.alloc(kKeyWords * nkeys, s);
     int64_t nseg_split = sc.nstage > 0 ? sc.keys_off[sc.nstage] : 0;   // segments of split stages
-    DBuf<uint32_t> words;   // hist1 | hist2 | cand_cnt | tiles done per segment | tile_below | tile_extra | lo_base | err
+    DBuf<uint32_t> words;   // hist1 | hist2 | cand_cnt | tiles done per segment | tile_below | lo_base
     int64_t nt = sc.total_tile;
     int64_t o_h1 = 0, o_h2 = nseg_split * 2 * kHistCopies * kBuckets1, o_cc = o_h2 + nseg_split * kBuckets2;
     int64_t o_sd = o_cc + nseg_split, o_tb = o_sd + nseg_split;
-    int64_t o_te = o_tb + nt, o_lb = o_te + nt, o_err = o_lb + nt, nwords = o_err + 1;
+    int64_t o_lb = o_tb + nt, nwords = o_lb + nt;
     words.alloc(nwords, s);
     DBuf<Cand> cand; cand.alloc(std::max<int64_t>(nseg_split, 1) * kCandCap, s);
     DBuf<Splitter> split; split.alloc(std::max<int64_t>(nseg_split, 1), s);

@@ -374,6 +374,7 @@ int fmm_plan(fmm_tree_t t, int p, double theta, int precision, const fmm_tuning*
         {
             TreeSchedule& sc = *t->t.sched;
             int key = (precision * 64 + tn.p2p_split) * 32 + tn.p2p_targets;   // the launch classes
+            std::lock_guard<std::mutex> lk(sc.plan_mu);
             auto it = sc.plan_cache.find(key);
             if (it != sc.plan_cache.end()) {
                 pl.ex_ref = it->second;

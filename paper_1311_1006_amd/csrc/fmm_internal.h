@@ -7,6 +7,7 @@
 #include <cstring>
 #include <map>
 #include <memory>
+#include <mutex>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -213,7 +214,9 @@ struct GeomJob {      // a box whose geometry comes from the bbox keys of a glob
 struct PlanExtra;
 
 struct TreeSchedule {
-    // launch lists of plans on trees of this layout, by (precision, P2P knob)
+    // launch lists of plans on trees of this layout, by (precision, P2P knob); trees
+    // of several threads share it
+    std::mutex plan_mu;
     std::map<int, std::shared_ptr<PlanExtra>> plan_cache;
     int nprob = 0;
     int64_t n = 0;

@@ -38,6 +38,7 @@ static int fail_malloc = -1;          // hipMalloc calls left before one that fa
 static long long list_flag = 0;       // what an 8-byte copy to the host delivers
 static std::string watched;           // model_watch: the kernel, the index of an int argument, its last value
 static int watched_arg, watched_value;
+static void (*sync_hook)();           // called by the next hipStreamSynchronize
 static dim3 cfg_grid, cfg_block;
 static size_t cfg_shared;
 static hipStream_t cfg_stream;
@@ -94,6 +95,7 @@ void model_watch(const char* part, int arg)
     watched_arg = arg;
 }
 int model_watched() { return watched_value; }
+void model_on_sync(void (*f)()) { sync_hook = f; }
 int model_created_in_capture() { return in_capture; }
 int model_mallocs() { return mallocs; }
 void model_fail_malloc(int after) { fail_malloc = after; }
@@ -142,7 +144,15 @@ hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned)
     return hipSuccess;
 }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t s) { join(host, streams[s]); return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t s)
+{
+    join(host, streams[s]);
+    if (void (*f)() = sync_hook) {
+        sync_hook = nullptr;
+        f();
+    }
+    return hipSuccess;
+}
 hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned)
 {
     join(streams[s], events[e]);

@@ -8,6 +8,7 @@ import glob
 import os
 import shutil
 import subprocess
+import threading
 
 import pytest
 
@@ -268,3 +269,26 @@ def test_near_field_of_fat_leaves_gathers_for_itself(model, n, L, p, flag, apart
     model.ok(model.call("evaluate", pl, s))
     assert model.lib.model_launches(b"k_gather") == apart
     assert model.lib.model_not_joined(s) == 0
+
+
+def test_two_threads_make_plans_of_one_layout(model):
+    # trees of their own that share a layout: while one thread prepares the layout's
+    # launch lists (here: waits for their copy) the other's fmm_plan waits
+    s, t = model.stream(), model.stream()
+    model.plan(model.tree(300, 3, s), s)               # the constant tables are there
+    mine, other = model.tree(5000, 5, s), model.tree(5000, 5, t)
+    waited, made = [], []
+    thread = threading.Thread(target=lambda: made.append(model.plan(other, t)))
+
+    def meanwhile():
+        thread.start()
+        thread.join(0.3)
+        waited.append(thread.is_alive())
+
+    hook = C.CFUNCTYPE(None)(meanwhile)
+    model.lib.model_on_sync(hook)
+    pl = model.plan(mine, s)
+    thread.join()
+    assert waited == [True] and len(made) == 1
+    for p, st in ((pl, s), (made[0], t)):
+        model.ok(model.call("evaluate", p, st))

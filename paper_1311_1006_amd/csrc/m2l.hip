@@ -465,9 +465,12 @@ __global__ void k_m2l_combine(int n, const int32_t* __restrict__ icnt,
 // weak pairs).  xitems[0 .. nx): (box, chunk); icnt/ioff per box; partial holds
 // the chunks of split lists.  batch: pair slots of
 // one item in each 16-pair MFMA block: 16 (one item per wavefront), 8 (two)
-// or 4 (four items share a wavefront); 0 = automatic (4, the fastest in both
-// precisions on the uniform million-point case: mixed 81 us against 93 us
-// with 8 slots, FP64 146 us against 161 us).  Above 32 terms the slots are fixed: 8
+// or 4 (four items share a wavefront); 0 = automatic: 4, the choice that is never
+// far from the best.  2 / 4 / 8 slots, us, p = 13 uniform: N = 1e6 on 9 levels FP64
+// 150 / 152 / 171, mixed 86 / 82 / 96; 300,000 on 8 49 / 48 / 49, 32 / 30 / 30; 1e5 on
+// 7 25 / 22 / 20, 21 / 15 / 14; 4000 on 5 25 / 16 / 11, 21 / 15 / 10.  At p = 29 in FP64
+// 2 slots are the faster for large problems (1e6: 490 / 526 / 631) and the slower for
+// small ones (30,000: 50 / 30 / 20).  Above 32 terms the slots are fixed: 8
 // in FP64 up to 48 terms (p = 39, before with 16: 1e6 points 1324 to 990 us, 1e5 96
 // to 74, 30,000 35 to 30, 4000 18 to 23), where wavefronts of more boxes leave
 // small problems idle (4 slots: 838, 79, 45 and 33 us), and 16 in mixed

@@ -42,9 +42,10 @@
 // near field of the points in leaves is the near-field kernel of the sources
 // (p2p.hip) with the points as its targets: sources of the leaf's strong list
 // staged in LDS, a lane subgroup per few points; with the derivative a kernel
-// of its own (k_pts_near_der; few points descend instead).  The descents of the other points run a
-// wavefront per point, lanes over the boxes of a frontier.  The far field is
-// one lane per point.  Locating, sorting and the descents wait for memory most
+// of its own (k_pts_near_der; where the points are few, or few per leaf, and in
+// leaves with long lists they descend instead).  The descents of the other
+// points run a wavefront per point, lanes over the boxes of a frontier.  The far
+// field is one lane per point.  Locating, sorting and the descents wait for memory most
 // of the time, so they run on a second stream beside the sources' far field.
 #include <algorithm>
 #include <cfloat>

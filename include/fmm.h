@@ -190,7 +190,7 @@ void fmm_tree_destroy(fmm_tree_t t);
  * lies nearer to one by a factor of about 2^(128/p) (mixed precision; 250 at
  * p = 16, 6 at p = 48) or 2^(1024/p) (FP64) than that radius, coefficients
  * overflow and the values of that leaf's points are NaN: of 20,000 uniform
- * points on 8 levels, 1 to 2 per leaf, 1 at p = 16 and 183 at p = 32 in mixed
+ * points on 8 levels, 1 to 2 per leaf, 1 at p = 16 and 186 at p = 32 in mixed
  * precision, none in FP64.  Choose n_levels with at least two points per leaf.
  */
 int fmm_plan(fmm_tree_t t, int p, double theta, int precision, const fmm_tuning* tune,

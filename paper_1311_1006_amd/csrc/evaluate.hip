@@ -500,7 +500,7 @@ void launch_log_constants(int nbox, const int32_t* w_beg, const int32_t* w_cnt, 
                           const int32_t* parent, const double* geom, const void* mp, const void* loc, int p,
                           double* c0, hipStream_t s);
 template <class T>
-void launch_l2p_log(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount,
+void launch_l2p_log(const int32_t* leaves, int nleaf, int64_t n, const int32_t* bstart, const int32_t* bcount,
                     const int32_t* parent, const double* geom, const double* X, const double* Y, const void* loc,
                     int p, const double* c0, const double* near, const int32_t* perm, double* u, hipStream_t s);
 
@@ -531,7 +531,7 @@ void evaluate_log_device(Plan& pl, const double* q, double* u, hipStream_t s, do
               pl.p, c0, s);
     run_p2p(pl, ex, s, nullptr, true);
     auto l2p = mixed ? launch_l2p_log<float> : launch_l2p_log<double>;
-    l2p(ex.leaves.p, (int)sc.nleaf, sc.d_box_start.p, sc.d_box_count.p, sc.d_box_parent.p, t.geom.p, t.x.p, t.y.p,
+    l2p(ex.leaves.p, (int)sc.nleaf, sc.n, sc.d_box_start.p, sc.d_box_count.p, sc.d_box_parent.p, t.geom.p, t.x.p, t.y.p,
         pl.local.p, pl.p, c0, pl.near.p, t.perm.p, u, s);
     // the harmonic state of the plan now holds these strengths: no adjoint of it
     pl.have_forward = false;

@@ -118,11 +118,15 @@ k_log_constants(int nbox, const int32_t* __restrict__ w_beg, const int32_t* __re
     if (live && lane == 0) c0[g] = acc;
 }
 
-// L2P of the logarithmic series at the points of every leaf (32 lanes per leaf,
-// eight leaves per workgroup: leaves hold about 30 points), plus the near field,
+// L2P of the logarithmic series at the points of every leaf, plus the near field,
 // scattered to input order.  The constant term is summed over the leaf and its
-// ancestors, root last.
-template <class T>
+// ancestors, root last.  G = 32 lanes per leaf, eight leaves per workgroup (leaves
+// hold about 30 points), or above kLogWide points per leaf a workgroup per leaf:
+// 32 lanes / 256, whole evaluation, us, mixed, p = 17: N = 150,000 on 5 levels (585
+// points per leaf) 733 / 714, 20,000 on 4 (312) 136 / 128, 20,000 on 5 (78) 90 / 88,
+// one leaf of 1000 at p = 40 108 / 75.
+constexpr int kLogWide = 64;
+template <class T, int G>
 __global__ void __launch_bounds__(256)
 k_l2p_log(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restrict__ bstart,
           const int32_t* __restrict__ bcount, const int32_t* __restrict__ parent, const double* __restrict__ geom,
@@ -130,21 +134,22 @@ k_l2p_log(const int32_t* __restrict__ leaves, int nleaf, const int32_t* __restri
           const double* __restrict__ c0, const double* __restrict__ near, const int32_t* __restrict__ perm,
           double* __restrict__ u)
 {
-    __shared__ double2 scf[8][kMaxP];
-    const int lane = threadIdx.x & 31;
-    const int li = blockIdx.x * 8 + (threadIdx.x >> 5);
-    if (li >= nleaf) return;   // (no workgroup barrier below)
-    double2* cf = scf[threadIdx.x >> 5];
+    __shared__ double2 scf[256 / G][kMaxP];
+    const int lane = threadIdx.x & (G - 1);
+    const int li = blockIdx.x * (256 / G) + threadIdx.x / G;
+    if (li >= nleaf) return;   // (a workgroup barrier below only where every workgroup has a leaf)
+    double2* cf = scf[threadIdx.x / G];
     const int g = leaves[li];
     const int st = bstart[g], n = bcount[g];
     const double cx = geom[4 * (int64_t)g], cy = geom[4 * (int64_t)g + 1], rs = geom[4 * (int64_t)g + 3];
     const T* b = loc + 2 * (int64_t)g * coef_ld<T>(p);
-    for (int l = lane; l < p; l += 32)
+    for (int l = lane; l < p; l += G)
         cf[l] = make_double2((double)b[2 * l] / (l + 1), (double)b[2 * l + 1] / (l + 1));
     double base = 0.0;
     for (int a = g; a >= 0; a = parent[a]) base += c0[a];
-    wave_sync();
-    for (int i = lane; i < n; i += 32) {
+    if constexpr (G > 64) __syncthreads();
+    else wave_sync();
+    for (int i = lane; i < n; i += G) {
         const int pos = st + i;
         double v = base;
         if (rs > 0.0) {
@@ -180,20 +185,22 @@ void launch_log_constants(int nbox, const int32_t* w_beg, const int32_t* w_cnt, 
 }
 
 template <class T>
-void launch_l2p_log(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount,
+void launch_l2p_log(const int32_t* leaves, int nleaf, int64_t n, const int32_t* bstart, const int32_t* bcount,
                     const int32_t* parent, const double* geom, const double* X, const double* Y, const void* loc,
                     int p, const double* c0, const double* near, const int32_t* perm, double* u, hipStream_t s)
 {
     if (nleaf == 0) return;
-    k_l2p_log<T><<<(unsigned)((nleaf + 7) / 8), 256, 0, s>>>(leaves, nleaf, bstart, bcount, parent, geom, X, Y,
-                                                             (const T*)loc, p, c0, near, perm, u);
+    const bool wide = n > kLogWide * (int64_t)nleaf;
+    auto l2p = wide ? k_l2p_log<T, 256> : k_l2p_log<T, 32>;
+    l2p<<<(unsigned)(wide ? nleaf : (nleaf + 7) / 8), 256, 0, s>>>(leaves, nleaf, bstart, bcount, parent, geom, X, Y,
+                                                                   (const T*)loc, p, c0, near, perm, u);
     check_launch("log l2p");
 }
 
 #define LOG_INSTANCE(T)                                                                                            \
     template void launch_log_constants<T>(int, const int32_t*, const int32_t*, const int32_t*, const int32_t*,     \
                                           const double*, const void*, const void*, int, double*, hipStream_t);     \
-    template void launch_l2p_log<T>(const int32_t*, int, const int32_t*, const int32_t*, const int32_t*,           \
+    template void launch_l2p_log<T>(const int32_t*, int, int64_t, const int32_t*, const int32_t*, const int32_t*,  \
                                     const double*, const double*, const double*, const void*, int, const double*,  \
                                     const double*, const int32_t*, double*, hipStream_t);
 LOG_INSTANCE(float)

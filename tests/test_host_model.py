@@ -292,3 +292,13 @@ def test_two_threads_make_plans_of_one_layout(model):
     assert waited == [True] and len(made) == 1
     for p, st in ((pl, s), (made[0], t)):
         model.ok(model.call("evaluate", p, st))
+
+
+@pytest.mark.parametrize("n,L,wide", [(1024, 3, 0), (1025, 3, 1), (100, 1, 1), (64, 1, 0)])
+def test_log_l2p_takes_a_workgroup_for_fat_leaves(model, n, L, wide):
+    s = model.stream()
+    pl = model.plan(model.tree(n, L, s), s)
+    model.lib.model_clear()
+    model.ok(model.call("log", pl, s))
+    assert model.lib.model_launches(b"k_l2p_logIdLi256E") == wide
+    assert model.lib.model_launches(b"k_l2p_logIdLi32E") == 1 - wide

@@ -418,11 +418,11 @@ static bool near_beside(const Plan& pl)
 // does not wait for P2M (which does the gather otherwise).  P2M takes the longer
 // the more points a leaf has and the more terms, while the extra gather reads every
 // strength twice: P2M's / its own, us: p = 39 FP64 N = 3000 on 3 levels (187
-// points per leaf) 98 / 82, N = 10,000 on 4 (156) 105 / 92, N = 10,000 on 5 (39) 72
-// / 68, N = 30,000 on 6 (29) 75 / 74, N = 1e5 on 7 (24) 139 / 144; p = 16 split lists
-// N = 1e5 on 5 (390) 374 / 349, 1e6 clustered on 9 (15) mixed 667 / 687, batch of
-// 128 problems (16) 1281 / 1334.
-constexpr int kGatherApart = 32;     // points per leaf
+// points per leaf) 98 / 82, N = 10,000 on 4 (156) 105 / 92,
+// N = 10,000 on 5 (39) 72 / 68 (mixed 64 / 67), N = 150,000 on 7 (36) mixed 138 / 150, N =
+// 1e5 on 7 (24) 139 / 144; p = 16 split lists N = 1e5 on 5 (390) 374 / 349, 1e6
+// clustered on 9 (15) mixed 667 / 687, batch of 128 problems (16) 1281 / 1334.
+constexpr int kGatherApart = 64;     // points per leaf
 
 // The second stream and its events, where they are used, made when the plan is
 // made (more than 32 terms) or its lists are final (split lists): the

@@ -1,5 +1,5 @@
 """Leaves of many points where the near field runs on the second stream and gathers
-the strengths itself (more than 32 points per leaf), and its neighbours: one
+the strengths itself (more than 64 points per leaf), and its neighbours: one
 stream below 16,385 points with split lists and below 2049 points with more than 32
 terms.  Every form of the evaluation against the direct sum (converged orders;
 1e-12 FP64, 1e-6 mixed) and against each other to the bit."""

@@ -256,11 +256,12 @@ def test_long_lists_of_points_with_the_derivative_are_descended(model, flag, lon
 
 @pytest.mark.parametrize("n,L,p,flag,apart", [(5000, 5, 12, 12, 0), (16384, 5, 12, 12, 0), (16385, 5, 12, 0, 0),
                                               (16385, 5, 12, 12, 1), (16385, 6, 12, 12, 0), (2048, 3, 40, 0, 0),
-                                              (2049, 3, 40, 0, 1), (2049, 5, 40, 0, 0)])
+                                              (2049, 3, 40, 0, 1), (2049, 5, 40, 0, 0), (4096, 4, 40, 0, 0),
+                                              (4097, 4, 40, 0, 1)])
 def test_near_field_of_fat_leaves_gathers_for_itself(model, n, L, p, flag, apart):
     # a gather of the strengths apart from P2M's: only on the second stream (split
     # lists above 16,384 points, or more than 32 terms above 2048) and with more
-    # than 32 points per leaf; the adjoint afterwards needs nothing of it
+    # than 64 points per leaf; the adjoint afterwards needs nothing of it
     s = model.stream()
     model.lib.model_list_flag(C.c_longlong(flag))
     pl = model.plan(model.tree(n, L, s), s, p=p)

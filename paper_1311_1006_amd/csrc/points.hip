@@ -63,7 +63,10 @@ void far_field_down(Plan& pl, hipStream_t s);
 // each, for the (4 targets per lane, 4 subgroups) shape
 constexpr int kPtsItem = 16;
 constexpr int64_t kTwoStreamPoints = 50000, kDescendPoints = 8192;   // see evaluate_points_device
-constexpr int kLongList = 512;      // of split layouts: longer strong lists are descended (likewise)
+// of split layouts: strong lists longer than this are descended, for many points
+// and for few (at most kFewPoints and kFewPerLeaf per leaf; likewise)
+constexpr int kLongList = 512, kLongListFew = 128;
+constexpr int64_t kFewPoints = 131072, kFewPerLeaf = 32;
 struct PtsItem {
     int32_t leaf, t0, tn, pad;
 };
@@ -732,16 +735,24 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     // and on small trees N = 30,000 with M = 8192, 8 per leaf, 84 / 100 (80 / 90).
     const bool all_descend = der && M <= std::max<int64_t>(kDescendPoints, (int64_t)nleaf * (mixed ? 2 : 3));
     // Where some strong list is split into work chunks, the points of leaves with
-    // more than kLongList boxes in theirs are descended too: the own kernel walks
-    // every fourth box in turn, a descent every 64th.  100,000 points beside the
-    // sources, all descents / this / own kernel alone, us: 300,000 sources of
-    // which 5 lie far off (one list of 16,384 boxes) 2500 / 2440 / 10,760, 300,000
-    // in clusters 3320 / 3040 / 4720, 30,000 in clusters (lists of up to 244 boxes)
-    // 860 / 790 / 790, 100,000 in clusters 1270 / 1310 / 1530; lines at 64 and 256
-    // boxes lie between.
+    // longer lists than a line are descended too: the own kernel walks every fourth
+    // box in turn, a descent every 64th.  100,000 points beside the sources, all
+    // descents / above 512 boxes / own kernel alone, us: 300,000 sources of which 5
+    // lie far off (one list of 16,384 boxes) 2500 / 2440 / 10,760, 300,000 in clusters
+    // 3320 / 3040 / 4720, 30,000 in clusters (lists of up to 244 boxes) 860 / 790 /
+    // 790, 100,000 in clusters 1270 / 1310 / 1530.  Few points leave the chip to the
+    // long lists, hence a lower line.  Clustered sources, uniform points, FP64, lines
+    // at 128 / 512 boxes: N = 20,000 on 7 levels M = 20,000 178 / 262, M = 100,000 281
+    // / 328; on 6 levels M = 20,000 206 / 242, 40,000 (39 per leaf) 268 / 261; N = 1e5 on
+    // 7 levels M = 100,000 736 / 812; N = 300,000 on 8 levels M = 98,304 1394 / 1693,
+    // 262,144 3399 / 3237; N = 1e6 on 8 levels M = 98,304 6756 / 6522, 262,144 18,377 /
+    // 14,361; N = 60,000 on 7 levels M = 300,000 1586 / 1086.  A line of 64 boxes (150 and
+    // 182 at N = 20,000) takes the lists of uniform sources at small theta too: N = 1e5
+    // on 6 levels, theta = 0.15, M = 30,720, mixed 1007 against 605 at 128.
     const bool part_descend = der && !all_descend && pl.split_p2p;
     const int32_t* nq_dev = off.p + (all_descend || part_descend ? nb : lb);
-    const int skip = part_descend ? kLongList : 0, longest = part_descend ? kLongList : INT32_MAX;
+    const int line = M <= std::min<int64_t>(kFewPoints, kFewPerLeaf * nleaf) ? kLongListFew : kLongList;
+    const int skip = part_descend ? line : 0, longest = part_descend ? line : INT32_MAX;
 #define DESC_ARGS                                                                                             \
     (const double2*)y, order.p, box.p, nq_dev, skip, L, sc.d_box_level.p, t.geom.p, sc.d_box_start.p,         \
         sc.d_box_count.p, pl.s_beg.p, pl.s_cnt.p, pl.s_ids.p

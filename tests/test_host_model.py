@@ -244,7 +244,8 @@ def test_points_with_the_derivative_few_per_leaf_are_descended(model, n, L, prec
 @pytest.mark.parametrize("flag,longest", [(0, 2 ** 31 - 1), (4, 512)])
 def test_long_lists_of_points_with_the_derivative_are_descended(model, flag, longest):
     # split strong lists: the own kernel (its 14th argument) leaves out what the
-    # descents (their 5th) take, leaves with more than 512 boxes in their list
+    # descents (their 5th) take, leaves with more than 512 boxes in their list, or 128
+    # where the points are few
     s = model.stream()
     model.lib.model_list_flag(C.c_longlong(flag))
     pl = model.plan(model.tree(5000, 5, s), s)
@@ -252,6 +253,18 @@ def test_long_lists_of_points_with_the_derivative_are_descended(model, flag, lon
         model.lib.model_watch(part, arg)
         model.ok(model.call("20000:field", pl, s))
         assert model.lib.model_watched() == value, part
+
+
+@pytest.mark.parametrize("L,M,line", [(6, 32768, 128), (6, 32769, 512), (8, 131072, 128), (8, 131073, 512)])
+def test_the_line_of_long_lists_by_the_number_of_points(model, L, M, line):
+    # up to 32 points per leaf (1024 leaves) and up to 131,072 points (16,384 leaves)
+    s = model.stream()
+    model.lib.model_list_flag(C.c_longlong(4))
+    pl = model.plan(model.tree(70000, L, s), s)
+    for part, arg in ((b"k_pts_near_der", 13), (b"k_pts_descend", 4)):
+        model.lib.model_watch(part, arg)
+        model.ok(model.call("%d:field" % M, pl, s))
+        assert model.lib.model_watched() == line, (part, M)
 
 
 @pytest.mark.parametrize("n,L,p,flag,apart", [(5000, 5, 12, 12, 0), (16384, 5, 12, 12, 0), (16385, 5, 12, 0, 0),

@@ -467,7 +467,7 @@ static void launch_field(const int32_t* leaves, int nleaf, const int32_t* bstart
     check_launch("field final");
 }
 
-// the field and its derivative at the points of shallow problems' leaves
+// the field and its derivative at the points of leaves outside the subtrees' kernels
 template <class T>
 void launch_l2p_field(const int32_t* leaves, int nleaf, const int32_t* bstart, const int32_t* bcount, int leaf_max,
                       const double* geom, const double* X, const double* Y, const void* loc, int p,

@@ -84,6 +84,17 @@ static void p2p_shape(int nt, int knob, int tknob, bool mixed, int* tg, int* sub
     *sub = s;
 }
 
+// Above this many points per leaf a problem's P2M and L2P are launches of their own
+// with 64 lanes per leaf, where the subtrees' kernels take 16: a lane's serial run
+// over the leaf is four times as short, for two launches more.  Own / subtrees', us,
+// phi and log: N = 20,000 on 4 levels (312 points per leaf) mixed p = 17 97 / 101 and
+// 118 / 127, N = 30,000 on 4 (468) 129 / 138 and 169 / 184, FP64 p = 64 193 / 205 and 339 /
+// 360, N = 1e5 on 5 (390) mixed p = 17 253 / 262 and 372 / 383 (but FP64 p = 64 389 / 378
+// and 762 / 778), N = 1e6 on 6 (976) 4446 / 4460 and 6760 / 6790.  Below the line they
+// are even or the launches cost more: N = 40,000 on 5 (156) mixed p = 17 107 / 107 and
+// 145 / 147, FP64 p = 64 156 / 140, N = 1e5 on 6 (97) mixed p = 40 137 / 120.
+constexpr int kFatLeaf = 256;
+
 // the subtree launches of every pass: for a problem with levels 0 .. L-1, L >=
 // 3, the roots are the boxes of level L-3; upward steps go from there to level
 // 1, downward ones from level 1 to level L-4
@@ -91,32 +102,41 @@ static void prepare_subtrees(const TreeSchedule& sc, SubPlan& sp, UploadPack& up
 {
     sp.uniform = sc.L[0] >= 3;
     sp.L = sc.L[0];
-    std::vector<int32_t> shallow;
+    std::vector<int32_t> shallow, fat;
+    std::vector<char> is_fat(sc.nprob, 0);
+    int nfat = 0;
     for (int b = 0; b < sc.nprob; ++b) {
         sp.uniform = sp.uniform && sc.L[b] == sc.L[0];
-        if (sc.L[b] >= 3) continue;
-        const int64_t base = sc.pbox[b] + level_base(sc.L[b] - 1);
-        for (int64_t j = 0; j < int64_t(1) << (2 * (sc.L[b] - 1)); ++j) {
-            shallow.push_back((int32_t)(base + j));
-            sp.shallow_max = std::max(sp.shallow_max, (int)sc.box_count[base + j]);
+        const int64_t base = sc.pbox[b] + level_base(sc.L[b] - 1), n = int64_t(1) << (2 * (sc.L[b] - 1));
+        is_fat[b] = sc.L[b] >= 3 && sc.off[b + 1] - sc.off[b] > kFatLeaf * n;
+        nfat += is_fat[b];
+        if (sc.L[b] >= 3 && !is_fat[b]) continue;
+        LeafSet& set = is_fat[b] ? sp.fat : sp.shallow;
+        for (int64_t j = 0; j < n; ++j) {
+            (is_fat[b] ? fat : shallow).push_back((int32_t)(base + j));
+            set.max = std::max(set.max, (int)sc.box_count[base + j]);
         }
     }
-    sp.nshallow = (int)shallow.size();
+    sp.shallow.n = (int)shallow.size();
+    sp.fat.n = (int)fat.size();
+    sp.all_fat = nfat == sc.nprob;
+    sp.listed = !sp.uniform || (nfat > 0 && !sp.all_fat);
     std::vector<int4> list;
     // one launch: for every problem the boxes of level lev(L), D(L) levels (D = 0: none)
-    auto step = [&](auto lev, auto D) {
-        SubStep st{(int64_t)list.size(), 0, lev(sp.L), D(sp.L)};
+    auto step = [&](auto lev, auto D, bool roots = false) {
+        SubStep st{(int64_t)list.size(), 0, lev(sp.L), D(sp.L) + (roots && sp.all_fat ? kSubFat : 0)};
         for (int b = 0; b < sc.nprob; ++b) {
             const int l = lev(sc.L[b]), d = D(sc.L[b]);
             if (d == 0) continue;
             const int64_t n = int64_t(1) << (2 * l);
             st.n += n;
-            if (!sp.uniform)
-                for (int64_t j = 0; j < n; ++j) list.push_back(make_int4((int)sc.pbox[b], l, (int)j, d));
+            if (sp.listed)
+                for (int64_t j = 0; j < n; ++j)
+                    list.push_back(make_int4((int)sc.pbox[b], l, (int)j, d + (roots && is_fat[b] ? kSubFat : 0)));
         }
         return st;
     };
-    sp.roots = step([](int L) { return L - 3; }, [](int L) { return L >= 3 ? 3 : 0; });
+    sp.roots = step([](int L) { return L - 3; }, [](int L) { return L >= 3 ? 3 : 0; }, true);
     for (int h = 0; h < 2; ++h) {
         const int m = h ? kSubLevelsHigh : kSubLevels;
         for (int k = 0; m * k < sc.max_levels - 4; ++k) {
@@ -127,7 +147,8 @@ static void prepare_subtrees(const TreeSchedule& sc, SubPlan& sp, UploadPack& up
             sp.down[h].push_back(step([m, k](int) { return 1 + m * k; },
                                       [m, k](int L) { return std::max(0, std::min(m, L - 4 - (1 + m * k))); }));
     }
-    up.add(sp.shallow, shallow);
+    up.add(sp.shallow.ids, shallow);
+    up.add(sp.fat.ids, fat);
     up.add(sp.list, list);
 }
 
@@ -270,11 +291,14 @@ static void run_up(Plan& pl, const double* m, const double* mt, void* mp, hipStr
     TreeSchedule& sc = *t.sched;
     PlanExtra& ex = *extra(pl);
     const GatherOut go{t.perm.p, (const double2*)m, keep ? (double2*)pl.mtree.p : nullptr};
+    for (const LeafSet* set : {&ex.sub.fat, &ex.sub.shallow})
+        launch_p2m<T>(set->ids.p, set->n, sc.d_box_start.p, sc.d_box_count.p, set->max, t.geom.p, t.x.p, t.y.p, mt,
+                      pl.p, mp, s, m ? &go : nullptr);
+    const bool gathered = ex.sub.all_fat;           // by P2M alone
+    if (after_gather && gathered) FMM_HIP(hipEventRecord(after_gather, s));
     launch_up_leaves<T>(ex.sub, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, mt, pl.p, mp, ex.fact.p,
                         m ? &go : nullptr, s);
-    launch_p2m<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max, t.geom.p,
-                  t.x.p, t.y.p, mt, pl.p, mp, s, m ? &go : nullptr);
-    if (after_gather) FMM_HIP(hipEventRecord(after_gather, s));
+    if (after_gather && !gathered) FMM_HIP(hipEventRecord(after_gather, s));
     launch_up_mid<T>(ex.sub, t.geom.p, pl.p, mp, ex.fact.p, s);
 }
 
@@ -289,12 +313,14 @@ static void run_down_leaves(Plan& pl, bool staged, void* loc, double* phi, doubl
     PlanExtra& ex = *extra(pl);
     launch_down_subtree<T>(ex.sub, staged, sc.d_box_start.p, sc.d_box_count.p, t.geom.p, t.x.p, t.y.p, loc, pl.p,
                            dphi ? pl.near4.p : pl.near.p, t.perm.p, phi, phi_near, phi_far, dphi, guard, ex.fact.p, s);
-    if (dphi)
-        launch_l2p_field<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max,
-                            t.geom.p, t.x.p, t.y.p, loc, pl.p, pl.near4.p, t.perm.p, phi, dphi, s);
-    else if (phi || phi_near || phi_far)
-        launch_l2p<T>(ex.sub.shallow.p, ex.sub.nshallow, sc.d_box_start.p, sc.d_box_count.p, ex.sub.shallow_max,
-                      t.geom.p, t.x.p, t.y.p, loc, pl.p, pl.near.p, t.perm.p, phi, phi_near, phi_far, s, guard);
+    for (const LeafSet* set : {&ex.sub.fat, &ex.sub.shallow}) {
+        if (dphi)
+            launch_l2p_field<T>(set->ids.p, set->n, sc.d_box_start.p, sc.d_box_count.p, set->max, t.geom.p, t.x.p,
+                                t.y.p, loc, pl.p, pl.near4.p, t.perm.p, phi, dphi, s);
+        else if (phi || phi_near || phi_far)
+            launch_l2p<T>(set->ids.p, set->n, sc.d_box_start.p, sc.d_box_count.p, set->max, t.geom.p, t.x.p, t.y.p,
+                          loc, pl.p, pl.near.p, t.perm.p, phi, phi_near, phi_far, s, guard);
+    }
 }
 
 struct PhaseTimer {

@@ -1,6 +1,6 @@
 // expansions.hip -- P2M and L2P of shallow problems (one or two levels: no
-// shift between levels; deeper ones: subtree.hip) and the point gathers (Sec.
-// 2.1, Fig. 2.2) on gfx950.
+// shift between levels) and of leaves with many points (others: subtree.hip), and
+// the point gathers (Sec. 2.1, Fig. 2.2) on gfx950.
 //
 // Expansions are stored scaled by the box's scaling radius rs (its radius,
 // or the nearest ancestor's radius when it is 0):

@@ -17,22 +17,31 @@ struct SubStep {
     int lev, D;         // trees of one depth: the level of the subtrees' roots, and their levels
 };
 constexpr int kSubLevels = 3, kSubLevelsHigh = 2;   // levels per launch above the roots, p <= 32 and more
+// Leaves whose P2M and L2P are launches of their own (expansions.hip, up to 64 lanes
+// per leaf) instead of parts of the subtrees' (16 lanes per leaf)
+struct LeafSet {
+    DView<int32_t> ids;
+    int n = 0, max = 0;         // their number, and the largest one's points
+};
+constexpr int kSubFat = 256;    // added to D in the list: the leaves are in `fat`
 struct SubPlan {
-    bool uniform = false;       // every problem has the same depth L >= 3: no list
+    bool uniform = false;       // every problem has the same depth L >= 3
+    bool listed = false;        // the launches read the list (problems of unlike depth, or fat and thin ones)
+    bool all_fat = false;       // not listed: every problem's leaves are in `fat`
     int L = 0;
     DView<int4> list;            // (root box of the problem, level, box of the level, levels D) per workgroup
     SubStep roots{};            // the boxes of level L-3 (problems of fewer levels: see shallow)
     // [0] for p <= 32, [1] for more terms (fewer levels per launch):
     std::vector<SubStep> up[2];    // levels L-4 .. 1, bottom up
     std::vector<SubStep> down[2];  // levels 2 .. L-4 from level 1, top down
-    DView<int32_t> shallow;      // the leaves of the problems of one or two levels (no shifts between levels)
-    int nshallow = 0, shallow_max = 0;   // their number, and the largest one's points
+    LeafSet shallow;            // the leaves of the problems of one or two levels (no shifts between levels)
+    LeafSet fat;                // those of deeper problems with many points per leaf (kFatLeaf)
 };
 // the same as a kernel argument
 struct SubWork {
     const int4* list;
     int lev, D, nper;           // without a list: every problem has NB boxes and nper subtrees of D levels
-    int64_t NB;                 // rooted at level lev
+    int64_t NB;                 // rooted at level lev (D as in the list)
 };
 
 struct PlanExtra {

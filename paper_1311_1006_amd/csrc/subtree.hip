@@ -15,7 +15,7 @@
 // of 16 terms that crosses the triangle's edge needs no test.
 //
 // Upward: one workgroup per box R of level L-3 forms the multipoles of its 16
-// leaves (P2M, with the gather of the strengths into tree order, which the
+// leaves (P2M, unless the leaves have launches of their own: LeafSet::fat, with the gather of the strengths into tree order, which the
 // near field reads), of its 4 children and of R itself, all from LDS; then one
 // workgroup per box of level a forms the levels a+D-1 .. a above the level a+D
 // that the previous launch wrote, until level 1 (nothing reads the root's
@@ -84,15 +84,17 @@ __device__ __forceinline__ int sub_box(int pb, int l, int64_t j) { return (int)(
 struct SubAt {
     int pb, lev, D;
     int64_t j;
+    bool fat;            // P2M and L2P of its leaves are done elsewhere
 };
 __device__ __forceinline__ SubAt sub_at(const SubWork& w)
 {
     if (w.list) {
         const int4 v = w.list[blockIdx.x];
-        return SubAt{v.x, v.y, v.w, v.z};
+        return SubAt{v.x, v.y, v.w & (kSubFat - 1), v.z, (v.w & kSubFat) != 0};
     }
     const int b = blockIdx.x / w.nper;
-    return SubAt{(int)((int64_t)b * w.NB), w.lev, w.D, (int64_t)(blockIdx.x % w.nper)};
+    return SubAt{(int)((int64_t)b * w.NB), w.lev, w.D & (kSubFat - 1), (int64_t)(blockIdx.x % w.nper),
+                 (w.D & kSubFat) != 0};
 }
 
 // centre and scaling radius of a box
@@ -255,7 +257,7 @@ k_up_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __res
     double v[V];
 #pragma unroll
     for (int i = 0; i < V; ++i) v[i] = 0.0;
-    for (int j = sl; j < n; j += 16) {
+    for (int j = at.fat ? n : sl; j < n; j += 16) {
         const int i = st + j;
         double2 z, t;
         if constexpr (GATHER != kGatherNone) {
@@ -282,7 +284,12 @@ k_up_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __res
         const int k = base + i;
         double2 c = make_double2(0.0, 0.0);
         if (k < p) {
-            c = store_coef<T>(mp, leaf, p, k, make_double2(v[2 * i], v[2 * i + 1]));
+            if (at.fat) {
+                const T* a = mp + 2 * ((int64_t)leaf * coef_ld<T>(p) + k);
+                c = make_double2((double)a[0], (double)a[1]);
+            } else {
+                c = store_coef<T>(mp, leaf, p, k, make_double2(v[2 * i], v[2 * i + 1]));
+            }
             const double s = sub_rpow<kBits<P>>(rl, k) * ifb[i];
             c.x *= s;
             c.y *= s;
@@ -654,7 +661,7 @@ k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __r
             sanc[gl][l] = r;
         });
     }
-    if constexpr (EVAL == 0) return;
+    if (EVAL == 0 || at.fat) return;
     wave_sync();
     // ---- L2P at the leaf's points (Horner), plus the near field, to input order
     const double inv = 1.0 / gf.rs;
@@ -711,7 +718,7 @@ k_down_leaf(SubWork work, const int32_t* __restrict__ bstart, const int32_t* __r
 
 static SubWork sub_work(const SubPlan& sp, const SubStep& st)
 {
-    if (!sp.uniform) return SubWork{sp.list.p + st.off, 0, 0, 0, 0};
+    if (sp.listed) return SubWork{sp.list.p + st.off, 0, 0, 0, 0};
     return SubWork{nullptr, st.lev, st.D, 1 << (2 * st.lev), nbox_levels(sp.L)};
 }
 
@@ -779,7 +786,9 @@ void launch_down_subtree(const SubPlan& sp, bool staged, const int32_t* bstart, 
     if (sp.roots.n == 0) return;
     const SubWork w = sub_work(sp, sp.roots);
     const unsigned grid = (unsigned)sp.roots.n;
-    const bool eval = phi != nullptr || phi_near != nullptr || phi_far != nullptr;
+    const bool own = sp.all_fat && !sp.listed;      // L2P elsewhere for all
+    const bool eval = !own && (phi != nullptr || phi_near != nullptr || phi_far != nullptr);
+    if (own) dphi = nullptr;
 #define DOWN_ARGS w, bstart, bcount, geom, X, Y, (T*)loc, p, (const double2*)nearf, perm, (double2*)phi, \
                   (double2*)phi_near, (double2*)phi_far, (double2*)dphi, guard, fact
 #define DOWN_CASE(P_)                                                                    \

@@ -285,6 +285,21 @@ def test_near_field_of_fat_leaves_gathers_for_itself(model, n, L, p, flag, apart
     assert model.lib.model_not_joined(s) == 0
 
 
+@pytest.mark.parametrize("n,L,fat", [(4096, 3, 0), (4097, 3, 1), (16384, 4, 0), (16385, 4, 1), (3000, 2, 0)])
+def test_leaves_of_many_points_have_their_own_launches(model, n, L, fat):
+    # above 256 points per leaf (three levels and more): P2M and L2P apart from the
+    # subtrees'; problems of one or two levels have no subtrees
+    s = model.stream()
+    pl = model.plan(model.tree(n, L, s), s)
+    model.ok(model.lib.fmm_plan_stats(pl, C.byref(F._Stats())))
+    for kind, l2p in (("evaluate", b"5k_l2pI"), ("field", b"13k_field_finalI")):
+        model.lib.model_clear()
+        model.ok(model.call(kind, pl, s))
+        assert model.lib.model_launches(b"5k_p2mI") == model.lib.model_launches(l2p) == (fat or L < 3), kind
+        assert model.lib.model_launches(b"k_up_leaf") == model.lib.model_launches(b"k_down_leaf") == (L >= 3), kind
+        assert model.lib.model_not_joined(s) == 0
+
+
 def test_two_threads_make_plans_of_one_layout(model):
     # trees of their own that share a layout: while one thread prepares the layout's
     # launch lists (here: waits for their copy) the other's fmm_plan waits

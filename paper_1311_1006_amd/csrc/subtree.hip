@@ -15,11 +15,12 @@
 // of 16 terms that crosses the triangle's edge needs no test.
 //
 // Upward: one workgroup per box R of level L-3 forms the multipoles of its 16
-// leaves (P2M, unless the leaves have launches of their own: LeafSet::fat, with the gather of the strengths into tree order, which the
-// near field reads), of its 4 children and of R itself, all from LDS; then one
-// workgroup per box of level a forms the levels a+D-1 .. a above the level a+D
-// that the previous launch wrote, until level 1 (nothing reads the root's
-// multipole).  Three launches at L = 9 instead of one per level.
+// leaves (P2M, with the gather of the strengths into tree order, which the near
+// field reads; leaves with many points have it done before, LeafSet::fat), of its 4
+// children and of R itself, all from LDS; then one workgroup per box of level a
+// forms the levels a+D-1 .. a above the level a+D that the previous launch wrote,
+// until level 1 (nothing reads the root's multipole).  Three launches at L = 9
+// instead of one per level.
 //
 // Downward, direct form: the local expansion of a box is its own M2L sum plus
 // the L2L image of its parent's complete expansion, hence plus the images,

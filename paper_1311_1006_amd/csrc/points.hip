@@ -65,8 +65,15 @@ constexpr int kPtsItem = 16;
 constexpr int64_t kTwoStreamPoints = 50000, kDescendPoints = 8192;   // see evaluate_points_device
 // of split layouts: strong lists longer than this are descended, for many points
 // and for few (at most kFewPoints and kFewPerLeaf per leaf; likewise)
-constexpr int kLongList = 512, kLongListFew = 128;
+constexpr int kLongList = 512, kLongListFew = 64;
 constexpr int64_t kFewPoints = 131072, kFewPerLeaf = 32;
+// the lists of uniform sources hold less than kUniformList / theta^2 boxes
+constexpr double kUniformList = 3.0;
+static int long_list(int64_t M, int64_t nleaf, double theta)
+{
+    if (M > std::min(kFewPoints, kFewPerLeaf * nleaf)) return kLongList;
+    return (int)std::min<double>(kLongList, std::max<double>(kLongListFew, kUniformList / (theta * theta)));
+}
 struct PtsItem {
     int32_t leaf, t0, tn, pad;
 };
@@ -742,16 +749,18 @@ void evaluate_points_device(Plan& pl, const double* m, const double* y, int64_t 
     // 3320 / 3040 / 4720, 30,000 in clusters (lists of up to 244 boxes) 860 / 790 /
     // 790, 100,000 in clusters 1270 / 1310 / 1530.  Few points leave the chip to the
     // long lists, hence a lower line.  Clustered sources, uniform points, FP64, lines
-    // at 128 / 512 boxes: N = 20,000 on 7 levels M = 20,000 178 / 262, M = 100,000 281
-    // / 328; on 6 levels M = 20,000 206 / 242, 40,000 (39 per leaf) 268 / 261; N = 1e5 on
-    // 7 levels M = 100,000 736 / 812; N = 300,000 on 8 levels M = 98,304 1394 / 1693,
-    // 262,144 3399 / 3237; N = 1e6 on 8 levels M = 98,304 6756 / 6522, 262,144 18,377 /
-    // 14,361; N = 60,000 on 7 levels M = 300,000 1586 / 1086.  A line of 64 boxes (150 and
-    // 182 at N = 20,000) takes the lists of uniform sources at small theta too: N = 1e5
-    // on 6 levels, theta = 0.15, M = 30,720, mixed 1007 against 605 at 128.
+    // at 64 / 128 / 512 boxes: N = 20,000 on 7 levels M = 20,000 150 / 178 / 262, M =
+    // 100,000 269 / 281 / 328; on 6 levels M = 20,000 182 / 206 / 242, 40,000 (39 per
+    // leaf) 281 / 268 / 261; N = 30,000 on 6 levels M = 20,000 254 / 293 / 343; N = 1e5 on
+    // 7 levels M = 100,000 766 / 736 / 812; N = 300,000 on 8 levels M = 98,304 1428 / 1394
+    // / 1693, 262,144 3400 / 3399 / 3237; N = 1e6 on 8 levels M = 98,304 6830 / 6756 /
+    // 6522, 262,144 18,091 / 18,377 / 14,361; N = 60,000 on 7 levels M = 300,000 1785 /
+    // 1586 / 1086.  Not for what every list of uniform sources holds at small theta: N
+    // = 1e5 on 6 levels, theta = 0.15, M = 30,720, mixed 1007 / 605 / 605, at 0.2 442 /
+    // 416 / 417.
     const bool part_descend = der && !all_descend && pl.split_p2p;
     const int32_t* nq_dev = off.p + (all_descend || part_descend ? nb : lb);
-    const int line = M <= std::min<int64_t>(kFewPoints, kFewPerLeaf * nleaf) ? kLongListFew : kLongList;
+    const int line = long_list(M, nleaf, pl.theta);
     const int skip = part_descend ? line : 0, longest = part_descend ? line : INT32_MAX;
 #define DESC_ARGS                                                                                             \
     (const double2*)y, order.p, box.p, nq_dev, skip, L, sc.d_box_level.p, t.geom.p, sc.d_box_start.p,         \

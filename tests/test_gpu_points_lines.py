@@ -66,7 +66,7 @@ def test_points_in_leaves_with_long_lists(orc, prec, bar, n, L):
 @pytest.mark.parametrize("prec,bar", [("fp64", 1e-12), ("mixed", 1e-6)])
 @pytest.mark.parametrize("M", [32768, 32769])
 def test_points_beside_clusters_at_the_line_of_the_lists(orc, prec, bar, M):
-    # 32 points per leaf: leaves with more than 128 boxes in their lists are
+    # 32 points per leaf: leaves with more than 64 boxes in their lists are
     # descended up to there, with more than 512 above it
     import torch
     assert torch.cuda.is_available(), "GPU tests need a HIP device"
@@ -77,7 +77,7 @@ def test_points_beside_clusters_at_the_line_of_the_lists(orc, prec, bar, M):
     y[::3] = z[rng.integers(0, z.size, y[::3].size)] + 1e-4
     pl = F.plan(F.build_tree(dev(z), 6), 30, 0.5, prec)
     cnt = np.diff(pl.download_list(0, 5, 0)[0])
-    assert (cnt > 128).any() and (cnt <= 128).any()
+    assert (cnt > 64).any() and (cnt <= 64).any()
     md = dev(m)
     phi, dphi = (host(x) for x in F.evaluate_points(pl, md, dev(y), field=True))
     part = slice(M - 5000, M)

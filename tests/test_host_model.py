@@ -66,11 +66,11 @@ class Model:
         self.ok(self.lib.fmm_build_tree(self.buf, off, nprob, (C.c_int * nprob)(*[L] * nprob), s, C.byref(h)))
         return h
 
-    def plan(self, tree, s, p=12, prec=0, flags=0):
+    def plan(self, tree, s, p=12, prec=0, flags=0, theta=0.5):
         t = F._Tuning()
         t.flags = flags
         h = C.c_void_p()
-        self.ok(self.lib.fmm_plan(tree, p, C.c_double(0.5), prec, C.byref(t), s, C.byref(h)))
+        self.ok(self.lib.fmm_plan(tree, p, C.c_double(theta), prec, C.byref(t), s, C.byref(h)))
         return h
 
     def call(self, op, pl, s):
@@ -244,8 +244,7 @@ def test_points_with_the_derivative_few_per_leaf_are_descended(model, n, L, prec
 @pytest.mark.parametrize("flag,longest", [(0, 2 ** 31 - 1), (4, 512)])
 def test_long_lists_of_points_with_the_derivative_are_descended(model, flag, longest):
     # split strong lists: the own kernel (its 14th argument) leaves out what the
-    # descents (their 5th) take, leaves with more than 512 boxes in their list, or 128
-    # where the points are few
+    # descents (their 5th) take, leaves with more than 512 boxes in their list
     s = model.stream()
     model.lib.model_list_flag(C.c_longlong(flag))
     pl = model.plan(model.tree(5000, 5, s), s)
@@ -255,12 +254,14 @@ def test_long_lists_of_points_with_the_derivative_are_descended(model, flag, lon
         assert model.lib.model_watched() == value, part
 
 
-@pytest.mark.parametrize("L,M,line", [(6, 32768, 128), (6, 32769, 512), (8, 131072, 128), (8, 131073, 512)])
-def test_the_line_of_long_lists_by_the_number_of_points(model, L, M, line):
+@pytest.mark.parametrize("L,M,theta,line", [(6, 32768, 0.5, 64), (6, 32769, 0.5, 512), (8, 131072, 0.5, 64),
+                                            (8, 131073, 0.5, 512), (6, 32768, 0.1875, 85), (6, 32768, 0.01, 512)])
+def test_the_line_of_long_lists_by_the_number_of_points(model, L, M, theta, line):
     # up to 32 points per leaf (1024 leaves) and up to 131,072 points (16,384 leaves)
+    # the larger of 64 and 3 / theta^2 boxes, else 512 (which is also the most)
     s = model.stream()
     model.lib.model_list_flag(C.c_longlong(4))
-    pl = model.plan(model.tree(70000, L, s), s)
+    pl = model.plan(model.tree(70000, L, s), s, theta=theta)
     for part, arg in ((b"k_pts_near_der", 13), (b"k_pts_descend", 4)):
         model.lib.model_watch(part, arg)
         model.ok(model.call("%d:field" % M, pl, s))

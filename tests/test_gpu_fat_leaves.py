@@ -89,7 +89,8 @@ def test_p2m_and_l2p_of_their_own(orc, prec, bar, n, L, p):
 
 @pytest.mark.parametrize("prec", ["fp64", "mixed"])
 @pytest.mark.parametrize("sizes,Ls", [((4097, 300, 5000), (3, 3, 3)), ((4097, 9000), (3, 3)),
-                                      ((4097, 700, 40, 17000, 700), (3, 2, 1, 4, 4)), ((40, 17000), (1, 4))])
+                                      ((4097, 700, 40, 17000, 700), (3, 2, 1, 4, 4)), ((40, 17000), (1, 4)),
+                                      ((70000, 3000), (5, 5)), ((3000, 70000, 500), (5, 5, 4))])
 @pytest.mark.parametrize("p", [16, 46])
 def test_fat_and_thin_problems_in_one_call(prec, sizes, Ls, p):
     # problems with and without launches of their own, of one depth and of several,
